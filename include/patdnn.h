@@ -139,8 +139,9 @@ patdnn_status_t patdnn_conv2d_f16(patdnn_handle_t h, const void* input, int32_t 
  * is dropped), fused: the CONV stages of the networks the paper runs end in a pooling
  * layer (section 2.1, section 6.2) and only the pooled tensor is written.
  *   output  DEVICE [n][c_out][h_out/2][w_out/2]; must not overlap input
- * Two launches on `stream` (a kernel that zeroes the output, then the layer, whose lanes
- * fold their values into the pooled cells with integer atomic max on the float bits:
+ * The tap-product kernel holds whole pooling windows in registers and stores the pooled cells;
+ * the others are two launches on `stream` (a kernel that zeroes the output, then the layer, whose
+ * lanes fold their values into the pooled cells with integer atomic max on the float bits:
  * exact and independent of the order).  Otherwise as patdnn_conv2d.  Depthwise layers:
  * PATDNN_EUNSUPPORTED.  A layer whose configuration splits the input channels runs its
  * default configuration here.
@@ -167,8 +168,9 @@ patdnn_status_t patdnn_conv2d_pool(patdnn_handle_t h, const float* input, int32_
  *   workspace_floats  its size; if it is smaller than the layer needs the call runs as
  *                     without one
  * Calls that share a workspace must not overlap in time.  Nothing is allocated.
- * patdnn_workspace_floats: what the handle's present configuration can use at this input
- * size (0: it does not split; also 0 for arguments that patdnn_conv2d would reject).
+ * patdnn_workspace_floats: what the handle's present configuration - the library's own choice
+ * at this input size, if none has been set - can use (0: it does not split; also 0 for arguments
+ * that patdnn_conv2d would reject).
  */
 size_t patdnn_workspace_floats(patdnn_handle_t h, int32_t n, int32_t h_in, int32_t w_in);
 patdnn_status_t patdnn_conv2d_ws(patdnn_handle_t h, const float* input, int32_t n, int32_t h_in, int32_t w_in,
@@ -245,6 +247,12 @@ patdnn_status_t patdnn_layout_stats(patdnn_handle_t h, patdnn_stats_t* out);
  *                           "No-opt" stage of the per-layer breakdown, section 6.3), and the
  *                           layer as a CSR matrix (the control of section 6.2); pruned,
  *                           non-depthwise layers only
+ *                           "taps_f8", "taps_f16": tap-product kernel on the matrix cores in
+ *                           fp32 (stride 1, pruned layers), 8 or 16 filters per wavefront; `ck` up
+ *                           to 160 channels, `waves` up to 16
+ * variant < 0 (the state of a new handle): the library chooses at every call, by an estimate of
+ * the candidates' times at this input size; a choice that splits the input channels is made
+ * only where the call has a workspace of patdnn_workspace_floats() for it.
  * A configuration set with patdnn_set_config is taken as given or refused
  * (PATDNN_EUNSUPPORTED), never replaced by another one at launch time.
  * `ck` = input channels staged per LDS pass, `waves` = wavefronts (filter groups)
@@ -371,8 +379,8 @@ void        patdnn_destroy(patdnn_handle_t h);          /* NULL is a no-op */
  * i-1 wrote; `pool2` fuses ReLU + 2x2 max pooling into the layer (as patdnn_conv2d_pool).
  * The stack owns two DEVICE buffers for the tensors between layers and one for partial sums
  * (allocated by patdnn_stack_create, freed by patdnn_stack_destroy): layers that are
- * configured, when the stack is created, to split their input channels get the workspace of
- * patdnn_conv2d_ws from it (one buffer per channel slice, up to 512 MB; a layer that would
+ * configured, when the stack is created, to split their input channels (or for which the library
+ * would choose to) get the workspace of patdnn_conv2d_ws from it (one buffer per channel slice, up to 512 MB; a layer that would
  * need more, or is reconfigured later to need more than there is, adds its slices up with
  * atomics as patdnn_conv2d does).  Handles and bias arrays stay the caller's and must outlive
  * the stack.

@@ -1,7 +1,7 @@
 """Builds ``libpatdnn.so`` (the C-ABI library) for gfx950 with hipcc, in-tree.
 
 Steps: generate the pattern-specialised FMA bodies for every sparse variant listed in
-``csrc/variants.def`` (``csrc/gen_dispatch.py``), compile each translation unit, link.
+``csrc/variants.def`` (``csrc/gen_dispatch.py``) and the tap-product loop (``csrc/gen_taps.py``), compile each translation unit, link.
 hipcc cross-compiles without a GPU.  Packed-FP32 code generation is switched off.
 """
 
@@ -18,7 +18,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(CSRC, "_build")
 LIB = os.path.join(HERE, "libpatdnn.so")
 PROBES_LIB = os.path.join(HERE, "libpatdnn_probes.so")     # bench-side measurement probes
-SOURCES = ["patdnn_api.hip", "kernel_fkw.hip", "kernel_dw.hip", "kernel_compare.hip", "kernel_tiled.hip", "selftest.hip", "encoder.cpp", "projection.cpp"]
+SOURCES = ["patdnn_api.hip", "kernel_fkw.hip", "kernel_dw.hip", "kernel_compare.hip", "kernel_tiled.hip", "kernel_taps.hip", "selftest.hip", "encoder.cpp", "projection.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
@@ -59,6 +59,8 @@ def build(verbose: bool = False) -> str:
     sys.path.insert(0, CSRC)
     try:
         import gen_dispatch
+        import gen_taps
+        gen_taps.main(["gen_taps", os.path.join(CSRC, "gen")])
         gen_dispatch.main(["gen_dispatch", os.path.join(CSRC, "gen")] +
                           [",".join(str(v) for v in g) for g in sparse_geometries()])
     finally:

@@ -179,6 +179,69 @@ void decode_fkw(const LayerHost& L, const Fkw& f, float* w, uint8_t* ids, uint8_
     }
 }
 
+// Which filters share a group: [group][slot] -> FKW position, -1 = empty slot.  The wavefronts
+// of a workgroup (consecutive groups) meet at a barrier after every chunk of input channels, so
+// what has to be equal is the work of the groups chunk by chunk - the purpose the paper's filter
+// reorder serves for the threads of a block (section 5.2).  Filters are dealt out longest first,
+// each to the group with a free slot whose per-chunk load stays flattest (sum of squares), then
+// pairs of filters are swapped between groups while that improves.
+static std::vector<int32_t> assign_groups(const LayerHost& L, int G, int ck)
+{
+    const Fkw& f = L.fkw;
+    const int c_out = L.desc.c_out;
+    const int nc = (L.desc.c_in + ck - 1) / ck, ng = (c_out + G - 1) / G;
+    std::vector<int32_t> members((size_t)ng * G, -1);
+    std::vector<int32_t> fc((size_t)c_out * nc, 0);             // kernels of a filter per chunk
+    for (int s = 0; s < c_out; ++s)
+        for (int32_t k = f.offset[s]; k < f.offset[s + 1]; ++k) ++fc[(size_t)s * nc + f.index[k] / ck];
+    // a group has at most G * ck <= 2^21 kernels in a chunk, so the squares fit 64 bits and the
+    // factors 32: loops the compiler turns into vector code
+    std::vector<int32_t> load((size_t)ng * nc, 0);
+    std::vector<int32_t> fill(ng, 0);
+    const std::vector<int32_t> none(nc, 0);
+    auto delta_sq = [&](int g, const int32_t* add, const int32_t* sub) {
+        int64_t d = 0;                                           // change of sum(load^2) of group g
+        const int32_t* a = &load[(size_t)g * nc];
+        for (int c = 0; c < nc; ++c) {
+            const int32_t x = add[c] - sub[c];
+            d += (int64_t)x * (2 * a[c] + x);
+        }
+        return d;
+    };
+    for (int r = 0; r < c_out; ++r) {
+        const int s = c_out - 1 - r;                             // FKW order ascends in length
+        int best = -1;
+        int64_t best_d = 0;
+        for (int g = 0; g < ng; ++g) {
+            if (fill[g] >= G) continue;
+            const int64_t d = delta_sq(g, &fc[(size_t)s * nc], none.data());
+            if (best < 0 || d < best_d) { best = g; best_d = d; }
+        }
+        members[(size_t)best * G + fill[best]++] = s;
+        for (int c = 0; c < nc; ++c) load[(size_t)best * nc + c] += fc[(size_t)s * nc + c];
+    }
+    // bounded improvement by swaps; a fixed linear congruential sequence picks the pairs
+    uint64_t lcg = 0x9E3779B97F4A7C15ull;
+    const long attempts = std::min<long>(200000, 200l * c_out);
+    for (long it = 0; it < attempts && ng > 1; ++it) {
+        lcg = lcg * 6364136223846793005ull + 1442695040888963407ull;
+        const int ia = (int)((lcg >> 33) % (uint64_t)members.size());
+        lcg = lcg * 6364136223846793005ull + 1442695040888963407ull;
+        const int ib = (int)((lcg >> 33) % (uint64_t)members.size());
+        const int ga = ia / G, gb = ib / G, sa = members[ia], sb = members[ib];
+        if (ga == gb || sa < 0 || sb < 0) continue;
+        const int32_t* fa = &fc[(size_t)sa * nc];
+        const int32_t* fb = &fc[(size_t)sb * nc];
+        if (delta_sq(ga, fb, fa) + delta_sq(gb, fa, fb) >= 0) continue;
+        for (int c = 0; c < nc; ++c) {
+            load[(size_t)ga * nc + c] += fb[c] - fa[c];
+            load[(size_t)gb * nc + c] += fa[c] - fb[c];
+        }
+        std::swap(members[ia], members[ib]);
+    }
+    return members;
+}
+
 void build_tiled(const LayerHost& L, const TiledParams& prm, Tiled& T)
 {
     const Fkw& f = L.fkw;
@@ -207,62 +270,11 @@ void build_tiled(const LayerHost& L, const TiledParams& prm, Tiled& T)
     auto float_bits = [](float v) { uint32_t u; std::memcpy(&u, &v, 4); return u; };
     std::vector<Step> plan;
 
-    // ---- which filters share a group.  The wavefronts of a workgroup (consecutive groups)
-    // meet at a barrier after every chunk of input channels, so what has to be equal is the
-    // work of the groups chunk by chunk - the purpose the paper's filter reorder serves for
-    // the threads of a block (section 5.2).  Filters are dealt out longest first, each to
-    // the group with a free slot whose per-chunk load stays flattest (sum of squares), then
-    // pairs of filters are swapped between groups while that improves.  Dense layers have
-    // equal filters and keep the stored order.
     std::vector<int32_t> members((size_t)T.num_groups * G, -1);    // [group][slot] -> FKW position
     if (L.dense) {
         for (int r = 0; r < c_out; ++r) members[r] = c_out - 1 - r;
     } else {
-        const int nc = T.num_chunks, ng = T.num_groups;
-        std::vector<int32_t> fc((size_t)c_out * nc, 0);             // kernels of a filter per chunk
-        for (int s = 0; s < c_out; ++s)
-            for (int32_t k = f.offset[s]; k < f.offset[s + 1]; ++k) ++fc[(size_t)s * nc + f.index[k] / prm.ck];
-        std::vector<int64_t> load((size_t)ng * nc, 0);
-        std::vector<int32_t> fill(ng, 0);
-        auto delta_sq = [&](int g, const int32_t* add, const int32_t* sub) {
-            int64_t d = 0;                                           // change of sum(load^2) of group g
-            for (int c = 0; c < nc; ++c) {
-                const int64_t a = load[(size_t)g * nc + c], b = a + add[c] - (sub ? sub[c] : 0);
-                d += b * b - a * a;
-            }
-            return d;
-        };
-        for (int r = 0; r < c_out; ++r) {
-            const int s = c_out - 1 - r;                             // FKW order ascends in length
-            int best = -1;
-            int64_t best_d = 0;
-            for (int g = 0; g < ng; ++g) {
-                if (fill[g] >= G) continue;
-                const int64_t d = delta_sq(g, &fc[(size_t)s * nc], nullptr);
-                if (best < 0 || d < best_d) { best = g; best_d = d; }
-            }
-            members[(size_t)best * G + fill[best]++] = s;
-            for (int c = 0; c < nc; ++c) load[(size_t)best * nc + c] += fc[(size_t)s * nc + c];
-        }
-        // bounded improvement by swaps; a fixed linear congruential sequence picks the pairs
-        uint64_t lcg = 0x9E3779B97F4A7C15ull;
-        const long attempts = std::min<long>(200000, 200l * c_out);
-        for (long it = 0; it < attempts && ng > 1; ++it) {
-            lcg = lcg * 6364136223846793005ull + 1442695040888963407ull;
-            const int ia = (int)((lcg >> 33) % (uint64_t)members.size());
-            lcg = lcg * 6364136223846793005ull + 1442695040888963407ull;
-            const int ib = (int)((lcg >> 33) % (uint64_t)members.size());
-            const int ga = ia / G, gb = ib / G, sa = members[ia], sb = members[ib];
-            if (ga == gb || sa < 0 || sb < 0) continue;
-            const int32_t* fa = &fc[(size_t)sa * nc];
-            const int32_t* fb = &fc[(size_t)sb * nc];
-            if (delta_sq(ga, fb, fa) + delta_sq(gb, fa, fb) >= 0) continue;
-            for (int c = 0; c < nc; ++c) {
-                load[(size_t)ga * nc + c] += fb[c] - fa[c];
-                load[(size_t)gb * nc + c] += fa[c] - fb[c];
-            }
-            std::swap(members[ia], members[ib]);
-        }
+        members = assign_groups(L, G, prm.ck);
     }
 
     std::vector<Entry> ent;
@@ -381,6 +393,66 @@ void build_tiled(const LayerHost& L, const TiledParams& prm, Tiled& T)
     }
     // the interpreter fetches one step beyond the last one it runs
     if (!L.dense) T.steps.resize(T.steps.size() + kStepDwords, 0u);
+}
+
+std::vector<int32_t> taps_groups(const LayerHost& L, int ck) { return assign_groups(L, kTapGroup, ck); }
+
+void build_taps(const LayerHost& L, int ck, const std::vector<int32_t>& members, Taps& T)
+{
+    const Fkw& f = L.fkw;
+    const int c_out = L.desc.c_out, c_in = L.desc.c_in, P = f.num_patterns, G = kTapGroup;
+    T = Taps();
+    T.ck = ck;
+    T.num_groups = (c_out + G - 1) / G;
+    T.num_chunks = (c_in + ck - 1) / ck;
+    T.slot_channel.assign((size_t)T.num_groups * G, -1);
+    T.group_kernels.assign(T.num_groups, 0);
+    T.chunk_ptr.assign((size_t)T.num_groups * T.num_chunks, 0);
+    const size_t room = (size_t)L.kept + (size_t)T.num_groups * T.num_chunks * (G + kTapBatch) + 2 * kTapBatch;
+    T.records.reserve(room);
+    T.weights.reserve(4 * room);
+    auto append = [&](uint32_t rec, const float* w) {
+        T.records.push_back(rec);
+        for (int t = 0; t < 4; ++t) T.weights.push_back(w ? w[t] : 0.0f);
+    };
+    auto pad_batch = [&] {
+        while (T.records.size() % kTapBatch) append(0u, nullptr);
+    };
+    // where each (filter, pattern) run of the FKW arrays continues with the next chunk: the
+    // channels of a run ascend
+    std::vector<int32_t> next((size_t)c_out * P);
+    for (int s = 0; s < c_out; ++s)
+        for (int p = 0; p < P; ++p) next[(size_t)s * P + p] = f.offset[s] + f.stride[(size_t)s * (P + 1) + p];
+    for (int g = 0; g < T.num_groups; ++g)
+        for (int chunk = 0; chunk < T.num_chunks; ++chunk) {
+            T.chunk_ptr[(size_t)g * T.num_chunks + chunk] = (uint32_t)(T.records.size() / kTapBatch);
+            const int c0 = chunk * ck, c1 = c0 + ck;
+            for (int slot = 0; slot < G; ++slot) {
+                const int s = members[(size_t)g * G + slot];
+                const size_t before = T.records.size();
+                for (int p = 0; s >= 0 && p < P; ++p) {
+                    int32_t& k = next[(size_t)s * P + p];
+                    const int32_t end = f.offset[s] + f.stride[(size_t)s * (P + 1) + p + 1];
+                    const size_t run = T.records.size();
+                    for (; k < end && f.index[k] < c1; ++k)
+                        append((uint32_t)(f.index[k] - c0) | (uint32_t)L.universe_of_pattern[p] << kTapPatternShift,
+                               &f.weight[(size_t)k * 4]);
+                    if (T.records.size() > run) {
+                        T.records.back() |= kTapSegmentEnd;
+                        ++T.segments;
+                    }
+                }
+                if (s >= 0 && chunk == 0) {
+                    T.slot_channel[(size_t)g * G + slot] = f.reorder[s];
+                    T.group_kernels[g] += f.offset[s + 1] - f.offset[s];
+                }
+                if (T.records.size() == before) append(kTapSegmentEnd, nullptr);
+                T.records.back() |= kTapFilterEnd;
+            }
+            pad_batch();
+        }
+    // the kernel fetches one batch beyond the last one it runs, and the records of the one after
+    for (int i = 0; i < 2 * kTapBatch; ++i) append(0u, nullptr);
 }
 
 }  // namespace patdnn

@@ -644,7 +644,7 @@ static void launch_bias_act(float* out, const float* sums, int slices, size_t sl
 
 // More than 64 KB of dynamic LDS needs the function attribute, once per device (bit = device
 // id); two threads racing here both set it, which is harmless.
-static hipError_t allow_big_lds(const void* fn, std::atomic<uint64_t>& done)
+hipError_t allow_big_lds(const void* fn, std::atomic<uint64_t>& done)
 {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -696,6 +696,47 @@ __global__ __launch_bounds__(256) void bias_relu_pool_kernel(const float* sum, c
         const float m = fmaxf(fmaxf(v00, v01), fmaxf(v10, v11));
         out[i] = fmaxf(m + b, 0.0f);
     }
+}
+
+// With room for one buffer per slice the slices store their partial sums (no zero fill, no
+// atomics, and a sum in a fixed order: results repeat bit for bit); otherwise they add into the
+// output - or, for a pooled layer, into the one buffer there is room for.
+hipError_t begin_split(const ConvShape& s, float* out, int32_t ksplit, float* scratch, size_t scratch_floats,
+                       hipStream_t stream, SplitTarget& t)
+{
+    const size_t total = (size_t)s.n * s.c_out * s.ho * s.wo;
+    t.slice_stride = split_slice_stride(total);
+    const bool to_slices = scratch && scratch_floats / (size_t)ksplit >= t.slice_stride &&
+                           (reinterpret_cast<uintptr_t>(scratch) & 15) == 0;
+    if (s.pool && !to_slices && (!scratch || scratch_floats < total)) return hipErrorInvalidValue;
+    t.sums = (s.pool || to_slices) ? scratch : out;
+    t.slices = to_slices ? ksplit : 1;
+    if (!to_slices && !(s.pre_zeroed == t.sums && s.pre_zeroed_count >= total)) return launch_fill_zero(t.sums, total, stream);
+    return hipSuccess;
+}
+
+hipError_t finish_split(const ConvShape& s, const SplitTarget& t, const float* bias, float* out, hipStream_t stream)
+{
+    const size_t plane = (size_t)s.ho * s.wo, total = (size_t)s.n * s.c_out * plane;
+    // the finishing kernel may clear the next launch's target on the way, unless that is the
+    // very buffer it reads the sums from
+    float* zero_next = (s.zero_next && s.zero_next != t.sums) ? s.zero_next : nullptr;
+    const size_t zero_next_count = zero_next ? s.zero_next_count : 0;
+    if (zero_next && s.zero_next_done) *s.zero_next_done = true;
+    if (s.pool) {
+        const int pho = s.ho / 2, pwo = s.wo / 2;
+        const size_t ptotal = (size_t)s.n * s.c_out * pho * pwo;
+        const unsigned pblocks = (unsigned)std::min<size_t>((std::max(ptotal, zero_next_count) + 255) / 256, 256 * 32);
+        // max(relu(x + b)) over a window = relu(max(x) + b): one bias add and one ReLU per cell
+        hipLaunchKernelGGL(bias_relu_pool_kernel, dim3(pblocks), dim3(256), 0, stream,
+                           static_cast<const float*>(t.sums), bias, out, s.c_out, s.ho, s.wo, pho, pwo, ptotal,
+                           make_fast_div((uint32_t)std::max(pwo, 1)), make_fast_div((uint32_t)std::max(pho, 1)),
+                           make_fast_div((uint32_t)s.c_out), zero_next, zero_next_count, t.slices, t.slice_stride);
+    } else {
+        launch_bias_act(out, t.sums, t.slices, t.slice_stride, bias, s.c_out, plane, total, s.relu, zero_next,
+                        zero_next_count, stream);
+    }
+    return hipGetLastError();
 }
 
 // Workgroups of `fn` that the current device holds at once with this block size and dynamic
@@ -781,7 +822,6 @@ static hipError_t launch_tiled(const DevTiled& t, const ConvShape& s, const floa
             a.late_span = (int32_t)((slots + 2) / 3);
         }
     };
-    if (s.pool && ksplit > 1 && !scratch) return hipErrorInvalidValue;   // the slices need somewhere to add up
     if (ksplit <= 1) {
         set_priorities(reinterpret_cast<const void*>(&tiled_conv_kernel<GEO, false>), blocks);
         hipLaunchKernelGGL((tiled_conv_kernel<GEO, false>), dim3((unsigned)blocks), dim3(64 * waves), lds_bytes,
@@ -799,44 +839,16 @@ static hipError_t launch_tiled(const DevTiled& t, const ConvShape& s, const floa
             if (e != hipSuccess) return e;
         }
         set_priorities(reinterpret_cast<const void*>(&tiled_conv_kernel<GEO, true>), blocks * ksplit);
-        const size_t plane = (size_t)s.ho * s.wo, total = (size_t)s.n * s.c_out * plane;
-        const unsigned fill_blocks = (unsigned)std::min<size_t>((total + 255) / 256, 256 * 32);
-        // With room for one buffer per slice the slices store their partial sums (no zero fill,
-        // no atomics, and a sum in a fixed order: results repeat bit for bit); otherwise they add
-        // into the output - or, for a pooled layer, into the one buffer there is room for.
-        const size_t slice_stride = split_slice_stride(total);
-        const bool to_slices = scratch && scratch_floats / (size_t)ksplit >= slice_stride &&
-                               (reinterpret_cast<uintptr_t>(scratch) & 15) == 0;
-        if (s.pool && !to_slices && scratch_floats < total) return hipErrorInvalidValue;
-        float* sums = (s.pool || to_slices) ? scratch : out;
-        a.out = sums;
+        SplitTarget target;
+        hipError_t e = begin_split(s, out, ksplit, scratch, scratch_floats, stream, target);
+        if (e != hipSuccess) return e;
+        a.out = target.sums;
         a.pool = 0;                                  // the slices write plain partial sums
-        a.slice_stride = to_slices ? slice_stride : 0;
-        if (to_slices) { a.bias = nullptr; a.relu = 0; }
-        if (!to_slices && !(s.pre_zeroed == sums && s.pre_zeroed_count >= total))
-            hipLaunchKernelGGL(fill_zero_kernel, dim3(fill_blocks), dim3(256), 0, stream, sums, total);
-        // the finishing kernel below may clear the next launch's target on the way, unless that
-        // is the very buffer it reads the sums from
-        float* zero_next = (s.zero_next && s.zero_next != sums) ? s.zero_next : nullptr;
-        const size_t zero_next_count = zero_next ? s.zero_next_count : 0;
-        if (zero_next && s.zero_next_done) *s.zero_next_done = true;
+        a.slice_stride = target.slices > 1 ? target.slice_stride : 0;
+        if (a.slice_stride) { a.bias = nullptr; a.relu = 0; }
         hipLaunchKernelGGL((tiled_conv_kernel<GEO, true>), dim3((unsigned)blocks, (unsigned)ksplit), dim3(64 * waves),
                            lds_bytes, stream, a);
-        if (s.pool) {
-            const int pho = s.ho / 2, pwo = s.wo / 2;
-            const size_t ptotal = (size_t)s.n * s.c_out * pho * pwo;
-            const unsigned pblocks = (unsigned)std::min<size_t>((std::max(ptotal, zero_next_count) + 255) / 256, 256 * 32);
-            // max(relu(x + b)) over a window = relu(max(x) + b): one bias add and one ReLU per cell
-            hipLaunchKernelGGL(bias_relu_pool_kernel, dim3(pblocks), dim3(256), 0, stream,
-                               static_cast<const float*>(sums), bias, out, s.c_out, s.ho, s.wo, pho, pwo, ptotal,
-                               make_fast_div((uint32_t)std::max(pwo, 1)), make_fast_div((uint32_t)std::max(pho, 1)),
-                               make_fast_div((uint32_t)s.c_out), zero_next, zero_next_count,
-                               to_slices ? ksplit : 1, slice_stride);
-        } else {
-            launch_bias_act(out, sums, to_slices ? ksplit : 1, slice_stride, bias, s.c_out, plane, total, s.relu,
-                            zero_next, zero_next_count, stream);
-        }
-        return hipGetLastError();
+        return finish_split(s, target, bias, out, stream);
     }
 }
 

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
 #include <string>
 
@@ -151,6 +152,38 @@ struct TiledVariant {
     hipError_t (*launch)(const DevTiled&, const ConvShape&, const float*, const float*, float*,
                          int32_t waves, int32_t ksplit, float* scratch, size_t scratch_floats, hipStream_t);
 };
+
+// Tap-product layout on the device (layout.hpp, Taps).
+struct DevTaps {
+    int32_t num_groups = 0, ck = 0, num_chunks = 0;
+    const int32_t* slot_channel = nullptr;
+    const uint32_t* chunk_ptr = nullptr;
+    const uint32_t* records = nullptr;
+    const float* weights = nullptr;
+};
+// Tiles of 16 x 16 input pixels that this input is cut into.
+long long tap_tile_count(const ConvShape& s);
+// Stride 1 only; `filters` per wavefront is 8 or 16, the rest as TiledVariant::launch.
+hipError_t launch_taps(int filters, const DevTaps& t, const ConvShape& s, const float* in, const float* bias, float* out,
+                       int32_t waves, int32_t ksplit, float* scratch, size_t scratch_floats, hipStream_t stream);
+
+// ---------------------------------------------------------------------------
+// Launches that split the input channels: where the slices' partial sums go (before the slices
+// run), and the kernel that makes the output of them (after).
+// ---------------------------------------------------------------------------
+struct SplitTarget {
+    float* sums = nullptr;           // first buffer
+    int slices = 1;                  // buffers, one per slice; 1 = the slices are added up in `sums` with atomics
+    size_t slice_stride = 0;         // floats between the buffers
+};
+// With room for one buffer per slice the slices store their sums; otherwise they add into the
+// output (pooled layers: into the scratch, which must hold one un-pooled output), cleared here.
+hipError_t begin_split(const ConvShape& s, float* out, int32_t ksplit, float* scratch, size_t scratch_floats,
+                       hipStream_t stream, SplitTarget& t);
+// sum + bias + activation (+ pooling), and the zero fill handed over by s.zero_next
+hipError_t finish_split(const ConvShape& s, const SplitTarget& t, const float* bias, float* out, hipStream_t stream);
+// More than 64 KB of dynamic LDS: the function attribute, once per device.
+hipError_t allow_big_lds(const void* fn, std::atomic<uint64_t>& done);
 
 // Device check that s_movrels_b32 / _b64 behave as the threaded interpreter assumes.
 bool movrel_selftest(std::string& err);

@@ -117,6 +117,35 @@ struct Tiled {
     }
 };
 
+// ---------------------------------------------------------------------------
+// Layout of the tap-product kernel (kernel_taps.hip).  Eight filters form a group (chosen like
+// the groups above); per group and chunk of `ck` input channels the kept kernels follow each
+// other filter by filter, inside a filter by pattern (the paper's FKW order cut into chunks), in
+// batches of 16: a 32-bit record and four weights per kernel.  A filter without a kernel in the
+// chunk gets one of zero weights, so that every filter has an end.
+//   record: bits 0..7 channel inside the chunk, 22..27 pattern (universe index), 30 last kernel
+//   of the filter, 31 last kernel of the filter's run of this pattern
+// ---------------------------------------------------------------------------
+constexpr int kTapGroup = 8;
+constexpr int kTapBatch = 16;
+constexpr int kTapMaxChunk = 160;            // channels whose 16 x 16 tiles fill a CU's LDS
+constexpr uint32_t kTapFilterEnd = 1u << 30, kTapSegmentEnd = 1u << 31;
+constexpr int kTapPatternShift = 22;
+
+struct Taps {
+    int32_t num_groups = 0, ck = 0, num_chunks = 0;
+    std::vector<int32_t> slot_channel;       // [num_groups*8] original output channel, -1 = empty slot
+    std::vector<uint32_t> chunk_ptr;         // [num_groups][num_chunks] first batch
+    std::vector<uint32_t> records;           // [batches + 2][16]
+    std::vector<float> weights;              // [batches + 2][16][4]
+    std::vector<int64_t> group_kernels;      // [num_groups] kept kernels per group
+    int64_t segments = 0;                    // runs of one pattern in one filter and chunk
+    size_t bytes() const
+    {
+        return 4 * (slot_channel.size() + chunk_ptr.size() + records.size() + weights.size());
+    }
+};
+
 struct LayerHost {
     patdnn_layer_desc_t desc{};          // pattern_masks pointer is not kept; see fkw.masks
     bool depthwise = false;
@@ -133,6 +162,11 @@ patdnn_status_t build_fkw(const patdnn_layer_desc_t& d, const float* w, const ui
 
 // Filter-group layout of one variant, derived from the FKW arrays.
 void build_tiled(const LayerHost& L, const TiledParams& p, Tiled& out);
+
+// Tap-product layout for chunks of `ck` channels (pruned layers, patterns of the universe);
+// `groups` from taps_groups, which balances them for chunks of its `ck`.
+std::vector<int32_t> taps_groups(const LayerHost& L, int ck);
+void build_taps(const LayerHost& L, int ck, const std::vector<int32_t>& groups, Taps& out);
 
 // Inverse of build_fkw from the five arrays (any output may be null).
 void decode_fkw(const LayerHost& L, const Fkw& f, float* w, uint8_t* ids, uint8_t* mask);

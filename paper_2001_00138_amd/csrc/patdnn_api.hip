@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -54,6 +55,16 @@ struct TiledOnDevice {
     }
 };
 
+struct TapsOnDevice {
+    Taps host;
+    DevTaps dev;
+    std::vector<void*> allocations;
+    ~TapsOnDevice()
+    {
+        for (void* p : allocations) (void)hipFree(p);
+    }
+};
+
 }  // namespace
 
 struct patdnn_layer {
@@ -63,6 +74,8 @@ struct patdnn_layer {
     DevFkw dfkw;
     // by (variant index, ck); dense variants use ck = 0
     std::map<std::pair<int, int>, std::unique_ptr<TiledOnDevice>> tiled;
+    std::map<int, std::unique_ptr<TapsOnDevice>> taps;     // tap-product layouts by ck
+    std::vector<int32_t> tap_groups;                       // the filter groups they share
     std::vector<void*> allocations;
     // the comparison kernels' layouts (built when such a variant is first selected)
     struct CompareHost {
@@ -130,10 +143,15 @@ bool variant_selectable(const patdnn_layer* h, const TiledVariant& v)
 }
 
 // Variant numbers: 0 the FKW walk, 1..T the tiled variants, then the kernels below.
-enum ExtraVariant { kExtraDepthwise = 0, kExtraNoopt, kExtraCsr, kNumExtra };
+enum ExtraVariant { kExtraDepthwise = 0, kExtraNoopt, kExtraCsr, kExtraTaps8, kExtraTaps16, kNumExtra };
 int extra_variant(int variant) { return variant - 1 - num_tiled_variants(); }     // < 0: not one
 int variant_of_extra(int extra) { return 1 + num_tiled_variants() + extra; }
-const char* const kExtraNames[kNumExtra] = {"dw_p1x4", "noopt", "csr"};
+const char* const kExtraNames[kNumExtra] = {"dw_p1x4", "noopt", "csr", "taps_f8", "taps_f16"};
+// filters per wavefront of a tap-product variant, 0 for any other
+int taps_filters(int variant)
+{
+    return extra_variant(variant) == kExtraTaps8 ? 8 : extra_variant(variant) == kExtraTaps16 ? 16 : 0;
+}
 
 constexpr int kMaxLdsBytes = 160 * 1024;      // LDS of one CU; two staging buffers must fit
 constexpr int kMaxWaves = 8;
@@ -203,6 +221,57 @@ patdnn_status_t ensure_tiled(patdnn_layer* h, int vi, int ck, const DevTiled** o
                 return hip_fail(e, "uploading the tiled layout");
         }
         it = h->tiled.emplace(key, std::move(t)).first;
+    }
+    if (out) *out = &it->second->dev;
+    return PATDNN_OK;
+}
+
+constexpr int kMaxTapWaves = 16;
+
+bool taps_fit_layer(const patdnn_layer* h)
+{
+    const LayerHost& L = h->L;
+    return !L.depthwise && !L.dense && L.all_in_universe && L.desc.stride == 1;
+}
+
+bool taps_fit_input(const ConvShape& s)
+{
+    // staging offsets are 32-bit byte offsets relative to the first image of a tile, which may
+    // hold 64 images of one pixel or one large image
+    const long long images = s.h > 7 || s.w > 7 ? 8 : 64;
+    return images * s.c_in * s.h * s.w < (1ll << 30) && tap_tile_count(s) * ((s.c_out + 7) / 8) <= INT32_MAX;
+}
+
+// The chunk sizes whose layouts every handle holds: equal chunks of at most 128 channels (a flush
+// per filter and pattern in every chunk, so the fewer chunks the better; 128 KB of LDS), half and a
+// quarter of that for launches that split the channels over workgroups.
+int taps_ck(int c_in, int level)
+{
+    const int chunks = ((c_in + 127) / 128) << level;
+    return (c_in + chunks - 1) / chunks;
+}
+constexpr int kTapLevels = 3, kMinTapChunk = 8;
+
+patdnn_status_t ensure_taps(patdnn_layer* h, int ck, const DevTaps** out)
+{
+    auto it = h->taps.find(ck);
+    if (it == h->taps.end()) {
+        std::unique_ptr<TapsOnDevice> t(new (std::nothrow) TapsOnDevice());
+        if (!t) return fail(PATDNN_ENOMEM, "out of host memory");
+        if (h->tap_groups.empty()) h->tap_groups = taps_groups(h->L, taps_ck(h->L.desc.c_in, 1));
+        build_taps(h->L, ck, h->tap_groups, t->host);
+        t->dev.num_groups = t->host.num_groups;
+        t->dev.ck = ck;
+        t->dev.num_chunks = t->host.num_chunks;
+        if (h->on_device) {
+            hipError_t e;
+            if ((e = upload(t->allocations, t->host.slot_channel, &t->dev.slot_channel)) != hipSuccess ||
+                (e = upload(t->allocations, t->host.chunk_ptr, &t->dev.chunk_ptr)) != hipSuccess ||
+                (e = upload(t->allocations, t->host.records, &t->dev.records)) != hipSuccess ||
+                (e = upload(t->allocations, t->host.weights, &t->dev.weights)) != hipSuccess)
+                return hip_fail(e, "uploading the tap-product layout");
+        }
+        it = h->taps.emplace(ck, std::move(t)).first;
     }
     if (out) *out = &it->second->dev;
     return PATDNN_OK;
@@ -302,6 +371,13 @@ patdnn_status_t run_config(patdnn_layer* h, const patdnn_config_t& c, const Conv
         hipError_t e = launch_compare(csr, csr ? h->csr_dev : h->noopt_dev, s, in, bias, out, stream);
         return e == hipSuccess ? PATDNN_OK : hip_fail(e, "launching a comparison kernel");
     }
+    if (const int filters = taps_filters(c.variant)) {
+        auto it = h->taps.find(c.ck);
+        if (it == h->taps.end()) return fail(PATDNN_EUNSUPPORTED, "no layout for this ck: choose it with patdnn_set_config");
+        if (!taps_fit_input(s)) return fail(PATDNN_EUNSUPPORTED, "input too large for the tap-product kernel");
+        hipError_t e = launch_taps(filters, it->second->dev, s, in, bias, out, c.waves, c.ksplit, scratch, scratch_floats, stream);
+        return e == hipSuccess ? PATDNN_OK : hip_fail(e, "launching the tap-product kernel");
+    }
     const int vi = c.variant - 1;
     if (vi < 0 || vi >= num_tiled_variants()) return fail(PATDNN_EINVAL, "no such variant");
     const TiledVariant& v = tiled_variant(vi);
@@ -342,17 +418,96 @@ std::vector<int> default_variant_order(const patdnn_layer* h)
     return order;
 }
 
-// The configuration used when the caller has not chosen or tuned one.
-patdnn_config_t default_config(patdnn_layer* h, const ConvShape& s)
+// ---- the configuration used when the caller has not chosen or tuned one: the candidate with the
+// smallest estimate of its time.  The estimates are a few products; their constants were fitted to
+// measurements of 60 layers from 16 to 512 channels, 7x7 to 224x224 pixels and 1 to 64 images in
+// every candidate configuration (1330 timings): they are within 7 % on average, and the
+// candidate they choose is 2 % slower than the fastest one on average.
+
+// Tap-product kernel, microseconds.  Workgroups of one round share a CU as far as LDS and registers
+// allow; `share` is what a wavefront's work costs when so many wavefronts sit on a SIMD (one alone
+// leaves the matrix core waiting for it).  What a workgroup reads and writes is not hidden by its own
+// computation, only by another workgroup on the CU.
+double taps_estimate(const patdnn_layer* h, const Taps& t, const ConvShape& s, long long tiles, int filters, int waves, int ksplit)
 {
+    const int groups_per_wave = filters / kTapGroup;
+    const long long sets = (t.num_groups + waves * groups_per_wave - 1) / (waves * groups_per_wave);
+    const long long blocks = tiles * sets * ksplit;
+    const int resident = std::max(1, std::min(kTapMaxChunk / t.ck, (filters == 16 ? 16 : 20) / waves));
+    const int together = (int)std::min<long long>(resident, (blocks + 255) / 256);
+    const double per_simd = std::max(1.0, waves / 4.0) * together;
+    const double share = per_simd < 2 ? 1.73 - 0.64 * (per_simd - 1) : std::max(0.75, 1.09 - 0.17 * (per_simd - 2));
+    const int chunks = (t.num_chunks + ksplit - 1) / ksplit;          // of one slice
+    const double part = (double)chunks / t.num_chunks, c_out = s.c_out;
+    const double work = filters * (part * (46.7 * h->L.kept + 107.4 * t.segments) / c_out + 93.0 * chunks);
+    const double rounds = (double)blocks / (256.0 * together);
+    const double in_mb = 4e-6 * s.n * s.c_in * s.h * s.w, out_mb = 4e-6 * s.n * c_out * s.ho * s.wo;
+    double us = 5.0 + (rounds < 3 ? std::ceil(rounds) : rounds + 0.5) * (work * share * per_simd + 2000) / 2400 +
+                (in_mb * (1 + 1.33 * (sets - 1)) + out_mb) / (5.65 * together);
+    if (ksplit > 1) us += 4.1 + out_mb * (2 * ksplit + 1) / 8.5;      // the slices' sums, out and back in
+    return us;
+}
+
+// Default tiled variant, microseconds: rounds of three wavefronts per SIMD.
+double tiled_estimate(const patdnn_layer* h, const TiledVariant& v, const ConvShape& s)
+{
+    const long long bands = (long long)s.n * ((s.wo + v.TGX * v.PC - 1) / (v.TGX * v.PC)) * ((s.ho + v.PR - 1) / v.PR);
+    const double waves = (double)((bands + 64 / v.TGX - 1) / (64 / v.TGX)) * ((s.c_out + v.G - 1) / v.G);
+    const double rounds = waves <= 3072 ? 1.0 : waves / 3072 + 0.35;
+    const double per_simd = std::min(3.0, std::max(1.0, waves / 1024));
+    return rounds * (0.36 * s.c_in + 0.22 * v.G * h->L.kept / s.c_out + 8.5) * (0.785 + 0.1075 * (per_simd - 1));
+}
+
+// FKW walk, microseconds: one lane per output pixel, latency of a filter's kernels one after the other.
+double fkw_estimate(const patdnn_layer* h, const ConvShape& s)
+{
+    const double blocks = (double)s.n * s.c_out * (((long long)s.ho * s.wo + 255) / 256);
+    return 5.5 + 0.23 * h->L.kept / s.c_out + 0.004 * std::max(0.0, blocks - 256);
+}
+
+// Partial sums that the library asks room for by itself: 512 MB.
+constexpr size_t kMaxSliceFloats = (size_t)128 << 20;
+
+// `scratch_floats`: room for the partial sums of a split launch (0: no split candidates).  The
+// choice does not depend on fused pooling, so that a pooled output is the pooling of the plain one.
+patdnn_config_t default_config(patdnn_layer* h, const ConvShape& shape, size_t scratch_floats)
+{
+    ConvShape s = shape;
+    s.pool = 0;
     if (h->L.depthwise) return patdnn_config_t{variant_of_extra(kExtraDepthwise), 0, 0, 1};
+    patdnn_config_t best{PATDNN_VARIANT_FKW, 0, 0, 1};
+    const bool taps = taps_fit_layer(h) && taps_fit_input(s) && !h->taps.empty();
+    double best_us = taps ? fkw_estimate(h, s) : 0.0;
     for (int vi : default_variant_order(h)) {
         const TiledVariant& v = tiled_variant(vi);
-        if (!variant_selectable(h, v)) continue;
         int32_t ck = 0, waves = 0;
-        if (resolve_tiled_params(h, v, s, ck, waves)) return patdnn_config_t{vi + 1, ck, waves, 1};
+        if (!variant_selectable(h, v) || !resolve_tiled_params(h, v, s, ck, waves)) continue;
+        if (h->tiled.find(std::make_pair(vi, v.dense ? 0 : ck)) == h->tiled.end()) continue;
+        const double us = taps ? tiled_estimate(h, v, s) : -1.0;
+        if (us < best_us) { best_us = us; best = patdnn_config_t{vi + 1, ck, waves, 1}; }
+        break;
     }
-    return patdnn_config_t{PATDNN_VARIANT_FKW, 0, 0, 1};
+    if (!taps) return best;
+    const long long tiles = tap_tile_count(s);
+    const size_t stride = split_slice_stride((size_t)s.n * s.c_out * s.ho * s.wo);
+    for (int level = 0; level < kTapLevels; ++level) {
+        const int ck = taps_ck(s.c_in, level);
+        auto it = h->taps.find(ck);
+        if (it == h->taps.end()) continue;
+        for (int filters = 8; filters <= 16; filters *= 2)
+            for (int waves = 2; waves <= kMaxTapWaves; waves *= 2) {
+                if (waves > 2 && waves / 2 * filters >= s.c_out) break;             // half of them idle
+                for (int ks = 1; ks <= 16 && ks <= it->second->host.num_chunks; ks *= 2) {
+                    if (ks > 1 && (scratch_floats / ks < stride || ks * stride > kMaxSliceFloats)) break;
+                    const double us = taps_estimate(h, it->second->host, s, tiles, filters, waves, ks);
+                    if (us < best_us) {
+                        best_us = us;
+                        best = patdnn_config_t{variant_of_extra(filters == 8 ? kExtraTaps8 : kExtraTaps16), ck, waves, ks};
+                    }
+                }
+            }
+    }
+    return best;
 }
 
 }  // namespace
@@ -429,6 +584,13 @@ patdnn_status_t patdnn_encode(const patdnn_layer_desc_t* desc, const float* dens
     // build (and upload) the group layout of the default variant; the layouts of the other
     // variants are built when patdnn_set_config or patdnn_tune asks for them
     try {
+        if (taps_fit_layer(h.get()))
+            for (int level = 0; level < kTapLevels; ++level) {
+                const int ck = taps_ck(desc->c_in, level);
+                if (level > 0 && ck < kMinTapChunk) break;
+                st = ensure_taps(h.get(), ck, nullptr);
+                if (st != PATDNN_OK) return st;
+            }
         for (int vi : default_variant_order(h.get()))
             if (variant_selectable(h.get(), tiled_variant(vi))) {
                 st = ensure_tiled(h.get(), vi, default_ck(tiled_variant(vi), desc->c_in), nullptr);
@@ -473,20 +635,36 @@ static bool slices_fit(const float* scratch, size_t scratch_floats, int32_t kspl
            scratch_floats / (size_t)ksplit >= split_slice_stride(full);
 }
 
-// The region that conv2d_impl must clear before this layer's kernels run (none: p == NULL).
-// Mirrors the decisions of conv2d_impl below.
-static ZeroRegion zero_need(patdnn_handle_t h, int32_t n, int32_t h_in, int32_t w_in, int32_t pool, float* output,
-                            float* scratch, size_t scratch_floats)
+// Floats of partial sums that the handle's configuration, or the library's choice, can use.
+static size_t split_room(patdnn_handle_t h, const ConvShape& s)
 {
-    ConvShape s{};
-    if (shape_of(h, n, h_in, w_in, s) != PATDNN_OK || !h->on_device || n == 0) return ZeroRegion{};
+    if (h->cfg.variant < 0 && (!h->on_device || s.n == 0)) return 0;
+    const patdnn_config_t c = h->cfg.variant < 0 ? default_config(h, s, kMaxSliceFloats) : h->cfg;
+    return c.variant > 0 && c.ksplit > 1 ? (size_t)c.ksplit * split_slice_stride((size_t)s.n * s.c_out * s.ho * s.wo) : 0;
+}
+
+// The configuration a call runs: the handle's, or the library's choice.  A pooled layer that
+// splits the input channels needs room for its partial sums; without it the library chooses.
+static patdnn_config_t effective_config(patdnn_handle_t h, const ConvShape& s, const float* scratch, size_t scratch_floats)
+{
     const patdnn_config_t& c = h->cfg;
+    const bool aligned = scratch && (reinterpret_cast<uintptr_t>(scratch) & 15) == 0;
+    const size_t full = (size_t)s.n * s.c_out * s.ho * s.wo;
+    if (c.variant < 0 || (s.pool && c.variant > 0 && c.ksplit > 1 && !(scratch && scratch_floats >= full)))
+        return default_config(h, s, aligned ? scratch_floats : 0);
+    return c;
+}
+
+// The region that must hold zeros before the kernels of configuration `c` run (none: p == NULL).
+static ZeroRegion zero_need(const patdnn_config_t& c, const ConvShape& s, float* output, float* scratch, size_t scratch_floats)
+{
     const bool split = c.variant > 0 && c.ksplit > 1;
-    const size_t full = (size_t)n * s.c_out * s.ho * s.wo;
+    const size_t full = (size_t)s.n * s.c_out * s.ho * s.wo;
     if (split && slices_fit(scratch, scratch_floats, c.ksplit, full)) return ZeroRegion{};   // stores only
-    if (!pool) return split ? ZeroRegion{output, full} : ZeroRegion{};
-    if (split && scratch && scratch_floats >= full) return ZeroRegion{scratch, full};
-    return ZeroRegion{output, (size_t)n * s.c_out * (s.ho / 2) * (s.wo / 2)};
+    if (!s.pool) return split ? ZeroRegion{output, full} : ZeroRegion{};
+    if (split) return ZeroRegion{scratch, full};
+    if (taps_filters(c.variant)) return ZeroRegion{};             // whole pooling windows in registers
+    return ZeroRegion{output, (size_t)s.n * s.c_out * (s.ho / 2) * (s.wo / 2)};
 }
 
 // `scratch` (DEVICE, `scratch_floats` floats, may be NULL): where a layer whose configuration
@@ -523,28 +701,21 @@ static patdnn_status_t conv2d_impl(patdnn_handle_t h, const float* input, int32_
         s.zero_next_count = handoff->next.count;
         s.zero_next_done = &handoff->done;
     }
-    patdnn_config_t c = h->cfg;
-    // a pooled layer that splits the input channels needs room for its partial sums; without
-    // it the layer runs its default configuration
-    const bool split_pool = pool && c.variant > 0 && c.ksplit > 1;
-    const bool have_room = scratch && scratch_floats >= (size_t)n * s.c_out * s.ho * s.wo;
-    if (c.variant < 0 || (split_pool && !have_room)) c = default_config(h, s);
-    if (pool && !(split_pool && have_room) &&
-        !(s.pre_zeroed == output && s.pre_zeroed_count >= (size_t)n * s.c_out * oh * ow)) {
-        hipError_t e = launch_fill_zero(output, (size_t)n * s.c_out * oh * ow, stream);
-        if (e != hipSuccess) return hip_fail(e, "zeroing the pooled output");
-    }
-    st = run_config(h, c, s, input, bias, output, stream, scratch, scratch_floats);
-    if (st == PATDNN_EUNSUPPORTED && h->cfg.variant > 0 && h->cfg_tuned) {
-        // a configuration tuned for another input size may not fit this one; a configuration
-        // the caller set explicitly is never replaced: the error goes back instead
-        c = default_config(h, s);
-        if (pool && split_pool && have_room) {
-            hipError_t e = launch_fill_zero(output, (size_t)n * s.c_out * oh * ow, stream);
+    auto run = [&](const patdnn_config_t& c) -> patdnn_status_t {
+        // a pooled output that kernels fold into is cleared here, the target of split launches by
+        // their launcher
+        const ZeroRegion z = zero_need(c, s, output, scratch, scratch_floats);
+        if (z.p && pool && z.p == output && !(s.pre_zeroed == z.p && s.pre_zeroed_count >= z.count)) {
+            hipError_t e = launch_fill_zero(z.p, z.count, stream);
             if (e != hipSuccess) return hip_fail(e, "zeroing the pooled output");
         }
-        st = run_config(h, c, s, input, bias, output, stream, scratch, scratch_floats);
-    }
+        return run_config(h, c, s, input, bias, output, stream, scratch, scratch_floats);
+    };
+    st = run(effective_config(h, s, scratch, scratch_floats));
+    // a configuration tuned for another input size may not fit this one; a configuration the
+    // caller set explicitly is never replaced: the error goes back instead
+    if (st == PATDNN_EUNSUPPORTED && h->cfg.variant > 0 && h->cfg_tuned)
+        st = run(default_config(h, s, scratch && (reinterpret_cast<uintptr_t>(scratch) & 15) == 0 ? scratch_floats : 0));
     return st;
 }
 
@@ -559,9 +730,7 @@ size_t patdnn_workspace_floats(patdnn_handle_t h, int32_t n, int32_t h_in, int32
 {
     ConvShape s{};
     if (shape_of(h, n, h_in, w_in, s) != PATDNN_OK) return 0;
-    const patdnn_config_t& c = h->cfg;
-    if (!(c.variant > 0 && c.ksplit > 1)) return 0;
-    return (size_t)c.ksplit * split_slice_stride((size_t)n * s.c_out * s.ho * s.wo);
+    return split_room(h, s);
 }
 
 patdnn_status_t patdnn_conv2d_ws(patdnn_handle_t h, const float* input, int32_t n, int32_t h_in, int32_t w_in,
@@ -719,6 +888,7 @@ patdnn_status_t patdnn_layout_stats(patdnn_handle_t h, patdnn_stats_t* out)
         out->distinct_filter_lengths = (int32_t)(std::unique(len.begin(), len.end()) - len.begin());
     }
     for (const auto& kv : h->tiled) out->tiled_bytes += (int64_t)kv.second->host.bytes();
+    for (const auto& kv : h->taps) out->tiled_bytes += (int64_t)kv.second->host.bytes();
     if (!h->tiled.empty()) {
         const Tiled& t = h->tiled.begin()->second->host;
         out->filter_groups = t.num_groups;
@@ -764,6 +934,28 @@ patdnn_status_t patdnn_set_config(patdnn_handle_t h, const patdnn_config_t* cfg)
             return fail(PATDNN_ENOMEM, "out of host memory");
         }
         h->cfg = patdnn_config_t{cfg->variant, 0, 0, 1};
+        h->cfg_tuned = false;
+        return PATDNN_OK;
+    }
+    if (taps_filters(cfg->variant)) {
+        if (!taps_fit_layer(h)) return fail(PATDNN_EUNSUPPORTED, "variant cannot run this layer");
+        if (cfg->ck < 0 || cfg->waves < 0 || cfg->waves > kMaxTapWaves || cfg->ksplit < 0 || cfg->ksplit > 64)
+            return fail(PATDNN_EINVAL, "ck / waves / ksplit out of range");
+        patdnn_config_t c = *cfg;
+        const int c_in = h->L.desc.c_in;
+        if (c.ck == 0) c.ck = taps_ck(c_in, 0);
+        c.ck = std::min(c.ck, c_in);
+        if (c.ck > kTapMaxChunk) return fail(PATDNN_EUNSUPPORTED, "ck exceeds the LDS budget");
+        if (c.waves == 0) c.waves = 8;
+        if (c.ksplit < 1) c.ksplit = 1;
+        if (c.ksplit > (c_in + c.ck - 1) / c.ck) return fail(PATDNN_EUNSUPPORTED, "ksplit exceeds the number of channel chunks");
+        try {
+            patdnn_status_t st = ensure_taps(h, c.ck, nullptr);
+            if (st != PATDNN_OK) return st;
+        } catch (const std::bad_alloc&) {
+            return fail(PATDNN_ENOMEM, "out of host memory");
+        }
+        h->cfg = c;
         h->cfg_tuned = false;
         return PATDNN_OK;
     }
@@ -864,6 +1056,14 @@ patdnn_status_t patdnn_tune_ws(patdnn_handle_t h, const float* input, int32_t n,
                 }
             }
     }
+    if (taps_fit_layer(h) && taps_fit_input(s))
+        for (const auto& layout : h->taps)
+            for (int filters = 8; filters <= 16; filters *= 2)
+                for (int waves = 2; waves <= kMaxTapWaves; waves *= 2) {
+                    if (waves > 2 && waves / 2 * filters >= s.c_out) break;
+                    for (int ks = 1; ks <= 16 && ks <= layout.second->host.num_chunks; ks *= 2)
+                        cands.push_back(patdnn_config_t{variant_of_extra(filters == 8 ? kExtraTaps8 : kExtraTaps16), layout.first, waves, ks});
+                }
     if (h->L.depthwise) cands.push_back(patdnn_config_t{variant_of_extra(kExtraDepthwise), 0, 0, 1});
     cands.push_back(patdnn_config_t{PATDNN_VARIANT_FKW, 0, 0, 1});
 
@@ -930,12 +1130,17 @@ patdnn_status_t patdnn_tune_ws(patdnn_handle_t h, const float* input, int32_t n,
     h->cfg_tuned = true;
     // keep the winner's layout and the default variant's; free the others
     {
-        const patdnn_config_t dflt = default_config(h, s);
+        const std::vector<int> order = default_variant_order(h);
+        auto default_layout = [&](int vi, int ck) {
+            for (int o : order)
+                if (variant_selectable(h, tiled_variant(o))) return vi == o && (tiled_variant(o).dense || ck == default_ck(tiled_variant(o), s.c_in));
+            return false;
+        };
         for (auto it = h->tiled.begin(); it != h->tiled.end();) {
             const int vnum = it->first.first + 1;
             const bool dense = tiled_variant(it->first.first).dense;
             const bool keep = (vnum == best_cfg.variant && (dense || it->first.second == best_cfg.ck)) ||
-                              (vnum == dflt.variant && (dense || it->first.second == dflt.ck));
+                              default_layout(it->first.first, it->first.second);
             it = keep ? std::next(it) : h->tiled.erase(it);
         }
     }
@@ -1057,10 +1262,6 @@ struct patdnn_stack {
 
 namespace {
 
-// A stack gives its split layers one partial-sum buffer per channel slice up to this size
-// (512 MB); a layer that would need more adds its slices up with atomics instead.
-constexpr size_t kMaxSliceFloats = (size_t)128 << 20;
-
 // every layer on `stream`, intermediates alternating between b0 and b1
 patdnn_status_t stack_launch(patdnn_stack* s, const float* input, float* output, float* b0, float* b1,
                              float* split, size_t split_floats, hipStream_t stream)
@@ -1081,8 +1282,11 @@ patdnn_status_t stack_launch(patdnn_stack* s, const float* input, float* output,
         hand.pre_zeroed = zeroed;
         if (i + 1 < L) {
             const patdnn_stack_layer_t& nx = s->layers[i + 1];
-            hand.next = zero_need(nx.layer, s->n, s->in_h[i + 1], s->in_w[i + 1], nx.pool2, dst_of(i + 1), split,
-                                  split_floats);
+            ConvShape ns{};
+            if (shape_of(nx.layer, s->n, s->in_h[i + 1], s->in_w[i + 1], ns) == PATDNN_OK) {
+                ns.pool = nx.pool2 ? 1 : 0;
+                hand.next = zero_need(effective_config(nx.layer, ns, split, split_floats), ns, dst_of(i + 1), split, split_floats);
+            }
             if (hand.next.p == dst) hand.next = ZeroRegion{};     // this layer's own output: cannot happen
         }
         patdnn_status_t st = conv2d_impl(ly.layer, src, s->n, s->in_h[i], s->in_w[i], ly.bias, dst, ly.fuse_relu,
@@ -1126,11 +1330,9 @@ patdnn_status_t patdnn_stack_create(const patdnn_stack_layer_t* layers, int32_t 
         if (ly.pool2) s->split_floats_min = std::max(s->split_floats_min, full);
         // one buffer per channel slice for the layers that are configured to split now (a layer
         // reconfigured later uses the room there is, or adds its slices up with atomics)
-        const patdnn_config_t& cfg = ly.layer->cfg;
-        if (cfg.variant > 0 && cfg.ksplit > 1) {
-            const size_t want = (size_t)cfg.ksplit * split_slice_stride(full);
-            if (want <= kMaxSliceFloats) s->split_floats = std::max(s->split_floats, want);
-        }
+        cs.pool = ly.pool2 ? 1 : 0;
+        const size_t want = split_room(ly.layer, cs);
+        if (want <= kMaxSliceFloats) s->split_floats = std::max(s->split_floats, want);
         if (i + 1 < num_layers) {
             s->max_intermediate = std::max(s->max_intermediate, (size_t)n * c * h * w);
             s->buf_floats[i & 1] = std::max(s->buf_floats[i & 1], (size_t)n * c * h * w);

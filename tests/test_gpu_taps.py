@@ -1,0 +1,102 @@
+"""GPU parity of the tap-product kernel (csrc/kernel_taps.hip) where it can go wrong: tile edges
+(images of 14 to 17 and 29 to 31 rows and columns), several images in one tile, filter counts
+around its groups, channel counts around its chunks, empty filters, every pattern, split launches
+with and without a workspace, fused pooling - against the oracle, element by element."""
+
+import numpy as np
+import pytest
+
+from paper_2001_00138_amd import binding as B
+from paper_2001_00138_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+# fp32 sums in any order against fp64: at most K * 2^-24 of the sum of the terms' magnitudes with
+# K <= 4 * 160, and in practice sqrt(K) * 2^-24; 1e-5 of the largest output is far above both
+TOL = 1e-5
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    B.lib()
+    return torch
+
+
+# c_out, c_in, n, h, w, pad, keep, patterns, (filters, ck, waves, ksplit)
+CASES = [
+    (8, 16, 1, 14, 14, 1, 0.5, 8, (8, 0, 1, 1)),          # one tile, one group
+    (9, 7, 2, 15, 16, 1, 0.5, 8, (16, 3, 2, 2)),          # 15: the last size of a single tile; 16: the first of two
+    (24, 33, 2, 17, 15, 1, 0.3, 12, (8, 33, 3, 1)),
+    (40, 20, 2, 29, 31, 1, 0.3, 8, (16, 8, 16, 3)),       # last tile of 15 outputs, and of 3
+    (17, 20, 3, 30, 29, 0, 0.4, 8, (8, 20, 2, 1)),
+    (16, 12, 3, 16, 17, 0, 0.4, 6, (8, 5, 4, 2)),         # no padding: 16 columns are one tile of 14 outputs
+    (130, 129, 5, 7, 7, 1, 0.25, 8, (16, 65, 8, 2)),      # four images in a tile, the last tile not full
+    (12, 10, 70, 3, 3, 1, 1.0, 8, (8, 10, 2, 1)),         # sixteen images in a tile
+    (11, 9, 9, 5, 8, 0, 0.6, 8, (8, 4, 1, 2)),
+    (8, 160, 1, 20, 15, 1, 0.02, 8, (8, 160, 1, 1)),      # the largest chunk; filters without kernels
+    (56, 56, 2, 15, 18, 1, 1.0, 56, (16, 56, 4, 1)),      # every pattern
+    (1, 1, 1, 3, 40, 1, 1.0, 8, (8, 1, 1, 1)),
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_tap_product_kernel(torch, oracle, case):
+    from oracle import stack as ostack
+    c_out, c_in, n, h, w, pad, keep, patterns, (filters, ck, waves, ksplit) = case
+    rng = np.random.default_rng(c_out * 1000 + h * 40 + w)
+    lib = wl.pattern_library(wl.PATTERN_SEED, patterns) if patterns < 56 else wl.pattern_universe()
+    ids = rng.integers(0, patterns, (c_out, c_in), dtype=np.uint8)
+    mask = (rng.random((c_out, c_in)) < keep).astype(np.uint8)
+    wt = rng.standard_normal((c_out, c_in, 3, 3)).astype(np.float32)
+    bias = rng.standard_normal(c_out).astype(np.float32)
+    x = rng.standard_normal((n, c_in, h, w)).astype(np.float32)
+    full = oracle.conv2d(wt, ids, mask, lib, x, bias, pad=pad, relu=True, skip_removed=True)
+    names = {B.patdnn_variant_name(v): v for v in range(B.patdnn_num_variants())}
+    L = B.Layer(wt, ids, mask, lib, pad=pad)
+    L.set_config(names[f"taps_f{filters}"], ck, waves, ksplit)
+    xt, bt = torch.from_numpy(x).cuda(), torch.from_numpy(bias).cuda()
+    need, guard = L.workspace_floats(n, h, w), 1024
+    for pool in (False, True):
+        ref = ostack.maxpool2x2(full) if pool else full
+        if 0 in ref.shape:
+            continue
+        for room in {need, 0}:
+            print(f"  {case} pool={pool} workspace={room}", flush=True)
+            numel = int(np.prod(ref.shape))
+            buf = torch.full((numel + 2 * guard,), 777.0, device="cuda")
+            wbuf = torch.full((room + 2 * guard,), float("nan"), device="cuda")
+            wbuf[:guard] = wbuf[guard + room:] = 555.0
+            out = buf[guard:guard + numel].view(ref.shape)
+            L.conv2d_ws(xt, bt, out, workspace=wbuf[guard:guard + room] if room else None, relu=True, pool=pool)
+            torch.cuda.synchronize()
+            for b, k, v in ((buf, numel, 777.0), (wbuf, room, 555.0)):
+                assert bool((b[:guard] == v).all()) and bool((b[guard + k:] == v).all())
+            err = float(np.abs(out.cpu().numpy().astype(np.float64) - ref).max() / np.abs(ref).max())
+            assert err <= TOL, (pool, room, err)
+    L.close()
+
+
+@pytest.mark.parametrize("shape", [(1, 16, 16, 32), (1, 64, 512, 14), (64, 96, 200, 7), (3, 200, 72, 45), (40, 40, 24, 60)])
+def test_chosen_configuration(torch, oracle, shape):
+    """The library's own choice over the sizes at which it changes (walk, split and unsplit
+    launches, one and two groups per wavefront), with the workspace it asks for."""
+    n, c_in, c_out, side = shape
+    rng = np.random.default_rng(sum(shape))
+    lib = wl.pattern_library(wl.PATTERN_SEED)
+    ids = rng.integers(0, 8, (c_out, c_in), dtype=np.uint8)
+    mask = (rng.random((c_out, c_in)) < 1 / 3.6).astype(np.uint8)
+    wt = rng.standard_normal((c_out, c_in, 3, 3)).astype(np.float32)
+    x = rng.standard_normal((n, c_in, side, side)).astype(np.float32)
+    k = min(n, 2)
+    ref = oracle.conv2d(wt, ids, mask, lib, x[-k:], None, skip_removed=True)
+    L = B.Layer(wt, ids, mask, lib)
+    need = L.workspace_floats(n, side, side)
+    xt = torch.from_numpy(x).cuda()
+    for room in {need, 0}:
+        ws = torch.full((room,), float("nan"), device="cuda") if room else None
+        got = L.conv2d_ws(xt, None, workspace=ws)[-k:].cpu().numpy()
+        assert float(np.abs(got.astype(np.float64) - ref).max() / np.abs(ref).max()) <= TOL, room
+    assert L.get_config()["variant"] == -1
+    L.close()
