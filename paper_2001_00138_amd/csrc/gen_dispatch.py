@@ -56,7 +56,8 @@ that it fits its slot, so the offsets the encoder computes are the real ones.
 
 Run by ``buildlib.py``; output goes to ``csrc/gen/`` and is not committed.
 ``program()`` returns the assembly as a list of lines; the host tests execute those
-lines on a small model of the machine against the encoder's streams.
+lines on a small model of the machine against the encoder's streams.  ``vector_weights()`` is
+applied on top of it for the variants whose blocks are long enough (``vector_weights_pay``).
 """
 
 import itertools
@@ -98,6 +99,13 @@ def pow2_at_least(n):
     return p
 
 
+def vector_weights_pay(nacc):
+    """Blocks of 56 multiply-adds (7 x 2 patches) gain more from weights in vector registers than the
+    four moves cost; blocks of 16 and 28 ran at the same speed with them or slower (a wavefront
+    alone on its SIMD issues at the old rate either way: 4 % slower on small launches)."""
+    return 4 * nacc >= 48
+
+
 def geometry(G, PR, PC, S, TGX, MODE):
     WR, WC = (PR - 1) * S + 3, (PC - 1) * S + 3
     band_cols = (TGX * PC - 1) * S + 3
@@ -112,13 +120,14 @@ def geometry(G, PR, PC, S, TGX, MODE):
         band_stride = band_cols
     nacc = PR * PC
     threaded = bool(MODE & 2)
-    tail = 7 if threaded else 1                        # 4-byte scalar instructions after the FMAs
+    vector = vector_weights_pay(nacc)
+    tail = (4 if vector else 0) + (7 if threaded else 1)   # 4-byte moves of the weights, scalar instructions
     block_bytes = pow2_at_least(4 * (4 * nacc + tail))
     num_ctrl = T_NUM_CTRL if threaded else C_NUM_CTRL
     return dict(WR=WR, WC=WC, pitch=pitch, band_stride=band_stride, band_cols=band_cols,
                 band_major=bool(MODE & 8), nacc=nacc, nwin=WR * WC, block_bytes=block_bytes,
                 table_off=num_ctrl * CTRL_SLOT, sets=2 if MODE & 1 else 1, threaded=threaded,
-                wide=bool(MODE & 4),
+                wide=bool(MODE & 4), vector=vector,
                 records=T_RECORDS if threaded else C_RECORDS, ctrl_bytes=CTRL_SLOT,
                 clobber=T_CLOBBER if threaded else C_CLOBBER)
 
@@ -372,8 +381,32 @@ def program(G, PR, PC, S, TGX, MODE):
     return build(G, PR, PC, S, TGX, MODE, g), g
 
 
+def vector_weights(lines, g):
+    """The program with the weights of every FMA block in vector registers.  A vector
+    instruction whose operands are all vector registers issues every 2 cycles as long as a
+    SIMD has a second wavefront to pair with; one that reads a scalar register takes 4
+    (measured: 2.4 against 4.2 clocks per v_fmac_f32 of a block).  A block therefore moves its four weights
+    over first: 4 moves at the old rate for 4 * PR * PC multiply-adds at the new one."""
+    # the address register is free inside a block
+    assert g["wide"]                                  # fixed registers follow the window
+    w = ["%[addr]"] + [f"v{WIDE_WINDOW_BASE + g['sets'] * g['nwin'] + t}" for t in range(3)]
+    out, inside = [], False
+    for line in lines:
+        fmac = line.startswith("v_fmac_f32")
+        if fmac and not inside:
+            out += [f"v_mov_b32 {w[t]}, s{W + t}" for t in range(4)]
+        inside = fmac
+        if fmac:
+            acc, scalar, x = line[len("v_fmac_f32"):].split(",")
+            line = f"v_fmac_f32{acc}, {w[int(scalar.strip()[1:]) - W]},{x}"
+        out.append(line)
+    return out
+
+
 def generate(G, PR, PC, S, TGX, MODE):
     lines, g = program(G, PR, PC, S, TGX, MODE)
+    if g["vector"]:
+        lines = vector_weights(lines, g)
     nacc, nwin, sets = g["nacc"], g["nwin"], g["sets"]
     L = []
     emit = L.append
@@ -413,7 +446,7 @@ def generate(G, PR, PC, S, TGX, MODE):
     lo, hi = g["clobber"]
     clob = ", ".join(f'"s{i}"' for i in range(lo, hi + 1))
     if g["wide"]:
-        clob += ", " + ", ".join(f'"v{WIDE_WINDOW_BASE + i}"' for i in range(sets * nwin))
+        clob += ", " + ", ".join(f'"v{WIDE_WINDOW_BASE + i}"' for i in range(sets * nwin + (3 if g["vector"] else 0)))
     emit(f"            : {outs}")
     emit(f"            : {ins}")
     emit(f'            : {clob}, "scc", "memory");')

@@ -237,15 +237,6 @@ __global__ __launch_bounds__(512) void tiled_conv_kernel(TiledArgs a)
     const int my_band = band0 + lb;
     // when TGX does not divide 64 the last lanes of the wavefront have no band
     const bool lane_ok = (64 % TGX == 0) || lb < NB;
-    const bool band_ok = lane_ok && my_band < a.num_bands;
-    int img = 0, oy0 = 0, ox0 = 0;
-    if (band_ok) {
-        const int t = (int)fast_div((uint32_t)my_band, a.div_bx), bxi = my_band - t * a.bx;
-        img = (int)fast_div((uint32_t)t, a.div_by);
-        const int byi = t - img * a.by;
-        oy0 = byi * PR;
-        ox0 = (bxi * TGX + gx) * PC;
-    }
     const int lane_off = lane_ok ? lb * GEO::BSTRIDE + gx * PC * S : 0;   // floats, inside one staged channel
 
     float acc[G][GEO::NACC];
@@ -357,6 +348,18 @@ __global__ __launch_bounds__(512) void tiled_conv_kernel(TiledArgs a)
             }
         }
         TL_MARK(3);                               // the chunk's kernels
+    }
+
+    // where the patch lies (worked out here: registers that would be held through the loop for it
+    // decide how many wavefronts fit a SIMD)
+    const bool band_ok = lane_ok && my_band < a.num_bands;
+    int img = 0, oy0 = 0, ox0 = 0;
+    if (band_ok) {
+        const int t = (int)fast_div((uint32_t)my_band, a.div_bx), bxi = my_band - t * a.bx;
+        img = (int)fast_div((uint32_t)t, a.div_by);
+        const int byi = t - img * a.by;
+        oy0 = byi * PR;
+        ox0 = (bxi * TGX + gx) * PC;
     }
 
     // ---- epilogue: bias, ReLU, scatter to the original output channel

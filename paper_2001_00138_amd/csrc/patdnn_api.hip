@@ -455,7 +455,7 @@ double tiled_estimate(const patdnn_layer* h, const TiledVariant& v, const ConvSh
     const double waves = (double)((bands + 64 / v.TGX - 1) / (64 / v.TGX)) * ((s.c_out + v.G - 1) / v.G);
     const double rounds = waves <= 3072 ? 1.0 : waves / 3072 + 0.35;
     const double per_simd = std::min(3.0, std::max(1.0, waves / 1024));
-    return rounds * (0.36 * s.c_in + 0.22 * v.G * h->L.kept / s.c_out + 8.5) * (0.785 + 0.1075 * (per_simd - 1));
+    return rounds * (0.336 * s.c_in + 0.195 * v.G * h->L.kept / s.c_out + 8.06) * (0.785 + 0.1075 * (per_simd - 1));
 }
 
 // FKW walk, microseconds: one lane per output pixel, latency of a filter's kernels one after the other.
