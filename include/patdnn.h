@@ -128,8 +128,11 @@ patdnn_status_t patdnn_conv2d(patdnn_handle_t h, const float* input, int32_t n, 
  * handle's fp32 weights rounded to binary16 (nearest, ties to even; done once by
  * patdnn_encode), the bias stays fp32, every product and sum is fp32, and the result is
  * rounded to binary16 once when it is stored.  Depthwise layers run the depthwise kernel
- * (bound by HBM bandwidth: half the bytes, about half the time); all other layers run the
- * filter-major FKW kernel - the tiled kernels are fp32 only.  Otherwise as patdnn_conv2d.
+ * (bound by HBM bandwidth: half the bytes, about half the time); all other layers run on the
+ * matrix cores, over weights that patdnn_encode has expanded to all nine taps with zeros
+ * (layers whose expanded weights exceed 256 MB: the filter-major FKW kernel).  A weight that
+ * pruning removed meets no input all the same: an infinite or NaN input reaches the outputs of
+ * kept weights only.  Otherwise as patdnn_conv2d.
  */
 patdnn_status_t patdnn_conv2d_f16(patdnn_handle_t h, const void* input, int32_t n, int32_t h_in, int32_t w_in,
                                   const float* bias, void* output, int32_t fuse_relu, void* stream);

@@ -1,0 +1,487 @@
+// 3x3 convolution on binary16 storage, on the matrix cores: the half-precision storage of the
+// paper's GPU runs (section 6.1) for pruned and dense layers, stride 1 or 2.
+//
+// v_mfma_f32_32x32x16_f16 multiplies 32 filters x 16 input channels with 16 channels x 32
+// pixels in 32 cycles: sixteen times the rate of the vector ALU.  That is more than the factor
+// 8.1 of multiply-adds which connectivity and pattern pruning leave out (at a keep ratio of 1/3.6
+// and four of nine taps), and a kept kernel by itself fills no matrix instruction.  The layer is
+// therefore expanded once, at encode time, to all nine taps with zeros where pruning removed a
+// weight, and runs as an implicit GEMM: products of binary16 values are exact, sums are fp32 as
+// before, and a zero adds nothing.
+//
+// The one case where a zero weight is not nothing is an input that is infinite or NaN (0 * inf).
+// Every output such an input reaches through any of the nine taps then has a sum that is not
+// finite, so the wavefront looks at its sums once, at the end, and computes the pixels concerned
+// again from the FKW arrays, whose walk meets the kept weights only.
+//
+// Work decomposition
+//   * Output columns are cut into strips of at most 32; the pixels of a strip are numbered
+//     row after row through all images, and a tile is PIX consecutive ones: no tile is padded
+//     out to an image's edge (the rows of all images, each with its zero padding, are
+//     thought of as one tall image of vh rows each).
+//   * A wavefront owns FM x PN blocks of 32 filters x 32 pixels; a workgroup WF x WP of
+//     them, and WK wavefronts share a block and take 16 input channels each of a chunk of 16 * WK
+//     (their sums meet in LDS): layers with few tiles.
+//   * A chunk of the tile's input rows is staged in LDS as [8 channels][row][column] of
+//     16 bytes, which is the order in which a lane wants its eight channels of a pixel; a
+//     wavefront gathers 64 pixels x 8 channels at a time with 2-byte loads (any row length,
+//     any alignment), zero where the image ends.  Two buffers, the next chunk's loads in
+//     flight while this one is computed.
+//   * Weights are read from L2 in fragment order, 16 bytes per lane.
+//
+// What bounds it: 128 -> 128 at 56 x 56, 64 images (59 GFLOP with the zeros, 51 MB in and out) takes
+// 94 us, 0.63 PFLOP/s, where the walk over the kept weights took 1990; one image of 256 -> 256 at
+// 28 x 28 9 us (57).  The gathering of eight channels is the larger part: 2-byte loads
+// took 124 us where 4-byte loads take 94, and it is the texture path that they share with the
+// weights; the rows staged are 1.4 times the pixels computed.
+#include <hip/hip_fp16.h>
+
+#include <algorithm>
+#include <atomic>
+
+#include "kernels.hpp"
+
+namespace patdnn {
+
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef float float16v __attribute__((ext_vector_type(16)));
+
+struct F16Args {
+    const __half* in;
+    const float* bias;
+    __half* out;
+    const uint4* weights;            // fragments [filter block][channel step][tap][lane]
+    // the FKW arrays (binary16 weights), for sums that are not finite
+    const int32_t *offset, *reorder, *index, *stride;
+    const __half* fkw_weight;
+    const uint16_t* masks;
+    int32_t num_patterns, taps;
+    int32_t n, c_in, c_out, h, w, ho, wo, conv_stride, pad, relu;
+    int32_t vh, sw, strips, pitch, npp;      // rows per image, strip width, strips, staged columns, staged pixels / 64 * 64
+    int32_t lead, pair_out;                  // columns staged before output column 0; output rows of aligned pairs
+    int32_t steps, fblocks, fsets, tiles;    // channel steps of 16, filter blocks, filter sets, tiles of a strip
+    int32_t pixels;                          // of a strip: n * ho * sw
+    FastDiv div_fsets, div_tiles, div_sw, div_ho, div_vh, div_pitch;
+};
+
+// Staging buffers: wavefronts that share a block stage so many channels that a second buffer would
+// cost more workgroups per CU than it hides.
+constexpr int f16_buffers(int wk) { return wk > 1 ? 1 : 2; }
+
+// One output from the FKW arrays: stored filter s, like the FKW kernel.
+static __device__ float fkw_output(const F16Args& a, int s, int img, int oy, int ox)
+{
+    const int32_t kbase = a.offset[s];
+    const int32_t* st = a.stride + (size_t)s * (a.num_patterns + 1);
+    const size_t plane = (size_t)a.h * a.w;
+    const __half* in_img = a.in + (size_t)img * a.c_in * plane;
+    float acc = 0.0f;
+    for (int p = 0; p < a.num_patterns; ++p)
+        for (int32_t k = kbase + st[p]; k < kbase + st[p + 1]; ++k) {
+            unsigned m = a.masks[p];
+            for (int t = 0; t < a.taps; ++t) {
+                const int pos = __builtin_ctz(m);
+                m &= m - 1;
+                const int y = oy * a.conv_stride + pos / 3 - a.pad, x = ox * a.conv_stride + pos % 3 - a.pad;
+                const bool ok = y >= 0 && y < a.h && x >= 0 && x < a.w;
+                const float v = ok ? __half2float(in_img[(size_t)a.index[k] * plane + (size_t)y * a.w + x]) : 0.0f;
+                acc = fmaf(__half2float(a.fkw_weight[(size_t)k * a.taps + t]), v, acc);
+            }
+        }
+    return acc;
+}
+
+// PAIR: rows of whole aligned pairs of pixels (see f16_tiles): staged two pixels per load, and
+// stored two pixels at a time where the output's rows are the same.
+template <int FM, int PN, int WF, int WP, int WK, bool PAIR>
+__global__ __launch_bounds__(64 * WF * WP * WK, 2) void f16_conv_kernel(F16Args a)
+{
+    extern __shared__ uint4 lds4[];
+    constexpr int WAVES = WF * WP * WK, PIX = 32 * PN * WP, G8 = 2 * WK;
+    constexpr int UPX = PAIR ? 2 : 1, AHEAD = 4 / UPX, BUFS = f16_buffers(WK);
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wk = wave % WK, wp = wave / WK % WP, wf = wave / (WK * WP);
+    // each XCD works on a contiguous range: the workgroups that stage the same tile share an L2
+    const int per_xcd = gridDim.x >> 3, rank = blockIdx.x >> 3;
+    const int bid = rank < per_xcd ? (blockIdx.x & 7) * per_xcd + rank : blockIdx.x;
+    const int tile_all = (int)fast_div((uint32_t)bid, a.div_fsets);
+    const int fset = bid - tile_all * a.fsets;
+    const int strip = (int)fast_div((uint32_t)tile_all, a.div_tiles);
+    const int pix0 = (tile_all - strip * a.tiles) * PIX;
+
+    auto split_row = [&](int q, int& img, int& oy, int& sx) {
+        const int r = (int)fast_div((uint32_t)q, a.div_sw);
+        sx = q - r * a.sw;
+        img = (int)fast_div((uint32_t)r, a.div_ho);
+        oy = r - img * a.ho;
+    };
+    int img0, oy0, sx0;
+    split_row(pix0, img0, oy0, sx0);
+    const int vrow0 = img0 * a.vh + oy0 * a.conv_stride;
+    const int plane = a.h * a.w;
+    const size_t tail = (size_t)(a.n - img0) * a.c_in * plane * 2;
+    const char* in_blk = (const char*)(a.in + (size_t)img0 * a.c_in * plane);
+
+    // ---- byte offset, from the tile's first image, of every staged pixel in its channel
+    // (~0u: padding, reads as zero)
+    const int last = min(pix0 + PIX, a.pixels) - 1;
+    int img1, oy1, sx1;
+    split_row(last, img1, oy1, sx1);
+    // units (64 lanes) that this tile's rows take; the buffers are sized for the largest tile
+    const int npb = (((img1 * a.vh + oy1 * a.conv_stride - vrow0 + 3) * a.pitch + 64 * UPX - 1) / (64 * UPX));
+    unsigned* const voffs = reinterpret_cast<unsigned*>(lds4 + BUFS * G8 * a.npp);
+    for (int e = threadIdx.x; e < npb * 64; e += 64 * WAVES) {
+        const int rr = (int)fast_div((uint32_t)(e * UPX), a.div_pitch), cc = e * UPX - rr * a.pitch;
+        const int v = vrow0 + rr, img = (int)fast_div((uint32_t)v, a.div_vh);
+        const int y = v - img * a.vh - a.pad, x = strip * a.sw * a.conv_stride + cc - a.lead;
+        const bool ok = img < a.n && y >= 0 && y < a.h && x >= 0 && x < a.w;
+        voffs[e] = ok ? 2u * (unsigned)((img - img0) * a.c_in * plane + y * a.w + x) : ~0u;
+    }
+
+    // ---- this lane's pixels: where they lie in a staged group of eight channels (in 16-byte units)
+    int base[PN];
+#pragma unroll
+    for (int p = 0; p < PN; ++p) {
+        const int q = min(pix0 + (wp * PN + p) * 32 + l32, last);
+        int img, oy, sx;
+        split_row(q, img, oy, sx);
+        base[p] = (img * a.vh + oy * a.conv_stride - vrow0) * a.pitch + sx * a.conv_stride + (a.lead - a.pad) + (2 * wk + half) * a.npp;
+    }
+    int fb[FM];
+#pragma unroll
+    for (int f = 0; f < FM; ++f) fb[f] = min((fset * WF + wf) * FM + f, a.fblocks - 1);
+
+    float16v acc[FM][PN];
+#pragma unroll
+    for (int f = 0; f < FM; ++f)
+#pragma unroll
+        for (int p = 0; p < PN; ++p) acc[f][p] = float16v{};
+
+    // ---- staging: unit u = 64 pixels (pairs) x 8 channels, units wave, wave + WAVES, ... of a chunk
+    const int units = npb * G8;
+    // out of range (reads as zero) from the end of the tensor on, and for ~0u
+    __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)in_blk, 0, (int)(unsigned)std::min<size_t>(tail, 0x80000000u), 0x00020000);
+    struct Unit { uint4 v[UPX]; };
+    // unit u is block u / G8 of group u % G8
+    auto load_unit = [&](int u, int c0) __attribute__((always_inline)) -> Unit {
+        const int off = (int)voffs[u / G8 * 64 + lane], cg = c0 + u % G8 * 8;
+        unsigned v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            // past the last channel its weights are zero; which pixel they meet does not matter
+            const int soff = min(cg + j, a.c_in - 1) * plane * 2;
+            if constexpr (PAIR) v[j] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, off, soff, 0);
+            else v[j] = (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rsrc, off, soff, 0);
+        }
+        Unit t;
+        if constexpr (PAIR) {
+            // low halves, then high halves, of two channels
+            auto lo = [&](int j) { return __builtin_amdgcn_perm(v[j + 1], v[j], 0x05040100u); };
+            auto hi = [&](int j) { return __builtin_amdgcn_perm(v[j + 1], v[j], 0x07060302u); };
+            t.v[0] = make_uint4(lo(0), lo(2), lo(4), lo(6));
+            t.v[1] = make_uint4(hi(0), hi(2), hi(4), hi(6));
+        } else {
+            t.v[0] = make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
+        }
+        return t;
+    };
+    auto store_unit = [&](int u, int buf, const Unit& t) __attribute__((always_inline)) {
+        uint4* dst = lds4 + (buf * G8 + u % G8) * a.npp + (u / G8 * 64 + lane) * UPX;
+#pragma unroll
+        for (int k = 0; k < UPX; ++k) dst[k] = t.v[k];
+    };
+    Unit ahead[AHEAD];
+    auto fetch = [&](int c0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k)
+            if (wave + k * WAVES < units) ahead[k] = load_unit(wave + k * WAVES, c0);
+    };
+    __syncthreads();                                  // the offsets
+    fetch(0);
+    int buf = 0;
+    for (int c0 = 0; c0 < 16 * a.steps; c0 += 16 * WK) {
+        if (BUFS == 1 && c0) __syncthreads();         // everyone has left the previous chunk
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k)
+            if (wave + k * WAVES < units) store_unit(wave + k * WAVES, buf, ahead[k]);
+        for (int u = wave + AHEAD * WAVES; u < units; u += WAVES) store_unit(u, buf, load_unit(u, c0));
+        // with two buffers one barrier per chunk: whoever is past it has finished with the other one
+        __syncthreads();
+        if (c0 + 16 * WK < 16 * a.steps) fetch(c0 + 16 * WK);
+        const int step = (c0 >> 4) + wk;
+        if (step < a.steps) {
+            const uint4* wt[FM];
+#pragma unroll
+            for (int f = 0; f < FM; ++f) wt[f] = a.weights + ((size_t)fb[f] * a.steps + step) * (9 * 64) + lane;
+            const uint4* src = lds4 + buf * G8 * a.npp;
+#pragma unroll
+            for (int kh = 0; kh < 3; ++kh)
+#pragma unroll
+                for (int kw = 0; kw < 3; ++kw) {
+                    half8 wv[FM];
+#pragma unroll
+                    for (int f = 0; f < FM; ++f) wv[f] = __builtin_bit_cast(half8, wt[f][(kh * 3 + kw) * 64]);
+#pragma unroll
+                    for (int p = 0; p < PN; ++p) {
+                        const half8 x = __builtin_bit_cast(half8, src[base[p] + kh * a.pitch + kw]);
+#pragma unroll
+                        for (int f = 0; f < FM; ++f)
+                            acc[f][p] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wv[f], x, acc[f][p], 0, 0, 0);
+                    }
+                }
+        }
+        if (BUFS == 2) buf ^= 1;
+    }
+
+    // ---- the wavefronts of a block add up their channels, in a fixed order; each keeps 16 / WK
+    // of the registers of every block
+    constexpr int RK = 16 / WK;
+    if constexpr (WK > 1) {
+        float* const sums = reinterpret_cast<float*>(lds4);
+        __syncthreads();
+#pragma unroll
+        for (int f = 0; f < FM; ++f)
+#pragma unroll
+            for (int p = 0; p < PN; ++p) {
+                if (f + p) __syncthreads();
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sums[(wave * 16 + r) * 64 + lane] = acc[f][p][r];
+                __syncthreads();
+#pragma unroll
+                for (int r = 0; r < RK; ++r) {
+                    float v = 0.0f;
+#pragma unroll
+                    for (int k = 0; k < WK; ++k) v += sums[((wave - wk + k) * 16 + wk * RK + r) * 64 + lane];
+                    acc[f][p][r] = v;
+                }
+            }
+    }
+
+    // ---- epilogue: register r of a block is filter 8 * (r / 4) + 4 * half + r % 4, pixel lane % 32
+    const size_t oplane = (size_t)a.ho * a.wo;
+    const int reg0 = WK > 1 ? wk * RK : 0;
+    auto slot_of = [&](int f, int r, int hf) {
+        return ((fset * WF + wf) * FM + f) * 32 + 8 * ((reg0 + r) >> 2) + 4 * hf + ((reg0 + r) & 3);
+    };
+    // channel and bias of a slot travel over the scalar path, for both halves
+    typedef const int32_t __attribute__((address_space(4))) * iptr;
+    typedef const float __attribute__((address_space(4))) * fptr;
+    auto channel_of = [&](int s) { return ((iptr)(uintptr_t)a.reorder)[min(s, a.c_out - 1)]; };
+    auto bias_of = [&](int co) { return a.bias ? ((fptr)(uintptr_t)a.bias)[co] : 0.0f; };
+    unsigned odd = 0;                                 // pixels of this lane with a sum that is not finite
+    bool ok[PN];
+    size_t off[PN];
+#pragma unroll
+    for (int p = 0; p < PN; ++p) {
+        const int q = pix0 + (wp * PN + p) * 32 + l32;
+        int img, oy, sx;
+        split_row(min(q, last), img, oy, sx);
+        const int ox = strip * a.sw + sx;
+        ok[p] = q <= last && ox < a.wo;
+        off[p] = (size_t)img * a.c_out * oplane + (size_t)oy * a.wo + ox;
+    }
+    const bool pair_out = PAIR && RK >= 2 && a.pair_out;
+#pragma unroll
+    for (int f = 0; f < FM; ++f)
+#pragma unroll
+        for (int r = 0; r < RK; r += 2) {
+            int co[2];
+            float b[2];
+            bool has[2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int s0 = slot_of(f, r + k, 0), s1 = slot_of(f, r + k, 1);
+                const int c0 = channel_of(s0), c1 = channel_of(s1);
+                const float b0 = bias_of(c0), b1 = bias_of(c1);
+                co[k] = half ? c1 : c0;
+                b[k] = half ? b1 : b0;
+                has[k] = (half ? s1 : s0) < a.c_out;
+            }
+#pragma unroll
+            for (int p = 0; p < PN; ++p) {
+                float v[2];
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    v[k] = acc[f][p][r + k];
+                    odd |= (unsigned)(ok[p] && !(fabsf(v[k]) < __builtin_inff())) << p;
+                    v[k] += b[k];
+                    if (a.relu) v[k] = fmaxf(v[k], 0.0f);
+                }
+                if (pair_out) {
+                    // neighbouring pixels trade: the even one takes both of filter r, the odd one both of r + 1
+                    const bool right = lane & 1;
+                    const float give = right ? v[0] : v[1];
+                    const float got = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(give), 0xB1, 0xf, 0xf, true));   // quad_perm [1,0,3,2]
+                    const __half2 h = right ? __floats2half2_rn(got, v[1]) : __floats2half2_rn(v[0], got);
+                    if (ok[p] && (right ? has[1] : has[0]))
+                        *reinterpret_cast<__half2*>(&a.out[off[p] - (right ? 1 : 0) + (size_t)(right ? co[1] : co[0]) * oplane]) = h;
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 2; ++k)
+                        if (ok[p] && has[k]) a.out[off[p] + (size_t)co[k] * oplane] = __float2half_rn(v[k]);
+                }
+            }
+        }
+    if (!odd) return;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // after the stores above, the neighbour's among them
+
+    for (int p = 0; p < PN; ++p) {
+        if (!(odd >> p & 1)) continue;
+        int im, y, sx;
+        split_row(pix0 + (wp * PN + p) * 32 + l32, im, y, sx);
+        const int x = strip * a.sw + sx;
+        for (int f = 0; f < FM; ++f)
+            for (int r = 0; r < RK; ++r) {
+                const int s = slot_of(f, r, half);
+                if (s >= a.c_out) continue;
+                const int co = a.reorder[s];
+                float v = fkw_output(a, s, im, y, x) + (a.bias ? a.bias[co] : 0.0f);
+                if (a.relu) v = fmaxf(v, 0.0f);
+                a.out[((size_t)im * a.c_out + co) * oplane + (size_t)y * a.wo + x] = __float2half_rn(v);
+            }
+    }
+}
+
+// One workgroup per stored filter: its kept weights to their places in the fragments.
+__global__ __launch_bounds__(256) void f16_expand_kernel(const int32_t* offset, const int32_t* index, const int32_t* stride,
+                                                         const __half* weight, const uint16_t* masks, int num_patterns,
+                                                         int taps, int steps, __half* out)
+{
+    const int s = blockIdx.x;
+    const int32_t* st = stride + (size_t)s * (num_patterns + 1);
+    const int32_t k0 = offset[s], kn = offset[s + 1] - k0;
+    for (int32_t k = threadIdx.x; k < kn; k += 256) {
+        int p = 0;
+        while (k >= st[p + 1]) ++p;
+        unsigned m = masks[p];
+        const int c = index[k0 + k];
+        for (int t = 0; t < taps; ++t) {
+            const int pos = __builtin_ctz(m);
+            m &= m - 1;
+            const size_t frag = ((size_t)(s >> 5) * steps + (c >> 4)) * 9 + pos;
+            out[(frag * 64 + ((c >> 3) & 1) * 32 + (s & 31)) * 8 + (c & 7)] = weight[(size_t)(k0 + k) * taps + t];
+        }
+    }
+}
+
+size_t f16_expanded_halves(int32_t c_in, int32_t c_out)
+{
+    return (size_t)((c_out + 31) / 32) * ((c_in + 15) / 16) * 9 * 64 * 8;
+}
+
+hipError_t launch_f16_expand(const DevFkw& f, int32_t c_in, int32_t c_out, void* out, hipStream_t stream)
+{
+    hipLaunchKernelGGL(f16_expand_kernel, dim3((unsigned)c_out), dim3(256), 0, stream, f.offset, f.index, f.stride,
+                       static_cast<const __half*>(f.weight_f16), f.masks, f.num_patterns, f.taps, (c_in + 15) / 16,
+                       static_cast<__half*>(out));
+    return hipGetLastError();
+}
+
+// How the pixels of an output are cut into tiles of `pix`; false where the kernel's 32-bit numbers
+// do not reach.
+static bool f16_tiles(const ConvShape& s, int pix, bool pair, F16Args& a)
+{
+    a.strips = (s.wo + 31) / 32;
+    a.sw = (s.wo + a.strips - 1) / a.strips;
+    a.vh = s.h + 2 * s.pad;
+    a.lead = s.pad;
+    a.pitch = (a.sw - 1) * s.stride + 3;
+    if (pair) {
+        // strips and staged rows start at even columns
+        a.sw = (a.sw + 1) / 2 * 2;
+        a.lead = 2 * s.pad;
+        a.pitch = ((a.sw - 1) * s.stride + 3 + s.pad + 1) / 2 * 2;
+    }
+    const long long pixels = (long long)s.n * s.ho * a.sw;
+    if (pixels > INT32_MAX - pix || (long long)s.n * a.vh > INT32_MAX) return false;
+    a.pixels = (int32_t)pixels;
+    a.tiles = (int32_t)((pixels + pix - 1) / pix);
+    // rows under a tile: of the output rows that `pix` pixels touch, and what lies between images
+    const int rows_out = (int)std::min<long long>((pix - 1 + a.sw - 1) / a.sw + 1, (long long)s.n * s.ho);
+    const int between = std::min(s.n - 1, (rows_out - 1 + s.ho - 1) / s.ho);
+    const int rows = (rows_out - 1) * s.stride + between * (a.vh - s.ho * s.stride) + 3;
+    a.npp = (rows * a.pitch + 127) / 128 * 128;
+    // byte offsets from a tile's first image
+    return (long long)(between + 2) * s.c_in * s.h * s.w < (1ll << 30);
+}
+
+template <int FM, int PN, int WF, int WP, int WK, bool PAIR>
+static hipError_t launch_f16_t(const F16Args& args, const ConvShape& s, long long blocks, size_t lds, hipStream_t stream)
+{
+    F16Args a = args;
+    a.div_fsets = make_fast_div((uint32_t)a.fsets);
+    a.div_tiles = make_fast_div((uint32_t)a.tiles);
+    a.div_sw = make_fast_div((uint32_t)a.sw);
+    a.div_ho = make_fast_div((uint32_t)a.ho);
+    a.div_vh = make_fast_div((uint32_t)a.vh);
+    a.div_pitch = make_fast_div((uint32_t)a.pitch);
+    if (lds > 64 * 1024) {
+        static std::atomic<uint64_t> allowed{0};
+        hipError_t e = allow_big_lds(reinterpret_cast<const void*>(&f16_conv_kernel<FM, PN, WF, WP, WK, PAIR>), allowed);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((f16_conv_kernel<FM, PN, WF, WP, WK, PAIR>), dim3((unsigned)blocks), dim3(64 * WF * WP * WK), lds, stream, a);
+    return hipGetLastError();
+}
+
+// The compiled shapes, in the order in which they are tried: the first that gives the chip
+// `min_blocks` workgroups.  Large blocks read every staged pixel and weight for more
+// multiply-adds, small ones reach more CUs, and wavefronts that split the channels shorten
+// the chain of the last layers of a network.  us per pass, largest to smallest shape (f2 p4, f2 p2,
+// f1 p2, then the splitting ones):
+//   128 -> 128 at 56x56, 64 images     94   99  103  147  188  232     (784 workgroups of the first)
+//    64 ->  64 at 112x112, 8 images    32   34   23   29   34   57     (784 of the third; half of the first idle)
+//   128 -> 256 at 56x56 / 2, 16 images 37   32   47   58   83   --     (196 of the second)
+//   512 -> 512 at 7x7, 64 images      136  146   95   52   68   69     (784 of the fourth)
+//   256 -> 256 at 28x28, one image     47   42   28   12    9    9     (200 of the fifth and sixth)
+//   512 -> 512 at 14x14, one image     81   75   50   21   22   16     (112)
+struct F16Shape {
+    int fm, pn, wf, wp, wk, min_blocks;
+    bool strided;                    // only where every filter set's staging counts four times: stride 2
+    hipError_t (*launch[2])(const F16Args&, const ConvShape&, long long, size_t, hipStream_t);
+};
+#define PATDNN_F16(fm, pn, wf, wp, wk, min_blocks, strided) \
+    {fm, pn, wf, wp, wk, min_blocks, strided, {&launch_f16_t<fm, pn, wf, wp, wk, false>, &launch_f16_t<fm, pn, wf, wp, wk, true>}}
+static const F16Shape kF16Shapes[] = {
+    PATDNN_F16(2, 4, 2, 2, 1, 256, false),
+    PATDNN_F16(2, 2, 2, 2, 1, 128, true),
+    PATDNN_F16(1, 2, 1, 4, 1, 256, false),
+    PATDNN_F16(1, 2, 1, 1, 4, 400, false),
+    PATDNN_F16(1, 1, 1, 1, 8, 0, false),
+    PATDNN_F16(1, 1, 1, 1, 4, 0, false),
+};
+#undef PATDNN_F16
+
+hipError_t launch_f16(const DevFkw& f, const ConvShape& s, const void* in, const float* bias, void* out, hipStream_t stream)
+{
+    F16Args a{};
+    a.in = static_cast<const __half*>(in); a.bias = bias; a.out = static_cast<__half*>(out);
+    a.weights = static_cast<const uint4*>(f.expanded_f16);
+    a.offset = f.offset; a.reorder = f.reorder; a.index = f.index; a.stride = f.stride; a.masks = f.masks;
+    a.fkw_weight = static_cast<const __half*>(f.weight_f16);
+    a.num_patterns = f.num_patterns; a.taps = f.taps;
+    a.n = s.n; a.c_in = s.c_in; a.c_out = s.c_out; a.h = s.h; a.w = s.w; a.ho = s.ho; a.wo = s.wo;
+    a.conv_stride = s.stride; a.pad = s.pad; a.relu = s.relu;
+    a.steps = (s.c_in + 15) / 16;
+    a.fblocks = (s.c_out + 31) / 32;
+    // two pixels per load and store: rows of an even length and a 4-byte aligned tensor
+    const bool pair = s.w % 2 == 0 && (reinterpret_cast<uintptr_t>(in) & 3) == 0;
+    a.pair_out = s.wo % 2 == 0 && (reinterpret_cast<uintptr_t>(out) & 3) == 0;
+    for (const F16Shape& v : kF16Shapes) {
+        const int filters = v.fm * v.wf;
+        if (filters >= 2 * a.fblocks) continue;                   // half of every workgroup idle
+        if (v.strided && s.stride == 1) continue;
+        if (v.wk == 8 && a.steps <= 4) continue;                  // four wavefronts hold all channels
+        if (!f16_tiles(s, 32 * v.pn * v.wp, pair, a)) continue;
+        a.fsets = (a.fblocks + filters - 1) / filters;
+        const long long blocks = (long long)a.strips * a.tiles * a.fsets;
+        const size_t lds = std::max((size_t)a.npp * (f16_buffers(v.wk) * 2 * v.wk * 16 + 4),
+                                    v.wk > 1 ? (size_t)v.wf * v.wp * v.wk * 4096 : 0);
+        if (blocks < v.min_blocks || blocks > INT32_MAX || lds > 160 * 1024) continue;
+        return v.launch[pair](a, s, blocks, lds, stream);
+    }
+    return launch_fkw_f16(f, s, in, bias, out, stream);           // beyond the kernel's 32-bit numbers
+}
+
+}  // namespace patdnn

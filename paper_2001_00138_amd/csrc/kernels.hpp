@@ -82,6 +82,9 @@ struct DevFkw {
     // half-precision-storage entry point: `weight` and `dw_weight` element for element
     const void* weight_f16 = nullptr;
     const void* dw_weight_f16 = nullptr;
+    // all nine taps of every kernel in binary16, zeros where pruning removed a weight, in the
+    // matrix instructions' order (kernel_f16.hip); NULL: depthwise layers and very large ones
+    const void* expanded_f16 = nullptr;
 };
 
 // Filter-group layout on the device: record streams (sparse) or 9-tap weights (dense).
@@ -114,11 +117,18 @@ hipError_t launch_compare(bool csr, const DevCompare& d, const ConvShape& s, con
 // Depthwise layers: one pass over input and output, 16-byte accesses, four outputs per lane.
 hipError_t launch_dw(const DevFkw& f, const ConvShape& s, const float* in, const float* bias,
                      float* out, hipStream_t stream);
-// The same two kernels on binary16 tensors and weights (fp32 arithmetic, fp32 bias).
+// The same two kernels on binary16 tensors and weights (fp32 arithmetic, fp32 bias); the walk where
+// launch_f16 does not reach.
 hipError_t launch_dw_f16(const DevFkw& f, const ConvShape& s, const void* in, const float* bias,
                          void* out, hipStream_t stream);
 hipError_t launch_fkw_f16(const DevFkw& f, const ConvShape& s, const void* in, const float* bias,
                           void* out, hipStream_t stream);
+// Pruned and dense layers on the matrix cores (needs DevFkw::expanded_f16).
+hipError_t launch_f16(const DevFkw& f, const ConvShape& s, const void* in, const float* bias,
+                      void* out, hipStream_t stream);
+size_t f16_expanded_halves(int32_t c_in, int32_t c_out);
+// Fills `out` (f16_expanded_halves, zeroed) from the FKW arrays.
+hipError_t launch_f16_expand(const DevFkw& f, int32_t c_in, int32_t c_out, void* out, hipStream_t stream);
 
 // ---------------------------------------------------------------------------
 // Tiled kernels: compile-time geometry per variant, run-time launch parameters.

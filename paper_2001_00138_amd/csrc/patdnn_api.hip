@@ -465,6 +465,9 @@ double fkw_estimate(const patdnn_layer* h, const ConvShape& s)
     return 5.5 + 0.23 * h->L.kept / s.c_out + 0.004 * std::max(0.0, blocks - 256);
 }
 
+// Binary16 weights with the removed ones as zeros: up to 256 MB a layer.
+constexpr size_t kMaxExpandedHalves = (size_t)128 << 20;
+
 // Partial sums that the library asks room for by itself: 512 MB.
 constexpr size_t kMaxSliceFloats = (size_t)128 << 20;
 
@@ -554,6 +557,16 @@ patdnn_status_t patdnn_encode(const patdnn_layer_desc_t* desc, const float* dens
             const uint16_t* dev16 = nullptr;
             if ((e = upload(h->allocations, w16, &dev16)) != hipSuccess) return hip_fail(e, "uploading the binary16 weights");
             h->dfkw.weight_f16 = dev16;
+        }
+        const size_t expanded = h->L.depthwise ? 0 : f16_expanded_halves(desc->c_in, desc->c_out);
+        if (expanded && expanded <= kMaxExpandedHalves) {
+            const std::vector<uint16_t> none;
+            const uint16_t* dev16 = nullptr;
+            if ((e = upload(h->allocations, none, &dev16, expanded)) != hipSuccess ||
+                (e = launch_f16_expand(h->dfkw, desc->c_in, desc->c_out, const_cast<uint16_t*>(dev16), nullptr)) != hipSuccess ||
+                (e = hipStreamSynchronize(nullptr)) != hipSuccess)
+                return hip_fail(e, "expanding the binary16 weights");
+            h->dfkw.expanded_f16 = dev16;
         }
         if (h->L.depthwise) {
             // per stored filter: the mask of its kernel's pattern and its four weights
@@ -775,6 +788,8 @@ patdnn_status_t patdnn_conv2d_f16(patdnn_handle_t h, const void* input, int32_t 
     s.relu = fuse_relu ? 1 : 0;
     hipError_t e = h->L.depthwise
                        ? launch_dw_f16(h->dfkw, s, input, bias, output, static_cast<hipStream_t>(stream))
+                   : h->dfkw.expanded_f16
+                       ? launch_f16(h->dfkw, s, input, bias, output, static_cast<hipStream_t>(stream))
                        : launch_fkw_f16(h->dfkw, s, input, bias, output, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? PATDNN_OK : hip_fail(e, "launching a binary16 kernel");
 }

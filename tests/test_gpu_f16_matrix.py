@@ -1,0 +1,99 @@
+"""GPU parity of the binary16 matrix-core kernel (csrc/kernel_f16.hip) where it can go wrong: odd and
+even rows (one and two pixels per load and store), strips, tiles that span images, channel and
+filter counts around its blocks, both strides, every launch shape - and inputs that are infinite or
+NaN, which must reach only the outputs whose kept weights meet them."""
+
+import numpy as np
+import pytest
+
+from paper_2001_00138_amd import binding as B
+from paper_2001_00138_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    B.lib()
+    return torch
+
+
+def _layer(rng, c_out, c_in, keep, stride, pad, dense=False):
+    ids = rng.integers(0, 8, (c_out, c_in), dtype=np.uint8)
+    mask = (rng.random((c_out, c_in)) < keep).astype(np.uint8)
+    wt = (rng.standard_normal((c_out, c_in, 3, 3)) * 0.3).astype(np.float32)
+    lib = wl.pattern_library(wl.PATTERN_SEED)
+    return (wt, ids, mask, lib), B.Layer(wt, ids, mask, lib, stride=stride, pad=pad, dense=dense)
+
+
+# c_out, c_in, n, h, w, stride, pad, keep, elements the input starts after an aligned address
+CASES = [
+    (130, 17, 2, 130, 128, 1, 1, 0.3, 0),      # 64 filters x 128 pixels a wavefront; last filter block nearly empty
+    (128, 33, 1, 182, 181, 1, 1, 0.3, 0),      # ... odd rows
+    (70, 20, 3, 107, 106, 2, 1, 0.3, 0),       # stride 2, 53 output columns: pairs in, single values out
+    (96, 31, 6, 66, 67, 2, 0, 0.4, 0),
+    (40, 16, 5, 120, 99, 1, 0, 0.3, 0),        # 32 x 64
+    (33, 5, 3, 161, 160, 1, 1, 0.5, 1),        # even rows at an odd address
+    (64, 64, 70, 14, 15, 1, 1, 0.3, 0),        # channels split over wavefronts, tiles over images
+    (200, 70, 9, 20, 30, 1, 1, 0.3, 0),
+    (33, 130, 2, 11, 7, 1, 1, 0.3, 0),         # eight wavefronts a block
+    (16, 64, 1, 32, 34, 1, 1, 0.5, 0),         # four
+    (31, 48, 40, 1, 1, 1, 1, 1.0, 0),          # one pixel an image
+    (48, 80, 33, 4, 4, 2, 0, 0.6, 0),          # a strip of one column, rounded up to a pair
+    (8, 100, 2, 40, 130, 2, 1, 0.4, 0),        # stride 2, strips of 33 columns cut down to 32
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_matrix_kernel(torch, case):
+    from oracle import fp16
+    c_out, c_in, n, h, w, stride, pad, keep, shift = case
+    rng = np.random.default_rng(c_out * 1000 + h * 40 + w)
+    (wt, ids, mask, lib), L = _layer(rng, c_out, c_in, keep, stride, pad)
+    bias = rng.standard_normal(c_out).astype(np.float32)
+    x16 = fp16.to_f16(rng.standard_normal((n, c_in, h, w)))
+    x16.reshape(-1)[::37] = fp16.to_f16(np.float64(3e-7))          # subnormal
+    want16, exact = fp16.conv2d_f16(wt, ids, mask, lib, x16, bias, stride=stride, pad=pad, relu=True, skip_removed=True)
+    xt = torch.zeros(x16.size + shift, dtype=torch.float16, device="cuda")[shift:].view(x16.shape)
+    xt.copy_(torch.from_numpy(x16))
+    guard, numel = 2048, int(np.prod(want16.shape))
+    buf = torch.full((numel + 2 * guard,), 7.0, dtype=torch.float16, device="cuda")
+    out = buf[guard:guard + numel].view(want16.shape)
+    print(f"  {case}", flush=True)
+    L.conv2d_f16(xt, torch.from_numpy(bias).cuda(), out, relu=True)
+    torch.cuda.synchronize()
+    assert bool((buf[:guard] == 7.0).all()) and bool((buf[guard + numel:] == 7.0).all())
+    # half a binary16 spacing for the rounding, 1e-5 of the largest output for the fp32 sum
+    got, scale = out.cpu().numpy().astype(np.float64), float(np.abs(exact).max())
+    bound = 2.0 ** -11 * np.maximum(np.abs(exact), 2.0 ** -14) + 1e-5 * scale
+    assert float((np.abs(got - exact) / bound).max()) <= 1.0
+    L.close()
+
+
+@pytest.mark.parametrize("shape", [(40, 24, 2, 97, 96, 1), (40, 24, 2, 97, 95, 1), (33, 130, 2, 11, 8, 2), (64, 64, 70, 7, 7, 1)])
+def test_infinite_and_nan_inputs(torch, shape):
+    from oracle import fp16
+    c_out, c_in, n, h, w, stride = shape
+    rng = np.random.default_rng(sum(shape))
+    (wt, ids, mask, lib), L = _layer(rng, c_out, c_in, 0.3, stride, 1)
+    x16 = fp16.to_f16(rng.standard_normal((n, c_in, h, w)))
+    for v in (np.inf, -np.inf, np.nan):
+        x16[rng.integers(n), rng.integers(c_in), rng.integers(h), rng.integers(w)] = v
+    # the walk over the kept weights, on the same values in fp32
+    W = B.Layer(fp16.to_f16(wt).astype(np.float32), ids, mask, lib, stride=stride)
+    W.set_config(0)
+    want16 = fp16.to_f16(W.conv2d(torch.from_numpy(x16.astype(np.float32)).cuda(), None).cpu().numpy())
+    W.close()
+    got = L.conv2d_f16(torch.from_numpy(x16).cuda(), None).cpu().numpy()
+    assert not np.isfinite(want16).all()
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(want16))
+    np.testing.assert_array_equal(got[np.isinf(want16)], want16[np.isinf(want16)])
+    ok = np.isfinite(want16)
+    assert np.isfinite(got[ok]).all()
+    # one binary16 spacing, and 1e-5 of the largest sum
+    err = np.abs(got[ok].astype(np.float64) - want16[ok])
+    assert float((err - 2.0 ** -10 * np.abs(want16[ok])).max()) <= 1e-5 * float(np.abs(want16[ok]).max()) + 2.0 ** -24
+    L.close()
