@@ -446,7 +446,7 @@ void build_taps(const LayerHost& L, int ck, const std::vector<int32_t>& members,
                     T.slot_channel[(size_t)g * G + slot] = f.reorder[s];
                     T.group_kernels[g] += f.offset[s + 1] - f.offset[s];
                 }
-                if (T.records.size() == before) append(kTapSegmentEnd, nullptr);
+                if (T.records.size() == before) append(kTapSegmentEnd | kTapNothing << kTapPatternShift, nullptr);
                 T.records.back() |= kTapFilterEnd;
             }
             pad_batch();

@@ -33,7 +33,7 @@ from gen_dispatch import universe
 
 GROUP = 8                      # filters of one stream
 TILE = 16                      # rows and columns of a tile
-FLUSH_BYTES = 256              # bytes per flush block (one per pattern)
+FLUSH_BYTES = 256              # bytes per flush block (one per pattern, and an empty one)
 END_BYTES = 512                # bytes per end-of-filter block
 AHEAD = 3                      # kernels whose pixels are on their way from LDS
 
@@ -157,6 +157,8 @@ def program(F, vbase):
                 asm(f"v_add_f32 {dst}, {v(D + 4 * r + t)}, {dst}")
         asm(f"s_setpc_b64 s[{RET}:{RET + 1}]")
         fit(f".Lflush{p}_%=", FLUSH_BYTES)
+    align(8)                                         # kTapNothing: a filter without kernels in this chunk
+    asm(f"s_setpc_b64 s[{RET}:{RET + 1}]")
 
     # ---- end-of-filter blocks, END_BYTES apart
     for f in range(F):

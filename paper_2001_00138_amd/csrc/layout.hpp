@@ -122,7 +122,8 @@ struct Tiled {
 // the groups above); per group and chunk of `ck` input channels the kept kernels follow each
 // other filter by filter, inside a filter by pattern (the paper's FKW order cut into chunks), in
 // batches of 16: a 32-bit record and four weights per kernel.  A filter without a kernel in the
-// chunk gets one of zero weights, so that every filter has an end.
+// chunk gets a record of pattern kTapNothing, so that every filter has an end: its products are
+// dropped (zero weights alone would turn an infinite pixel into a NaN).
 //   record: bits 0..7 channel inside the chunk, 22..27 pattern (universe index), 30 last kernel
 //   of the filter, 31 last kernel of the filter's run of this pattern
 // ---------------------------------------------------------------------------
@@ -131,6 +132,7 @@ constexpr int kTapBatch = 16;
 constexpr int kTapMaxChunk = 160;            // channels whose 16 x 16 tiles fill a CU's LDS
 constexpr uint32_t kTapFilterEnd = 1u << 30, kTapSegmentEnd = 1u << 31;
 constexpr int kTapPatternShift = 22;
+constexpr uint32_t kTapNothing = 56;         // one past the universe
 
 struct Taps {
     int32_t num_groups = 0, ck = 0, num_chunks = 0;

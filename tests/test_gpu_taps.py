@@ -100,3 +100,32 @@ def test_chosen_configuration(torch, oracle, shape):
         assert float(np.abs(got.astype(np.float64) - ref).max() / np.abs(ref).max()) <= TOL, room
     assert L.get_config()["variant"] == -1
     L.close()
+
+
+@pytest.mark.parametrize("filters,ksplit", [(8, 1), (16, 1), (8, 2)])
+def test_infinite_input_reaches_kept_kernels_only(torch, filters, ksplit):
+    """A filter without a kernel in a chunk of channels keeps its bias and its other chunks' sum where
+    that chunk's input is infinite or NaN."""
+    rng = np.random.default_rng(5)
+    c_out, c_in, h = 16, 16, 12
+    lib = wl.pattern_library(wl.PATTERN_SEED, 8)
+    ids = rng.integers(0, 8, (c_out, c_in), dtype=np.uint8)
+    mask = np.ones((c_out, c_in), np.uint8)
+    mask[::2, :8] = 0                          # even filters: nothing in the first chunk
+    mask[3] = 0                                # no kernel at all
+    wt = rng.standard_normal((c_out, c_in, 3, 3)).astype(np.float32)
+    bias = rng.standard_normal(c_out).astype(np.float32)
+    x = rng.standard_normal((1, c_in, h, h)).astype(np.float32)
+    x[0, 0, 3, 3], x[0, 0, 8, 8] = np.inf, np.nan          # the first channel of the first chunk
+    names = {B.patdnn_variant_name(v): v for v in range(B.patdnn_num_variants())}
+    got = {}
+    for name, cfg in (("fkw", (0, 0, 0, 1)), ("taps", (names[f"taps_f{filters}"], 8, 1, ksplit))):
+        L = B.Layer(wt, ids, mask, lib)
+        L.set_config(*cfg)
+        xt, bt = torch.from_numpy(x).cuda(), torch.from_numpy(bias).cuda()
+        got[name] = L.conv2d(xt, bt, relu=False).cpu().numpy()
+        L.close()
+    assert np.array_equal(np.isfinite(got["taps"]), np.isfinite(got["fkw"]))
+    assert np.isfinite(got["taps"][0, ::2]).all() and (got["taps"][0, 3] == bias[3]).all()
+    ok = np.isfinite(got["fkw"])
+    assert np.abs(got["taps"][ok] - got["fkw"][ok]).max() <= TOL * np.abs(got["fkw"][ok]).max()
