@@ -17,9 +17,14 @@
 // results in 16 bits, section 6.1): there the bytes, and with them the time, halve.
 #include <hip/hip_fp16.h>
 
+#include <algorithm>
+
 #include "kernels.hpp"
 
 namespace patdnn {
+
+// LDS that dw_planes_kernel may take: three workgroups on a CU
+constexpr long long kDwPlanesLds = 52 * 1024;
 
 template <class T>
 struct DwArgs {
@@ -209,6 +214,168 @@ __global__ __launch_bounds__(256) void dw_conv_kernel(DwArgs<T> a)
 }
 
 template <class T>
+struct DwPlanesArgs {
+    const int32_t* taps;         // [c] by channel: four positions in nibbles, ascending; -1: kernel removed
+    const float4* weight;        // [c] its weights in fp32
+    const T* in;
+    const float* bias;
+    T* out;
+    int32_t c, h, w, ho, wo, pad, relu;
+    int32_t total, planes;       // n * c; planes of a workgroup, a multiple of the elements of 16 bytes
+    int32_t in_units, out_units; // LDS for the staged planes and the results, in 16 bytes
+    FastDiv div_c, div_hw, div_w, div_px, div_wo;
+};
+
+// Planes whose rows are no whole vectors.  Planes lie one after the other in memory, through
+// channels and images, so a workgroup takes a run of them that starts at a multiple of 16 bytes,
+// reads it with 16-byte loads whatever the row length, and lays the rows out in LDS with one zero
+// column and one zero row between neighbours: that is every plane's padding, so a tap is an LDS
+// read at a constant distance and a multiply-add.  A thread keeps one output pixel and walks the
+// planes; results leave through LDS with 16-byte stores.  Channels stay in memory order (tap
+// positions and weights are looked up per plane), since nothing here branches on the pattern.
+// The sums are those of dw_conv_kernel, term by term.
+// What bounds it: below about 12 MB of tensors the launch (9 us a pass); above, address arithmetic of
+// the LDS layout on both sides, 2.0 to 2.7 TB/s.  The row kernel's lanes load single elements of such rows.
+// us per pass, row kernel -> this one, 64 images: 960 channels of 7x7 binary16 15.9 -> 9.2, fp32
+// 15.2 -> 9.7; 576 of 14x14 binary16 28.0 -> 15.5, fp32 26.1 -> 17.5, stride 2 17.8 -> 12.5; 96 of 37x35
+// binary16 27.9 -> 18.3, fp32 33.9 -> 22.6.
+template <int S, class T>
+__global__ __launch_bounds__(256) void dw_planes_kernel(DwPlanesArgs<T> a)
+{
+    extern __shared__ uint4 lds4[];
+    constexpr int V = 16 / sizeof(T), AHEAD = 2;
+    T* const staged = reinterpret_cast<T*>(lds4);
+    T* const result = reinterpret_cast<T*>(lds4 + a.in_units);
+    float4* const weights = reinterpret_cast<float4*>(lds4 + a.in_units + a.out_units);
+    int4* const info = reinterpret_cast<int4*>(weights + a.planes);   // tap distances (four times 16 bits), bias, removed
+    const int tid = threadIdx.x;
+    const int g0 = (int)blockIdx.x * a.planes, np = min(a.planes, a.total - g0);
+    const int hw = a.h * a.w, px = a.ho * a.wo, pitch = a.w + 1, in_count = np * hw, out_count = np * px;
+    const T* src = a.in + (size_t)g0 * hw;
+    union Vec { uint4 u; T t[V]; };
+    auto load = [&](int i) __attribute__((always_inline)) -> uint4 {
+        if ((i + 1) * V <= in_count) return reinterpret_cast<const uint4*>(src)[i];
+        Vec v;
+        v.u = make_uint4(0, 0, 0, 0);
+#pragma unroll
+        for (int k = 0; k < V; ++k)
+            if (i * V + k < in_count) v.t[k] = src[i * V + k];
+        return v.u;
+    };
+    auto scatter = [&](int i, uint4 u) __attribute__((always_inline)) {
+        Vec v;
+        v.u = u;
+        const int e = i * V;
+        const int p = (int)fast_div((uint32_t)e, a.div_hw), r = e - p * hw;
+        int y = (int)fast_div((uint32_t)r, a.div_w), x = r - y * a.w;
+        int at = (p * (a.h + 1) + y + 1) * pitch + x + 1;
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+            if (e + k < in_count) staged[at] = v.t[k];
+            ++at;
+            if (++x == a.w) {
+                x = 0;
+                ++at;
+                if (++y == a.h) { y = 0; at += pitch; }
+            }
+        }
+    };
+    const int vecs = (in_count + V - 1) / V;
+    uint4 ahead[AHEAD];
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k)
+        if (tid + k * 256 < vecs) ahead[k] = load(tid + k * 256);
+    for (int p = tid; p < np; p += 256) {
+        const int co = g0 + p - (int)fast_div((uint32_t)(g0 + p), a.div_c) * a.c;
+        const int taps = a.taps[co];
+        float4 wv = a.weight[co];
+        if constexpr (sizeof(T) == 2) {
+            wv.x = __half2float(__float2half_rn(wv.x)); wv.y = __half2float(__float2half_rn(wv.y));
+            wv.z = __half2float(__float2half_rn(wv.z)); wv.w = __half2float(__float2half_rn(wv.w));
+        }
+        auto dist = [&](int k) { const int pos = (taps >> (4 * k)) & 15; return taps < 0 ? 0 : pos / 3 * pitch + pos % 3; };
+        weights[p] = wv;
+        info[p] = make_int4(dist(0) | dist(1) << 16, dist(2) | dist(3) << 16, __float_as_int(a.bias ? a.bias[co] : 0.0f), taps < 0);
+    }
+    for (int i = tid; i < a.in_units; i += 256) lds4[i] = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k)
+        if (tid + k * 256 < vecs) scatter(tid + k * 256, ahead[k]);
+    for (int i = tid + AHEAD * 256; i < vecs; i += 256) scatter(i, load(i));
+    __syncthreads();
+
+    // planes with at most 256 outputs: as many at a time as there are threads for
+    const int side = px <= 256 ? 256 / px : 1;
+    const int mine = px <= 256 ? (int)fast_div((uint32_t)tid, a.div_px) : 0;
+    for (int q0 = 0; q0 < px; q0 += 256) {
+        const int q = px <= 256 ? tid - mine * px : q0 + tid;
+        if (mine < side && q < px) {
+            const int oy = (int)fast_div((uint32_t)q, a.div_wo), ox = q - oy * a.wo;
+            const int base = (oy * S - a.pad + 1) * pitch + ox * S - a.pad + 1;
+#pragma unroll 2
+            for (int p = mine; p < np; p += side) {
+                const float4 wv = weights[p];
+                const int4 in = info[p];
+                const T* at = staged + base + p * (a.h + 1) * pitch;
+                float acc = fmaf(wv.x, ld1(at + (in.x & 0xFFFF)), 0.0f);
+                acc = fmaf(wv.y, ld1(at + (int)((unsigned)in.x >> 16)), acc);
+                acc = fmaf(wv.z, ld1(at + (in.y & 0xFFFF)), acc);
+                acc = fmaf(wv.w, ld1(at + (int)((unsigned)in.y >> 16)), acc);
+                acc = (in.w ? 0.0f : acc) + __int_as_float(in.z);
+                if (a.relu) acc = fmaxf(acc, 0.0f);
+                st1(result + p * px + q, acc);
+            }
+        }
+    }
+    __syncthreads();
+    T* dst = a.out + (size_t)g0 * px;
+    for (int i = tid; i * V < out_count; i += 256) {
+        if ((i + 1) * V <= out_count) {
+            reinterpret_cast<uint4*>(dst)[i] = lds4[a.in_units + i];
+        } else {
+            for (int e = i * V; e < out_count; ++e) dst[e] = result[e];
+        }
+    }
+}
+
+// True where dw_planes_kernel took the layer.
+template <class T>
+static bool launch_dw_planes(const DevFkw& f, const ConvShape& s, const T* in, const float* bias, T* out, hipStream_t stream)
+{
+    constexpr int V = 16 / sizeof(T);
+    if (!f.dw_taps || s.pad > 1 || ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15) != 0) return false;
+    const long long hw = (long long)s.h * s.w, px = (long long)s.ho * s.wo, total = (long long)s.n * s.c_out;
+    if (total > INT32_MAX - 4096 || hw > 4096) return false;
+    // about 6 KB of input: six workgroups and more on a CU at a time, whose loads overlap; fewer
+    // planes where that leaves CUs without work
+    const long long most = std::max(1ll, std::min({256ll, 6144 / (hw * (long long)sizeof(T)), total / 1024}));
+    const long long planes = (most + V - 1) / V * V;
+    const long long in_units = (((planes * (s.h + 1) + 1) * (s.w + 1) + 1) * (long long)sizeof(T) + 15) / 16;
+    const long long out_units = planes * px / V;
+    const long long lds = (in_units + out_units + 2 * planes) * 16;
+    // Planes are not cut up: too few workgroups leave CUs idle while the others walk large planes (96
+    // channels of 37x35 binary16: 16 images, 192 workgroups 12.7 us against the row kernel's 9.3;
+    // 44 images, 528 workgroups 17.4 against 20.8).  Small planes are equal from 256 on
+    // (21x21, 384 workgroups: 9.3 and 9.2) and ahead above.
+    if (lds > kDwPlanesLds || (total + planes - 1) / planes < (lds > 16 * 1024 ? 512 : 256)) return false;
+    DwPlanesArgs<T> a{};
+    a.taps = f.dw_taps; a.weight = reinterpret_cast<const float4*>(f.dw_tap_weight);
+    a.in = in; a.bias = bias; a.out = out;
+    a.c = s.c_out; a.h = s.h; a.w = s.w; a.ho = s.ho; a.wo = s.wo; a.pad = s.pad; a.relu = s.relu;
+    a.total = (int32_t)total; a.planes = (int32_t)planes; a.in_units = (int32_t)in_units; a.out_units = (int32_t)out_units;
+    a.div_c = make_fast_div((uint32_t)s.c_out);
+    a.div_hw = make_fast_div((uint32_t)hw);
+    a.div_w = make_fast_div((uint32_t)s.w);
+    a.div_px = make_fast_div((uint32_t)px);
+    a.div_wo = make_fast_div((uint32_t)s.wo);
+    const dim3 grid((unsigned)((total + planes - 1) / planes)), block(256);
+    if (s.stride == 1) hipLaunchKernelGGL((dw_planes_kernel<1, T>), grid, block, (size_t)lds, stream, a);
+    else hipLaunchKernelGGL((dw_planes_kernel<2, T>), grid, block, (size_t)lds, stream, a);
+    return true;
+}
+
+template <class T>
 static hipError_t launch_dw_t(const DevFkw& f, const T* weights, const ConvShape& s, const T* in, const float* bias,
                               T* out, hipStream_t stream)
 {
@@ -236,6 +403,9 @@ static hipError_t launch_dw_t(const DevFkw& f, const T* weights, const ConvShape
     constexpr uintptr_t kAlign = 4 * sizeof(T) - 1;
     const bool vec = s.w % 4 == 0 && (reinterpret_cast<uintptr_t>(in) & kAlign) == 0;
     const bool vst = s.wo % 4 == 0 && (reinterpret_cast<uintptr_t>(out) & kAlign) == 0;
+    // rows that are whole vectors on the way in stay with the row kernel (192 channels of 28x28 at
+    // stride 2, binary16: 11.0 us, 11.3 with planes in LDS)
+    if (!vec && launch_dw_planes<T>(f, s, in, bias, out, stream)) return hipGetLastError();
     const dim3 grid((unsigned)blocks), block(256);
 #define PATDNN_DW_LAUNCH(S, V, W) hipLaunchKernelGGL((dw_conv_kernel<S, 4, V, W, T>), grid, block, 0, stream, a)
     if (wide) {

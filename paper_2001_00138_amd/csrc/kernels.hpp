@@ -78,6 +78,10 @@ struct DevFkw {
     // kernel was removed) and its four weights
     const int32_t* dw_mask = nullptr;
     const float* dw_weight = nullptr;
+    // the same by channel, four tap positions in nibbles (-1: removed); NULL where a weight is
+    // not finite in binary16 (zero padding must not meet it)
+    const int32_t* dw_taps = nullptr;
+    const float* dw_tap_weight = nullptr;
     // the weights once more as IEEE binary16 (round to nearest even), for the
     // half-precision-storage entry point: `weight` and `dw_weight` element for element
     const void* weight_f16 = nullptr;

@@ -591,6 +591,23 @@ patdnn_status_t patdnn_encode(const patdnn_layer_desc_t* desc, const float* dens
                 (e = upload(h->allocations, dweight16, &dev16)) != hipSuccess)
                 return hip_fail(e, "uploading the depthwise arrays");
             h->dfkw.dw_weight_f16 = dev16;
+            std::vector<int32_t> taps((size_t)c, -1);
+            std::vector<float> tap_weight((size_t)c * 4);
+            bool finite = true;
+            for (int s = 0; s < c; ++s) {
+                const int co = f.reorder[s];
+                unsigned nibbles = 0;
+                for (int pos = 8; pos >= 0; --pos)
+                    if (dmask[s] >> pos & 1) nibbles = nibbles << 4 | (unsigned)pos;
+                if (dmask[s]) taps[co] = (int32_t)nibbles;
+                for (int t = 0; t < 4; ++t) {
+                    tap_weight[(size_t)co * 4 + t] = dweight[(size_t)s * 4 + t];
+                    finite = finite && (dweight16[(size_t)s * 4 + t] & 0x7C00) != 0x7C00;
+                }
+            }
+            if (finite && ((e = upload(h->allocations, taps, &h->dfkw.dw_taps)) != hipSuccess ||
+                           (e = upload(h->allocations, tap_weight, &h->dfkw.dw_tap_weight)) != hipSuccess))
+                return hip_fail(e, "uploading the depthwise arrays");
         }
         h->on_device = true;
     }
