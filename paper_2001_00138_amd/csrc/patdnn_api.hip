@@ -420,9 +420,10 @@ std::vector<int> default_variant_order(const patdnn_layer* h)
 
 // ---- the configuration used when the caller has not chosen or tuned one: the candidate with the
 // smallest estimate of its time.  The estimates are a few products; their constants were fitted to
-// measurements of 60 layers from 16 to 512 channels, 7x7 to 224x224 pixels and 1 to 64 images in
-// every candidate configuration (1330 timings): they are within 7 % on average, and the
-// candidate they choose is 2 % slower than the fastest one on average.
+// measurements of layers from 16 to 512 channels, 7x7 to 224x224 pixels and 1 to 64 images in every
+// candidate configuration; on 110 other layers of 6 to 56 patterns (profiles/planner_choice.txt) the
+// chosen candidate is 2 % slower than the fastest one on average without a workspace, 5 % with
+// one, and at most 36 %.
 
 // Tap-product kernel, microseconds.  Workgroups of one round share a CU as far as LDS and registers
 // allow; `share` is what a wavefront's work costs when so many wavefronts sit on a SIMD (one alone
@@ -458,11 +459,15 @@ double tiled_estimate(const patdnn_layer* h, const TiledVariant& v, const ConvSh
     return rounds * (0.336 * s.c_in + 0.195 * v.G * h->L.kept / s.c_out + 8.06) * (0.785 + 0.1075 * (per_simd - 1));
 }
 
-// FKW walk, microseconds: one lane per output pixel, latency of a filter's kernels one after the other.
+// FKW walk, microseconds: a wavefront walks the kernels of one filter, pattern by pattern, for 64
+// output pixels, one load after the other; launches of more wavefronts than the chip holds pay for
+// each of them.  (Fitted to 90 layers of 16 to 512 channels, 6 to 56 patterns and 9 us to 9 ms: 14 %
+// on average.)
 double fkw_estimate(const patdnn_layer* h, const ConvShape& s)
 {
-    const double blocks = (double)s.n * s.c_out * (((long long)s.ho * s.wo + 255) / 256);
-    return 5.5 + 0.23 * h->L.kept / s.c_out + 0.004 * std::max(0.0, blocks - 256);
+    const double kernels = (double)h->L.kept / s.c_out, patterns = h->L.fkw.num_patterns;
+    const double waves = (double)s.n * s.c_out * (((long long)s.ho * s.wo + 63) / 64);
+    return 4.9 + 0.223 * kernels + 0.192 * patterns + waves * (9.8e-5 * kernels + 2.8e-5 * patterns);
 }
 
 // Binary16 weights with the removed ones as zeros: up to 256 MB a layer.
@@ -746,6 +751,17 @@ static patdnn_status_t conv2d_impl(patdnn_handle_t h, const float* input, int32_
     // caller set explicitly is never replaced: the error goes back instead
     if (st == PATDNN_EUNSUPPORTED && h->cfg.variant > 0 && h->cfg_tuned)
         st = run(default_config(h, s, scratch && (reinterpret_cast<uintptr_t>(scratch) & 15) == 0 ? scratch_floats : 0));
+    return st;
+}
+
+// For tests, not part of the interface: what the library chooses for this input size and so much
+// workspace.  Works on host-only handles too.
+patdnn_status_t patdnn_internal_choice(patdnn_handle_t h, int32_t n, int32_t h_in, int32_t w_in,
+                                       size_t workspace_floats, patdnn_config_t* out)
+{
+    ConvShape s{};
+    patdnn_status_t st = shape_of(h, n, h_in, w_in, s);
+    if (st == PATDNN_OK) *out = default_config(h, s, workspace_floats);
     return st;
 }
 
