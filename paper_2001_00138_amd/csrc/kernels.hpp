@@ -87,7 +87,8 @@ struct DevFkw {
     const void* weight_f16 = nullptr;
     const void* dw_weight_f16 = nullptr;
     // all nine taps of every kernel in binary16, zeros where pruning removed a weight, in the
-    // matrix instructions' order (kernel_f16.hip); NULL: depthwise layers and very large ones
+    // matrix instructions' order (kernel_f16.hip); NULL: depthwise layers, very large ones and
+    // those with a weight that is not finite in binary16
     const void* expanded_f16 = nullptr;
 };
 

@@ -552,18 +552,20 @@ patdnn_status_t patdnn_encode(const patdnn_layer_desc_t* desc, const float* dens
             return hip_fail(e, "uploading the FKW arrays");
         h->dfkw.num_patterns = f.num_patterns;
         h->dfkw.taps = f.taps;
+        bool finite16 = true;
         {
             // the weights once more in binary16 (round to nearest even) for patdnn_conv2d_f16
             std::vector<uint16_t> w16(f.weight.size());
             for (size_t i = 0; i < w16.size(); ++i) {
                 const _Float16 hv = static_cast<_Float16>(f.weight[i]);
                 std::memcpy(&w16[i], &hv, 2);
+                finite16 = finite16 && (w16[i] & 0x7C00) != 0x7C00;
             }
             const uint16_t* dev16 = nullptr;
             if ((e = upload(h->allocations, w16, &dev16)) != hipSuccess) return hip_fail(e, "uploading the binary16 weights");
             h->dfkw.weight_f16 = dev16;
         }
-        const size_t expanded = h->L.depthwise ? 0 : f16_expanded_halves(desc->c_in, desc->c_out);
+        const size_t expanded = h->L.depthwise || !finite16 ? 0 : f16_expanded_halves(desc->c_in, desc->c_out);
         if (expanded && expanded <= kMaxExpandedHalves) {
             const std::vector<uint16_t> none;
             const uint16_t* dev16 = nullptr;

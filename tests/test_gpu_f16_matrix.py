@@ -73,22 +73,34 @@ def test_matrix_kernel(torch, case):
     L.close()
 
 
-@pytest.mark.parametrize("shape", [(40, 24, 2, 97, 96, 1), (40, 24, 2, 97, 95, 1), (33, 130, 2, 11, 8, 2), (64, 64, 70, 7, 7, 1)])
+# (c_out, c_in, n, h, w, stride): blocks over all channels and blocks whose channels are split, paired and single rows
+@pytest.mark.parametrize("shape", [(40, 24, 2, 97, 96, 1), (40, 24, 2, 97, 95, 1), (33, 130, 2, 11, 8, 2), (64, 64, 70, 7, 7, 1),
+                                   (130, 17, 17, 130, 128, 1), (130, 17, 17, 130, 129, 1),
+                                   (70, 20, 10, 107, 106, 2), (70, 20, 10, 107, 105, 2)])
 def test_infinite_and_nan_inputs(torch, shape):
     from oracle import fp16
     c_out, c_in, n, h, w, stride = shape
     rng = np.random.default_rng(sum(shape))
     (wt, ids, mask, lib), L = _layer(rng, c_out, c_in, 0.3, stride, 1)
+    # kept weights of zero, which an infinite input turns into NaN, and of either sign
+    L.close()
+    zero = rng.random(wt.shape) < 0.1
+    wt[zero] = np.where(rng.random(zero.sum()) < 0.5, 0.0, -0.0)
+    L = B.Layer(wt, ids, mask, lib, stride=stride)
     x16 = fp16.to_f16(rng.standard_normal((n, c_in, h, w)))
-    for v in (np.inf, -np.inf, np.nan):
+    for v in (np.inf, -np.inf, np.nan) * 3:
         x16[rng.integers(n), rng.integers(c_in), rng.integers(h), rng.integers(w)] = v
+    x16[0, 0, 2, 2], x16[0, 1, 2, 3], x16[0, 2, 3, 2] = np.inf, -np.inf, np.inf       # that meet in one output
+    bias = rng.standard_normal(c_out).astype(np.float32)
     # the walk over the kept weights, on the same values in fp32
     W = B.Layer(fp16.to_f16(wt).astype(np.float32), ids, mask, lib, stride=stride)
     W.set_config(0)
-    want16 = fp16.to_f16(W.conv2d(torch.from_numpy(x16.astype(np.float32)).cuda(), None).cpu().numpy())
+    bt = torch.from_numpy(bias).cuda()
+    want16 = fp16.to_f16(W.conv2d(torch.from_numpy(x16.astype(np.float32)).cuda(), bt).cpu().numpy())
     W.close()
-    got = L.conv2d_f16(torch.from_numpy(x16).cuda(), None).cpu().numpy()
-    assert not np.isfinite(want16).all()
+    print(f"  {shape}", flush=True)
+    got = L.conv2d_f16(torch.from_numpy(x16).cuda(), bt).cpu().numpy()
+    assert np.isnan(want16).any() and np.isposinf(want16).any() and np.isneginf(want16).any()
     np.testing.assert_array_equal(np.isnan(got), np.isnan(want16))
     np.testing.assert_array_equal(got[np.isinf(want16)], want16[np.isinf(want16)])
     ok = np.isfinite(want16)
@@ -97,3 +109,57 @@ def test_infinite_and_nan_inputs(torch, shape):
     err = np.abs(got[ok].astype(np.float64) - want16[ok])
     assert float((err - 2.0 ** -10 * np.abs(want16[ok])).max()) <= 1e-5 * float(np.abs(want16[ok]).max()) + 2.0 ** -24
     L.close()
+
+
+def test_infinite_inputs_cost_no_more_than_the_walk(torch):
+    """One input in ten thousand infinite, which touches nearly every tile.  The walk over the kept
+    weights takes 20 times what the finite layer takes on the matrix cores."""
+    rng = np.random.default_rng(3)
+    _, L = _layer(rng, 128, 128, 1 / 3.6, 1, 1)
+    x = torch.randn(64, 128, 56, 56, device="cuda").half()
+    out = torch.empty_like(x)
+
+    def ms():
+        best = []
+        for _ in range(5):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            L.conv2d_f16(x, None, out)
+            e1.record()
+            torch.cuda.synchronize()
+            best.append(e0.elapsed_time(e1))
+        return min(best)
+
+    finite = ms()
+    x.view(-1)[torch.randperm(x.numel(), device="cuda")[:x.numel() // 10000]] = float("inf")
+    some = ms()
+    print(f"  finite {finite:.3f} ms, with infinities {some:.3f} ms", flush=True)
+    assert some <= 20 * finite
+    L.close()
+
+
+@pytest.mark.parametrize("case", [(24, 20, 3, 13, 13, 1, False), (32, 16, 2, 21, 20, 2, False), (48, 5, 2, 18, 33, 1, True)])
+def test_weights_beyond_binary16(torch, case):
+    """A weight that is infinite in binary16 meets zero padding and zero inputs as a NaN, so such layers
+    keep the walk over the kept weights; the other filters are as ever."""
+    from oracle import fp16
+    c_out, c_in, n, h, w, stride, dense = case
+    rng = np.random.default_rng(sum(case))
+    ids = rng.integers(0, 8, (c_out, c_in), dtype=np.uint8)
+    mask = (rng.random((c_out, c_in)) < (1.0 if dense else 0.3)).astype(np.uint8)
+    wt = (rng.standard_normal((c_out, c_in, 3, 3)) * 0.3).astype(np.float32)
+    lib = wl.pattern_library(wl.PATTERN_SEED)
+    mask[7, 3] = 1
+    wt[7, 3] = 1e6
+    bias = rng.standard_normal(c_out).astype(np.float32)
+    x16 = fp16.to_f16(np.maximum(rng.standard_normal((n, c_in, h, w)), 0.0))
+    L = B.Layer(wt, ids, mask, lib, stride=stride, dense=dense)
+    got = L.conv2d_f16(torch.from_numpy(x16).cuda(), torch.from_numpy(bias).cuda()).cpu().numpy()
+    L.close()
+    others = np.arange(c_out) != 7
+    # the oracle, without the infinite weight
+    wt[7, 3] = 0.0
+    _, exact = fp16.conv2d_f16(wt, ids, mask, lib, x16, bias, stride=stride, pad=1, dense=dense, skip_removed=True)
+    bound = 2.0 ** -11 * np.maximum(np.abs(exact), 2.0 ** -14) + 1e-5 * float(np.abs(exact).max())
+    assert float((np.abs(got.astype(np.float64) - exact) / bound)[:, others].max()) <= 1.0
+    assert not np.isfinite(got[:, 7]).any()
