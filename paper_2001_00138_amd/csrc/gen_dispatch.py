@@ -122,7 +122,12 @@ def geometry(G, PR, PC, S, TGX, MODE):
     threaded = bool(MODE & 2)
     vector = vector_weights_pay(nacc)
     tail = (4 if vector else 0) + (7 if threaded else 1)   # 4-byte moves of the weights, scalar instructions
-    block_bytes = pow2_at_least(4 * (4 * nacc + tail))
+    # The blocks that a layer runs (one per slot and pattern of its library) have to stay in the instruction
+    # cache.  268 bytes in slots of 272, 512 or 320, 512 -> 512 at 28 x 28, 64 images, us: 8 patterns 673, 669,
+    # 677; 12 patterns 700, 733, 702; all 56 826, 871, 841 (252 bytes of scalar weights in slots of 256:
+    # 653, 652, 750, and 580 against 537 at 128 -> 128, 112 x 112).  Blocks of a power of two fill it.
+    code_bytes = 4 * (4 * nacc + tail)
+    block_bytes = (code_bytes + 15) // 16 * 16 if vector else pow2_at_least(code_bytes)
     num_ctrl = T_NUM_CTRL if threaded else C_NUM_CTRL
     return dict(WR=WR, WC=WC, pitch=pitch, band_stride=band_stride, band_cols=band_cols,
                 band_major=bool(MODE & 8), nacc=nacc, nwin=WR * WC, block_bytes=block_bytes,
@@ -140,15 +145,12 @@ class _Asm:
     def __call__(self, line):
         self.lines.append(line)
 
-    def begin_block(self, log2):
-        """Aligned start of a block that must fit 2**log2 bytes."""
-        self(f".p2align {log2}")
+    def begin_block(self):
         self(f".Lblk{self.nblocks}_%=:")
 
-    def end_block(self, log2):
-        self(f".if . - .Lblk{self.nblocks}_%= > {1 << log2}")
-        self('.error "code block larger than its slot"')
-        self(".endif")
+    def end_block(self, size):
+        """The next block starts `size` bytes after this one; an error where this one is longer."""
+        self(f".org .Lblk{self.nblocks}_%=+{size}")
         self.nblocks += 1
 
 
@@ -201,7 +203,6 @@ def _program_call(G, PR, PC, S, TGX, MODE, g):
     TGT, RET, BASE, SP, WOFF = C_TGT, C_RET, C_BASE, C_SP, C_WOFF
     R = C_RECORDS
     ctrl_log2 = CTRL_SLOT.bit_length() - 1
-    block_log2 = g["block_bytes"].bit_length() - 1
     asm = _Asm()
     # ---- set-up: table address, first step
     asm(f"s_getpc_b64 s[{BASE}:{BASE + 1}]")
@@ -238,8 +239,10 @@ def _program_call(G, PR, PC, S, TGX, MODE, g):
     asm("s_branch .LstepA%=")
 
     # ---- control blocks, CTRL_SLOT bytes apart
+    asm(f".p2align {ctrl_log2}")
+
     def ctrl_begin(k):
-        asm.begin_block(ctrl_log2)
+        asm.begin_block()
         if k == 0:
             asm(".Lbase%=:")
 
@@ -250,32 +253,31 @@ def _program_call(G, PR, PC, S, TGX, MODE, g):
         if not DW:
             asm("s_waitcnt lgkmcnt(0)")
         asm(f"s_setpc_b64 s[{RET}:{RET + 1}]")
-        asm.end_block(ctrl_log2)
+        asm.end_block(CTRL_SLOT)
     ctrl_begin(PF_NONE)
     asm(f"s_setpc_b64 s[{RET}:{RET + 1}]")
-    asm.end_block(ctrl_log2)
+    asm.end_block(CTRL_SLOT)
     ctrl_begin(DONE_A)
     asm("s_branch .LstepB%=")
-    asm.end_block(ctrl_log2)
+    asm.end_block(CTRL_SLOT)
     ctrl_begin(DONE_B)
     asm("s_branch .LstepA%=")
-    asm.end_block(ctrl_log2)
+    asm.end_block(CTRL_SLOT)
     ctrl_begin(END)                          # the exit is beyond the reach of s_branch
     asm(f"s_add_u32 s{TGT}, s{BASE}, .Lexit%=-.Lbase%=")
     asm(f"s_addc_u32 s{TGT + 1}, s{BASE + 1}, 0")
     asm(f"s_setpc_b64 s[{TGT}:{TGT + 1}]")
-    asm.end_block(ctrl_log2)
-    asm(f".p2align {ctrl_log2}")
+    asm.end_block(CTRL_SLOT)
 
     # ---- the table: block ((set*G + slot)*56 + pattern) at table_off + index*block_bytes
     for ws in range(g["sets"]):
         for slot in range(G):
             for taps in universe():
-                asm.begin_block(block_log2)
+                asm.begin_block()
                 for line in _fmas(G, PR, PC, S, g, ws, slot, taps):
                     asm(line)
                 asm(f"s_setpc_b64 s[{RET}:{RET + 1}]")
-                asm.end_block(block_log2)
+                asm.end_block(g["block_bytes"])
     asm(".Lexit%=:")
     asm("s_waitcnt lgkmcnt(0)")
     return asm.lines
@@ -285,7 +287,6 @@ def _program_threaded(G, PR, PC, S, TGX, MODE, g):
     DW = MODE & 1
     TGT, BASE, SP, SAVE = T_TGT, T_BASE, T_SP, T_SAVE
     ctrl_log2 = CTRL_SLOT.bit_length() - 1
-    block_log2 = g["block_bytes"].bit_length() - 1
     asm = _Asm()
 
     def fetch(dst):
@@ -310,10 +311,11 @@ def _program_threaded(G, PR, PC, S, TGX, MODE, g):
     jump("%[entry]")
 
     # ---- step transitions: control block 3*set + action, then the end block
+    asm(f".p2align {ctrl_log2}")
     first = True
     for cur, nxt in ((SET_A, SET_B), (SET_B, SET_A)):
         for action in range(3):
-            asm.begin_block(ctrl_log2)
+            asm.begin_block()
             if first:
                 asm(".Lbase%=:")
                 first = False
@@ -336,19 +338,18 @@ def _program_threaded(G, PR, PC, S, TGX, MODE, g):
                     asm("s_waitcnt lgkmcnt(0)")
                 fetch(nxt)
             asm(f"s_setpc_b64 s[{TGT}:{TGT + 1}]")
-            asm.end_block(ctrl_log2)
-    asm.begin_block(ctrl_log2)               # end of the chunk's stream
+            asm.end_block(CTRL_SLOT)
+    asm.begin_block()               # end of the chunk's stream
     asm("s_waitcnt lgkmcnt(0)")              # the step fetched ahead
     asm(f"s_mov_b32 m0, s{SAVE}")
     jump(".Lexit%=-.Lbase%=")
-    asm.end_block(ctrl_log2)
-    asm(f".p2align {ctrl_log2}")
+    asm.end_block(CTRL_SLOT)
 
     # ---- the table
     for ws in range(g["sets"]):
         for slot in range(G):
             for taps in universe():
-                asm.begin_block(block_log2)
+                asm.begin_block()
                 # the next record's block address first: it is ready long before the jump
                 asm(f"s_movrels_b32 s{TGT}, s{SET_A + 4}")
                 asm(f"s_add_u32 s{TGT}, s{TGT}, s{BASE}")
@@ -360,7 +361,7 @@ def _program_threaded(G, PR, PC, S, TGX, MODE, g):
                 asm(f"s_movrels_b64 s[{W + 2}:{W + 3}], s[{SET_A + 2}:{SET_A + 3}]")
                 asm(f"s_add_u32 m0, m0, {T_REC_DWORDS}")
                 asm(f"s_setpc_b64 s[{TGT}:{TGT + 1}]")
-                asm.end_block(block_log2)
+                asm.end_block(g["block_bytes"])
     asm(".Lexit%=:")
     return asm.lines
 

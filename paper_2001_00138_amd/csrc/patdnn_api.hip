@@ -456,7 +456,11 @@ double tiled_estimate(const patdnn_layer* h, const TiledVariant& v, const ConvSh
     const double waves = (double)((bands + 64 / v.TGX - 1) / (64 / v.TGX)) * ((s.c_out + v.G - 1) / v.G);
     const double rounds = waves <= 3072 ? 1.0 : waves / 3072 + 0.35;
     const double per_simd = std::min(3.0, std::max(1.0, waves / 1024));
-    return rounds * (0.336 * s.c_in + 0.195 * v.G * h->L.kept / s.c_out + 8.06) * (0.785 + 0.1075 * (per_simd - 1));
+    // libraries of more than eight patterns: the blocks in use outgrow the instruction cache, the more
+    // so the more kernels a wavefront runs (512 -> 512 at 28 x 28, 56 patterns: 825 us, 8 patterns 673)
+    const double kernels = (double)h->L.kept / s.c_out, over8 = std::log2(std::max(1.0, h->L.fkw.num_patterns / 8.0));
+    return rounds * (0.336 * s.c_in + 0.195 * v.G * kernels + 8.06) * (0.785 + 0.1075 * (per_simd - 1)) *
+           (1.0 + (0.03 + 5e-4 * std::min(kernels, 200.0)) * over8);
 }
 
 // FKW walk, microseconds: a wavefront walks the kernels of one filter, pattern by pattern, for 64

@@ -14,7 +14,7 @@ result except for double rounding on rare ties.
 
 Addresses: the program is laid out from ``CODE_BASE`` with the sizes of the real
 encodings (4 bytes, 8 with a 32-bit literal, 8 for SMEM and DS), honouring
-``.p2align``.  The generated code checks at assembly time that every block fits its
+``.p2align`` and ``.org``.  The generated code checks at assembly time that every block fits its
 slot, so block starts - the only jump targets - coincide with the real layout.
 """
 
@@ -54,6 +54,12 @@ class Program:
             if line.startswith(".p2align"):
                 a = 1 << int(line.split()[1])
                 pc = (pc + a - 1) // a * a
+                continue
+            if line.startswith(".org"):
+                label, size = line.split()[1].split("+")
+                if pc > self.labels[label] + int(size):
+                    raise ModelError(f"{label} is longer than {size} bytes")
+                pc = self.labels[label] + int(size)
                 continue
             if line.startswith((".if", ".error", ".endif")):
                 continue

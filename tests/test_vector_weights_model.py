@@ -50,3 +50,21 @@ def test_weights_in_vector_registers(oracle, monkeypatch, c_out, c_in, n, h, w, 
     name = "t_g8_p7x2_s1_x8_thw1b"
     assert name in [B.patdnn_variant_name(v) for v in range(B.patdnn_num_variants())]
     tim._check(oracle, d, x, ck, only=(name,))
+
+
+def test_blocks_fill_their_slots():
+    """Blocks lie where the encoder's offsets put them, and those of the largest variant close to each
+    other: the instruction cache has to hold what a layer's patterns use."""
+    import gen_dispatch
+    from paper_2001_00138_amd import buildlib
+    for key in buildlib.sparse_geometries():
+        lines, g = gen_dispatch.program(*key)
+        if g["vector"]:
+            lines = gen_dispatch.vector_weights(lines, g)
+        starts = [i for i, l in enumerate(lines) if l.startswith(".Lblk")]
+        table = starts[-g["sets"] * key[0] * 56:]
+        for a, b in zip(table, table[1:]):
+            code = 4 * sum(not l.startswith(".") for l in lines[a:b])      # instructions of four bytes all
+            assert lines[b - 1] == f".org {lines[a][:-1]}+{g['block_bytes']}"
+            assert 0 <= g["block_bytes"] - code < (16 if g["vector"] else g["block_bytes"] // 2)
+        assert g["table_off"] % 512 == 0
