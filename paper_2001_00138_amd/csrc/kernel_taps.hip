@@ -40,8 +40,6 @@ struct TapLoop;
 
 #include "gen/taps_all.inc"
 
-constexpr int kTile = 16, kTileOut = 14;
-
 struct TapArgs {
     const float* in;
     const float* bias;
@@ -196,28 +194,6 @@ __global__ __launch_bounds__(1024) void tap_conv_kernel(TapArgs a)
     }
 }
 
-// Tiles of this output size: images per tile, tiles per image.
-static void tap_tiles(const ConvShape& s, TapArgs& a)
-{
-    auto side = [&](int size, int32_t& tiles, int32_t& images, int32_t& pitch) {
-        const int used = size + s.pad;                // an image and the padding before it (the next one's is behind it)
-        tiles = used <= kTile ? 1 : 1 + (used - kTile + kTileOut - 1) / kTileOut;
-        pitch = used + (s.pool ? used & 1 : 0);       // pooling windows start at even rows and columns
-        images = tiles == 1 ? std::max(1, (kTile + pitch - used) / pitch) : 1;
-        if (images == 1) pitch = 2 * kTile;           // one image: never a second one
-    };
-    side(s.w, a.bx, a.sx, a.px);
-    side(s.h, a.by, a.sy, a.py);
-}
-
-long long tap_tile_count(const ConvShape& s)
-{
-    TapArgs a{};
-    tap_tiles(s, a);
-    const int per = a.sx * a.sy;
-    return (long long)((s.n + per - 1) / per) * a.bx * a.by;
-}
-
 template <int F>
 static hipError_t launch_taps_f(const DevTaps& t, const ConvShape& s, const float* in, const float* bias, float* out,
                                 int32_t waves, int32_t ksplit, float* scratch, size_t scratch_floats, hipStream_t stream)
@@ -230,7 +206,8 @@ static hipError_t launch_taps_f(const DevTaps& t, const ConvShape& s, const floa
     a.num_groups = t.num_groups; a.ck = t.ck; a.num_chunks = t.num_chunks; a.waves = waves;
     constexpr int NG = F / kTapGroup;
     a.fgsets = (t.num_groups + waves * NG - 1) / (waves * NG);
-    tap_tiles(s, a);
+    const TapTiles tiles = tap_tiles(s);
+    a.sx = tiles.sx; a.sy = tiles.sy; a.px = tiles.px; a.py = tiles.py; a.bx = tiles.bx; a.by = tiles.by;
     a.div_fgsets = make_fast_div((uint32_t)a.fgsets);
     a.div_bx = make_fast_div((uint32_t)a.bx);
     a.div_by = make_fast_div((uint32_t)a.by);

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cstdint>
 #include <string>
@@ -176,8 +177,37 @@ struct DevTaps {
     const uint32_t* records = nullptr;
     const float* weights = nullptr;
 };
-// Tiles of 16 x 16 input pixels that this input is cut into.
-long long tap_tile_count(const ConvShape& s);
+// How an input is cut into tiles of 16 x 16 input pixels (14 x 14 outputs inside an image).
+constexpr int kTile = 16, kTileOut = 14;
+struct TapTiles {
+    int32_t sx = 1, sy = 1, px = 0, py = 0;      // images side by side in a tile, and their pitch
+    int32_t bx = 1, by = 1;                      // tiles per image (1 where sx, sy exceed 1)
+};
+inline TapTiles tap_tiles(const ConvShape& s)
+{
+    TapTiles t;
+    auto side = [&](int size, int32_t& tiles, int32_t& images, int32_t& pitch) {
+        const int used = size + s.pad;                // an image and the padding before it (the next one's is behind it)
+        tiles = used <= kTile ? 1 : 1 + (used - kTile + kTileOut - 1) / kTileOut;
+        pitch = used + (s.pool ? used & 1 : 0);       // pooling windows start at even rows and columns
+        images = tiles == 1 ? std::max(1, (kTile + pitch - used) / pitch) : 1;
+        if (images == 1) pitch = 2 * kTile;           // one image: never a second one
+    };
+    side(s.w, t.bx, t.sx, t.px);
+    side(s.h, t.by, t.sy, t.py);
+    return t;
+}
+inline long long tap_tile_count(const ConvShape& s)
+{
+    const TapTiles t = tap_tiles(s);
+    return (long long)((s.n + t.sx * t.sy - 1) / (t.sx * t.sy)) * t.bx * t.by;
+}
+// Staging offsets are 32-bit byte offsets from the first image of a tile.
+inline bool taps_fit_input(const ConvShape& s)
+{
+    const TapTiles t = tap_tiles(s);
+    return (long long)t.sx * t.sy * s.c_in * s.h * s.w < (1ll << 30) && tap_tile_count(s) * ((s.c_out + 7) / 8) <= INT32_MAX;
+}
 // Stride 1 only; `filters` per wavefront is 8 or 16, the rest as TiledVariant::launch.
 hipError_t launch_taps(int filters, const DevTaps& t, const ConvShape& s, const float* in, const float* bias, float* out,
                        int32_t waves, int32_t ksplit, float* scratch, size_t scratch_floats, hipStream_t stream);

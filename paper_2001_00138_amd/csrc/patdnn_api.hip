@@ -234,14 +234,6 @@ bool taps_fit_layer(const patdnn_layer* h)
     return !L.depthwise && !L.dense && L.all_in_universe && L.desc.stride == 1;
 }
 
-bool taps_fit_input(const ConvShape& s)
-{
-    // staging offsets are 32-bit byte offsets relative to the first image of a tile, which may
-    // hold 64 images of one pixel or one large image
-    const long long images = s.h > 7 || s.w > 7 ? 8 : 64;
-    return images * s.c_in * s.h * s.w < (1ll << 30) && tap_tile_count(s) * ((s.c_out + 7) / 8) <= INT32_MAX;
-}
-
 // The chunk sizes whose layouts every handle holds: equal chunks of at most 128 channels (a flush
 // per filter and pattern in every chunk, so the fewer chunks the better; 128 KB of LDS), half and a
 // quarter of that for launches that split the channels over workgroups.
@@ -488,7 +480,7 @@ patdnn_config_t default_config(patdnn_layer* h, const ConvShape& shape, size_t s
     s.pool = 0;
     if (h->L.depthwise) return patdnn_config_t{variant_of_extra(kExtraDepthwise), 0, 0, 1};
     patdnn_config_t best{PATDNN_VARIANT_FKW, 0, 0, 1};
-    const bool taps = taps_fit_layer(h) && taps_fit_input(s) && !h->taps.empty();
+    const bool taps = taps_fit_layer(h) && taps_fit_input(s) && taps_fit_input(shape) && !h->taps.empty();
     double best_us = taps ? fkw_estimate(h, s) : 0.0;
     for (int vi : default_variant_order(h)) {
         const TiledVariant& v = tiled_variant(vi);
