@@ -76,6 +76,7 @@ struct patdnn_layer {
     std::map<std::pair<int, int>, std::unique_ptr<TiledOnDevice>> tiled;
     std::map<int, std::unique_ptr<TapsOnDevice>> taps;     // tap-product layouts by ck
     std::vector<int32_t> tap_groups;                       // the filter groups they share
+    std::vector<int> order;                                // tiled variants that can run the layer, as they are tried
     std::vector<void*> allocations;
     // the comparison kernels' layouts (built when such a variant is first selected)
     struct CompareHost {
@@ -393,20 +394,21 @@ patdnn_status_t run_config(patdnn_layer* h, const patdnn_config_t& c, const Conv
     return e == hipSuccess ? PATDNN_OK : hip_fail(e, "launching a tiled kernel");
 }
 
-// Tiled variants in the order in which an untuned layer tries them: first the variant that the
-// tuner prefers on most measured layers (threaded dispatch, 7x2 patch, one staging buffer; it
-// needs the scalar relative moves that the self-test checks on the device), then the order
-// of variants.def, whose first line (call dispatch) has no such requirement.
+// Tiled variants that can run the layer, in the order in which it tries them when nothing is
+// configured: first the variant that the tuner prefers on most measured layers (threaded dispatch,
+// 7x2 patch, one staging buffer; it needs the scalar relative moves that the self-test checks on the
+// device), then the order of variants.def, whose first line (call dispatch) has no such requirement.
+// Worked out once per handle: a call allocates nothing.
 std::vector<int> default_variant_order(const patdnn_layer* h)
 {
     std::vector<int> order;
     for (int vi = 0; vi < num_tiled_variants(); ++vi)
         if (std::string(tiled_variant(vi).name) == "t_g8_p7x2_s1_x8_thw1b") {
             std::string why;
-            if (!h->on_device || movrel_selftest(why)) order.push_back(vi);
+            if (variant_selectable(h, tiled_variant(vi)) && (!h->on_device || movrel_selftest(why))) order.push_back(vi);
         }
     for (int vi = 0; vi < num_tiled_variants(); ++vi)
-        if (order.empty() || vi != order[0]) order.push_back(vi);
+        if (variant_selectable(h, tiled_variant(vi)) && (order.empty() || vi != order[0])) order.push_back(vi);
     return order;
 }
 
@@ -482,10 +484,10 @@ patdnn_config_t default_config(patdnn_layer* h, const ConvShape& shape, size_t s
     patdnn_config_t best{PATDNN_VARIANT_FKW, 0, 0, 1};
     const bool taps = taps_fit_layer(h) && taps_fit_input(s) && taps_fit_input(shape) && !h->taps.empty();
     double best_us = taps ? fkw_estimate(h, s) : 0.0;
-    for (int vi : default_variant_order(h)) {
+    for (int vi : h->order) {
         const TiledVariant& v = tiled_variant(vi);
         int32_t ck = 0, waves = 0;
-        if (!variant_selectable(h, v) || !resolve_tiled_params(h, v, s, ck, waves)) continue;
+        if (!resolve_tiled_params(h, v, s, ck, waves)) continue;
         if (h->tiled.find(std::make_pair(vi, v.dense ? 0 : ck)) == h->tiled.end()) continue;
         const double us = taps ? tiled_estimate(h, v, s) : -1.0;
         if (us < best_us) { best_us = us; best = patdnn_config_t{vi + 1, ck, waves, 1}; }
@@ -624,12 +626,12 @@ patdnn_status_t patdnn_encode(const patdnn_layer_desc_t* desc, const float* dens
                 st = ensure_taps(h.get(), ck, nullptr);
                 if (st != PATDNN_OK) return st;
             }
-        for (int vi : default_variant_order(h.get()))
-            if (variant_selectable(h.get(), tiled_variant(vi))) {
-                st = ensure_tiled(h.get(), vi, default_ck(tiled_variant(vi), desc->c_in), nullptr);
-                if (st != PATDNN_OK) return st;
-                break;
-            }
+        h->order = default_variant_order(h.get());
+        if (!h->order.empty()) {
+            const int vi = h->order[0];
+            st = ensure_tiled(h.get(), vi, default_ck(tiled_variant(vi), desc->c_in), nullptr);
+            if (st != PATDNN_OK) return st;
+        }
     } catch (const std::bad_alloc&) {
         return fail(PATDNN_ENOMEM, "out of host memory");
     }
@@ -658,6 +660,7 @@ struct ZeroHandoff {
     ZeroRegion pre_zeroed;   // in: already holds zeros when the layer starts
     ZeroRegion next;         // in: what the next layer will want zeroed
     bool done = false;       // out: `next` was cleared by this layer
+    const patdnn_config_t* plan = nullptr;    // in: this layer's effective_config, where it is known already
 };
 
 // A split launch stores its slices to buffers of their own (no zero fill, no atomics) if the
@@ -744,7 +747,7 @@ static patdnn_status_t conv2d_impl(patdnn_handle_t h, const float* input, int32_
         }
         return run_config(h, c, s, input, bias, output, stream, scratch, scratch_floats);
     };
-    st = run(effective_config(h, s, scratch, scratch_floats));
+    st = run(handoff && handoff->plan ? *handoff->plan : effective_config(h, s, scratch, scratch_floats));
     // a configuration tuned for another input size may not fit this one; a configuration the
     // caller set explicitly is never replaced: the error goes back instead
     if (st == PATDNN_EUNSUPPORTED && h->cfg.variant > 0 && h->cfg_tuned)
@@ -1176,11 +1179,8 @@ patdnn_status_t patdnn_tune_ws(patdnn_handle_t h, const float* input, int32_t n,
     h->cfg_tuned = true;
     // keep the winner's layout and the default variant's; free the others
     {
-        const std::vector<int> order = default_variant_order(h);
         auto default_layout = [&](int vi, int ck) {
-            for (int o : order)
-                if (variant_selectable(h, tiled_variant(o))) return vi == o && (tiled_variant(o).dense || ck == default_ck(tiled_variant(o), s.c_in));
-            return false;
+            return !h->order.empty() && vi == h->order[0] && (tiled_variant(vi).dense || ck == default_ck(tiled_variant(vi), s.c_in));
         };
         for (auto it = h->tiled.begin(); it != h->tiled.end();) {
             const int vnum = it->first.first + 1;
@@ -1321,17 +1321,23 @@ patdnn_status_t stack_launch(patdnn_stack* s, const float* input, float* output,
     // layer has just finished reading) or the partial-sum buffer, never what this layer itself
     // still reads or writes (the launcher checks the one case that could coincide).
     ZeroRegion zeroed;
-    for (int i = 0; i < L; ++i) {
+    patdnn_config_t plan{}, next_plan{};          // of this layer and the next one (planned is false: not worked out)
+    bool planned = false, next_planned = false;
+    for (int i = 0; i < L; ++i, plan = next_plan, planned = next_planned) {
         float* dst = dst_of(i);
         const patdnn_stack_layer_t& ly = s->layers[i];
         ZeroHandoff hand;
         hand.pre_zeroed = zeroed;
+        if (planned) hand.plan = &plan;
+        next_planned = false;
         if (i + 1 < L) {
             const patdnn_stack_layer_t& nx = s->layers[i + 1];
             ConvShape ns{};
             if (shape_of(nx.layer, s->n, s->in_h[i + 1], s->in_w[i + 1], ns) == PATDNN_OK) {
                 ns.pool = nx.pool2 ? 1 : 0;
-                hand.next = zero_need(effective_config(nx.layer, ns, split, split_floats), ns, dst_of(i + 1), split, split_floats);
+                next_plan = effective_config(nx.layer, ns, split, split_floats);
+                next_planned = true;
+                hand.next = zero_need(next_plan, ns, dst_of(i + 1), split, split_floats);
             }
             if (hand.next.p == dst) hand.next = ZeroRegion{};     // this layer's own output: cannot happen
         }
