@@ -126,24 +126,26 @@ patdnn_status_t build_fkw(const patdnn_layer_desc_t& d, const float* w, const ui
     f.index.resize(kept_total);
     f.weight.resize((size_t)kept_total * f.taps);
     int32_t pos = 0;
+    std::vector<int32_t> next(P);                // where the next kernel of a pattern goes
     for (int s = 0; s < d.c_out; ++s) {
         const int co = order[s];
         f.offset[s] = pos;
         int32_t* st = &f.stride[(size_t)s * (P + 1)];
         for (int p = 0; p < P; ++p) {
             st[p] = pos - f.offset[s];
-            for (int k = 0; k < kpf; ++k) {          // ascending input channel inside a pattern
-                const size_t kid = (size_t)co * kpf + k;
-                if (!kept_at(co, k)) continue;
-                if (!dense && ids[kid] != p) continue;
-                f.index[pos] = depthwise ? co : k;
-                const unsigned m = f.masks[p];
-                float* dst = &f.weight[(size_t)pos * f.taps];
-                int t = 0;
-                for (int q = 0; q < 9; ++q)
-                    if ((m >> q) & 1u) dst[t++] = w[kid * 9 + q];
-                ++pos;
-            }
+            next[p] = pos;
+            pos += counts[(size_t)co * P + p];
+        }
+        for (int k = 0; k < kpf; ++k) {              // ascending input channel inside a pattern
+            const size_t kid = (size_t)co * kpf + k;
+            if (!kept_at(co, k)) continue;
+            const int p = dense ? 0 : ids[kid];
+            const int32_t at = next[p]++;
+            f.index[at] = depthwise ? co : k;
+            const unsigned m = f.masks[p];
+            float* dst = &f.weight[(size_t)at * f.taps];
+            for (int q = 0; q < 9; ++q)
+                if ((m >> q) & 1u) *dst++ = w[kid * 9 + q];
         }
         st[P] = pos - f.offset[s];
     }

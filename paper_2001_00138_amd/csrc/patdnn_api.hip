@@ -96,27 +96,59 @@ struct patdnn_layer {
 
 namespace {
 
-template <class T>
-hipError_t upload(std::vector<void*>& owner, const std::vector<T>& v, const T** out, size_t extra = 0)
-{
-    *out = nullptr;
-    const size_t bytes = (v.size() + extra) * sizeof(T);
-    if (bytes == 0) return hipSuccess;
-    void* p = nullptr;
-    hipError_t e = hipMalloc(&p, bytes);
-    if (e != hipSuccess) return e;
-    owner.push_back(p);
-    if (extra) {
-        e = hipMemset(p, 0, bytes);
-        if (e != hipSuccess) return e;
+// Host arrays on their way to the device: one allocation for all of them, and one copy where they are
+// small - an allocation and a copy take some 15 us whatever their size, and a layer has two dozen arrays.
+class Upload {
+public:
+    // `v` must stay as it is until commit(), which sets *out (NULL for an empty array)
+    template <class T>
+    void add(const std::vector<T>& v, const T** out)
+    {
+        place(v.data(), v.size() * sizeof(T), out);
     }
-    if (!v.empty()) {
-        e = hipMemcpy(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice);
-        if (e != hipSuccess) return e;
+    // room for `count` elements that a kernel will write
+    template <class T>
+    void room(size_t count, const T** out)
+    {
+        place(nullptr, count * sizeof(T), out);
     }
-    *out = static_cast<const T*>(p);
-    return hipSuccess;
-}
+    hipError_t commit(std::vector<void*>& owner)
+    {
+        if (!total) return hipSuccess;
+        void* p = nullptr;
+        hipError_t e = hipMalloc(&p, total);
+        if (e != hipSuccess) return e;
+        owner.push_back(p);
+        char* const dev = static_cast<char*>(p);
+        const bool together = copied <= 256 * 1024;
+        std::vector<char> stage(together ? copied : 0);
+        for (const Item& i : items) {
+            if (i.src && together) std::memcpy(&stage[i.at], i.src, i.bytes);
+            else if (i.src && (e = hipMemcpy(dev + i.at, i.src, i.bytes, hipMemcpyHostToDevice)) != hipSuccess) return e;
+            i.set(i.out, dev + i.at);
+        }
+        return stage.empty() ? hipSuccess : hipMemcpy(dev, stage.data(), stage.size(), hipMemcpyHostToDevice);
+    }
+
+private:
+    struct Item {
+        const void* src;
+        size_t bytes, at;
+        void* out;
+        void (*set)(void* out, void* device);
+    };
+    template <class T>
+    void place(const void* src, size_t bytes, const T** out)
+    {
+        *out = nullptr;
+        if (!bytes) return;
+        items.push_back(Item{src, bytes, total, out, [](void* o, void* d) { *static_cast<const T**>(o) = static_cast<const T*>(d); }});
+        if (src) copied = total + bytes;
+        total = (total + bytes + 255) / 256 * 256;
+    }
+    std::vector<Item> items;
+    size_t total = 0, copied = 0;             // bytes of the allocation; up to the end of the last array that is copied
+};
 
 bool variant_fits_layer(const patdnn_layer* h, const TiledVariant& v)
 {
@@ -214,12 +246,13 @@ patdnn_status_t ensure_tiled(patdnn_layer* h, int vi, int ck, const DevTiled** o
         t->dev.ck = ck;
         t->dev.num_chunks = t->host.num_chunks;
         if (h->on_device) {
-            hipError_t e;
-            if ((e = upload(t->allocations, t->host.slot_channel, &t->dev.slot_channel)) != hipSuccess ||
-                (e = upload(t->allocations, t->host.chunk_ptr, &t->dev.chunk_ptr)) != hipSuccess ||
-                (e = upload(t->allocations, t->host.steps, &t->dev.steps)) != hipSuccess ||
-                (e = upload(t->allocations, t->host.w9, &t->dev.w9)) != hipSuccess)
-                return hip_fail(e, "uploading the tiled layout");
+            Upload up;
+            up.add(t->host.slot_channel, &t->dev.slot_channel);
+            up.add(t->host.chunk_ptr, &t->dev.chunk_ptr);
+            up.add(t->host.steps, &t->dev.steps);
+            up.add(t->host.w9, &t->dev.w9);
+            const hipError_t e = up.commit(t->allocations);
+            if (e != hipSuccess) return hip_fail(e, "uploading the tiled layout");
         }
         it = h->tiled.emplace(key, std::move(t)).first;
     }
@@ -257,12 +290,13 @@ patdnn_status_t ensure_taps(patdnn_layer* h, int ck, const DevTaps** out)
         t->dev.ck = ck;
         t->dev.num_chunks = t->host.num_chunks;
         if (h->on_device) {
-            hipError_t e;
-            if ((e = upload(t->allocations, t->host.slot_channel, &t->dev.slot_channel)) != hipSuccess ||
-                (e = upload(t->allocations, t->host.chunk_ptr, &t->dev.chunk_ptr)) != hipSuccess ||
-                (e = upload(t->allocations, t->host.records, &t->dev.records)) != hipSuccess ||
-                (e = upload(t->allocations, t->host.weights, &t->dev.weights)) != hipSuccess)
-                return hip_fail(e, "uploading the tap-product layout");
+            Upload up;
+            up.add(t->host.slot_channel, &t->dev.slot_channel);
+            up.add(t->host.chunk_ptr, &t->dev.chunk_ptr);
+            up.add(t->host.records, &t->dev.records);
+            up.add(t->host.weights, &t->dev.weights);
+            const hipError_t e = up.commit(t->allocations);
+            if (e != hipSuccess) return hip_fail(e, "uploading the tap-product layout");
         }
         it = h->taps.emplace(ck, std::move(t)).first;
     }
@@ -312,15 +346,16 @@ patdnn_status_t ensure_compare(patdnn_layer* h)
         h->compare_built = true;
     }
     if (h->on_device && !h->compare_on_device) {
-        hipError_t e;
-        if ((e = upload(h->allocations, h->noopt_host.row_ptr, &h->noopt_dev.row_ptr)) != hipSuccess ||
-            (e = upload(h->allocations, h->noopt_host.col, &h->noopt_dev.col)) != hipSuccess ||
-            (e = upload(h->allocations, h->noopt_host.kmask, &h->noopt_dev.kmask)) != hipSuccess ||
-            (e = upload(h->allocations, h->noopt_host.val, &h->noopt_dev.val)) != hipSuccess ||
-            (e = upload(h->allocations, h->csr_host.row_ptr, &h->csr_dev.row_ptr)) != hipSuccess ||
-            (e = upload(h->allocations, h->csr_host.col, &h->csr_dev.col)) != hipSuccess ||
-            (e = upload(h->allocations, h->csr_host.val, &h->csr_dev.val)) != hipSuccess)
-            return hip_fail(e, "uploading the comparison layouts");
+        Upload up;
+        up.add(h->noopt_host.row_ptr, &h->noopt_dev.row_ptr);
+        up.add(h->noopt_host.col, &h->noopt_dev.col);
+        up.add(h->noopt_host.kmask, &h->noopt_dev.kmask);
+        up.add(h->noopt_host.val, &h->noopt_dev.val);
+        up.add(h->csr_host.row_ptr, &h->csr_dev.row_ptr);
+        up.add(h->csr_host.col, &h->csr_dev.col);
+        up.add(h->csr_host.val, &h->csr_dev.val);
+        const hipError_t e = up.commit(h->allocations);
+        if (e != hipSuccess) return hip_fail(e, "uploading the comparison layouts");
         h->compare_on_device = true;
     }
     return PATDNN_OK;
@@ -471,6 +506,86 @@ double fkw_estimate(const patdnn_layer* h, const ConvShape& s)
 // Binary16 weights with the removed ones as zeros: up to 256 MB a layer.
 constexpr size_t kMaxExpandedHalves = (size_t)128 << 20;
 
+// The FKW arrays and what is derived from them, to the device.
+patdnn_status_t upload_layer(patdnn_layer* h)
+{
+    hipError_t e = hipGetDevice(&h->device);
+    if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
+    const Fkw& f = h->L.fkw;
+    DevFkw& d = h->dfkw;
+    d.num_patterns = f.num_patterns;
+    d.taps = f.taps;
+    Upload up;
+    up.add(f.offset, &d.offset);
+    up.add(f.reorder, &d.reorder);
+    up.add(f.index, &d.index);
+    up.add(f.stride, &d.stride);
+    up.add(f.weight, &d.weight);
+    up.add(f.masks, &d.masks);
+    // the weights once more in binary16 (round to nearest even) for patdnn_conv2d_f16
+    const auto to_f16 = [](const std::vector<float>& from, std::vector<uint16_t>& to) {
+        bool finite = true;
+        to.resize(from.size());
+        for (size_t i = 0; i < to.size(); ++i) {
+            const _Float16 hv = static_cast<_Float16>(from[i]);
+            std::memcpy(&to[i], &hv, 2);
+            finite = finite && (to[i] & 0x7C00) != 0x7C00;
+        }
+        return finite;
+    };
+    std::vector<uint16_t> w16;
+    const bool finite16 = to_f16(f.weight, w16);
+    const uint16_t *weight16 = nullptr, *expanded16 = nullptr, *dw_weight16 = nullptr;
+    up.add(w16, &weight16);
+    std::vector<int32_t> dmask, taps;
+    std::vector<float> dweight, tap_weight;
+    std::vector<uint16_t> dweight16;
+    if (h->L.depthwise) {
+        // per stored filter: the mask of its kernel's pattern and its four weights; and by channel, the
+        // four tap positions in nibbles
+        const int c = h->L.desc.c_out, P = f.num_patterns;
+        dmask.assign((size_t)c, 0);
+        dweight.assign((size_t)c * 4, 0.0f);
+        taps.assign((size_t)c, -1);
+        tap_weight.assign((size_t)c * 4, 0.0f);
+        for (int s = 0; s < c; ++s) {
+            if (f.offset[s + 1] == f.offset[s]) continue;
+            const int32_t* st = &f.stride[(size_t)s * (P + 1)];
+            for (int p = 0; p < P; ++p)
+                if (st[p + 1] > st[p]) dmask[s] = f.masks[p];
+            const int co = f.reorder[s];
+            unsigned nibbles = 0;
+            for (int pos = 8; pos >= 0; --pos)
+                if (dmask[s] >> pos & 1) nibbles = nibbles << 4 | (unsigned)pos;
+            taps[co] = (int32_t)nibbles;
+            for (int t = 0; t < 4; ++t)
+                tap_weight[(size_t)co * 4 + t] = dweight[(size_t)s * 4 + t] = f.weight[(size_t)f.offset[s] * 4 + t];
+        }
+        up.add(dmask, &d.dw_mask);
+        up.add(dweight, &d.dw_weight);
+        if (to_f16(dweight, dweight16)) {         // else zero padding would meet an infinite weight
+            up.add(taps, &d.dw_taps);
+            up.add(tap_weight, &d.dw_tap_weight);
+        }
+        up.add(dweight16, &dw_weight16);
+    }
+    size_t expanded = h->L.depthwise || !finite16 ? 0 : f16_expanded_halves(h->L.desc.c_in, h->L.desc.c_out);
+    if (expanded > kMaxExpandedHalves) expanded = 0;
+    up.room(expanded, &expanded16);
+    if ((e = up.commit(h->allocations)) != hipSuccess) return hip_fail(e, "uploading the layer");
+    d.weight_f16 = weight16;
+    d.dw_weight_f16 = dw_weight16;
+    if (expanded) {
+        if ((e = hipMemsetAsync(const_cast<uint16_t*>(expanded16), 0, expanded * 2, nullptr)) != hipSuccess ||
+            (e = launch_f16_expand(d, h->L.desc.c_in, h->L.desc.c_out, const_cast<uint16_t*>(expanded16), nullptr)) != hipSuccess ||
+            (e = hipStreamSynchronize(nullptr)) != hipSuccess)
+            return hip_fail(e, "expanding the binary16 weights");
+        d.expanded_f16 = expanded16;
+    }
+    h->on_device = true;
+    return PATDNN_OK;
+}
+
 // Partial sums that the library asks room for by itself: 512 MB.
 constexpr size_t kMaxSliceFloats = (size_t)128 << 20;
 
@@ -537,88 +652,13 @@ patdnn_status_t patdnn_encode(const patdnn_layer_desc_t* desc, const float* dens
     }
     if (st != PATDNN_OK) return fail(st, err);
 
-    if (!(desc->flags & PATDNN_HOST_ONLY)) {
-        hipError_t e = hipGetDevice(&h->device);
-        if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
-        const Fkw& f = h->L.fkw;
-        if ((e = upload(h->allocations, f.offset, &h->dfkw.offset)) != hipSuccess ||
-            (e = upload(h->allocations, f.reorder, &h->dfkw.reorder)) != hipSuccess ||
-            (e = upload(h->allocations, f.index, &h->dfkw.index)) != hipSuccess ||
-            (e = upload(h->allocations, f.stride, &h->dfkw.stride)) != hipSuccess ||
-            (e = upload(h->allocations, f.weight, &h->dfkw.weight)) != hipSuccess ||
-            (e = upload(h->allocations, f.masks, &h->dfkw.masks)) != hipSuccess)
-            return hip_fail(e, "uploading the FKW arrays");
-        h->dfkw.num_patterns = f.num_patterns;
-        h->dfkw.taps = f.taps;
-        bool finite16 = true;
-        {
-            // the weights once more in binary16 (round to nearest even) for patdnn_conv2d_f16
-            std::vector<uint16_t> w16(f.weight.size());
-            for (size_t i = 0; i < w16.size(); ++i) {
-                const _Float16 hv = static_cast<_Float16>(f.weight[i]);
-                std::memcpy(&w16[i], &hv, 2);
-                finite16 = finite16 && (w16[i] & 0x7C00) != 0x7C00;
-            }
-            const uint16_t* dev16 = nullptr;
-            if ((e = upload(h->allocations, w16, &dev16)) != hipSuccess) return hip_fail(e, "uploading the binary16 weights");
-            h->dfkw.weight_f16 = dev16;
-        }
-        const size_t expanded = h->L.depthwise || !finite16 ? 0 : f16_expanded_halves(desc->c_in, desc->c_out);
-        if (expanded && expanded <= kMaxExpandedHalves) {
-            const std::vector<uint16_t> none;
-            const uint16_t* dev16 = nullptr;
-            if ((e = upload(h->allocations, none, &dev16, expanded)) != hipSuccess ||
-                (e = launch_f16_expand(h->dfkw, desc->c_in, desc->c_out, const_cast<uint16_t*>(dev16), nullptr)) != hipSuccess ||
-                (e = hipStreamSynchronize(nullptr)) != hipSuccess)
-                return hip_fail(e, "expanding the binary16 weights");
-            h->dfkw.expanded_f16 = dev16;
-        }
-        if (h->L.depthwise) {
-            // per stored filter: the mask of its kernel's pattern and its four weights
-            const int c = desc->c_out, P = f.num_patterns;
-            std::vector<int32_t> dmask((size_t)c, 0);
-            std::vector<float> dweight((size_t)c * 4, 0.0f);
-            for (int s = 0; s < c; ++s) {
-                if (f.offset[s + 1] == f.offset[s]) continue;
-                const int32_t* st = &f.stride[(size_t)s * (P + 1)];
-                for (int p = 0; p < P; ++p)
-                    if (st[p + 1] > st[p]) dmask[s] = f.masks[p];
-                for (int t = 0; t < 4; ++t) dweight[(size_t)s * 4 + t] = f.weight[(size_t)f.offset[s] * 4 + t];
-            }
-            std::vector<uint16_t> dweight16(dweight.size());
-            for (size_t i = 0; i < dweight16.size(); ++i) {
-                const _Float16 hv = static_cast<_Float16>(dweight[i]);
-                std::memcpy(&dweight16[i], &hv, 2);
-            }
-            const uint16_t* dev16 = nullptr;
-            if ((e = upload(h->allocations, dmask, &h->dfkw.dw_mask)) != hipSuccess ||
-                (e = upload(h->allocations, dweight, &h->dfkw.dw_weight)) != hipSuccess ||
-                (e = upload(h->allocations, dweight16, &dev16)) != hipSuccess)
-                return hip_fail(e, "uploading the depthwise arrays");
-            h->dfkw.dw_weight_f16 = dev16;
-            std::vector<int32_t> taps((size_t)c, -1);
-            std::vector<float> tap_weight((size_t)c * 4);
-            bool finite = true;
-            for (int s = 0; s < c; ++s) {
-                const int co = f.reorder[s];
-                unsigned nibbles = 0;
-                for (int pos = 8; pos >= 0; --pos)
-                    if (dmask[s] >> pos & 1) nibbles = nibbles << 4 | (unsigned)pos;
-                if (dmask[s]) taps[co] = (int32_t)nibbles;
-                for (int t = 0; t < 4; ++t) {
-                    tap_weight[(size_t)co * 4 + t] = dweight[(size_t)s * 4 + t];
-                    finite = finite && (dweight16[(size_t)s * 4 + t] & 0x7C00) != 0x7C00;
-                }
-            }
-            if (finite && ((e = upload(h->allocations, taps, &h->dfkw.dw_taps)) != hipSuccess ||
-                           (e = upload(h->allocations, tap_weight, &h->dfkw.dw_tap_weight)) != hipSuccess))
-                return hip_fail(e, "uploading the depthwise arrays");
-        }
-        h->on_device = true;
-    }
-    // build (and upload) the group layout of the default variant; the layouts of the other
-    // variants are built when patdnn_set_config or patdnn_tune asks for them
     try {
+        if (!(desc->flags & PATDNN_HOST_ONLY)) {
+            st = upload_layer(h.get());
+            if (st != PATDNN_OK) return st;
+        }
+        // build (and upload) the group layout of the default variant; the layouts of the other
+        // variants are built when patdnn_set_config or patdnn_tune asks for them
         if (taps_fit_layer(h.get()))
             for (int level = 0; level < kTapLevels; ++level) {
                 const int ck = taps_ck(desc->c_in, level);
