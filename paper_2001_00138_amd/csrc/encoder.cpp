@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <cstring>
 #include <numeric>
+#include <type_traits>
 
 namespace patdnn {
 
@@ -187,26 +188,34 @@ void decode_fkw(const LayerHost& L, const Fkw& f, float* w, uint8_t* ids, uint8_
 // reorder serves for the threads of a block (section 5.2).  Filters are dealt out longest first,
 // each to the group with a free slot whose per-chunk load stays flattest (sum of squares), then
 // pairs of filters are swapped between groups while that improves.
-static std::vector<int32_t> assign_groups(const LayerHost& L, int G, int ck)
+// T: an integer that holds twice a group's kernels in a chunk, and one filter's more.
+template <class T>
+static std::vector<int32_t> assign_groups_of(const LayerHost& L, int G, int ck)
 {
     const Fkw& f = L.fkw;
     const int c_out = L.desc.c_out;
     const int nc = (L.desc.c_in + ck - 1) / ck, ng = (c_out + G - 1) / G;
     std::vector<int32_t> members((size_t)ng * G, -1);
-    std::vector<int32_t> fc((size_t)c_out * nc, 0);             // kernels of a filter per chunk
+    std::vector<T> fc((size_t)c_out * nc, 0);             // kernels of a filter per chunk
     for (int s = 0; s < c_out; ++s)
         for (int32_t k = f.offset[s]; k < f.offset[s + 1]; ++k) ++fc[(size_t)s * nc + f.index[k] / ck];
-    // a group has at most G * ck <= 2^21 kernels in a chunk, so the squares fit 64 bits and the
-    // factors 32: loops the compiler turns into vector code
-    std::vector<int32_t> load((size_t)ng * nc, 0);
+    std::vector<T> load((size_t)ng * nc, 0);
     std::vector<int32_t> fill(ng, 0);
-    const std::vector<int32_t> none(nc, 0);
-    auto delta_sq = [&](int g, const int32_t* add, const int32_t* sub) {
+    const std::vector<T> none(nc, 0);
+    auto delta_sq = [&](int g, const T* add, const T* sub) {
         int64_t d = 0;                                           // change of sum(load^2) of group g
-        const int32_t* a = &load[(size_t)g * nc];
-        for (int c = 0; c < nc; ++c) {
-            const int32_t x = add[c] - sub[c];
-            d += (int64_t)x * (2 * a[c] + x);
+        const T* a = &load[(size_t)g * nc];
+        // products of 16-bit numbers added up in 32 bits for as long as they fit: vector instructions
+        constexpr int kRun = sizeof(T) == 2 ? 1024 : 1 << 30;
+        for (int c0 = 0; c0 < nc;) {
+            const int c1 = c0 + std::min(nc - c0, kRun);
+            std::conditional_t<sizeof(T) == 2, int32_t, int64_t> sum = 0;
+            for (int c = c0; c < c1; ++c) {
+                const T x = (T)(add[c] - sub[c]), y = (T)(2 * a[c] + x);
+                sum += (decltype(sum))x * y;
+            }
+            d += sum;
+            c0 = c1;
         }
         return d;
     };
@@ -232,8 +241,8 @@ static std::vector<int32_t> assign_groups(const LayerHost& L, int G, int ck)
         const int ib = (int)((lcg >> 33) % (uint64_t)members.size());
         const int ga = ia / G, gb = ib / G, sa = members[ia], sb = members[ib];
         if (ga == gb || sa < 0 || sb < 0) continue;
-        const int32_t* fa = &fc[(size_t)sa * nc];
-        const int32_t* fb = &fc[(size_t)sb * nc];
+        const T* fa = &fc[(size_t)sa * nc];
+        const T* fb = &fc[(size_t)sb * nc];
         if (delta_sq(ga, fb, fa) + delta_sq(gb, fa, fb) >= 0) continue;
         for (int c = 0; c < nc; ++c) {
             load[(size_t)ga * nc + c] += fb[c] - fa[c];
@@ -242,6 +251,13 @@ static std::vector<int32_t> assign_groups(const LayerHost& L, int G, int ck)
         std::swap(members[ia], members[ib]);
     }
     return members;
+}
+
+static std::vector<int32_t> assign_groups(const LayerHost& L, int G, int ck)
+{
+    // 16 bits for vectors of chunks, with factors below 2^15 and 1024 products of them below 2^31
+    const int64_t most = (int64_t)ck * (2 * G + 1);
+    return L.desc.c_in / ck >= 8 && most < (1 << 15) && most * ck < (1 << 21) ? assign_groups_of<int16_t>(L, G, ck) : assign_groups_of<int32_t>(L, G, ck);
 }
 
 void build_tiled(const LayerHost& L, const TiledParams& prm, Tiled& T)
@@ -408,18 +424,17 @@ void build_taps(const LayerHost& L, int ck, const std::vector<int32_t>& members,
     T.num_groups = (c_out + G - 1) / G;
     T.num_chunks = (c_in + ck - 1) / ck;
     T.slot_channel.assign((size_t)T.num_groups * G, -1);
-    T.group_kernels.assign(T.num_groups, 0);
     T.chunk_ptr.assign((size_t)T.num_groups * T.num_chunks, 0);
-    const size_t room = (size_t)L.kept + (size_t)T.num_groups * T.num_chunks * (G + kTapBatch) + 2 * kTapBatch;
-    T.records.reserve(room);
-    T.weights.reserve(4 * room);
+    // at most: every kernel, an end for every filter and chunk, every batch filled up
+    T.records.resize((size_t)L.kept + (size_t)T.num_groups * T.num_chunks * (G + kTapBatch) + 2 * kTapBatch);
+    T.weights.resize(4 * T.records.size());
+    size_t count = 0;
     auto append = [&](uint32_t rec, const float* w) {
-        T.records.push_back(rec);
-        for (int t = 0; t < 4; ++t) T.weights.push_back(w ? w[t] : 0.0f);
+        T.records[count] = rec;
+        if (w) std::memcpy(&T.weights[4 * count], w, 4 * sizeof(float));
+        ++count;
     };
-    auto pad_batch = [&] {
-        while (T.records.size() % kTapBatch) append(0u, nullptr);
-    };
+    auto pad_batch = [&] { count = (count + kTapBatch - 1) / kTapBatch * kTapBatch; };      // zeros
     // where each (filter, pattern) run of the FKW arrays continues with the next chunk: the
     // channels of a run ascend
     std::vector<int32_t> next((size_t)c_out * P);
@@ -427,34 +442,33 @@ void build_taps(const LayerHost& L, int ck, const std::vector<int32_t>& members,
         for (int p = 0; p < P; ++p) next[(size_t)s * P + p] = f.offset[s] + f.stride[(size_t)s * (P + 1) + p];
     for (int g = 0; g < T.num_groups; ++g)
         for (int chunk = 0; chunk < T.num_chunks; ++chunk) {
-            T.chunk_ptr[(size_t)g * T.num_chunks + chunk] = (uint32_t)(T.records.size() / kTapBatch);
+            T.chunk_ptr[(size_t)g * T.num_chunks + chunk] = (uint32_t)(count / kTapBatch);
             const int c0 = chunk * ck, c1 = c0 + ck;
             for (int slot = 0; slot < G; ++slot) {
                 const int s = members[(size_t)g * G + slot];
-                const size_t before = T.records.size();
+                const size_t before = count;
                 for (int p = 0; s >= 0 && p < P; ++p) {
                     int32_t& k = next[(size_t)s * P + p];
                     const int32_t end = f.offset[s] + f.stride[(size_t)s * (P + 1) + p + 1];
-                    const size_t run = T.records.size();
+                    const size_t run = count;
                     for (; k < end && f.index[k] < c1; ++k)
                         append((uint32_t)(f.index[k] - c0) | (uint32_t)L.universe_of_pattern[p] << kTapPatternShift,
                                &f.weight[(size_t)k * 4]);
-                    if (T.records.size() > run) {
-                        T.records.back() |= kTapSegmentEnd;
+                    if (count > run) {
+                        T.records[count - 1] |= kTapSegmentEnd;
                         ++T.segments;
                     }
                 }
-                if (s >= 0 && chunk == 0) {
-                    T.slot_channel[(size_t)g * G + slot] = f.reorder[s];
-                    T.group_kernels[g] += f.offset[s + 1] - f.offset[s];
-                }
-                if (T.records.size() == before) append(kTapSegmentEnd | kTapNothing << kTapPatternShift, nullptr);
-                T.records.back() |= kTapFilterEnd;
+                if (s >= 0 && chunk == 0) T.slot_channel[(size_t)g * G + slot] = f.reorder[s];
+                if (count == before) append(kTapSegmentEnd | kTapNothing << kTapPatternShift, nullptr);
+                T.records[count - 1] |= kTapFilterEnd;
             }
             pad_batch();
         }
     // the kernel fetches one batch beyond the last one it runs, and the records of the one after
-    for (int i = 0; i < 2 * kTapBatch; ++i) append(0u, nullptr);
+    count += 2 * kTapBatch;
+    T.records.resize(count);
+    T.weights.resize(4 * count);
 }
 
 }  // namespace patdnn

@@ -140,7 +140,6 @@ struct Taps {
     std::vector<uint32_t> chunk_ptr;         // [num_groups][num_chunks] first batch
     std::vector<uint32_t> records;           // [batches + 2][16]
     std::vector<float> weights;              // [batches + 2][16][4]
-    std::vector<int64_t> group_kernels;      // [num_groups] kept kernels per group
     int64_t segments = 0;                    // runs of one pattern in one filter and chunk
     size_t bytes() const
     {

@@ -56,7 +56,8 @@ struct TiledOnDevice {
 };
 
 struct TapsOnDevice {
-    Taps host;
+    Taps host;                            // its arrays are on the device only
+    size_t bytes = 0;                     // of the arrays
     DevTaps dev;
     std::vector<void*> allocations;
     ~TapsOnDevice()
@@ -298,6 +299,11 @@ patdnn_status_t ensure_taps(patdnn_layer* h, int ck, const DevTaps** out)
             const hipError_t e = up.commit(t->allocations);
             if (e != hipSuccess) return hip_fail(e, "uploading the tap-product layout");
         }
+        t->bytes = t->host.bytes();
+        // the planner needs the numbers only
+        t->host.slot_channel = std::vector<int32_t>();
+        t->host.chunk_ptr = t->host.records = std::vector<uint32_t>();
+        t->host.weights = std::vector<float>();
         it = h->taps.emplace(ck, std::move(t)).first;
     }
     if (out) *out = &it->second->dev;
@@ -977,7 +983,7 @@ patdnn_status_t patdnn_layout_stats(patdnn_handle_t h, patdnn_stats_t* out)
         out->distinct_filter_lengths = (int32_t)(std::unique(len.begin(), len.end()) - len.begin());
     }
     for (const auto& kv : h->tiled) out->tiled_bytes += (int64_t)kv.second->host.bytes();
-    for (const auto& kv : h->taps) out->tiled_bytes += (int64_t)kv.second->host.bytes();
+    for (const auto& kv : h->taps) out->tiled_bytes += (int64_t)kv.second->bytes;
     if (!h->tiled.empty()) {
         const Tiled& t = h->tiled.begin()->second->host;
         out->filter_groups = t.num_groups;
