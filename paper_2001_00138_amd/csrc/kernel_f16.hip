@@ -511,6 +511,45 @@ static const F16Shape kF16Shapes[] = {
 };
 #undef PATDNN_F16
 
+// The shape that a launch takes, as an index of kF16Shapes (-1: beyond the kernel's 32-bit numbers).
+struct F16Plan {
+    int shape = -1;
+    long long blocks = 0;
+    size_t lds = 0;
+};
+static F16Plan f16_plan(const ConvShape& s, bool pair, F16Args& a)
+{
+    F16Plan plan;
+    a.steps = (s.c_in + 15) / 16;
+    a.fblocks = (s.c_out + 31) / 32;
+    for (const F16Shape& v : kF16Shapes) {
+        const int filters = v.fm * v.wf;
+        if (filters >= 2 * a.fblocks) continue;                   // half of every workgroup idle
+        if (v.strided && s.stride == 1) continue;
+        if (v.wk == 8 && a.steps <= 4) continue;                  // four wavefronts hold all channels
+        if (!f16_tiles(s, 32 * v.pn * v.wp, pair, a)) continue;
+        a.fsets = (a.fblocks + filters - 1) / filters;
+        plan.blocks = (long long)a.strips * a.tiles * a.fsets;
+        plan.lds = std::max((size_t)a.npp * (f16_buffers(v.wk) * 2 * v.wk * 16 + 4),
+                            v.wk > 1 ? (size_t)v.wf * v.wp * v.wk * 4096 : 0);
+        if (plan.blocks < v.min_blocks || plan.blocks > INT32_MAX || plan.lds > 160 * 1024) continue;
+        plan.shape = (int)(&v - kF16Shapes);
+        break;
+    }
+    return plan;
+}
+
+// two pixels per load: rows of an even length and a 4-byte aligned tensor
+static bool f16_pair(const ConvShape& s, const void* in) { return s.w % 2 == 0 && (reinterpret_cast<uintptr_t>(in) & 3) == 0; }
+
+int f16_choice(const ConvShape& s, const void* in)
+{
+    F16Args a{};
+    const bool pair = f16_pair(s, in);
+    const int shape = f16_plan(s, pair, a).shape;
+    return shape < 0 ? -1 : 2 * shape + pair;
+}
+
 hipError_t launch_f16(const DevFkw& f, const ConvShape& s, const void* in, const float* bias, void* out, hipStream_t stream)
 {
     F16Args a{};
@@ -519,25 +558,12 @@ hipError_t launch_f16(const DevFkw& f, const ConvShape& s, const void* in, const
     a.reorder = f.reorder;
     a.n = s.n; a.c_in = s.c_in; a.c_out = s.c_out; a.h = s.h; a.w = s.w; a.ho = s.ho; a.wo = s.wo;
     a.conv_stride = s.stride; a.pad = s.pad; a.relu = s.relu;
-    a.steps = (s.c_in + 15) / 16;
-    a.fblocks = (s.c_out + 31) / 32;
-    // two pixels per load and store: rows of an even length and a 4-byte aligned tensor
-    const bool pair = s.w % 2 == 0 && (reinterpret_cast<uintptr_t>(in) & 3) == 0;
+    // two pixels per store likewise
     a.pair_out = s.wo % 2 == 0 && (reinterpret_cast<uintptr_t>(out) & 3) == 0;
-    for (const F16Shape& v : kF16Shapes) {
-        const int filters = v.fm * v.wf;
-        if (filters >= 2 * a.fblocks) continue;                   // half of every workgroup idle
-        if (v.strided && s.stride == 1) continue;
-        if (v.wk == 8 && a.steps <= 4) continue;                  // four wavefronts hold all channels
-        if (!f16_tiles(s, 32 * v.pn * v.wp, pair, a)) continue;
-        a.fsets = (a.fblocks + filters - 1) / filters;
-        const long long blocks = (long long)a.strips * a.tiles * a.fsets;
-        const size_t lds = std::max((size_t)a.npp * (f16_buffers(v.wk) * 2 * v.wk * 16 + 4),
-                                    v.wk > 1 ? (size_t)v.wf * v.wp * v.wk * 4096 : 0);
-        if (blocks < v.min_blocks || blocks > INT32_MAX || lds > 160 * 1024) continue;
-        return v.launch[pair](a, s, blocks, lds, stream);
-    }
-    return launch_fkw_f16(f, s, in, bias, out, stream);           // beyond the kernel's 32-bit numbers
+    const bool pair = f16_pair(s, in);
+    const F16Plan plan = f16_plan(s, pair, a);
+    if (plan.shape < 0) return launch_fkw_f16(f, s, in, bias, out, stream);
+    return kF16Shapes[plan.shape].launch[pair](a, s, plan.blocks, plan.lds, stream);
 }
 
 }  // namespace patdnn

@@ -132,6 +132,9 @@ hipError_t launch_fkw_f16(const DevFkw& f, const ConvShape& s, const void* in, c
 // Pruned and dense layers on the matrix cores (needs DevFkw::expanded_f16).
 hipError_t launch_f16(const DevFkw& f, const ConvShape& s, const void* in, const float* bias,
                       void* out, hipStream_t stream);
+// What it launches: twice the index of the launch shape, plus one where rows are staged in pairs of
+// pixels; -1: the walk.
+int f16_choice(const ConvShape& s, const void* in);
 size_t f16_expanded_halves(int32_t c_in, int32_t c_out);
 // Fills `out` (f16_expanded_halves, zeroed) from the FKW arrays.
 hipError_t launch_f16_expand(const DevFkw& f, int32_t c_in, int32_t c_out, void* out, hipStream_t stream);

@@ -812,6 +812,13 @@ patdnn_status_t patdnn_internal_choice(patdnn_handle_t h, int32_t n, int32_t h_i
     return st;
 }
 
+// Likewise: what patdnn_conv2d_f16 launches for a tensor at `input` (see f16_choice; not for depthwise layers).
+int32_t patdnn_internal_f16_choice(patdnn_handle_t h, const void* input, int32_t n, int32_t h_in, int32_t w_in)
+{
+    ConvShape s{};
+    return shape_of(h, n, h_in, w_in, s) == PATDNN_OK ? f16_choice(s, input) : -2;
+}
+
 patdnn_status_t patdnn_conv2d(patdnn_handle_t h, const float* input, int32_t n, int32_t h_in,
                               int32_t w_in, const float* bias, float* output, int32_t fuse_relu,
                               void* stream)

@@ -1,7 +1,10 @@
 """GPU parity of the binary16 matrix-core kernel (csrc/kernel_f16.hip) where it can go wrong: odd and
 even rows (one and two pixels per load and store), strips, tiles that span images, channel and
-filter counts around its blocks, both strides, every launch shape - and inputs that are infinite or
-NaN, which must reach only the outputs whose kept weights meet them."""
+filter counts around its blocks, both strides, every launch shape (asserted) - and inputs that are
+infinite or NaN, which must reach only the outputs whose kept weights meet them, in every launch
+shape; subnormal values; and layers that keep the walk over the kept weights."""
+
+import ctypes
 
 import numpy as np
 import pytest
@@ -29,28 +32,46 @@ def _layer(rng, c_out, c_in, keep, stride, pad, dense=False):
     return (wt, ids, mask, lib), B.Layer(wt, ids, mask, lib, stride=stride, pad=pad, dense=dense)
 
 
-# c_out, c_in, n, h, w, stride, pad, keep, elements the input starts after an aligned address
+# What a case launches (see f16_choice in csrc/kernels.hpp): twice the launch shape - 0 blocks of 64 filters
+# x 128 pixels a wavefront, 1 64 x 64 (stride 2), 2 32 x 64, 3 four wavefronts on 32 x 64, 4 eight and 5 four
+# on 32 x 32 - plus one where rows are staged in pairs.
+def _launches(layer, pointer, n, h, w):
+    choice = B.lib().patdnn_internal_f16_choice
+    choice.argtypes = [ctypes.c_void_p] * 2 + [ctypes.c_int32] * 3
+    choice.restype = ctypes.c_int32
+    return choice(layer.handle, pointer, n, h, w)
+
+
+# c_out, c_in, n, h, w, stride, pad, keep, elements the input starts after an aligned address, what is launched
 CASES = [
-    (130, 17, 2, 130, 128, 1, 1, 0.3, 0),      # 64 filters x 128 pixels a wavefront; last filter block nearly empty
-    (128, 33, 1, 182, 181, 1, 1, 0.3, 0),      # ... odd rows
-    (70, 20, 3, 107, 106, 2, 1, 0.3, 0),       # stride 2, 53 output columns: pairs in, single values out
-    (96, 31, 6, 66, 67, 2, 0, 0.4, 0),
-    (40, 16, 5, 120, 99, 1, 0, 0.3, 0),        # 32 x 64
-    (33, 5, 3, 161, 160, 1, 1, 0.5, 1),        # even rows at an odd address
-    (64, 64, 70, 14, 15, 1, 1, 0.3, 0),        # channels split over wavefronts, tiles over images
-    (200, 70, 9, 20, 30, 1, 1, 0.3, 0),
-    (33, 130, 2, 11, 7, 1, 1, 0.3, 0),         # eight wavefronts a block
-    (16, 64, 1, 32, 34, 1, 1, 0.5, 0),         # four
-    (31, 48, 40, 1, 1, 1, 1, 1.0, 0),          # one pixel an image
-    (48, 80, 33, 4, 4, 2, 0, 0.6, 0),          # a strip of one column, rounded up to a pair
-    (8, 100, 2, 40, 130, 2, 1, 0.4, 0),        # stride 2, strips of 33 columns cut down to 32
+    (130, 17, 2, 130, 128, 1, 1, 0.3, 0, 1),   # last filter block nearly empty
+    (130, 17, 2, 130, 129, 1, 1, 0.3, 0, 0),   # ... odd rows
+    (70, 20, 10, 107, 106, 2, 1, 0.3, 0, 3),   # stride 2, 53 output columns: pairs in, single values out
+    (70, 20, 10, 107, 105, 2, 1, 0.3, 0, 2),
+    (128, 33, 1, 182, 181, 1, 1, 0.3, 0, 4),
+    (64, 64, 8, 112, 112, 1, 1, 0.3, 0, 5),
+    (70, 20, 3, 107, 106, 2, 1, 0.3, 0, 7),
+    (96, 31, 6, 66, 67, 2, 0, 0.4, 0, 10),
+    (40, 16, 5, 120, 99, 1, 0, 0.3, 0, 4),
+    (33, 5, 3, 161, 160, 1, 1, 0.5, 1, 4),     # even rows at an odd address
+    (64, 64, 70, 14, 15, 1, 1, 0.3, 0, 6),     # channels split over wavefronts, tiles over images
+    (200, 70, 9, 20, 30, 1, 1, 0.3, 0, 7),
+    (33, 130, 2, 11, 7, 1, 1, 0.3, 0, 8),
+    (16, 64, 1, 32, 34, 1, 1, 0.5, 0, 11),
+    (31, 48, 40, 1, 1, 1, 1, 1.0, 0, 10),      # one pixel an image
+    (48, 80, 33, 4, 4, 2, 0, 0.6, 0, 9),       # a strip of one column, rounded up to a pair
+    (8, 100, 2, 40, 130, 2, 1, 0.4, 0, 9),     # stride 2, three strips of 22 columns, the last one not full
 ]
+
+
+def test_cases_launch_every_shape():
+    assert {c[-1] for c in CASES} == set(range(12)) == {c[-1] for c in NON_FINITE}
 
 
 @pytest.mark.parametrize("case", CASES)
 def test_matrix_kernel(torch, case):
     from oracle import fp16
-    c_out, c_in, n, h, w, stride, pad, keep, shift = case
+    c_out, c_in, n, h, w, stride, pad, keep, shift, launches = case
     rng = np.random.default_rng(c_out * 1000 + h * 40 + w)
     (wt, ids, mask, lib), L = _layer(rng, c_out, c_in, keep, stride, pad)
     bias = rng.standard_normal(c_out).astype(np.float32)
@@ -63,6 +84,7 @@ def test_matrix_kernel(torch, case):
     buf = torch.full((numel + 2 * guard,), 7.0, dtype=torch.float16, device="cuda")
     out = buf[guard:guard + numel].view(want16.shape)
     print(f"  {case}", flush=True)
+    assert _launches(L, xt.data_ptr(), n, h, w) == launches
     L.conv2d_f16(xt, torch.from_numpy(bias).cuda(), out, relu=True)
     torch.cuda.synchronize()
     assert bool((buf[:guard] == 7.0).all()) and bool((buf[guard + numel:] == 7.0).all())
@@ -73,14 +95,17 @@ def test_matrix_kernel(torch, case):
     L.close()
 
 
-# (c_out, c_in, n, h, w, stride): blocks over all channels and blocks whose channels are split, paired and single rows
-@pytest.mark.parametrize("shape", [(40, 24, 2, 97, 96, 1), (40, 24, 2, 97, 95, 1), (33, 130, 2, 11, 8, 2), (64, 64, 70, 7, 7, 1),
-                                   (130, 17, 17, 130, 128, 1), (130, 17, 17, 130, 129, 1),
-                                   (70, 20, 10, 107, 106, 2), (70, 20, 10, 107, 105, 2)])
+# c_out, c_in, n, h, w, stride, what is launched
+NON_FINITE = [(130, 17, 2, 130, 128, 1, 1), (130, 17, 2, 130, 129, 1, 0), (70, 20, 10, 107, 106, 2, 3), (70, 20, 10, 107, 105, 2, 2),
+              (40, 24, 5, 97, 96, 1, 5), (40, 24, 5, 97, 95, 1, 4), (40, 24, 2, 97, 96, 1, 7), (40, 24, 2, 97, 95, 1, 6),
+              (33, 130, 2, 11, 8, 2, 9), (33, 130, 2, 11, 9, 2, 8), (64, 64, 70, 7, 8, 1, 11), (64, 64, 70, 7, 7, 1, 10)]
+
+
+@pytest.mark.parametrize("shape", NON_FINITE)
 def test_infinite_and_nan_inputs(torch, shape):
     from oracle import fp16
-    c_out, c_in, n, h, w, stride = shape
-    rng = np.random.default_rng(sum(shape))
+    c_out, c_in, n, h, w, stride, launches = shape
+    rng = np.random.default_rng(sum(shape[:-1]))
     (wt, ids, mask, lib), L = _layer(rng, c_out, c_in, 0.3, stride, 1)
     # kept weights of zero, which an infinite input turns into NaN, and of either sign
     L.close()
@@ -99,7 +124,9 @@ def test_infinite_and_nan_inputs(torch, shape):
     want16 = fp16.to_f16(W.conv2d(torch.from_numpy(x16.astype(np.float32)).cuda(), bt).cpu().numpy())
     W.close()
     print(f"  {shape}", flush=True)
-    got = L.conv2d_f16(torch.from_numpy(x16).cuda(), bt).cpu().numpy()
+    xt = torch.from_numpy(x16).cuda()
+    assert _launches(L, xt.data_ptr(), n, h, w) == launches
+    got = L.conv2d_f16(xt, bt).cpu().numpy()
     assert np.isnan(want16).any() and np.isposinf(want16).any() and np.isneginf(want16).any()
     np.testing.assert_array_equal(np.isnan(got), np.isnan(want16))
     np.testing.assert_array_equal(got[np.isinf(want16)], want16[np.isinf(want16)])
@@ -163,3 +190,24 @@ def test_weights_beyond_binary16(torch, case):
     bound = 2.0 ** -11 * np.maximum(np.abs(exact), 2.0 ** -14) + 1e-5 * float(np.abs(exact).max())
     assert float((np.abs(got.astype(np.float64) - exact) / bound)[:, others].max()) <= 1.0
     assert not np.isfinite(got[:, 7]).any()
+
+
+@pytest.mark.parametrize("inputs,weights", [(3e-7, 0.3), (1.0, 3e-7), (3e-7, 30.0)])
+def test_subnormal_values(torch, inputs, weights):
+    """Binary16 inputs, weights and results below 2^-14: none of them is flushed to zero."""
+    from oracle import fp16
+    rng = np.random.default_rng(8)
+    c_out, c_in, n, h, w = 40, 70, 2, 20, 21
+    ids = rng.integers(0, 8, (c_out, c_in), dtype=np.uint8)
+    mask = (rng.random((c_out, c_in)) < 0.5).astype(np.uint8)
+    wt = (rng.standard_normal((c_out, c_in, 3, 3)) * weights).astype(np.float32)
+    lib = wl.pattern_library(wl.PATTERN_SEED)
+    x16 = fp16.to_f16(rng.standard_normal((n, c_in, h, w)) * inputs)
+    _, exact = fp16.conv2d_f16(wt, ids, mask, lib, x16, None, stride=1, pad=1, skip_removed=True)
+    L = B.Layer(wt, ids, mask, lib)
+    got = L.conv2d_f16(torch.from_numpy(x16).cuda(), None).cpu().numpy().astype(np.float64)
+    L.close()
+    # half a binary16 spacing, and the fp32 sum's 1e-5 of the largest output
+    bound = 2.0 ** -11 * np.maximum(np.abs(exact), 2.0 ** -14) + 1e-5 * float(np.abs(exact).max())
+    assert float(np.abs(exact).max()) > 32 * 2.0 ** -24
+    assert float((np.abs(got - exact) / bound).max()) <= 1.0

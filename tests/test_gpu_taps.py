@@ -3,6 +3,8 @@
 around its groups, channel counts around its chunks, empty filters, every pattern, split launches
 with and without a workspace, fused pooling - against the oracle, element by element."""
 
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -62,7 +64,9 @@ def test_tap_product_kernel(torch, oracle, case):
         ref = ostack.maxpool2x2(full) if pool else full
         if 0 in ref.shape:
             continue
-        for room in {need, 0}:
+        # no room: the slices add up in the output, or the library chooses; one buffer: a pooled layer's
+        # slices add up there
+        for room in {need, 0, full.size if pool and ksplit > 1 else 0}:
             print(f"  {case} pool={pool} workspace={room}", flush=True)
             numel = int(np.prod(ref.shape))
             buf = torch.full((numel + 2 * guard,), 777.0, device="cuda")
@@ -78,10 +82,16 @@ def test_tap_product_kernel(torch, oracle, case):
     L.close()
 
 
-@pytest.mark.parametrize("shape", [(1, 16, 16, 32), (1, 64, 512, 14), (64, 96, 200, 7), (3, 200, 72, 45), (40, 40, 24, 60)])
-def test_chosen_configuration(torch, oracle, shape):
-    """The library's own choice over the sizes at which it changes (walk, split and unsplit
-    launches, one and two groups per wavefront), with the workspace it asks for."""
+# n, c_in, c_out, side; the family chosen with a workspace, whether it splits the channels, and without one
+CHOICES = [((1, 16, 16, 32), "fkw", False, "fkw"), ((1, 64, 512, 14), "fkw", False, "fkw"), ((64, 96, 200, 7), "taps_f8", True, "taps_f8"),
+           ((3, 200, 72, 45), "taps_f8", True, "taps_f8"), ((40, 40, 24, 60), "taps_f8", False, "taps_f8"),
+           ((6, 20, 48, 150), "t_g8_p7x2_s1_x8_thw1b", False, "t_g8_p7x2_s1_x8_thw1b"), ((32, 64, 512, 28), "taps_f16", False, "taps_f16")]
+
+
+@pytest.mark.parametrize("shape,with_room,split,without", CHOICES)
+def test_chosen_configuration(torch, oracle, shape, with_room, split, without):
+    """The library's own choice over the sizes at which it changes (walk, tiled kernel, split and unsplit
+    launches, one and two groups per wavefront), with the workspace it asks for and without."""
     n, c_in, c_out, side = shape
     rng = np.random.default_rng(sum(shape))
     lib = wl.pattern_library(wl.PATTERN_SEED)
@@ -93,8 +103,15 @@ def test_chosen_configuration(torch, oracle, shape):
     ref = oracle.conv2d(wt, ids, mask, lib, x[-k:], None, skip_removed=True)
     L = B.Layer(wt, ids, mask, lib)
     need = L.workspace_floats(n, side, side)
+    assert (need > 0) == split
+    choice = B.lib().patdnn_internal_choice
+    choice.argtypes = [ctypes.c_void_p] + [ctypes.c_int32] * 3 + [ctypes.c_size_t, ctypes.c_void_p]
     xt = torch.from_numpy(x).cuda()
     for room in {need, 0}:
+        cfg = B.Config()
+        assert choice(L.handle, n, side, side, room, ctypes.byref(cfg)) == 0
+        assert B.patdnn_variant_name(cfg.variant) == (with_room if room else without)
+        assert (cfg.ksplit > 1) == (room > 0)
         ws = torch.full((room,), float("nan"), device="cuda") if room else None
         got = L.conv2d_ws(xt, None, workspace=ws)[-k:].cpu().numpy()
         assert float(np.abs(got.astype(np.float64) - ref).max() / np.abs(ref).max()) <= TOL, room
@@ -129,3 +146,56 @@ def test_infinite_input_reaches_kept_kernels_only(torch, filters, ksplit):
     assert np.isfinite(got["taps"][0, ::2]).all() and (got["taps"][0, 3] == bias[3]).all()
     ok = np.isfinite(got["fkw"])
     assert np.abs(got["taps"][ok] - got["fkw"][ok]).max() <= TOL * np.abs(got["fkw"][ok]).max()
+
+
+@pytest.mark.parametrize("shape", [(70, 3, 3, 1), (9, 5, 8, 0), (5, 7, 7, 1)])
+@pytest.mark.parametrize("filters,ksplit", [(8, 1), (16, 2)])
+def test_infinite_input_stays_in_its_image(torch, shape, filters, ksplit):
+    """Images that share a tile lie next to each other in registers and lanes: an infinite or NaN pixel
+    reaches the outputs that the walk over the kept weights gives it, and no other image."""
+    n, h, w, pad = shape
+    rng = np.random.default_rng(n)
+    c_out, c_in = 16, 16
+    lib = wl.pattern_library(wl.PATTERN_SEED, 8)
+    ids = rng.integers(0, 8, (c_out, c_in), dtype=np.uint8)
+    mask = (rng.random((c_out, c_in)) < 0.4).astype(np.uint8)
+    wt = rng.standard_normal((c_out, c_in, 3, 3)).astype(np.float32)
+    x = rng.standard_normal((n, c_in, h, w)).astype(np.float32)
+    for img, v in ((1, np.inf), (n - 2, np.nan)):            # corners, whose taps reach past the image
+        for y, z in ((0, 0), (0, w - 1), (h - 1, 0), (h - 1, w - 1)):
+            x[img, rng.integers(c_in), y, z] = v
+    names = {B.patdnn_variant_name(v): v for v in range(B.patdnn_num_variants())}
+    got = {}
+    for name, cfg in (("fkw", (0, 0, 0, 1)), ("taps", (names[f"taps_f{filters}"], 8, 1, ksplit))):
+        L = B.Layer(wt, ids, mask, lib, pad=pad)
+        L.set_config(*cfg)
+        got[name] = L.conv2d(torch.from_numpy(x).cuda(), None).cpu().numpy()
+        L.close()
+    assert not np.isfinite(got["fkw"]).all()
+    assert np.array_equal(np.isnan(got["taps"]), np.isnan(got["fkw"]))
+    assert np.array_equal(got["taps"][np.isinf(got["fkw"])], got["fkw"][np.isinf(got["fkw"])])
+    ok = np.isfinite(got["fkw"])
+    assert ok[[i for i in range(n) if i not in (1, n - 2)]].all()
+    assert np.abs(got["taps"][ok] - got["fkw"][ok]).max() <= TOL * np.abs(got["fkw"][ok]).max()
+
+
+@pytest.mark.parametrize("inputs,weights", [(1e-40, 0.3), (1e-20, 1e-20), (1.0, 1e-40)])
+def test_subnormal_values(torch, oracle, inputs, weights):
+    """The matrix unit keeps subnormal inputs, weights and sums."""
+    rng = np.random.default_rng(4)
+    c_out, c_in, h = 24, 40, 17
+    lib = wl.pattern_library(wl.PATTERN_SEED)
+    ids = rng.integers(0, 8, (c_out, c_in), dtype=np.uint8)
+    mask = (rng.random((c_out, c_in)) < 0.5).astype(np.uint8)
+    wt = (rng.standard_normal((c_out, c_in, 3, 3)) * weights).astype(np.float32)
+    x = (rng.standard_normal((1, c_in, h, h)) * inputs).astype(np.float32)
+    ref = oracle.conv2d(wt, ids, mask, lib, x, None, skip_removed=True)
+    names = {B.patdnn_variant_name(v): v for v in range(B.patdnn_num_variants())}
+    for variant in ("taps_f8", "taps_f16"):
+        L = B.Layer(wt, ids, mask, lib)
+        L.set_config(names[variant])
+        got = L.conv2d(torch.from_numpy(x).cuda(), None).cpu().numpy().astype(np.float64)
+        L.close()
+        # half a subnormal spacing per term
+        assert 0 < np.abs(ref).max() < 2.0 ** -125
+        assert np.abs(got - ref).max() <= 4 * c_in / 2 * 2.0 ** -149 + TOL * np.abs(ref).max()

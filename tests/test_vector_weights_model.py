@@ -25,8 +25,8 @@ class VectorWave(gcn_model.Wave):
         return super().rd32(a)
 
 
-@pytest.mark.parametrize("c_out,c_in,n,h,w,ck", [(8, 6, 1, 7, 16, 6), (11, 9, 1, 9, 18, 4)])
-def test_weights_in_vector_registers(oracle, monkeypatch, c_out, c_in, n, h, w, ck):
+@pytest.mark.parametrize("c_out,c_in,n,h,w,ck,patterns", [(8, 6, 1, 7, 16, 6, 8), (11, 9, 1, 9, 18, 4, 8), (8, 16, 1, 7, 16, 8, 56)])
+def test_weights_in_vector_registers(oracle, monkeypatch, c_out, c_in, n, h, w, ck, patterns):
     import gen_dispatch
     plain = gen_dispatch.program
 
@@ -41,9 +41,9 @@ def test_weights_in_vector_registers(oracle, monkeypatch, c_out, c_in, n, h, w, 
     monkeypatch.setattr(gcn_model, "Wave", VectorWave)
     monkeypatch.setattr(tim, "_programs", {})
     rng = np.random.default_rng(c_out + c_in)
-    lib = wl.pattern_library(wl.PATTERN_SEED)
+    lib = wl.pattern_library(wl.PATTERN_SEED) if patterns < 56 else wl.pattern_universe()
     d = {"weights": rng.standard_normal((c_out, c_in, 3, 3)).astype(np.float32), "pattern_masks": lib,
-         "pattern_ids": rng.integers(0, 8, (c_out, c_in), dtype=np.uint8),
+         "pattern_ids": rng.integers(0, patterns, (c_out, c_in), dtype=np.uint8),
          "kernel_mask": (rng.random((c_out, c_in)) < 0.5).astype(np.uint8),
          "bias": rng.standard_normal(c_out).astype(np.float32)}
     x = rng.standard_normal((n, c_in, h, w)).astype(np.float32)
