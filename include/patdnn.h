@@ -224,7 +224,7 @@ typedef struct {
     int32_t num_patterns;      /* patterns of the layer (1 for dense) */
     int64_t fkw_weight_bytes;  /* weight array */
     int64_t fkw_index_bytes;   /* offset + reorder + index + stride arrays */
-    int64_t tiled_bytes;       /* device bytes of the per-filter-group layouts the tiled kernels read */
+    int64_t tiled_bytes;       /* device bytes of the per-filter-group layouts the tiled and tap-product kernels read */
     int32_t min_filter_length, max_filter_length;
     int32_t distinct_filter_lengths;
     int32_t filter_groups;     /* groups of the default tiled layout (0 if none) */
@@ -256,7 +256,8 @@ patdnn_status_t patdnn_layout_stats(patdnn_handle_t h, patdnn_stats_t* out);
  *                           to 160 channels, `waves` up to 16
  * variant < 0 (the state of a new handle): the library chooses at every call, by an estimate of
  * the candidates' times at this input size; a choice that splits the input channels is made
- * only where the call has a workspace of patdnn_workspace_floats() for it.
+ * only where the call's workspace holds one partial sum per slice (patdnn_workspace_floats() for
+ * the choice without that limit; with less room fewer slices, added in another order).
  * A configuration set with patdnn_set_config is taken as given or refused
  * (PATDNN_EUNSUPPORTED), never replaced by another one at launch time.
  * `ck` = input channels staged per LDS pass, `waves` = wavefronts (filter groups)

@@ -30,16 +30,18 @@
 //     (their sums meet in LDS): layers with few tiles.
 //   * A chunk of the tile's input rows is staged in LDS as [8 channels][row][column] of
 //     16 bytes, which is the order in which a lane wants its eight channels of a pixel; a
-//     wavefront gathers 64 pixels x 8 channels at a time with 2-byte loads (any row length,
-//     any alignment), zero where the image ends.  Two buffers, the next chunk's loads in
-//     flight while this one is computed.
+//     wavefront gathers 64 units x 8 channels at a time, zero where the image ends: a unit is a pair
+//     of pixels (4-byte loads) where rows have an even length and start on whole pairs, else one pixel
+//     (2-byte loads).  Two buffers, the next chunk's loads in flight while this one is computed; one
+//     buffer where wavefronts split the channels, whose chunks are larger.
 //   * Weights are read from L2 in fragment order, 16 bytes per lane.
 //
 // What bounds it: 128 -> 128 at 56 x 56, 64 images (59 GFLOP with the zeros, 51 MB in and out) takes
-// 94 us, 0.63 PFLOP/s, where the walk over the kept weights took 1990; one image of 256 -> 256 at
-// 28 x 28 9 us (57).  The gathering of eight channels is the larger part: 2-byte loads
-// took 124 us where 4-byte loads take 94, and it is the texture path that they share with the
-// weights; the rows staged are 1.4 times the pixels computed.
+// 97 us on resident tensors and 101 on changing ones, 0.6 PFLOP/s, where the walk over the kept weights
+// took 1990; one image of 256 -> 256 at 28 x 28 9 us (57).  The matrix cores are busy 31 % of the SIMDs'
+// cycles.  The gathering of eight channels is the larger part: 2-byte loads took 124 us where 4-byte
+// loads took 94, and it is the texture path that they share with the weights; the rows staged are
+// 1.4 times the pixels computed.
 #include <hip/hip_fp16.h>
 
 #include <algorithm>

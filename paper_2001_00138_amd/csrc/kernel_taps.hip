@@ -18,15 +18,16 @@
 //     lane's four rows side by side, one ds_read_b128 per kernel and lane.
 //   * Output sums stay in registers over the chunks; each lane writes its own four rows.
 //
-// What bounds it: with four wavefronts per SIMD a kernel costs 42 clocks on 256 pixels, 36 of them
-// the four matrix instructions, 16 of every 49 input pixels of an inner tile are halo (14 x 14 of
-// 16 x 16), and a flush (16 adds, about 48 clocks with its jump) follows every 4.4 kernels at 128
-// channels a chunk and a keep ratio of 1/3.6.  A workgroup's own reads and writes are hidden only by
-// another workgroup on its CU, so layers of few channels and large planes (64 -> 64 at 224 x 224: 0.80 ms
-// for 64 images) are left to the tiled kernel (0.64).  Measured, before (tiled kernel, its
-// best configuration) -> now: 512 -> 512 at 28 x 28, 64 images 0.69 -> 0.51 ms (58 TFLOP/s of kept
-// weights), at 14 x 14 0.20 -> 0.14, at 7 x 7 0.098 -> 0.052; one image of 64 -> 64 at 224 x 224
-// 35 -> 24 us, of 512 -> 512 at 14 x 14 28 -> 21 us (split).
+// What bounds it (256 -> 256 at 56 x 56, 64 images, 550 us): the matrix cores are busy 46 % of the SIMDs'
+// cycles, four instructions of 8 cycles for a kernel on 256 pixels (42 clocks with four wavefronts per
+// SIMD); the adds of a flush (16, about 48 clocks with its jump, after every 4.4 kernels at 128 channels a
+// chunk and a keep ratio of 1/3.6) and of the filters' ends take 18 to 36 %; a third of a wavefront's
+// life is waiting.  15 of every 64 input pixels of an inner tile are halo (14 x 14 of 16 x 16).  A
+// workgroup's own reads and writes are hidden only by another workgroup on its CU, so layers of few
+// channels and large planes (64 -> 64 at 224 x 224: 0.80 ms for 64 images) are left to the tiled kernel
+// (0.60).  Measured, the tiled kernel's best configuration -> this one: 512 -> 512 at 28 x 28, 64 images
+// 0.67 -> 0.54 ms (54 TFLOP/s of kept weights), at 14 x 14 0.19 -> 0.15, at 7 x 7 0.098 -> 0.053; one
+// image of 64 -> 64 at 224 x 224 35 -> 24 us, of 512 -> 512 at 14 x 14 28 -> 21 us (split).
 #include <algorithm>
 #include <atomic>
 
