@@ -130,8 +130,9 @@ patdnn_status_t patdnn_conv2d(patdnn_handle_t h, const float* input, int32_t n, 
  * rounded to binary16 once when it is stored.  Depthwise layers run the depthwise kernel
  * (bound by HBM bandwidth: half the bytes, about half the time); all other layers run on the
  * matrix cores, over weights that patdnn_encode has expanded to all nine taps with zeros
- * (layers whose expanded weights exceed 256 MB, or with a weight that is not finite in binary16:
- * the filter-major FKW kernel).  A weight that
+ * (layers whose expanded weights exceed 256 MB, or with a weight that is not finite in binary16, and
+ * calls where it is the faster one, with few filters or next to nothing kept: the filter-major FKW
+ * kernel).  A weight that
  * pruning removed meets no input all the same: an infinite or NaN input reaches the outputs of
  * kept weights only.  Otherwise as patdnn_conv2d.
  */

@@ -509,6 +509,24 @@ double fkw_estimate(const patdnn_layer* h, const ConvShape& s)
     return 4.9 + 0.223 * kernels + 0.192 * patterns + waves * (9.8e-5 * kernels + 2.8e-5 * patterns);
 }
 
+// Binary16 layers, microseconds: the walk as above, and the matrix kernel, which multiplies the removed
+// weights too and fills its channels to 16 and its filters to 32: a chain of channel steps, multiply-adds,
+// inputs staged once per 128 filters, outputs.  Fitted to 400 layers of 1 to 512 channels, keep ratios
+// from 0.003 and dense ones: 14 % and 8 % on average, on 400 others 15 % and 9 %.  The walk is taken
+// where it is ahead by more than 15 % (few filters, or next to nothing kept): 17 -> 3 at 175 x 175 / 2, 15 images,
+// one kernel in a hundred 9 us against 28; of the 800 layers 9 are then more than 15 % behind the walk, 56
+// without it.  Layers of 16 channels and filters and more at keep ratios from 1/3.6 are none of these.
+bool f16_walk_pays(const patdnn_layer* h, const ConvShape& s)
+{
+    const double kernels = (double)h->L.kept / s.c_out * h->L.fkw.taps / 4, patterns = h->L.fkw.num_patterns;
+    const double pixels = (double)s.n * s.ho * s.wo, waves = (double)s.n * s.c_out * (((long long)s.ho * s.wo + 63) / 64);
+    const double walk = std::max(9.4, 5.2 + 0.368 * kernels + 0.079 * patterns + waves * (1.47e-4 * kernels + 2.4e-5 * patterns));
+    const double c16 = (s.c_in + 15) / 16 * 16.0, f32 = (s.c_out + 31) / 32 * 32.0;
+    const double matrix = std::max(9.4, 7.1 + 0.156 * c16 / 16 + 1.16e-8 * pixels * c16 * f32 +
+                                            1.44e-6 * s.n * s.h * s.w * c16 * std::ceil(f32 / 128) + 0.84e-6 * pixels * s.c_out);
+    return walk * 1.15 < matrix;
+}
+
 // Binary16 weights with the removed ones as zeros: up to 256 MB a layer.
 constexpr size_t kMaxExpandedHalves = (size_t)128 << 20;
 
@@ -816,7 +834,8 @@ patdnn_status_t patdnn_internal_choice(patdnn_handle_t h, int32_t n, int32_t h_i
 int32_t patdnn_internal_f16_choice(patdnn_handle_t h, const void* input, int32_t n, int32_t h_in, int32_t w_in)
 {
     ConvShape s{};
-    return shape_of(h, n, h_in, w_in, s) == PATDNN_OK ? f16_choice(s, input) : -2;
+    if (shape_of(h, n, h_in, w_in, s) != PATDNN_OK) return -2;
+    return f16_walk_pays(h, s) ? -1 : f16_choice(s, input);
 }
 
 patdnn_status_t patdnn_conv2d(patdnn_handle_t h, const float* input, int32_t n, int32_t h_in,
@@ -875,7 +894,7 @@ patdnn_status_t patdnn_conv2d_f16(patdnn_handle_t h, const void* input, int32_t 
     s.relu = fuse_relu ? 1 : 0;
     hipError_t e = h->L.depthwise
                        ? launch_dw_f16(h->dfkw, s, input, bias, output, static_cast<hipStream_t>(stream))
-                   : h->dfkw.expanded_f16
+                   : h->dfkw.expanded_f16 && !f16_walk_pays(h, s)
                        ? launch_f16(h->dfkw, s, input, bias, output, static_cast<hipStream_t>(stream))
                        : launch_fkw_f16(h->dfkw, s, input, bias, output, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? PATDNN_OK : hip_fail(e, "launching a binary16 kernel");

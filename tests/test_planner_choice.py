@@ -56,3 +56,46 @@ def test_choice_is_close_to_the_fastest(case):
     # the estimates are up to 40 % off, and up to 10 us the launch is most of it
     assert us <= 1.4 * min(walk, tiled, taps), name
     L.close()
+
+
+# c_in, c_out, n, h, w, stride, pad, patterns, kept kernels, dense; us of the walk over the kept weights and
+# of the matrix kernel
+MEASURED_F16 = [
+    ((157, 6, 11, 173, 160, 2, 1, 8, 12, 0), (9, 92)),
+    ((101, 6, 61, 98, 98, 2, 0, 12, 6, 0), (10, 96)),
+    ((362, 2, 8, 137, 137, 2, 1, 56, 13, 0), (14, 104)),
+    ((136, 2, 15, 96, 96, 2, 1, 8, 2, 0), (9, 53)),
+    ((161, 4, 4, 209, 224, 1, 0, 8, 6, 0), (9, 46)),
+    ((390, 16, 31, 29, 29, 1, 1, 8, 21, 0), (10, 32)),
+    ((151, 17, 19, 68, 68, 1, 1, 8, 6, 0), (11, 34)),
+    ((308, 1, 10, 59, 59, 2, 1, 8, 3, 0), (9, 30)),
+    ((507, 23, 27, 26, 26, 1, 1, 8, 37, 0), (9, 29)),
+    ((448, 11, 36, 26, 24, 1, 1, 8, 15, 0), (9, 28)),
+    ((64, 70, 18, 91, 94, 1, 1, 6, 4480, 1), (2121, 55)),
+    ((64, 324, 36, 26, 28, 1, 1, 12, 20736, 1), (1450, 30)),
+    ((52, 19, 1, 3, 3, 1, 0, 8, 279, 0), (12, 9)),
+    ((18, 108, 21, 3, 3, 1, 0, 6, 558, 0), (13, 9)),
+    ((59, 23, 1, 5, 5, 1, 1, 8, 427, 0), (14, 10)),
+    ((16, 20, 1, 4, 6, 1, 1, 12, 320, 1), (15, 9)),
+    ((1, 5, 61, 176, 176, 1, 1, 12, 5, 1), (72, 62)),
+    ((128, 128, 64, 56, 56, 1, 1, 8, 4551, 0), (1990, 100)),
+    ((256, 256, 1, 28, 28, 1, 1, 8, 18204, 0), (57, 9)),
+]
+
+
+@pytest.mark.parametrize("case", MEASURED_F16)
+def test_binary16_choice_is_close_to_the_fastest(case):
+    (c_in, c_out, n, h, w, stride, pad, patterns, kept, dense), (walk, matrix) = case
+    rng = np.random.default_rng(kept)
+    mask = np.zeros(c_out * c_in, np.uint8)
+    mask[rng.permutation(mask.size)[:kept]] = 1
+    lib = wl.pattern_library(wl.PATTERN_SEED, patterns) if patterns < 56 else wl.pattern_universe()
+    L = B.Layer(np.ones((c_out, c_in, 3, 3), np.float32), rng.integers(0, patterns, (c_out, c_in), dtype=np.uint8),
+                mask.reshape(c_out, c_in), lib, stride=stride, pad=pad, dense=bool(dense), host_only=True)
+    choice = B.lib().patdnn_internal_f16_choice
+    choice.argtypes = [ctypes.c_void_p] * 2 + [ctypes.c_int32] * 3
+    choice.restype = ctypes.c_int32
+    got = choice(L.handle, 4096, n, h, w)
+    L.close()
+    assert got >= -1
+    assert (walk if got < 0 else matrix) <= 1.4 * min(walk, matrix), got
