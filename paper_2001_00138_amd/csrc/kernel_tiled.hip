@@ -30,6 +30,7 @@
 #include <atomic>
 #include <cstdlib>
 #include <mutex>
+#include <new>
 #include <type_traits>
 #include <vector>
 
@@ -759,7 +760,11 @@ static long long resident_workgroups(const void* fn, int threads, size_t lds_byt
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds_bytes) == hipSuccess &&
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess)
         slots = (long long)per_cu * cus;
-    known.push_back(Entry{dev, fn, threads, lds_bytes, slots});
+    try {
+        known.push_back(Entry{dev, fn, threads, lds_bytes, slots});
+    } catch (const std::bad_alloc&) {
+        // asked again next time
+    }
     return slots;
 }
 

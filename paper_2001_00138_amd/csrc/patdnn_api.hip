@@ -25,16 +25,30 @@ namespace {
 
 thread_local std::string g_err;
 
-patdnn_status_t fail(patdnn_status_t s, const std::string& msg)
+// Nothing leaves the C interface as an exception: a text that finds no memory is dropped, ...
+template <class... Parts>
+patdnn_status_t fail(patdnn_status_t s, const Parts&... parts)
 {
-    g_err = msg;
+    try {
+        g_err.clear();
+        (g_err.append(parts), ...);
+    } catch (const std::bad_alloc&) {
+        g_err.clear();
+    }
     return s;
 }
 
-patdnn_status_t hip_fail(hipError_t e, const char* what)
+patdnn_status_t hip_fail(hipError_t e, const char* what) { return fail(PATDNN_EHIP, what, ": ", hipGetErrorString(e)); }
+
+// ... and an entry point whose work allocates runs it in here.
+template <class F>
+patdnn_status_t guarded(F&& work)
 {
-    g_err = std::string(what) + ": " + hipGetErrorString(e);
-    return PATDNN_EHIP;
+    try {
+        return work();
+    } catch (const std::bad_alloc&) {
+        return fail(PATDNN_ENOMEM, "out of host memory");
+    }
 }
 
 }  // namespace
@@ -116,6 +130,7 @@ public:
     hipError_t commit(std::vector<void*>& owner)
     {
         if (!total) return hipSuccess;
+        owner.reserve(owner.size() + 1);
         void* p = nullptr;
         hipError_t e = hipMalloc(&p, total);
         if (e != hipSuccess) return e;
@@ -226,7 +241,7 @@ patdnn_status_t ensure_tiled(patdnn_layer* h, int vi, int ck, const DevTiled** o
     if (it == h->tiled.end()) {
         if (v.threaded && h->on_device) {
             std::string why;
-            if (!movrel_selftest(why)) return fail(PATDNN_EUNSUPPORTED, "threaded variants are off: " + why);
+            if (!movrel_selftest(why)) return fail(PATDNN_EUNSUPPORTED, "threaded variants are off: ", why);
         }
         std::unique_ptr<TiledOnDevice> t(new (std::nothrow) TiledOnDevice());
         if (!t) return fail(PATDNN_ENOMEM, "out of host memory");
@@ -327,8 +342,8 @@ patdnn_status_t ensure_compare(patdnn_layer* h)
                 for (int32_t k = f.offset[s] + st[p]; k < f.offset[s] + st[p + 1]; ++k)
                     per_filter[(size_t)f.reorder[s]].push_back(K{f.index[k], (int32_t)f.masks[p], &f.weight[(size_t)k * 4]});
         }
-        auto& no = h->noopt_host;
-        auto& cs = h->csr_host;
+        auto& no = h->noopt_host = patdnn_layer::CompareHost();
+        auto& cs = h->csr_host = patdnn_layer::CompareHost();
         no.row_ptr.assign(1, 0);
         cs.row_ptr.assign(1, 0);
         for (int co = 0; co < c_out; ++co) {
@@ -665,18 +680,11 @@ patdnn_status_t patdnn_encode(const patdnn_layer_desc_t* desc, const float* dens
 {
     if (out) *out = nullptr;
     if (!desc || !out) return fail(PATDNN_EINVAL, "desc / out is NULL");
-    std::unique_ptr<patdnn_layer> h(new (std::nothrow) patdnn_layer());
-    if (!h) return fail(PATDNN_ENOMEM, "out of host memory");
-    std::string err;
-    patdnn_status_t st;
-    try {
-        st = build_fkw(*desc, dense_weights, pattern_ids, kernel_mask, h->L, err);
-    } catch (const std::bad_alloc&) {
-        return fail(PATDNN_ENOMEM, "out of host memory");
-    }
-    if (st != PATDNN_OK) return fail(st, err);
-
-    try {
+    return guarded([&]() -> patdnn_status_t {
+        std::unique_ptr<patdnn_layer> h(new patdnn_layer());
+        std::string err;
+        patdnn_status_t st = build_fkw(*desc, dense_weights, pattern_ids, kernel_mask, h->L, err);
+        if (st != PATDNN_OK) return fail(st, err);
         if (!(desc->flags & PATDNN_HOST_ONLY)) {
             st = upload_layer(h.get());
             if (st != PATDNN_OK) return st;
@@ -696,11 +704,9 @@ patdnn_status_t patdnn_encode(const patdnn_layer_desc_t* desc, const float* dens
             st = ensure_tiled(h.get(), vi, default_ck(tiled_variant(vi), desc->c_in), nullptr);
             if (st != PATDNN_OK) return st;
         }
-    } catch (const std::bad_alloc&) {
-        return fail(PATDNN_ENOMEM, "out of host memory");
-    }
-    *out = h.release();
-    return PATDNN_OK;
+        *out = h.release();
+        return PATDNN_OK;
+    });
 }
 
 patdnn_status_t patdnn_output_shape(patdnn_handle_t h, int32_t n, int32_t h_in, int32_t w_in,
@@ -990,7 +996,7 @@ patdnn_status_t patdnn_export_csr(patdnn_handle_t h, int64_t* nnz, int32_t* row_
     return PATDNN_OK;
 }
 
-patdnn_status_t patdnn_layout_stats(patdnn_handle_t h, patdnn_stats_t* out)
+static patdnn_status_t layout_stats(patdnn_handle_t h, patdnn_stats_t* out)
 {
     if (!h || !out) return fail(PATDNN_EINVAL, "handle / out is NULL");
     const Fkw& f = h->L.fkw;
@@ -1022,6 +1028,11 @@ patdnn_status_t patdnn_layout_stats(patdnn_handle_t h, patdnn_stats_t* out)
     return PATDNN_OK;
 }
 
+patdnn_status_t patdnn_layout_stats(patdnn_handle_t h, patdnn_stats_t* out)
+{
+    return guarded([&] { return layout_stats(h, out); });
+}
+
 int32_t patdnn_num_variants(void) { return 1 + num_tiled_variants() + kNumExtra; }
 
 const char* patdnn_variant_name(int32_t variant)
@@ -1032,7 +1043,7 @@ const char* patdnn_variant_name(int32_t variant)
     return tiled_variant(variant - 1).name;
 }
 
-patdnn_status_t patdnn_set_config(patdnn_handle_t h, const patdnn_config_t* cfg)
+static patdnn_status_t set_config(patdnn_handle_t h, const patdnn_config_t* cfg)
 {
     if (!h || !cfg) return fail(PATDNN_EINVAL, "handle / cfg is NULL");
     if (cfg->variant < 0) {               // back to automatic choice
@@ -1048,12 +1059,8 @@ patdnn_status_t patdnn_set_config(patdnn_handle_t h, const patdnn_config_t* cfg)
         return PATDNN_OK;
     }
     if (extra_variant(cfg->variant) == kExtraNoopt || extra_variant(cfg->variant) == kExtraCsr) {
-        try {
-            patdnn_status_t st = ensure_compare(h);
-            if (st != PATDNN_OK) return st;
-        } catch (const std::bad_alloc&) {
-            return fail(PATDNN_ENOMEM, "out of host memory");
-        }
+        const patdnn_status_t st = ensure_compare(h);
+        if (st != PATDNN_OK) return st;
         h->cfg = patdnn_config_t{cfg->variant, 0, 0, 1};
         h->cfg_tuned = false;
         return PATDNN_OK;
@@ -1070,12 +1077,8 @@ patdnn_status_t patdnn_set_config(patdnn_handle_t h, const patdnn_config_t* cfg)
         if (c.waves == 0) c.waves = 8;
         if (c.ksplit < 1) c.ksplit = 1;
         if (c.ksplit > (c_in + c.ck - 1) / c.ck) return fail(PATDNN_EUNSUPPORTED, "ksplit exceeds the number of channel chunks");
-        try {
-            patdnn_status_t st = ensure_taps(h, c.ck, nullptr);
-            if (st != PATDNN_OK) return st;
-        } catch (const std::bad_alloc&) {
-            return fail(PATDNN_ENOMEM, "out of host memory");
-        }
+        const patdnn_status_t st = ensure_taps(h, c.ck, nullptr);
+        if (st != PATDNN_OK) return st;
         h->cfg = c;
         h->cfg_tuned = false;
         return PATDNN_OK;
@@ -1100,12 +1103,8 @@ patdnn_status_t patdnn_set_config(patdnn_handle_t h, const patdnn_config_t* cfg)
         const TiledVariant& v = tiled_variant(c.variant - 1);
         if (c.ck == 0) c.ck = default_ck(v, h->L.desc.c_in);
         c.ck = std::min(c.ck, h->L.desc.c_in);
-        try {
-            patdnn_status_t st = ensure_tiled(h, c.variant - 1, c.ck, nullptr);
-            if (st != PATDNN_OK) return st;
-        } catch (const std::bad_alloc&) {
-            return fail(PATDNN_ENOMEM, "out of host memory");
-        }
+        const patdnn_status_t st = ensure_tiled(h, c.variant - 1, c.ck, nullptr);
+        if (st != PATDNN_OK) return st;
         // an explicit configuration is taken as given or refused, never replaced at launch time
         const int num_chunks = v.dense ? (h->L.desc.c_in + c.ck - 1) / c.ck
                                        : h->tiled.find(std::make_pair(c.variant - 1, c.ck))->second->host.num_chunks;
@@ -1114,6 +1113,11 @@ patdnn_status_t patdnn_set_config(patdnn_handle_t h, const patdnn_config_t* cfg)
     h->cfg = c;
     h->cfg_tuned = false;
     return PATDNN_OK;
+}
+
+patdnn_status_t patdnn_set_config(patdnn_handle_t h, const patdnn_config_t* cfg)
+{
+    return guarded([&] { return set_config(h, cfg); });
 }
 
 patdnn_status_t patdnn_get_config(patdnn_handle_t h, patdnn_config_t* cfg)
@@ -1130,7 +1134,7 @@ patdnn_status_t patdnn_tune(patdnn_handle_t h, const float* input, int32_t n, in
     return patdnn_tune_ws(h, input, n, h_in, w_in, bias, output, nullptr, 0, stream_, best_us);
 }
 
-patdnn_status_t patdnn_tune_ws(patdnn_handle_t h, const float* input, int32_t n, int32_t h_in,
+static patdnn_status_t tune_ws(patdnn_handle_t h, const float* input, int32_t n, int32_t h_in,
                                int32_t w_in, const float* bias, float* output, float* workspace,
                                size_t workspace_floats, void* stream_, float* best_us)
 {
@@ -1188,10 +1192,16 @@ patdnn_status_t patdnn_tune_ws(patdnn_handle_t h, const float* input, int32_t n,
     if (h->L.depthwise) cands.push_back(patdnn_config_t{variant_of_extra(kExtraDepthwise), 0, 0, 1});
     cands.push_back(patdnn_config_t{PATDNN_VARIANT_FKW, 0, 0, 1});
 
-    hipEvent_t e0, e1;
+    struct Event {
+        hipEvent_t e = nullptr;
+        ~Event()
+        {
+            if (e) (void)hipEventDestroy(e);
+        }
+    } first, second;
     hipError_t e;
-    if ((e = hipEventCreate(&e0)) != hipSuccess) return hip_fail(e, "hipEventCreate");
-    if ((e = hipEventCreate(&e1)) != hipSuccess) { (void)hipEventDestroy(e0); return hip_fail(e, "hipEventCreate"); }
+    if ((e = hipEventCreate(&first.e)) != hipSuccess || (e = hipEventCreate(&second.e)) != hipSuccess) return hip_fail(e, "hipEventCreate");
+    const hipEvent_t e0 = first.e, e1 = second.e;
     float best = -1.0f;
     patdnn_config_t best_cfg = cands.back();
     patdnn_status_t result = PATDNN_OK;
@@ -1240,8 +1250,6 @@ patdnn_status_t patdnn_tune_ws(patdnn_handle_t h, const float* input, int32_t n,
             if (best < 0.0f || ms < best) { best = ms; best_cfg = cands[timed[k].second]; }
         }
     }
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
     if (result != PATDNN_OK) return result;
     // leave a valid result of the chosen configuration in `output`
     st = run_config(h, best_cfg, s, input, bias, output, stream, workspace, workspace_floats);
@@ -1264,6 +1272,13 @@ patdnn_status_t patdnn_tune_ws(patdnn_handle_t h, const float* input, int32_t n,
     }
     if (best_us) *best_us = best * 1000.0f;
     return PATDNN_OK;
+}
+
+patdnn_status_t patdnn_tune_ws(patdnn_handle_t h, const float* input, int32_t n, int32_t h_in,
+                               int32_t w_in, const float* bias, float* output, float* workspace,
+                               size_t workspace_floats, void* stream_, float* best_us)
+{
+    return guarded([&] { return tune_ws(h, input, n, h_in, w_in, bias, output, workspace, workspace_floats, stream_, best_us); });
 }
 
 static patdnn_status_t find_tiled(patdnn_handle_t h, int32_t variant, int32_t ck, TiledOnDevice** out)
@@ -1339,9 +1354,11 @@ patdnn_status_t patdnn_export_tiled(patdnn_handle_t h, int32_t variant, int32_t 
 
 patdnn_status_t patdnn_selftest(void)
 {
-    std::string why;
-    if (!movrel_selftest(why)) return fail(PATDNN_EUNSUPPORTED, why);
-    return PATDNN_OK;
+    return guarded([]() -> patdnn_status_t {
+        std::string why;
+        if (!movrel_selftest(why)) return fail(PATDNN_EUNSUPPORTED, why);
+        return PATDNN_OK;
+    });
 }
 
 void patdnn_destroy(patdnn_handle_t h) { delete h; }
@@ -1426,7 +1443,7 @@ patdnn_status_t stack_launch(patdnn_stack* s, const float* input, float* output,
 
 extern "C" {
 
-patdnn_status_t patdnn_stack_create(const patdnn_stack_layer_t* layers, int32_t num_layers, int32_t n,
+static patdnn_status_t stack_create(const patdnn_stack_layer_t* layers, int32_t num_layers, int32_t n,
                                     int32_t h_in, int32_t w_in, patdnn_stack_t* out)
 {
     if (out) *out = nullptr;
@@ -1476,6 +1493,12 @@ patdnn_status_t patdnn_stack_create(const patdnn_stack_layer_t* layers, int32_t 
     }
     *out = s.release();
     return PATDNN_OK;
+}
+
+patdnn_status_t patdnn_stack_create(const patdnn_stack_layer_t* layers, int32_t num_layers, int32_t n,
+                                    int32_t h_in, int32_t w_in, patdnn_stack_t* out)
+{
+    return guarded([&] { return stack_create(layers, num_layers, n, h_in, w_in, out); });
 }
 
 patdnn_status_t patdnn_stack_output_shape(patdnn_stack_t s, int32_t out_nchw[4])
