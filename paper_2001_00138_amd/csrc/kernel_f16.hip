@@ -12,12 +12,12 @@
 // The one case where a zero weight is not nothing is an input that is infinite or NaN (0 * inf).
 // Every output such an input reaches through any of the nine taps then has a sum that is not
 // finite, so the wavefront looks at its sums once, at the end, and computes the blocks of pixels
-// concerned again, from the tensor itself: the sum over the finite inputs, and in two more
-// accumulators whether an infinity or a NaN met a kept weight, and with which sign (kept weights that
+// concerned again, from the tensor itself: in two accumulators whether an infinity or a NaN met a kept
+// weight, and with which sign, and then the sum over the finite inputs (kept weights that
 // are zero are stored as -0, so that they can be told from the removed ones).  Layers with a weight
 // that is not finite in binary16 run the walk over the kept weights instead.
-// 128 -> 128 at 56 x 56, 64 images: 97 us with finite inputs, 630 with one infinity in ten thousand
-// inputs, 1070 with nothing but NaN; one lane after the other walking the FKW arrays for its own
+// 128 -> 128 at 56 x 56, 64 images: 97 us with finite inputs, 1060 with one infinity in ten thousand
+// inputs, 1700 with nothing but NaN; one lane after the other walking the FKW arrays for its own
 // pixels took 19400 and 23800, the walk over the whole layer takes 2000.
 //
 // Work decomposition
@@ -69,6 +69,8 @@ struct F16Args {
     FastDiv div_fsets, div_tiles, div_sw, div_ho, div_vh, div_pitch;
 };
 
+typedef const F16Args __attribute__((address_space(4))) * F16ArgsPtr;      // the kernel's own arguments
+
 // Staging buffers: wavefronts that share a block stage so many channels that a second buffer would
 // cost more workgroups per CU than it hides.
 constexpr int f16_buffers(int wk) { return wk > 1 ? 1 : 2; }
@@ -104,10 +106,121 @@ static __device__ __forceinline__ void split_weights(ushort8 w, half8& kept, hal
     sign = __builtin_bit_cast(half8, s);
 }
 
+// Products of eight channels and one tap at a time, over all channels: of the finite inputs (plain), or of
+// what tells where inputs are not (up, down; see f16_again).
+template <bool PLAIN>
+static __device__ __forceinline__ void f16_walk(F16ArgsPtr a, __amdgpu_buffer_rsrc_t rsrc, unsigned image, const uint4* wt, int y, int x,
+                                                float16v& up, float16v& down)
+{
+    const int plane = a->h * a->w;
+#pragma unroll 1
+    for (int step = 0; step < a->steps; ++step)
+#pragma unroll 1
+        for (int pos = 0; pos < 9; ++pos) {
+            const int iy = y * a->conv_stride + pos / 3 - a->pad, ix = x * a->conv_stride + pos % 3 - a->pad;
+            const bool inside = iy >= 0 && iy < a->h && ix >= 0 && ix < a->w;
+            // past the last channel its weights are zeros of removed kernels, which meet nothing
+            unsigned at = image + 2u * (unsigned)(step * 16 * plane + iy * a->w + ix);
+            ushort8 bits;
+            bool some = false;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                bits[j] = (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rsrc, inside ? (int)at : -1, 0, 0);
+                at += 2u * (unsigned)plane;
+                some |= (bits[j] & 0x7FFF) >= 0x7C00;
+            }
+            const NonFinite v = split_inputs(bits);
+            const uint4 w = wt[(step * 9 + pos) * 64];
+            if constexpr (PLAIN) {
+                up = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, w), v.finite, up, 0, 0, 0);
+            } else {
+                if (!__any(some)) continue;
+                half8 kept, sign;
+                split_weights(__builtin_bit_cast(ushort8, w), kept, sign);
+                up = __builtin_amdgcn_mfma_f32_32x32x16_f16(kept, v.any, up, 0, 0, 0);
+                up = __builtin_amdgcn_mfma_f32_32x32x16_f16(sign, v.sign, up, 0, 0, 0);
+                down = __builtin_amdgcn_mfma_f32_32x32x16_f16(kept, v.any, down, 0, 0, 0);
+                down = __builtin_amdgcn_mfma_f32_32x32x16_f16(sign, -v.sign, down, 0, 0, 0);
+            }
+        }
+}
+
+// Blocks with a sum that is not finite (`odd`: a bit per block of the lane's pixels), once more; every
+// wavefront of a block goes over all channels here.  Everything is worked out again from the kernel's
+// arguments, read again, and one accumulator pair at a time, so that the kernel proper holds no register
+// for it: the registers it needs decide how many wavefronts fit.
+template <int FM, int PN, int WF, int WP, int WK>
+static __device__ __forceinline__ void f16_again(unsigned odd, int wave)
+{
+    constexpr int PIX = 32 * PN * WP, RK = 16 / WK;
+    F16ArgsPtr a = (F16ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(a));
+    auto div = [](int n, const FastDiv __attribute__((address_space(4))) & d) { return (int)fast_div((uint32_t)n, FastDiv{d.m, d.shift}); };
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int wk = wave % WK, wp = wave / WK % WP, wf = wave / (WK * WP);
+    const int per_xcd = gridDim.x >> 3, rank = blockIdx.x >> 3;
+    const int bid = rank < per_xcd ? (blockIdx.x & 7) * per_xcd + rank : blockIdx.x;
+    const int tile_all = div(bid, a->div_fsets), fset = bid - tile_all * a->fsets;
+    const int strip = div(tile_all, a->div_tiles);
+    const int pix0 = (tile_all - strip * a->tiles) * PIX, last = min(pix0 + PIX, a->pixels) - 1;
+    const int img0 = div(div(pix0, a->div_sw), a->div_ho);
+    const int plane = a->h * a->w;
+    const size_t oplane = (size_t)a->ho * a->wo, tail = (size_t)(a->n - img0) * a->c_in * plane * 2;
+    __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(a->in + (size_t)img0 * a->c_in * plane), 0,
+                                                                    (int)(unsigned)std::min<size_t>(tail, 0x80000000u), 0x00020000);
+#pragma unroll 1
+    for (int p = 0; p < PN; ++p) {
+        const bool mine = odd >> p & 1;
+        if (!__any(mine)) continue;
+        const int q = min(pix0 + (wp * PN + p) * 32 + l32, last);
+        const int row = div(q, a->div_sw), im = div(row, a->div_ho);
+        const int y = row - im * a->ho, x = strip * a->sw + q - row * a->sw;
+        const unsigned image = 2u * (unsigned)(((im - img0) * a->c_in + half * 8) * plane);
+#pragma unroll 1
+        for (int f = 0; f < FM; ++f) {
+            const int block = (fset * WF + wf) * FM + f;
+            if (block >= a->fblocks) break;
+            const uint4* const wt = a->weights + (size_t)block * a->steps * (9 * 64) + lane;
+            // `up` is positive where an infinity of positive product or a NaN met a kept weight, `down`
+            // where one of negative product or a NaN did: sums of whole numbers that cancel exactly
+            float16v up{}, down{};
+            f16_walk<false>(a, rsrc, image, wt, y, x, up, down);
+            unsigned plus = 0, minus = 0;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                plus |= (unsigned)(up[r] > 0.0f) << r;
+                minus |= (unsigned)(down[r] > 0.0f) << r;
+            }
+            float16v sum{};
+            f16_walk<true>(a, rsrc, image, wt, y, x, sum, down);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                __builtin_amdgcn_sched_barrier(0);    // one store after the other
+                const int s = block * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+                if (mine && r / RK == (WK > 1 ? wk : 0) && s < a->c_out) {
+                    const int co = a->reorder[s];
+                    float v = sum[r];
+                    if (minus >> r & 1) v = -__builtin_inff();
+                    if (plus >> r & 1) v = minus >> r & 1 ? __builtin_nanf("") : __builtin_inff();
+                    v += a->bias ? a->bias[co] : 0.0f;
+                    if (a->relu) v = fmaxf(v, 0.0f);
+                    a->out[((size_t)im * a->c_out + co) * oplane + (size_t)y * a->wo + x] = __float2half_rn(v);
+                }
+            }
+        }
+    }
+}
+
+// Wavefronts per SIMD that the registers of so many blocks allow.  Said to the compiler, which would
+// otherwise save registers for more and wait for every load of the channel loop by itself (10 to 15 % on the
+// splitting shapes).
+constexpr int f16_waves(int blocks, bool most) { return blocks >= 8 ? 2 : blocks >= 4 ? 4 : !most ? 2 : blocks >= 2 ? 5 : 6; }
+
 // PAIR: rows of whole aligned pairs of pixels (see f16_tiles): staged two pixels per load, and
 // stored two pixels at a time where the output's rows are the same.
 template <int FM, int PN, int WF, int WP, int WK, bool PAIR>
-__global__ __launch_bounds__(64 * WF * WP * WK, FM * PN >= 8 ? 2 : FM * PN >= 4 ? 4 : 5) void f16_conv_kernel(F16Args a)
+__global__ __launch_bounds__(64 * WF * WP * WK) __attribute__((amdgpu_waves_per_eu(f16_waves(FM * PN, false), f16_waves(FM * PN, true))))
+void f16_conv_kernel(F16Args a)
 {
     extern __shared__ uint4 lds4[];
     constexpr int WAVES = WF * WP * WK, PIX = 32 * PN * WP, G8 = 2 * WK;
@@ -133,8 +246,6 @@ __global__ __launch_bounds__(64 * WF * WP * WK, FM * PN >= 8 ? 2 : FM * PN >= 4 
     split_row(pix0, img0, oy0, sx0);
     const int vrow0 = img0 * a.vh + oy0 * a.conv_stride;
     const int plane = a.h * a.w;
-    const size_t tail = (size_t)(a.n - img0) * a.c_in * plane * 2;
-    const char* in_blk = (const char*)(a.in + (size_t)img0 * a.c_in * plane);
 
     // ---- byte offset, from the tile's first image, of every staged pixel in its channel
     // (~0u: padding, reads as zero)
@@ -173,6 +284,8 @@ __global__ __launch_bounds__(64 * WF * WP * WK, FM * PN >= 8 ? 2 : FM * PN >= 4 
 
     // ---- staging: unit u = 64 pixels (pairs) x 8 channels, units wave, wave + WAVES, ... of a chunk
     const int units = npb * G8;
+    const size_t tail = (size_t)(a.n - img0) * a.c_in * plane * 2;
+    const char* in_blk = (const char*)(a.in + (size_t)img0 * a.c_in * plane);
     // out of range (reads as zero) from the end of the tensor on, and for ~0u
     __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)in_blk, 0, (int)(unsigned)std::min<size_t>(tail, 0x80000000u), 0x00020000);
     struct Unit { uint4 v[UPX]; };
@@ -187,6 +300,9 @@ __global__ __launch_bounds__(64 * WF * WP * WK, FM * PN >= 8 ? 2 : FM * PN >= 4 
             if constexpr (PAIR) v[j] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, off, soff, 0);
             else v[j] = (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rsrc, off, soff, 0);
         }
+        // the last load must not take the offset's register: that would part the eight loads (an s_nop between
+        // them, 6 % on the splitting shapes of unpaired rows)
+        asm volatile("" : : "v"(off));
         Unit t;
         if constexpr (PAIR) {
             // low halves, then high halves, of two channels
@@ -338,67 +454,7 @@ __global__ __launch_bounds__(64 * WF * WP * WK, FM * PN >= 8 ? 2 : FM * PN >= 4 
         }
     if (!__any(odd)) return;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // after the stores above, the neighbour's among them
-
-    // ---- blocks with a sum that is not finite, once more; every wavefront of a block goes over all
-    // channels here
-#pragma unroll 1
-    for (int p = 0; p < PN; ++p) {
-        const bool mine = odd >> p & 1;
-        if (!__any(mine)) continue;
-        int im, y, sx;
-        split_row(min(pix0 + (wp * PN + p) * 32 + l32, last), im, y, sx);
-        const int x = strip * a.sw + sx;
-        const unsigned image = 2u * (unsigned)(((im - img0) * a.c_in + half * 8) * plane);
-#pragma unroll 1
-        for (int f = 0; f < FM; ++f) {
-            const int block = (fset * WF + wf) * FM + f;
-            if (block >= a.fblocks) break;
-            const uint4* const wt = a.weights + (size_t)block * a.steps * (9 * 64) + lane;
-            // `up` is positive where an infinity of positive product or a NaN met a kept weight, `down`
-            // where one of negative product or a NaN did: sums of whole numbers that cancel exactly
-            float16v sum{}, up{}, down{};
-#pragma unroll 1
-            for (int step = 0; step < a.steps; ++step)
-#pragma unroll 1
-                for (int pos = 0; pos < 9; ++pos) {
-                    const int iy = y * a.conv_stride + pos / 3 - a.pad, ix = x * a.conv_stride + pos % 3 - a.pad;
-                    const bool inside = iy >= 0 && iy < a.h && ix >= 0 && ix < a.w;
-                    // past the last channel its weights are zeros of removed kernels, which meet nothing
-                    unsigned at = image + 2u * (unsigned)(step * 16 * plane + iy * a.w + ix);
-                    ushort8 bits;
-                    bool some = false;
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        bits[j] = (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rsrc, inside ? (int)at : -1, 0, 0);
-                        at += 2u * (unsigned)plane;
-                        some |= (bits[j] & 0x7FFF) >= 0x7C00;
-                    }
-                    const NonFinite v = split_inputs(bits);
-                    const uint4 w = wt[(step * 9 + pos) * 64];
-                    sum = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, w), v.finite, sum, 0, 0, 0);
-                    if (!__any(some)) continue;
-                    half8 kept, sign;
-                    split_weights(__builtin_bit_cast(ushort8, w), kept, sign);
-                    up = __builtin_amdgcn_mfma_f32_32x32x16_f16(kept, v.any, up, 0, 0, 0);
-                    up = __builtin_amdgcn_mfma_f32_32x32x16_f16(sign, v.sign, up, 0, 0, 0);
-                    down = __builtin_amdgcn_mfma_f32_32x32x16_f16(kept, v.any, down, 0, 0, 0);
-                    down = __builtin_amdgcn_mfma_f32_32x32x16_f16(sign, -v.sign, down, 0, 0, 0);
-                }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                __builtin_amdgcn_sched_barrier(0);    // one store after the other: registers decide how many wavefronts fit
-                const int s = block * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-                if (mine && r / RK == (WK > 1 ? wk : 0) && s < a.c_out) {
-                    const int co = a.reorder[s];
-                    const bool plus = up[r] > 0.0f, minus = down[r] > 0.0f;
-                    float v = plus ? (minus ? __builtin_nanf("") : __builtin_inff()) : minus ? -__builtin_inff() : sum[r];
-                    v += a.bias ? a.bias[co] : 0.0f;
-                    if (a.relu) v = fmaxf(v, 0.0f);
-                    a.out[((size_t)im * a.c_out + co) * oplane + (size_t)y * a.wo + x] = __float2half_rn(v);
-                }
-            }
-        }
-    }
+    f16_again<FM, PN, WF, WP, WK>(odd, wave);
 }
 
 // One workgroup per stored filter: its kept weights to their places in the fragments, zeros as -0

@@ -527,13 +527,16 @@ double fkw_estimate(const patdnn_layer* h, const ConvShape& s)
 // Binary16 layers, microseconds: the walk as above, and the matrix kernel, which multiplies the removed
 // weights too and fills its channels to 16 and its filters to 32: a chain of channel steps, multiply-adds,
 // inputs staged once per 128 filters, outputs.  Fitted to 400 layers of 1 to 512 channels, keep ratios
-// from 0.003 and dense ones: 14 % and 8 % on average, on 400 others 15 % and 9 %.  The walk is taken
-// where it is ahead by more than 15 % (few filters, or next to nothing kept): 17 -> 3 at 175 x 175 / 2, 15 images,
-// one kernel in a hundred 9 us against 28; of the 800 layers 9 are then more than 15 % behind the walk, 56
-// without it.  Layers of 16 channels and filters and more at keep ratios from 1/3.6 are none of these.
+// from 0.003 and dense ones: 14 % and 8 % on average, on 400 others 15 % and 9 %.  The walk is taken for
+// filters of at most eight kernels and where it is ahead by more than 15 % (longer chains of cold loads are
+// up to 1.7 times the estimate): 17 -> 3 at 175 x 175 / 2, 15 images, one kernel in a hundred 9 us against
+// 28.  Of the 800 layers 11 are then more than 15 % behind the walk (56 without it) and 5 more than 10 %
+// behind the matrix kernel.  Layers of 16 channels and filters and more at keep ratios from 1/3.6 are
+// none of these.
 bool f16_walk_pays(const patdnn_layer* h, const ConvShape& s)
 {
     const double kernels = (double)h->L.kept / s.c_out * h->L.fkw.taps / 4, patterns = h->L.fkw.num_patterns;
+    if (kernels > 8.0) return false;
     const double pixels = (double)s.n * s.ho * s.wo, waves = (double)s.n * s.c_out * (((long long)s.ho * s.wo + 63) / 64);
     const double walk = std::max(9.4, 5.2 + 0.368 * kernels + 0.079 * patterns + waves * (1.47e-4 * kernels + 2.4e-5 * patterns));
     const double c16 = (s.c_in + 15) / 16 * 16.0, f32 = (s.c_out + 31) / 32 * 32.0;
@@ -610,8 +613,12 @@ patdnn_status_t upload_layer(patdnn_layer* h)
     }
     size_t expanded = h->L.depthwise || !finite16 ? 0 : f16_expanded_halves(h->L.desc.c_in, h->L.desc.c_out);
     if (expanded > kMaxExpandedHalves) expanded = 0;
-    up.room(expanded, &expanded16);
-    if ((e = up.commit(h->allocations)) != hipSuccess) return hip_fail(e, "uploading the layer");
+    // from a megabyte on by themselves, at the start of a page (512 -> 512 at 7 x 7, 64 images: 26.5 us, 27.2
+    // behind the other arrays)
+    Upload own;
+    (expanded >= 1 << 19 ? own : up).room(expanded, &expanded16);
+    if ((e = up.commit(h->allocations)) != hipSuccess || (e = own.commit(h->allocations)) != hipSuccess)
+        return hip_fail(e, "uploading the layer");
     d.weight_f16 = weight16;
     d.dw_weight_f16 = dw_weight16;
     if (expanded) {
