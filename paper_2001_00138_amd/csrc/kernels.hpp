@@ -15,8 +15,8 @@ namespace patdnn {
 struct ConvShape {
     int32_t n, c_in, c_out, h, w, ho, wo, stride, pad, relu;
     // pool != 0: ReLU, then 2x2 max pooling with stride 2 (floor), fused into the epilogue.
-    // The output tensor is [n][c_out][ho/2][wo/2] and, for all kernels but the tap-product one (whole
-    // windows in registers), must hold zeros when the kernel starts: every lane folds its values in
+    // The output tensor is [n][c_out][ho/2][wo/2] and, for all kernels but the tap-product and the split
+    // one (whole windows in registers), must hold zeros when the kernel starts: every lane folds its values in
     // with an unsigned integer atomic max on the float bits, which orders non-negative floats like the
     // floats themselves.
     int32_t pool = 0;
@@ -92,6 +92,10 @@ struct DevFkw {
     // matrix instructions' order (kernel_f16.hip); NULL: depthwise layers, very large ones and
     // those with a weight that is not finite in binary16
     const void* expanded_f16 = nullptr;
+    // likewise as pairs of binary16 numbers (kernel_split.hip), and per stored filter, to whole blocks of 64,
+    // its channel (-1: none) and the power of two that its weights were multiplied with
+    const void* split_f16 = nullptr;
+    const int32_t* split_filters = nullptr;
 };
 
 // Filter-group layout on the device: record streams (sparse) or 9-tap weights (dense).
@@ -139,6 +143,15 @@ int f16_choice(const ConvShape& s, const void* in);
 size_t f16_expanded_halves(int32_t c_in, int32_t c_out);
 // Fills `out` (f16_expanded_halves, zeroed) from the FKW arrays.
 hipError_t launch_f16_expand(const DevFkw& f, int32_t c_in, int32_t c_out, void* out, hipStream_t stream);
+
+// fp32 on the binary16 matrix cores (needs DevFkw::split_f16).
+// False where its numbers do not reach; else the units of work that the busiest workgroup has, the channel steps of
+// each and the pixels of a wavefront.
+bool split_cost(const ConvShape& s, int& rounds, int& steps, int& pixels);
+hipError_t launch_split(const DevFkw& f, const ConvShape& s, const float* in, const float* bias, float* out, hipStream_t stream);
+size_t split_expanded_halves(int32_t c_in, int32_t c_out);
+// Fills `out` (split_expanded_halves, zeroed) from the FKW arrays and split_filters.
+hipError_t launch_split_expand(const DevFkw& f, int32_t c_in, int32_t c_out, void* out, hipStream_t stream);
 
 // ---------------------------------------------------------------------------
 // Tiled kernels: compile-time geometry per variant, run-time launch parameters.

@@ -85,6 +85,7 @@ struct TapsOnDevice {
 struct patdnn_layer {
     LayerHost L;
     bool on_device = false;
+    bool split = false;                                    // the weights as pairs of binary16 numbers exist
     int device = -1;
     DevFkw dfkw;
     // by (variant index, ck); dense variants use ck = 0
@@ -192,10 +193,10 @@ bool variant_selectable(const patdnn_layer* h, const TiledVariant& v)
 }
 
 // Variant numbers: 0 the FKW walk, 1..T the tiled variants, then the kernels below.
-enum ExtraVariant { kExtraDepthwise = 0, kExtraNoopt, kExtraCsr, kExtraTaps8, kExtraTaps16, kNumExtra };
+enum ExtraVariant { kExtraDepthwise = 0, kExtraNoopt, kExtraCsr, kExtraTaps8, kExtraTaps16, kExtraSplit, kNumExtra };
 int extra_variant(int variant) { return variant - 1 - num_tiled_variants(); }     // < 0: not one
 int variant_of_extra(int extra) { return 1 + num_tiled_variants() + extra; }
-const char* const kExtraNames[kNumExtra] = {"dw_p1x4", "noopt", "csr", "taps_f8", "taps_f16"};
+const char* const kExtraNames[kNumExtra] = {"dw_p1x4", "noopt", "csr", "taps_f8", "taps_f16", "split_f16"};
 // filters per wavefront of a tap-product variant, 0 for any other
 int taps_filters(int variant)
 {
@@ -420,6 +421,13 @@ patdnn_status_t run_config(patdnn_layer* h, const patdnn_config_t& c, const Conv
         hipError_t e = launch_compare(csr, csr ? h->csr_dev : h->noopt_dev, s, in, bias, out, stream);
         return e == hipSuccess ? PATDNN_OK : hip_fail(e, "launching a comparison kernel");
     }
+    if (extra_variant(c.variant) == kExtraSplit) {
+        if (!h->dfkw.split_f16) return fail(PATDNN_EUNSUPPORTED, "variant cannot run this layer");
+        int rounds = 0, steps = 0, pixels = 0;
+        if (!split_cost(s, rounds, steps, pixels)) return fail(PATDNN_EUNSUPPORTED, "input too large for the split kernel");
+        hipError_t e = launch_split(h->dfkw, s, in, bias, out, stream);
+        return e == hipSuccess ? PATDNN_OK : hip_fail(e, "launching the split kernel");
+    }
     if (const int filters = taps_filters(c.variant)) {
         auto it = h->taps.find(c.ck);
         if (it == h->taps.end()) return fail(PATDNN_EUNSUPPORTED, "no layout for this ck: choose it with patdnn_set_config");
@@ -513,6 +521,17 @@ double tiled_estimate(const patdnn_layer* h, const TiledVariant& v, const ConvSh
            (1.0 + (0.03 + 5e-4 * std::min(kernels, 200.0)) * over8);
 }
 
+// Default stride-2 variant, microseconds: a wavefront of 16 filters and 64 columns of four rows goes through the
+// channels one after the other; up to some two wavefronts per SIMD that chain is the time.  (Nine layers of 77
+// to 352 channels, 77 to 586 us: 8 % on average.)
+double tiled2_estimate(const patdnn_layer* h, const ConvShape& s)
+{
+    const double kernels = (double)h->L.kept / s.c_out;
+    const long long bands = (long long)s.n * ((s.wo + 15) / 16) * ((s.ho + 3) / 4);
+    const double per_simd = (double)((bands + 3) / 4) * ((s.c_out + 15) / 16) / 1024;
+    return 5.0 + (0.265 * s.c_in + 1.25 * kernels) * (per_simd < 1.9 ? 1.1 + 0.1 * per_simd : 1.4 + 0.42 * per_simd);
+}
+
 // FKW walk, microseconds: a wavefront walks the kernels of one filter, pattern by pattern, for 64
 // output pixels, one load after the other; launches of more wavefronts than the chip holds pay for
 // each of them.  (Fitted to 90 layers of 16 to 512 channels, 6 to 56 patterns and 9 us to 9 ms: 14 %
@@ -547,6 +566,55 @@ bool f16_walk_pays(const patdnn_layer* h, const ConvShape& s)
 
 // Binary16 weights with the removed ones as zeros: up to 256 MB a layer.
 constexpr size_t kMaxExpandedHalves = (size_t)128 << 20;
+
+// Per stored filter the power of two that brings its largest weight to 2^14 .. 2^15; false where a weight is
+// not finite, or so small beside its filter's largest that nothing of it would be left in binary16.
+bool split_exponents(const LayerHost& L, std::vector<int32_t>& out)
+{
+    const Fkw& f = L.fkw;
+    out.assign((size_t)(L.desc.c_out + 63) / 64 * 128, -1);
+    for (int s = 0; s < L.desc.c_out; ++s) {
+        out[2 * (size_t)s] = f.reorder[s];
+        int32_t& exponent = out[2 * (size_t)s + 1] = 0;
+        float most = 0.0f, least = INFINITY;
+        for (size_t i = (size_t)f.offset[s] * f.taps; i < (size_t)f.offset[s + 1] * f.taps; ++i) {
+            const float w = std::fabs(f.weight[i]);
+            if (!(w < INFINITY)) return false;
+            if (w > 0.0f) least = std::min(least, w);
+            most = std::max(most, w);
+        }
+        if (most == 0.0f) continue;
+        int e = 0;
+        std::frexp(most, &e);                         // most < 2^e
+        exponent = 15 - e;
+        if (std::ldexp((double)least, exponent) < 0x1p-24) return false;
+    }
+    return true;
+}
+
+// Pruned layers for which the split kernel exists: where it is no less exact than the kernels that it stands in
+// for, which add a filter's products one after the other.  Errors against 64 bits, in 1e-8 of the result's
+// norm: theirs grow as 1.82 sqrt(2 kernels per filter); the split kernel has 7.3 from the halves' last
+// bits, and adds sixteen channels of a tap at a time, 1.66 sqrt(such additions that add anything).  (kept
+// 1/3.6: 64 channels 11.5 and 12.2, 128 15.4 and 15.1, 512 29.6 and 26.3; half of 64 channels 14.5 and 13.7.)
+// At stride 1 it is slower than the others for less than about 0.4 of the kernels (128 -> 128 at 112 x 112, 64
+// images: 1/3.6 615 us against 560, one half 600 against 960).
+bool split_layer(const LayerHost& L)
+{
+    if (L.depthwise || L.dense || L.kept == 0) return false;
+    const double c_in = L.desc.c_in, kernels = (double)L.kept / L.desc.c_out, keep = kernels / c_in;
+    if (L.desc.stride == 1 && keep < 0.4) return false;
+    const double additions = 9.0 / 16 * c_in * (1.0 - std::pow(1.0 - 4.0 / 9 * keep, 16.0));
+    if (53.3 + 2.75 * additions > 6.62 * kernels) return false;
+    std::vector<int32_t> exponents;
+    return split_expanded_halves(L.desc.c_in, L.desc.c_out) <= kMaxExpandedHalves && split_exponents(L, exponents);
+}
+
+// Its time, microseconds: units of work one after the other, channel steps and stores of each.  (Fitted to 14 layers.)
+double split_estimate(int rounds, int steps, int pixels)
+{
+    return 8.0 + rounds * (3.9 * steps + (pixels == 64 ? 8.7 : 3.5));
+}
 
 // The FKW arrays and what is derived from them, to the device.
 patdnn_status_t upload_layer(patdnn_layer* h)
@@ -611,12 +679,17 @@ patdnn_status_t upload_layer(patdnn_layer* h)
         }
         up.add(dweight16, &dw_weight16);
     }
+    std::vector<int32_t> split_filters;
+    const size_t split = h->split && split_exponents(h->L, split_filters) ? split_expanded_halves(h->L.desc.c_in, h->L.desc.c_out) : 0;
+    const uint16_t* split16 = nullptr;
+    if (split) up.add(split_filters, &d.split_filters);
     size_t expanded = h->L.depthwise || !finite16 ? 0 : f16_expanded_halves(h->L.desc.c_in, h->L.desc.c_out);
     if (expanded > kMaxExpandedHalves) expanded = 0;
     // from a megabyte on by themselves, at the start of a page (512 -> 512 at 7 x 7, 64 images: 26.5 us, 27.2
     // behind the other arrays)
     Upload own;
     (expanded >= 1 << 19 ? own : up).room(expanded, &expanded16);
+    (split >= 1 << 19 ? own : up).room(split, &split16);
     if ((e = up.commit(h->allocations)) != hipSuccess || (e = own.commit(h->allocations)) != hipSuccess)
         return hip_fail(e, "uploading the layer");
     d.weight_f16 = weight16;
@@ -627,6 +700,13 @@ patdnn_status_t upload_layer(patdnn_layer* h)
             (e = hipStreamSynchronize(nullptr)) != hipSuccess)
             return hip_fail(e, "expanding the binary16 weights");
         d.expanded_f16 = expanded16;
+    }
+    if (split) {
+        if ((e = hipMemsetAsync(const_cast<uint16_t*>(split16), 0, split * 2, nullptr)) != hipSuccess ||
+            (e = launch_split_expand(d, h->L.desc.c_in, h->L.desc.c_out, const_cast<uint16_t*>(split16), nullptr)) != hipSuccess ||
+            (e = hipStreamSynchronize(nullptr)) != hipSuccess)
+            return hip_fail(e, "splitting the weights");
+        d.split_f16 = split16;
     }
     h->on_device = true;
     return PATDNN_OK;
@@ -654,7 +734,16 @@ patdnn_config_t default_config(patdnn_layer* h, const ConvShape& shape, size_t s
         if (us < best_us) { best_us = us; best = patdnn_config_t{vi + 1, ck, waves, 1}; }
         break;
     }
-    if (!taps) return best;
+    // the split kernel stands in for those two only: the tap-product kernel is the more exact one
+    const auto or_split = [&](const patdnn_config_t& c) {
+        int rounds = 0, steps = 0, pixels = 0;
+        if (!h->split || !split_cost(shape, rounds, steps, pixels) || !split_cost(s, rounds, steps, pixels)) return c;
+        const double other = taps ? best_us : c.variant == PATDNN_VARIANT_FKW ? fkw_estimate(h, s) : tiled2_estimate(h, s);
+        // (the estimate of the stride-2 variant is the coarser one)
+        if (split_estimate(rounds, steps, pixels) * (s.stride == 1 ? 1.03 : 1.15) > other) return c;
+        return patdnn_config_t{variant_of_extra(kExtraSplit), 0, 0, 1};
+    };
+    if (!taps) return or_split(best);
     const long long tiles = tap_tile_count(s);
     const size_t stride = split_slice_stride((size_t)s.n * s.c_out * s.ho * s.wo);
     for (int level = 0; level < kTapLevels; ++level) {
@@ -674,7 +763,7 @@ patdnn_config_t default_config(patdnn_layer* h, const ConvShape& shape, size_t s
                 }
             }
     }
-    return best;
+    return taps_filters(best.variant) ? best : or_split(best);
 }
 
 }  // namespace
@@ -692,6 +781,7 @@ patdnn_status_t patdnn_encode(const patdnn_layer_desc_t* desc, const float* dens
         std::string err;
         patdnn_status_t st = build_fkw(*desc, dense_weights, pattern_ids, kernel_mask, h->L, err);
         if (st != PATDNN_OK) return fail(st, err);
+        h->split = split_layer(h->L);
         if (!(desc->flags & PATDNN_HOST_ONLY)) {
             st = upload_layer(h.get());
             if (st != PATDNN_OK) return st;
@@ -776,7 +866,7 @@ static ZeroRegion zero_need(const patdnn_config_t& c, const ConvShape& s, float*
     if (split && slices_fit(scratch, scratch_floats, c.ksplit, full)) return ZeroRegion{};   // stores only
     if (!s.pool) return split ? ZeroRegion{output, full} : ZeroRegion{};
     if (split) return ZeroRegion{scratch, full};
-    if (taps_filters(c.variant)) return ZeroRegion{};             // whole pooling windows in registers
+    if (taps_filters(c.variant) || extra_variant(c.variant) == kExtraSplit) return ZeroRegion{};    // whole pooling windows in registers
     return ZeroRegion{output, (size_t)s.n * s.c_out * (s.ho / 2) * (s.wo / 2)};
 }
 
@@ -1072,6 +1162,12 @@ static patdnn_status_t set_config(patdnn_handle_t h, const patdnn_config_t* cfg)
         h->cfg_tuned = false;
         return PATDNN_OK;
     }
+    if (extra_variant(cfg->variant) == kExtraSplit) {
+        if (!h->split) return fail(PATDNN_EUNSUPPORTED, "variant cannot run this layer");
+        h->cfg = patdnn_config_t{cfg->variant, 0, 0, 1};
+        h->cfg_tuned = false;
+        return PATDNN_OK;
+    }
     if (taps_filters(cfg->variant)) {
         if (!taps_fit_layer(h)) return fail(PATDNN_EUNSUPPORTED, "variant cannot run this layer");
         if (cfg->ck < 0 || cfg->waves < 0 || cfg->waves > kMaxTapWaves || cfg->ksplit < 0 || cfg->ksplit > 64)
@@ -1197,6 +1293,8 @@ static patdnn_status_t tune_ws(patdnn_handle_t h, const float* input, int32_t n,
                         cands.push_back(patdnn_config_t{variant_of_extra(filters == 8 ? kExtraTaps8 : kExtraTaps16), layout.first, waves, ks});
                 }
     if (h->L.depthwise) cands.push_back(patdnn_config_t{variant_of_extra(kExtraDepthwise), 0, 0, 1});
+    int rounds = 0, steps = 0, pixels = 0;
+    if (h->split && !taps_fit_layer(h) && split_cost(s, rounds, steps, pixels)) cands.push_back(patdnn_config_t{variant_of_extra(kExtraSplit), 0, 0, 1});
     cands.push_back(patdnn_config_t{PATDNN_VARIANT_FKW, 0, 0, 1});
 
     struct Event {

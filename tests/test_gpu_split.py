@@ -1,0 +1,167 @@
+"""GPU parity of fp32 layers on the binary16 matrix cores (csrc/kernel_split.hip) where it can go wrong: odd and
+even rows, strips, tiles over several images, remainders of channels and filters, every launch shape, both
+strides, pooled windows, inputs of all magnitudes, sums that are not finite - and where the library chooses it."""
+
+import ctypes
+
+import numpy as np
+import pytest
+
+from paper_2001_00138_amd import binding as B
+from paper_2001_00138_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+# 22 bits of each factor and fp32 sums: an error of about 2^-23 of each product, and sqrt(K) 2^-24 of the sum of
+# the terms' magnitudes; 1e-5 of the largest output is far above both
+TOL = 1e-5
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    B.lib()
+    return torch
+
+
+def _variant(name):
+    return {B.patdnn_variant_name(v): v for v in range(B.patdnn_num_variants())}[name]
+
+
+def _layer(rng, c_in, c_out, keep, stride=1, pad=1, scale=1.0):
+    lib = wl.pattern_library(wl.PATTERN_SEED)
+    ids = rng.integers(0, 8, (c_out, c_in), dtype=np.uint8)
+    mask = (rng.random((c_out, c_in)) < keep).astype(np.uint8)
+    wt = (rng.standard_normal((c_out, c_in, 3, 3)) * scale).astype(np.float32)
+    return (wt, ids, mask, lib), B.Layer(wt, ids, mask, lib, stride=stride, pad=pad)
+
+
+# c_in, c_out, n, h, w, stride, pad, keep, floats in front of the tensor
+CASES = [
+    (128, 64, 2, 14, 14, 1, 1, 0.9, 0),         # one block of 64 filters
+    (31, 65, 3, 17, 33, 1, 1, 1.0, 0),          # one more filter than a block, one channel short of a step, two strips
+    (33, 130, 2, 12, 34, 1, 0, 1.0, 0),         # two steps; pairs of pixels; a strip that is not full
+    (33, 130, 2, 12, 34, 1, 0, 1.0, 1),         # the same rows off their pairs
+    (160, 40, 5, 7, 7, 2, 1, 0.5, 0),           # tiles over several images
+    (128, 200, 1, 57, 41, 2, 1, 0.3, 0),
+    (96, 70, 2, 64, 64, 2, 0, 0.8, 0),
+    (64, 24, 2, 39, 13, 2, 1, 1.0, 0),          # narrow rows: the smallest tiles, for one block of filters
+    (40, 12, 9, 3, 3, 1, 1, 1.0, 0),
+    (48, 100, 7, 3, 3, 2, 0, 1.0, 0),           # one output pixel an image
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_split_kernel(torch, oracle, case):
+    from oracle import stack as ostack
+    c_in, c_out, n, h, w, stride, pad, keep, shift = case
+    rng = np.random.default_rng(c_in * 1000 + w)
+    data, L = _layer(rng, c_in, c_out, keep, stride, pad)
+    bias = rng.standard_normal(c_out).astype(np.float32)
+    x = rng.standard_normal((n, c_in, h, w)).astype(np.float32)
+    full = oracle.conv2d(*data, x, bias, stride=stride, pad=pad, relu=True, skip_removed=True)
+    L.set_config(_variant("split_f16"))
+    xt = torch.empty(x.size + shift, device="cuda")[shift:].view(x.shape)
+    xt.copy_(torch.from_numpy(x))
+    bt, guard = torch.from_numpy(bias).cuda(), 1024
+    for pool in (False, True):
+        ref = ostack.maxpool2x2(full) if pool else full
+        if 0 in ref.shape:
+            continue
+        print(f"  {case} pool={pool}", flush=True)
+        numel = int(np.prod(ref.shape))
+        buf = torch.full((numel + 2 * guard,), 777.0, device="cuda")
+        out = buf[guard:guard + numel].view(ref.shape)
+        L.conv2d_ws(xt, bt, out, relu=True, pool=pool)
+        assert bool((buf[:guard] == 777.0).all()) and bool((buf[guard + numel:] == 777.0).all())
+        assert float(np.abs(out.cpu().numpy().astype(np.float64) - ref).max() / np.abs(ref).max()) <= TOL
+    L.close()
+
+
+@pytest.mark.parametrize("inputs,weights", [(1e-40, 1.0), (1e-30, 1e-6), (1e30, 1e-20), (1.0, 1e30)])
+def test_magnitudes(torch, oracle, inputs, weights):
+    """Scales far from one, and inputs whose later channels are 10^4 times the first ones'."""
+    rng = np.random.default_rng(8)
+    data, L = _layer(rng, 96, 40, 0.6, 2, scale=weights)
+    x = (rng.standard_normal((2, 96, 19, 22)) * inputs).astype(np.float32)
+    x[:, 32:] *= np.float32(1e4) if inputs < 1e20 else np.float32(1)
+    ref = oracle.conv2d(*data, x, None, stride=2, skip_removed=True)
+    L.set_config(_variant("split_f16"))
+    got = L.conv2d(torch.from_numpy(x).cuda(), None, relu=False).cpu().numpy().astype(np.float64)
+    L.close()
+    assert 0 < np.abs(ref).max() < 3e38
+    # half a subnormal spacing for the result, and as much for each input
+    assert np.abs(got - ref).max() <= TOL * np.abs(ref).max() + 2.0 ** -149
+
+
+def test_small_values_beside_large_ones(torch, oracle):
+    """Images share tiles: one of inputs 10^5 times the others' costs these no more than their last bits."""
+    rng = np.random.default_rng(9)
+    data, L = _layer(rng, 64, 40, 1.0, 2)
+    x = rng.standard_normal((6, 64, 6, 6)).astype(np.float32)
+    x[2] *= np.float32(1e5)
+    ref = oracle.conv2d(*data, x, None, stride=2, skip_removed=True)
+    L.set_config(_variant("split_f16"))
+    got = L.conv2d(torch.from_numpy(x).cuda(), None, relu=False).cpu().numpy().astype(np.float64)
+    L.close()
+    for i in range(6):
+        assert np.abs(got[i] - ref[i]).max() <= TOL * np.abs(ref[i]).max(), i
+
+
+@pytest.mark.parametrize("c_out,h,stride,pool", [(70, 21, 2, False), (33, 20, 1, True), (130, 34, 1, False)])
+@pytest.mark.parametrize("share", [1e-4, 1e-2, 1.0])
+def test_not_finite_inputs(torch, c_out, h, stride, pool, share):
+    """Infinite and NaN inputs reach the outputs that the walk over the kept weights gives them, kept zeros
+    among the weights, and the others stay as they are."""
+    rng = np.random.default_rng(c_out)
+    data, _ = _layer(rng, 48, c_out, 0.6, stride)
+    data[0][:, 3] = 0
+    L = B.Layer(*data, stride=stride)
+    x = rng.standard_normal((3, 48, h, h + 2)).astype(np.float32)
+    kind = rng.random(x.shape)
+    x[kind < share] = np.nan
+    x[kind < 0.6 * share] = -np.inf
+    x[kind < 0.4 * share] = np.inf
+    got = {}
+    for name in ("fkw", "split_f16"):
+        L.set_config(_variant(name))
+        got[name] = L.conv2d_ws(torch.from_numpy(x).cuda(), None, relu=False, pool=pool).cpu().numpy()
+    L.close()
+    a, b = got["fkw"], got["split_f16"]
+    assert np.array_equal(np.isnan(a), np.isnan(b)) and np.array_equal(a[np.isinf(a)], b[np.isinf(a)])
+    ok = np.isfinite(a)
+    assert np.array_equal(ok, np.isfinite(b))
+    assert not ok.any() or np.abs(a[ok] - b[ok]).max() <= TOL * max(np.abs(a[ok]).max(), 1e-30)
+
+
+# c_in, c_out, side, n, stride, keep; what is chosen
+CHOICES = [((128, 128, 56, 8, 2, 1 / 3.6), "split_f16"), ((64, 64, 56, 8, 2, 1 / 3.6), "t_g16_p4x1_s2_x16_th"),
+           ((64, 64, 56, 2, 2, 0.5), "split_f16"), ((328, 125, 72, 47, 1, 0.5), "split_f16"), ((64, 64, 112, 32, 1, 1.0), "split_f16"),
+           ((128, 128, 112, 16, 1, 1 / 3.6), None)]
+
+
+@pytest.mark.parametrize("shape,name", CHOICES)
+def test_choice_is_no_less_exact(torch, shape, name):
+    """The library takes the kernel where its error against 64 bits is no larger than that of the kernel it stands
+    in for (2 % for the draw of the numbers), and not where the tap-product kernel is chosen."""
+    c_in, c_out, side, n, stride, keep = shape
+    rng = np.random.default_rng(side)
+    (wt, ids, mask, lib), L = _layer(rng, c_in, c_out, keep, stride)
+    cfg = B.Config()
+    choice = B.lib().patdnn_internal_choice
+    choice.argtypes = [ctypes.c_void_p] + [ctypes.c_int32] * 3 + [ctypes.c_size_t, ctypes.c_void_p]
+    assert choice(L.handle, n, side, side, 0, ctypes.byref(cfg)) == 0
+    chosen = B.patdnn_variant_name(cfg.variant)
+    assert chosen == name if name else chosen != "split_f16"
+    if chosen == "split_f16":
+        x = torch.randn((1, c_in, side, side), device="cuda", generator=torch.Generator("cuda").manual_seed(1)).clamp_(min=0)
+        bits = (lib.astype(np.int64)[ids][..., None] >> np.arange(9)) & 1
+        dense = torch.from_numpy((wt.reshape(c_out, c_in, 9) * bits * mask[..., None]).reshape(c_out, -1).astype(np.float64)).cuda()
+        ref = (dense @ torch.nn.functional.unfold(x.double(), 3, padding=1, stride=stride)).reshape(L.output_shape(1, side, side))
+        err = {}
+        for v in ("fkw", "split_f16"):
+            L.set_config(_variant(v))
+            err[v] = float((L.conv2d(x, None, relu=False).double() - ref).norm() / ref.norm())
+        assert err["split_f16"] <= 1.02 * err["fkw"], err
+    L.close()
