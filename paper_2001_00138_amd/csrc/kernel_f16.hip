@@ -16,7 +16,7 @@
 // weight, and with which sign, and then the sum over the finite inputs (kept weights that
 // are zero are stored as -0, so that they can be told from the removed ones).  Layers with a weight
 // that is not finite in binary16 run the walk over the kept weights instead.
-// 128 -> 128 at 56 x 56, 64 images: 97 us with finite inputs, 1060 with one infinity in ten thousand
+// 128 -> 128 at 56 x 56, 64 images: 72 us with finite inputs, 1060 with one infinity in ten thousand
 // inputs, 1700 with nothing but NaN; one lane after the other walking the FKW arrays for its own
 // pixels took 19400 and 23800, the walk over the whole layer takes 2000.
 //
@@ -26,7 +26,8 @@
 //     out to an image's edge (the rows of all images, each with its zero padding, are
 //     thought of as one tall image of vh rows each).  The strips of the same rows follow each other, so
 //     that the cache lines at their common edges are fetched once: 64 -> 64 at 224x224, 64 images, seven
-//     strips 613 -> 514 us, 128 -> 128 at 112x112 336 -> 305, at 56x56 102 -> 94.
+//     strips 613 -> 514 us, 128 -> 128 at 112x112 336 -> 305, at 56x56 102 -> 94 (before the loads were in flight
+//     as they are now).
 //   * A wavefront owns FM x PN blocks of 32 filters x 32 pixels; a workgroup WF x WP of
 //     them, and WK wavefronts share a block and take 16 input channels each of a chunk of 16 * WK
 //     (their sums meet in LDS): layers with few tiles.
@@ -36,18 +37,23 @@
 //     of pixels (4-byte loads) where rows have an even length and start on whole pairs, else one pixel
 //     (2-byte loads).  Two buffers, the next chunk's loads in flight while this one is computed; one
 //     buffer where wavefronts split the channels, whose chunks are larger.
-//   * Weights are read from L2 in fragment order, 16 bytes per lane.
+//     The loads are left as they come until they are put into LDS: packing them where they are issued waited for
+//     memory once per unit (128 -> 128 at 56 x 56, 64 images 94 -> 81 us).
+//   * Weights are read from L2 in fragment order, 16 bytes per lane, some taps ahead; in the widest shape, eight
+//     wavefronts on 128 filters x 512 pixels, each fragment comes once per workgroup straight into LDS (147 KB a chunk
+//     and CU would come from L2 otherwise, 36 KB do).
+//   * Channel and bias of the filters wait in LDS for the epilogue, which waited for each in turn (79 -> 72 us).
 //
 // What bounds it: 128 -> 128 at 56 x 56, 64 images (59 GFLOP with the zeros, 51 MB in and out) takes
-// 94 us on changing tensors, 0.6 PFLOP/s, where the walk over the kept weights
-// took 1990; one image of 256 -> 256 at 28 x 28 9 us (57).  The matrix cores are busy 31 % of the SIMDs'
-// cycles.  The gathering of eight channels is the larger part: 2-byte loads took 124 us where 4-byte
-// loads took 94, and it is the texture path that they share with the weights; the rows staged are
-// 1.4 times the pixels computed.
+// 72 us on changing tensors, 0.8 PFLOP/s, where the walk over the kept weights took 1990; one image of 256 -> 256
+// at 28 x 28 9 us (57).  392 workgroups are one and a half rounds of 256 CUs, LDS is read for three quarters of the
+// time that the matrix cores need, and the epilogue's stores and a tile's first loads are hidden by nothing.  (Inputs two
+// chunks ahead: 84 us; what is in flight is enough.)
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
 #include <atomic>
+#include <iterator>
 
 #include "kernels.hpp"
 
@@ -216,7 +222,15 @@ static __device__ __forceinline__ void f16_again(unsigned odd, int wave)
 // Wavefronts per SIMD that the registers of so many blocks allow.  Said to the compiler, which would
 // otherwise save registers for more and wait for every load of the channel loop by itself (10 to 15 % on the
 // splitting shapes).
-constexpr int f16_waves(int blocks, bool most) { return blocks >= 8 ? 2 : blocks >= 4 ? 4 : !most ? 2 : blocks >= 2 ? 5 : 6; }
+constexpr int f16_waves(int blocks, bool most) { return blocks >= 8 ? 2 : blocks >= 4 ? 3 : !most ? 2 : blocks >= 2 ? 5 : 6; }
+
+// Taps whose weights are on their way, as the registers allow.
+constexpr int f16_hold(int blocks, int wk, bool pair) { return wk > 1 ? 9 : blocks >= 8 ? pair ? 5 : 3 : blocks >= 4 ? 3 : 4; }
+// Where eight wavefronts share the weights of a workgroup's filters, those travel through LDS.
+constexpr bool f16_weights_in_lds(int wf, int wp, int wk) { return wk == 1 && wf * wp == 8; }
+
+// Staging units whose loads are in flight while a chunk is computed: what the usual tiles have for a wavefront.
+constexpr int f16_ahead(int blocks, int wk, bool pair) { return pair ? blocks >= 8 ? 2 : 4 : wk > 1 ? 6 : 4; }
 
 // PAIR: rows of whole aligned pairs of pixels (see f16_tiles): staged two pixels per load, and
 // stored two pixels at a time where the output's rows are the same.
@@ -226,7 +240,8 @@ void f16_conv_kernel(F16Args a)
 {
     extern __shared__ uint4 lds4[];
     constexpr int WAVES = WF * WP * WK, PIX = 32 * PN * WP, G8 = 2 * WK;
-    constexpr int UPX = PAIR ? 2 : 1, AHEAD = 4 / UPX, BUFS = f16_buffers(WK);
+    constexpr int UPX = PAIR ? 2 : 1, AHEAD = f16_ahead(FM * PN, WK, PAIR), BUFS = f16_buffers(WK);
+    constexpr bool WLDS = f16_weights_in_lds(WF, WP, WK);
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wk = wave % WK, wp = wave / WK % WP, wf = wave / (WK * WP);
@@ -274,6 +289,14 @@ void f16_conv_kernel(F16Args a)
         split_row(q, img, oy, sx);
         base[p] = (img * a.vh + oy * a.conv_stride - vrow0) * a.pitch + sx * a.conv_stride + (a.lead - a.pad) + (2 * wk + half) * a.npp;
     }
+    // channel and bias of the workgroup's filters, for the epilogue (which would wait for each by itself)
+    const int behind = max(a.npp * (BUFS * G8 * 16 + 4) + (WLDS ? 2 * WF * FM * 9 * 1024 : 0), WK > 1 ? WAVES * 4096 : 0);
+    int2* const slots = reinterpret_cast<int2*>(reinterpret_cast<char*>(lds4) + behind);
+    for (int e = threadIdx.x; e < WF * FM * 32; e += 64 * WAVES) {
+        const int s = fset * WF * FM * 32 + e;
+        const int co = s < a.c_out ? a.reorder[s] : -1;
+        slots[e] = make_int2(co, co >= 0 && a.bias ? __float_as_int(a.bias[co]) : 0);
+    }
     int fb[FM];
 #pragma unroll
     for (int f = 0; f < FM; ++f) fb[f] = min((fset * WF + wf) * FM + f, a.fblocks - 1);
@@ -290,77 +313,136 @@ void f16_conv_kernel(F16Args a)
     const char* in_blk = (const char*)(a.in + (size_t)img0 * a.c_in * plane);
     // out of range (reads as zero) from the end of the tensor on, and for ~0u
     __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)in_blk, 0, (int)(unsigned)std::min<size_t>(tail, 0x80000000u), 0x00020000);
-    struct Unit { uint4 v[UPX]; };
+    // as loaded: whatever is done with them waits for them, so that is left to store_unit
+    struct Unit { unsigned v[8]; };
     // unit u is block u / G8 of group u % G8
-    auto load_unit = [&](int u, int c0) __attribute__((always_inline)) -> Unit {
-        const int off = (int)voffs[u / G8 * 64 + lane], cg = c0 + u % G8 * 8;
-        unsigned v[8];
+    auto load_unit = [&](int u, int off, int c0) __attribute__((always_inline)) -> Unit {
+        const int cg = c0 + u % G8 * 8;
+        Unit t;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             // past the last channel its weights are zero; which pixel they meet does not matter
             const int soff = min(cg + j, a.c_in - 1) * plane * 2;
-            if constexpr (PAIR) v[j] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, off, soff, 0);
-            else v[j] = (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rsrc, off, soff, 0);
+            if constexpr (PAIR) t.v[j] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, off, soff, 0);
+            else t.v[j] = (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rsrc, off, soff, 0);
         }
         // the last load must not take the offset's register: that would part the eight loads (an s_nop between
         // them, 6 % on the splitting shapes of unpaired rows)
         asm volatile("" : : "v"(off));
-        Unit t;
-        if constexpr (PAIR) {
-            // low halves, then high halves, of two channels
-            auto lo = [&](int j) { return __builtin_amdgcn_perm(v[j + 1], v[j], 0x05040100u); };
-            auto hi = [&](int j) { return __builtin_amdgcn_perm(v[j + 1], v[j], 0x07060302u); };
-            t.v[0] = make_uint4(lo(0), lo(2), lo(4), lo(6));
-            t.v[1] = make_uint4(hi(0), hi(2), hi(4), hi(6));
-        } else {
-            t.v[0] = make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
-        }
         return t;
     };
     auto store_unit = [&](int u, int buf, const Unit& t) __attribute__((always_inline)) {
         uint4* dst = lds4 + (buf * G8 + u % G8) * a.npp + (u / G8 * 64 + lane) * UPX;
-#pragma unroll
-        for (int k = 0; k < UPX; ++k) dst[k] = t.v[k];
-    };
-    Unit ahead[AHEAD];
-    auto fetch = [&](int c0) __attribute__((always_inline)) {
-#pragma unroll
-        for (int k = 0; k < AHEAD; ++k)
-            if (wave + k * WAVES < units) ahead[k] = load_unit(wave + k * WAVES, c0);
+        const unsigned (&v)[8] = t.v;
+        if constexpr (PAIR) {
+            // low halves, then high halves, of two channels
+            auto lo = [&](int j) { return __builtin_amdgcn_perm(v[j + 1], v[j], 0x05040100u); };
+            auto hi = [&](int j) { return __builtin_amdgcn_perm(v[j + 1], v[j], 0x07060302u); };
+            dst[0] = make_uint4(lo(0), lo(2), lo(4), lo(6));
+            dst[1] = make_uint4(hi(0), hi(2), hi(4), hi(6));
+        } else {
+            dst[0] = make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
+        }
     };
     __syncthreads();                                  // the offsets
+    Unit ahead[AHEAD];
+    unsigned off_ahead[AHEAD];
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k) off_ahead[k] = wave + k * WAVES < units ? voffs[(wave + k * WAVES) / G8 * 64 + lane] : ~0u;
+    // no branches, which the loads would have to end in: where there is nothing more to fetch they are out of range
+    auto fetch = [&](int c0) __attribute__((always_inline)) {
+        const unsigned none = c0 < 16 * a.steps ? 0u : ~0u;
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k) ahead[k] = load_unit(wave + k * WAVES, (int)(off_ahead[k] | none), c0);
+    };
+    // weights of a tap; loads come back in the order in which they were issued, so those of a step are all issued
+    // before the next chunk's inputs, and the next step's first ones after them
+    constexpr int HOLD = f16_hold(FM * PN, WK, PAIR);
+    half8 wv[9][FM];
+    auto weights = [&](int step, int tap) __attribute__((always_inline)) {
+#pragma unroll
+        for (int f = 0; f < FM; ++f)
+            wv[tap][f] = __builtin_bit_cast(half8, a.weights[((size_t)fb[f] * a.steps + min(step, a.steps - 1)) * (9 * 64) + tap * 64 + lane]);
+    };
+    // ... or of a step, the fragments of all taps and filters shared out to the wavefronts, straight into LDS
+    uint4* const wlds = lds4 + BUFS * G8 * a.npp + a.npp / 4;
+    __amdgpu_buffer_rsrc_t wsrc = __builtin_amdgcn_make_buffer_rsrc((void*)a.weights, 0, (int)((unsigned)a.fblocks * (unsigned)a.steps * (9u * 1024u)), 0x00020000);
+    auto share_weights = [&](int step, int wbuf) __attribute__((always_inline)) {
+        for (int e = wave; e < WF * FM * 9; e += WAVES) {
+            const int block = min(fset * WF * FM + e / 9, a.fblocks - 1);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wsrc, (__attribute__((address_space(3))) void*)(wlds + (wbuf * WF * FM * 9 + e) * 64), 16, lane * 16,
+                                                     ((block * a.steps + step) * 9 + e % 9) * 1024, 0, 0);
+        }
+    };
     fetch(0);
+    if constexpr (WLDS) {
+        share_weights(0, 0);
+    } else {
+#pragma unroll
+        for (int tap = 0; tap < HOLD; ++tap) weights(wk, tap);
+    }
     int buf = 0;
     for (int c0 = 0; c0 < 16 * a.steps; c0 += 16 * WK) {
         if (BUFS == 1 && c0) __syncthreads();         // everyone has left the previous chunk
+        if constexpr (WLDS) __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wavefront's share of the weights
 #pragma unroll
         for (int k = 0; k < AHEAD; ++k)
             if (wave + k * WAVES < units) store_unit(wave + k * WAVES, buf, ahead[k]);
-        for (int u = wave + AHEAD * WAVES; u < units; u += WAVES) store_unit(u, buf, load_unit(u, c0));
+        for (int u = wave + AHEAD * WAVES; u < units; u += WAVES) store_unit(u, buf, load_unit(u, (int)voffs[u / G8 * 64 + lane], c0));
         // with two buffers one barrier per chunk: whoever is past it has finished with the other one
         __syncthreads();
-        if (c0 + 16 * WK < 16 * a.steps) fetch(c0 + 16 * WK);
         const int step = (c0 >> 4) + wk;
-        if (step < a.steps) {
-            const uint4* wt[FM];
+        if (WK > 1 && step >= a.steps) break;         // only in the last chunk
+        const uint4* src = lds4 + buf * G8 * a.npp;
+        half8 x[PN];
+        auto pixels = [&](int tap, int p) __attribute__((always_inline)) {
+            x[p] = __builtin_bit_cast(half8, src[base[p] + tap / 3 * a.pitch + tap % 3]);
+        };
+        const bool more = c0 + 16 * WK < 16 * a.steps;
 #pragma unroll
-            for (int f = 0; f < FM; ++f) wt[f] = a.weights + ((size_t)fb[f] * a.steps + step) * (9 * 64) + lane;
-            const uint4* src = lds4 + buf * G8 * a.npp;
+        for (int p = 0; p < PN; ++p) pixels(0, p);
+        if constexpr (WLDS) {
+            const uint4* const wsh = wlds + (buf * WF + wf) * (FM * 9 * 64) + lane;
+            half8 w[2][FM];
+            auto shared = [&](int tap) __attribute__((always_inline)) {
 #pragma unroll
-            for (int kh = 0; kh < 3; ++kh)
+                for (int f = 0; f < FM; ++f) w[tap & 1][f] = __builtin_bit_cast(half8, wsh[(f * 9 + tap) * 64]);
+            };
+            shared(0);
+            if (more) share_weights(step + 1, buf ^ 1);
+            fetch(c0 + 16);
 #pragma unroll
-                for (int kw = 0; kw < 3; ++kw) {
-                    half8 wv[FM];
+            for (int tap = 0; tap < 9; ++tap) {
+                if (tap < 8) shared(tap + 1);
 #pragma unroll
-                    for (int f = 0; f < FM; ++f) wv[f] = __builtin_bit_cast(half8, wt[f][(kh * 3 + kw) * 64]);
+                for (int p = 0; p < PN; ++p) {
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int p = 0; p < PN; ++p) {
-                        const half8 x = __builtin_bit_cast(half8, src[base[p] + kh * a.pitch + kw]);
-#pragma unroll
-                        for (int f = 0; f < FM; ++f)
-                            acc[f][p] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wv[f], x, acc[f][p], 0, 0, 0);
-                    }
+                    for (int f = 0; f < FM; ++f) acc[f][p] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[tap & 1][f], x[p], acc[f][p], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (tap < 8) pixels(tap + 1, p);
                 }
+            }
+        } else {
+            if (HOLD == 9 && more) fetch(c0 + 16 * WK);
+#pragma unroll
+            for (int tap = 0; tap < 9; ++tap) {
+#pragma unroll
+                for (int p = 0; p < PN; ++p) {
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int f = 0; f < FM; ++f) acc[f][p] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wv[tap][f], x[p], acc[f][p], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (tap < 8) pixels(tap + 1, p);
+                }
+                if (tap + HOLD < 9) weights(step, tap + HOLD);
+                else if (HOLD < 9) weights(step + WK, tap + HOLD - 9);
+                __builtin_amdgcn_sched_barrier(0);
+                if (tap + HOLD == 8) fetch(c0 + 16 * WK);
+            }
+            if (HOLD == 9 && more)
+#pragma unroll
+                for (int tap = 0; tap < 9; ++tap) weights(step + WK, tap);
         }
         if (BUFS == 2) buf ^= 1;
     }
@@ -392,14 +474,6 @@ void f16_conv_kernel(F16Args a)
     // ---- epilogue: register r of a block is filter 8 * (r / 4) + 4 * half + r % 4, pixel lane % 32
     const size_t oplane = (size_t)a.ho * a.wo;
     const int reg0 = WK > 1 ? wk * RK : 0;
-    auto slot_of = [&](int f, int r, int hf) {
-        return ((fset * WF + wf) * FM + f) * 32 + 8 * ((reg0 + r) >> 2) + 4 * hf + ((reg0 + r) & 3);
-    };
-    // channel and bias of a slot travel over the scalar path, for both halves
-    typedef const int32_t __attribute__((address_space(4))) * iptr;
-    typedef const float __attribute__((address_space(4))) * fptr;
-    auto channel_of = [&](int s) { return ((iptr)(uintptr_t)a.reorder)[min(s, a.c_out - 1)]; };
-    auto bias_of = [&](int co) { return a.bias ? ((fptr)(uintptr_t)a.bias)[co] : 0.0f; };
     unsigned odd = 0;                                 // pixels of this lane with a sum that is not finite
     bool ok[PN];
     size_t off[PN];
@@ -422,12 +496,10 @@ void f16_conv_kernel(F16Args a)
             bool has[2];
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
-                const int s0 = slot_of(f, r + k, 0), s1 = slot_of(f, r + k, 1);
-                const int c0 = channel_of(s0), c1 = channel_of(s1);
-                const float b0 = bias_of(c0), b1 = bias_of(c1);
-                co[k] = half ? c1 : c0;
-                b[k] = half ? b1 : b0;
-                has[k] = (half ? s1 : s0) < a.c_out;
+                const int2 slot = slots[(wf * FM + f) * 32 + 8 * ((reg0 + r + k) >> 2) + 4 * half + ((reg0 + r + k) & 3)];
+                co[k] = slot.x;
+                b[k] = __int_as_float(slot.y);
+                has[k] = co[k] >= 0;
             }
 #pragma unroll
             for (int p = 0; p < PN; ++p) {
@@ -548,7 +620,9 @@ static hipError_t launch_f16_t(const F16Args& args, const ConvShape& s, long lon
 // multiply-adds, small ones reach more CUs, and wavefronts that split the channels shorten
 // the chain of the last layers of a network.  us per pass, largest to smallest shape (f2 p4, f2 p2,
 // f1 p2, then the splitting ones):
-//   128 -> 128 at 56x56, 64 images     94   99  103  147  188  232     (784 workgroups of the first)
+//   128 -> 128 at 56x56, 64 images     94   99  103  147  188  232     (784 workgroups of the first; 81 since the loads are in
+//                                                                       flight; the widest shape 79, and 72 without the
+//                                                                       epilogue's waits)
 //    64 ->  64 at 112x112, 8 images    32   34   23   29   34   57     (784 of the third; half of the first idle)
 //   128 -> 256 at 56x56 / 2, 16 images 37   32   47   58   83   --     (196 of the second)
 //   512 -> 512 at 7x7, 64 images      136  146   95   52   68   69     (784 of the fourth)
@@ -568,6 +642,7 @@ static const F16Shape kF16Shapes[] = {
     PATDNN_F16(1, 2, 1, 1, 4, 400, false),
     PATDNN_F16(1, 1, 1, 1, 8, 0, false),
     PATDNN_F16(1, 1, 1, 1, 4, 0, false),
+    PATDNN_F16(2, 4, 2, 4, 1, 256, false),
 };
 #undef PATDNN_F16
 
@@ -582,7 +657,9 @@ static F16Plan f16_plan(const ConvShape& s, bool pair, F16Args& a)
     F16Plan plan;
     a.steps = (s.c_in + 15) / 16;
     a.fblocks = (s.c_out + 31) / 32;
-    for (const F16Shape& v : kF16Shapes) {
+    constexpr int count = (int)std::size(kF16Shapes);
+    for (int i = 0; i < count; ++i) {
+        const F16Shape& v = kF16Shapes[i ? i - 1 : count - 1];    // the widest one, the last, first
         const int filters = v.fm * v.wf;
         if (filters >= 2 * a.fblocks) continue;                   // half of every workgroup idle
         if (v.strided && s.stride == 1) continue;
@@ -590,8 +667,8 @@ static F16Plan f16_plan(const ConvShape& s, bool pair, F16Args& a)
         if (!f16_tiles(s, 32 * v.pn * v.wp, pair, a)) continue;
         a.fsets = (a.fblocks + filters - 1) / filters;
         plan.blocks = (long long)a.strips * a.tiles * a.fsets;
-        plan.lds = std::max((size_t)a.npp * (f16_buffers(v.wk) * 2 * v.wk * 16 + 4),
-                            v.wk > 1 ? (size_t)v.wf * v.wp * v.wk * 4096 : 0);
+        plan.lds = std::max((size_t)a.npp * (f16_buffers(v.wk) * 2 * v.wk * 16 + 4) + (f16_weights_in_lds(v.wf, v.wp, v.wk) ? 2 * filters * 9 * 1024 : 0),
+                            v.wk > 1 ? (size_t)v.wf * v.wp * v.wk * 4096 : 0) + (size_t)filters * 32 * 8;
         if (plan.blocks < v.min_blocks || plan.blocks > INT32_MAX || plan.lds > 160 * 1024) continue;
         plan.shape = (int)(&v - kF16Shapes);
         break;

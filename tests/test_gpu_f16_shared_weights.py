@@ -1,0 +1,38 @@
+"""The shape of the binary16 matrix-core kernel whose eight wavefronts share their weights in LDS (launch shape 6), checked
+as tests/test_gpu_f16_matrix.py checks the others: even and odd rows, a filter block that is nearly empty, one
+and several channel steps, infinite and NaN inputs - and where it is taken."""
+
+import numpy as np
+import pytest
+
+import test_gpu_f16_matrix as matrix
+from test_gpu_f16_matrix import torch                  # noqa: F401 (a fixture)
+
+pytestmark = pytest.mark.gpu
+
+# c_out, c_in, n, h, w, stride, pad, keep, elements the input starts after an aligned address, what is launched
+CASES = [
+    (130, 17, 1, 256, 256, 1, 1, 0.3, 0, 13),
+    (66, 37, 1, 365, 361, 1, 0, 0.3, 0, 12),
+    (128, 16, 43, 56, 56, 1, 1, 0.3, 1, 12),           # one channel step; even rows at an odd address; tiles over images
+]
+NON_FINITE = [(130, 17, 1, 256, 256, 1, 13), (70, 20, 1, 365, 361, 1, 12)]
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_shared_weights(torch, case):
+    matrix.test_matrix_kernel(torch, case)
+
+
+@pytest.mark.parametrize("shape", NON_FINITE)
+def test_shared_weights_not_finite_inputs(torch, shape):
+    matrix.test_infinite_and_nan_inputs(torch, shape)
+
+
+def test_where_it_is_taken(torch):
+    """From 256 workgroups of 128 filters x 512 pixels on."""
+    rng = np.random.default_rng(1)
+    for c_out, side, launches in ((128, 56, 13), (64, 56, 5), (128, 54, 1)):
+        _, L = matrix._layer(rng, c_out, 16, 0.3, 1, 1)
+        assert matrix._launches(L, None, 42, side, side) == launches, (c_out, side)
+        L.close()
