@@ -80,13 +80,19 @@ __device__ __forceinline__ void ldv(const __half* p, float* v)
         ld4(p, v[0], v[1], v[2], v[3]);
     }
 }
-template <int NP>
+// STREAM: stores that do not stay in the L2s
+template <bool STREAM, int NP>
 __device__ __forceinline__ void stv(float* p, const float (&v)[NP])
 {
+    typedef float float4s __attribute__((ext_vector_type(4)));
 #pragma unroll
-    for (int k = 0; k < NP; k += 4) *reinterpret_cast<float4*>(p + k) = make_float4(v[k], v[k + 1], v[k + 2], v[k + 3]);
+    for (int k = 0; k < NP; k += 4) {
+        const float4s q = {v[k], v[k + 1], v[k + 2], v[k + 3]};
+        if constexpr (STREAM) __builtin_nontemporal_store(q, reinterpret_cast<float4s*>(p + k));
+        else *reinterpret_cast<float4s*>(p + k) = q;
+    }
 }
-template <int NP>
+template <bool STREAM, int NP>
 __device__ __forceinline__ void stv(__half* p, const float (&v)[NP])
 {
     unsigned w[NP / 2];
@@ -101,7 +107,7 @@ __device__ __forceinline__ void stv(__half* p, const float (&v)[NP])
 
 // S: stride.  NP: outputs per lane (4, or 8 where the rows allow and the launcher finds it faster).  VEC: rows start aligned to NP elements (w % NP == 0,
 // aligned base) -> vector loads.  VST: output rows aligned to NP elements -> one vector store.
-template <int S, int NP, bool VEC, bool VST, class T>
+template <int S, int NP, bool VEC, bool VST, class T, bool STREAM>
 __global__ __launch_bounds__(256) void dw_conv_kernel(DwArgs<T> a)
 {
     constexpr int NC = (NP - 1) * S + 3;           // input columns under NP outputs
@@ -205,7 +211,7 @@ __global__ __launch_bounds__(256) void dw_conv_kernel(DwArgs<T> a)
     }
     T* dst = a.out + (((size_t)n * a.c + co) * a.ho + oy) * (size_t)a.wo + ox0;
     if constexpr (VST) {
-        stv<NP>(dst, acc);
+        stv<STREAM, NP>(dst, acc);
     } else {
 #pragma unroll
         for (int i = 0; i < NP; ++i)
@@ -407,20 +413,25 @@ static hipError_t launch_dw_t(const DevFkw& f, const T* weights, const ConvShape
     // stride 2, binary16: 11.0 us, 11.3 with planes in LDS)
     if (!vec && launch_dw_planes<T>(f, s, in, bias, out, stream)) return hipGetLastError();
     const dim3 grid((unsigned)blocks), block(256);
-#define PATDNN_DW_LAUNCH(S, V, W) hipLaunchKernelGGL((dw_conv_kernel<S, 4, V, W, T>), grid, block, 0, stream, a)
-    if (wide) {
-        if (s.stride == 1) hipLaunchKernelGGL((dw_conv_kernel<1, 8, true, true, T>), grid, block, 0, stream, a);
-        else hipLaunchKernelGGL((dw_conv_kernel<2, 8, true, true, T>), grid, block, 0, stream, a);
-    } else if (s.stride == 1) {
-        if (vec && vst) PATDNN_DW_LAUNCH(1, true, true);
-        else if (vec) PATDNN_DW_LAUNCH(1, true, false);
-        else if (vst) PATDNN_DW_LAUNCH(1, false, true);
-        else PATDNN_DW_LAUNCH(1, false, false);
+    // fp32 outputs beyond half of the 32 MB that the L2s hold leave nothing there, and the inputs more room: 144 channels of
+    // 56x56, 64 images 64.4 -> 60.4 us, 96 of 112x112, 32 images 84 -> 80, 144 of 112x112 / 2, 64 images 122 -> 119, 16 images of
+    // the first (29 MB) 15.5 -> 14.5
+    const bool stream_out = sizeof(T) == 4 && (size_t)s.n * s.c_out * s.ho * s.wo * sizeof(T) > ((size_t)16 << 20);
+#define PATDNN_DW_LAUNCH(S, NP, V, W) \
+    if (W && stream_out) hipLaunchKernelGGL((dw_conv_kernel<S, NP, V, W, T, W && sizeof(T) == 4>), grid, block, 0, stream, a); \
+    else hipLaunchKernelGGL((dw_conv_kernel<S, NP, V, W, T, false>), grid, block, 0, stream, a)
+    if (wide && s.stride == 1) { PATDNN_DW_LAUNCH(1, 8, true, true); }
+    else if (wide) { PATDNN_DW_LAUNCH(2, 8, true, true); }
+    else if (s.stride == 1) {
+        if (vec && vst) { PATDNN_DW_LAUNCH(1, 4, true, true); }
+        else if (vec) { PATDNN_DW_LAUNCH(1, 4, true, false); }
+        else if (vst) { PATDNN_DW_LAUNCH(1, 4, false, true); }
+        else { PATDNN_DW_LAUNCH(1, 4, false, false); }
     } else {
-        if (vec && vst) PATDNN_DW_LAUNCH(2, true, true);
-        else if (vec) PATDNN_DW_LAUNCH(2, true, false);
-        else if (vst) PATDNN_DW_LAUNCH(2, false, true);
-        else PATDNN_DW_LAUNCH(2, false, false);
+        if (vec && vst) { PATDNN_DW_LAUNCH(2, 4, true, true); }
+        else if (vec) { PATDNN_DW_LAUNCH(2, 4, true, false); }
+        else if (vst) { PATDNN_DW_LAUNCH(2, 4, false, true); }
+        else { PATDNN_DW_LAUNCH(2, 4, false, false); }
     }
 #undef PATDNN_DW_LAUNCH
     return hipGetLastError();
