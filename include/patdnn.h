@@ -255,6 +255,9 @@ patdnn_status_t patdnn_layout_stats(patdnn_handle_t h, patdnn_stats_t* out);
  *                           "taps_f8", "taps_f16": tap-product kernel on the matrix cores in
  *                           fp32 (stride 1, pruned layers), 8 or 16 filters per wavefront; `ck` up
  *                           to 160 channels, `waves` up to 16
+ *                           "split_f16": pruned layers in fp32 on the binary16 matrix cores
+ *                           "dense_mfma": dense layers of up to four input channels on the
+ *                           fp32 matrix cores
  * variant < 0 (the state of a new handle): the library chooses at every call, by an estimate of
  * the candidates' times at this input size; a choice that splits the input channels is made
  * only where the call's workspace holds one partial sum per slice (patdnn_workspace_floats() for

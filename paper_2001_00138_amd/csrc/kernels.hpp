@@ -153,6 +153,11 @@ size_t split_expanded_halves(int32_t c_in, int32_t c_out);
 // Fills `out` (split_expanded_halves, zeroed) from the FKW arrays and split_filters.
 hipError_t launch_split_expand(const DevFkw& f, int32_t c_in, int32_t c_out, void* out, hipStream_t stream);
 
+// Dense layers of up to so many input channels on the fp32 matrix cores (kernel_dense.hip); weights finite.
+constexpr int kDenseChannels = 4;
+bool dense_fits(const ConvShape& s);
+hipError_t launch_dense(const DevFkw& f, const ConvShape& s, const float* in, const float* bias, float* out, hipStream_t stream);
+
 // ---------------------------------------------------------------------------
 // Tiled kernels: compile-time geometry per variant, run-time launch parameters.
 // ---------------------------------------------------------------------------

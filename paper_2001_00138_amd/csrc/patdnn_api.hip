@@ -85,6 +85,7 @@ struct TapsOnDevice {
 struct patdnn_layer {
     LayerHost L;
     bool on_device = false;
+    bool dense_mfma = false;                               // the kernel of dense layers of few channels runs this one
     bool split = false;                                    // the weights as pairs of binary16 numbers exist
     int device = -1;
     DevFkw dfkw;
@@ -193,10 +194,10 @@ bool variant_selectable(const patdnn_layer* h, const TiledVariant& v)
 }
 
 // Variant numbers: 0 the FKW walk, 1..T the tiled variants, then the kernels below.
-enum ExtraVariant { kExtraDepthwise = 0, kExtraNoopt, kExtraCsr, kExtraTaps8, kExtraTaps16, kExtraSplit, kNumExtra };
+enum ExtraVariant { kExtraDepthwise = 0, kExtraNoopt, kExtraCsr, kExtraTaps8, kExtraTaps16, kExtraSplit, kExtraDense, kNumExtra };
 int extra_variant(int variant) { return variant - 1 - num_tiled_variants(); }     // < 0: not one
 int variant_of_extra(int extra) { return 1 + num_tiled_variants() + extra; }
-const char* const kExtraNames[kNumExtra] = {"dw_p1x4", "noopt", "csr", "taps_f8", "taps_f16", "split_f16"};
+const char* const kExtraNames[kNumExtra] = {"dw_p1x4", "noopt", "csr", "taps_f8", "taps_f16", "split_f16", "dense_mfma"};
 // filters per wavefront of a tap-product variant, 0 for any other
 int taps_filters(int variant)
 {
@@ -428,6 +429,12 @@ patdnn_status_t run_config(patdnn_layer* h, const patdnn_config_t& c, const Conv
         hipError_t e = launch_split(h->dfkw, s, in, bias, out, stream);
         return e == hipSuccess ? PATDNN_OK : hip_fail(e, "launching the split kernel");
     }
+    if (extra_variant(c.variant) == kExtraDense) {
+        if (!h->dense_mfma) return fail(PATDNN_EUNSUPPORTED, "variant cannot run this layer");
+        if (!dense_fits(s)) return fail(PATDNN_EUNSUPPORTED, "input too large for the dense kernel");
+        hipError_t e = launch_dense(h->dfkw, s, in, bias, out, stream);
+        return e == hipSuccess ? PATDNN_OK : hip_fail(e, "launching the dense kernel");
+    }
     if (const int filters = taps_filters(c.variant)) {
         auto it = h->taps.find(c.ck);
         if (it == h->taps.end()) return fail(PATDNN_EUNSUPPORTED, "no layout for this ck: choose it with patdnn_set_config");
@@ -610,6 +617,16 @@ bool split_layer(const LayerHost& L)
     return split_expanded_halves(L.desc.c_in, L.desc.c_out) <= kMaxExpandedHalves && split_exponents(L, exponents);
 }
 
+// Dense layers of few channels: filters are stored in the order of their channels there, and zero padding, which the
+// matrix cores multiply, must not meet a weight that is not finite (the walk leaves it out).
+bool dense_layer(const LayerHost& L)
+{
+    if (!L.dense || L.depthwise || L.desc.c_in > kDenseChannels || L.desc.stride > 2) return false;
+    for (float w : L.fkw.weight)
+        if (!std::isfinite(w)) return false;
+    return true;
+}
+
 // Its time, microseconds: units of work one after the other, channel steps and stores of each.  (Fitted to 14 layers.)
 double split_estimate(int rounds, int steps, int pixels)
 {
@@ -722,6 +739,7 @@ patdnn_config_t default_config(patdnn_layer* h, const ConvShape& shape, size_t s
     ConvShape s = shape;
     s.pool = 0;
     if (h->L.depthwise) return patdnn_config_t{variant_of_extra(kExtraDepthwise), 0, 0, 1};
+    if (h->dense_mfma && dense_fits(s)) return patdnn_config_t{variant_of_extra(kExtraDense), 0, 0, 1};
     patdnn_config_t best{PATDNN_VARIANT_FKW, 0, 0, 1};
     const bool taps = taps_fit_layer(h) && taps_fit_input(s) && taps_fit_input(shape) && !h->taps.empty();
     double best_us = taps ? fkw_estimate(h, s) : 0.0;
@@ -782,6 +800,7 @@ patdnn_status_t patdnn_encode(const patdnn_layer_desc_t* desc, const float* dens
         patdnn_status_t st = build_fkw(*desc, dense_weights, pattern_ids, kernel_mask, h->L, err);
         if (st != PATDNN_OK) return fail(st, err);
         h->split = split_layer(h->L);
+        h->dense_mfma = dense_layer(h->L);
         if (!(desc->flags & PATDNN_HOST_ONLY)) {
             st = upload_layer(h.get());
             if (st != PATDNN_OK) return st;
@@ -1162,8 +1181,8 @@ static patdnn_status_t set_config(patdnn_handle_t h, const patdnn_config_t* cfg)
         h->cfg_tuned = false;
         return PATDNN_OK;
     }
-    if (extra_variant(cfg->variant) == kExtraSplit) {
-        if (!h->split) return fail(PATDNN_EUNSUPPORTED, "variant cannot run this layer");
+    if (extra_variant(cfg->variant) == kExtraSplit || extra_variant(cfg->variant) == kExtraDense) {
+        if (!(extra_variant(cfg->variant) == kExtraSplit ? h->split : h->dense_mfma)) return fail(PATDNN_EUNSUPPORTED, "variant cannot run this layer");
         h->cfg = patdnn_config_t{cfg->variant, 0, 0, 1};
         h->cfg_tuned = false;
         return PATDNN_OK;
@@ -1293,6 +1312,7 @@ static patdnn_status_t tune_ws(patdnn_handle_t h, const float* input, int32_t n,
                         cands.push_back(patdnn_config_t{variant_of_extra(filters == 8 ? kExtraTaps8 : kExtraTaps16), layout.first, waves, ks});
                 }
     if (h->L.depthwise) cands.push_back(patdnn_config_t{variant_of_extra(kExtraDepthwise), 0, 0, 1});
+    if (h->dense_mfma && dense_fits(s)) cands.push_back(patdnn_config_t{variant_of_extra(kExtraDense), 0, 0, 1});
     int rounds = 0, steps = 0, pixels = 0;
     if (h->split && !taps_fit_layer(h) && split_cost(s, rounds, steps, pixels)) cands.push_back(patdnn_config_t{variant_of_extra(kExtraSplit), 0, 0, 1});
     cands.push_back(patdnn_config_t{PATDNN_VARIANT_FKW, 0, 0, 1});
