@@ -256,6 +256,8 @@ patdnn_status_t patdnn_layout_stats(patdnn_handle_t h, patdnn_stats_t* out);
  *                           fp32 (stride 1, pruned layers), 8 or 16 filters per wavefront; `ck` up
  *                           to 160 channels, `waves` up to 16
  *                           "split_f16": pruned layers in fp32 on the binary16 matrix cores
+ *                           (outputs keep fp32's precision whatever lies beside their inputs; values
+ *                           that make ordinary ones vanish beside them, -1e30 say, cost time)
  *                           "dense_mfma": dense layers of up to four input channels on the
  *                           fp32 matrix cores
  * variant < 0 (the state of a new handle): the library chooses at every call, by an estimate of

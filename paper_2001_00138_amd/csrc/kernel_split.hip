@@ -10,8 +10,13 @@
 // and at stride 2, where those leave lanes idle.
 //
 // Range: each filter's weights are scaled to 2^14 .. 2^15 once, at encode time, and a tile's inputs to at most
-// 2^15 as they come in, both by powers of two.  A value then keeps all its bits down to 2^-26 of the largest one
-// beside it, and 2^-36 of a unit below that; sums are rescaled when later channels need it.
+// 2^15 as they come in, both by powers of two; sums are rescaled when later channels need it.  A scaled input of
+// 2^-14 and more (some 2^-28 of the largest one beside it) keeps its 22 bits, smaller ones are off by up to 2^-36: a
+// tile has one scale for pixels, channels and images that have nothing to do with each other.  The wavefronts that
+// stage mark the pixels of such inputs, and where sums over marked pixels are so small that it could be seen in
+// them (more than 2^-24 of the sum), they are worked out again in fp32 (see split_again).  128 -> 128 at 56 x 56 / 2, 64
+// images: 87 us for normal numbers through a ReLU, 85 for three times normal ones through a GELU (marked pixels in every
+// tile), 400 with one value of -1e30 in every image, 520 where all is worked out again (the stride-2 kernel: 100).
 //
 // Work decomposition
 //   * Pixels are cut into strips, rows and tiles as in kernel_f16.hip; two rows are numbered together
@@ -21,7 +26,7 @@
 //     largest magnitude of the next is found, and the one after it is split and put into LDS, while the matrix
 //     cores work on a fourth; a barrier per step.  The matrix instructions leave the vector ALU to the other wavefront, and
 //     loads of weights (from L2 in fragment order, a tap ahead) do not wait behind those of the inputs.
-//   * Sums that are not finite are worked out again from the tensor (see split_again).
+//   * Sums that are not finite, or too small for the scale, are worked out again from the tensor (see split_again).
 //
 // What bounds it: the matrix cores are busy 60 to 75 % of a computing wavefront's steps, and wait for its stores
 // (some 9000 cycles a tile).  us, the vector kernels' -> this one's: 128 -> 128 at 56 x 56 / 2, 64 images, kept 1/3.6 105 -> 85;
@@ -46,7 +51,8 @@ struct SplitArgs {
     const float* bias;
     float* out;
     const uint4* weights;            // fragments [64 filters][channel step][tap][16 of the filters][high, low][lane]
-    const int2* filters;             // stored filter, to whole blocks of 64: channel (-1: none), power of two its weights were multiplied with
+    const int2* filters;             // stored filter, to whole blocks of 64: channel (-1: none), power of two its weights were multiplied with (kSplitEmpty: it has none)
+    float seen;                      // a sum over marked pixels may be that small (see split_filters)
     int32_t n, c_in, c_out, h, w, ho, wo, conv_stride, pad, relu, pool;
     int32_t vh, sw, strips, pitch, lead, npp, npb;       // rows per image, strip width, strips, staged columns, those before output column 0, staged pixels of a buffer, units of them
     int32_t rp, hr;                              // rows that are numbered together (2: pooling windows), ho / rp
@@ -98,13 +104,25 @@ static __device__ __forceinline__ void split_pixel(SplitArgsPtr a, int q, int& i
 
 // units of 64 lanes x 8 channels that a staging wavefront holds per step, a lane with one pixel or a pair
 constexpr int split_units(bool pair) { return pair ? 5 : 9; }
-constexpr int kSplitTop = 11;        // exponent that the largest input of a tile is brought to
+constexpr int kSplitTop = 13;        // exponent that the largest input of a tile is brought to
 constexpr int kSplitMost = 14;       // up to which exponent later channels are taken as they are
+constexpr int kSplitLeast = -14;     // below it an input has not all of its bits
+constexpr int kSplitDrop = 64;       // a scale that falls by more might take earlier channels' sums out of range
+
+// Pixels of a unit of work under which inputs lie below the scale: one byte for each staged pixel, and whether
+// there are any, or every pixel counts as one.  Three units have theirs at a time: the one that is computed, the
+// next, whose inputs are coming in, and the last, whose bytes are cleared.
+constexpr int kSplitMarks = 3;
+enum { kSplitSome = 1, kSplitAll = 2 };
+
+// LDS behind the staging buffers: largest input of three chunks, kSplitSome / kSplitAll of three units, exponents
+// of two chunks, marks of three units.
+constexpr int split_lds(int npp) { return npp * (16 * 16 + kSplitMarks) + 32; }
 
 // The scale of a tile's inputs, a power of two, as its channels come in (every staging wavefront keeps
 // the same).
 struct SplitScale {
-    int sx = 0;
+    int sx = 0, first = 0;
     bool set = false;
     // `top`: bits of the largest magnitude of the channels to come
     __device__ __forceinline__ void next(unsigned top)
@@ -112,9 +130,18 @@ struct SplitScale {
         if (!top) return;
         const int e = max((int)(top >> 23), 1) - 127;
         if (!set || e + sx > kSplitMost) sx = min(kSplitTop - e, 127);
+        if (!set) first = sx;
         set = true;
     }
+    // twice the bits of the smallest magnitude that keeps its own, less one (see split_low)
+    __device__ __forceinline__ unsigned least() const
+    {
+        const int e = kSplitLeast - sx + 127;
+        return ((e > 0 ? (unsigned)e << 23 : 1u << (e + 22)) << 1) - 1;
+    }
 };
+// Orders magnitudes, with zero as the largest.
+static __device__ __forceinline__ unsigned split_low(float v) { return (__float_as_uint(v) << 1) - 1; }
 
 // Two inputs as the high and the low parts of their products with m (a power of two): mixed-precision
 // multiply-adds scale, round and pack at once.
@@ -154,57 +181,60 @@ static __device__ __forceinline__ float split_pool(float v)
     return fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xf, 0xf, true)));   // quad_perm [2,3,0,1]
 }
 
-// ---- where sums are not finite
-// The inputs of eight channels and a tap: 1 where one is not finite, +-1 for an infinity, and the finite
-// ones split as in the kernel proper.
+// ---- blocks that are worked out again
+// The inputs of eight channels and a tap.  Those that are not finite: 1 in `any`, +-1 in `sign` for an infinity, 0
+// in `v`.
 struct SplitInputs {
-    half8 any, sign, high, low;
+    half8 any, sign;
     bool some;
+    float v[8];
 };
-static __device__ __forceinline__ SplitInputs split_inputs(__amdgpu_buffer_rsrc_t rsrc, int at, int plane, int left, float m)
+static __device__ __forceinline__ SplitInputs split_inputs(const unsigned (&bits)[8])
 {
     SplitInputs r;
     r.some = false;
-    unsigned any[4] = {}, sign[4] = {}, high[4], low[4];
-    float v[8];
+    unsigned any[4] = {}, sign[4] = {};
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        const unsigned b = (unsigned)__builtin_amdgcn_raw_buffer_load_b32(rsrc, j < left ? at : -1, j * plane * 4, 0), e = b & 0x7FFFFFFFu;
+        const unsigned b = bits[j], e = b & 0x7FFFFFFFu;
         const bool odd = e >= 0x7F800000u;
         any[j >> 1] |= (odd ? 0x3C00u : 0u) << (j & 1) * 16;
         sign[j >> 1] |= (e == 0x7F800000u ? 0x3C00u | (b >> 16 & 0x8000u) : 0u) << (j & 1) * 16;
         r.some |= odd;
-        v[j] = odd ? 0.0f : __uint_as_float(b);
+        r.v[j] = odd ? 0.0f : __uint_as_float(b);
     }
-#pragma unroll
-    for (int j = 0; j < 8; j += 2) split_pair(v[j], v[j + 1], m, high[j >> 1], low[j >> 1]);
     r.any = __builtin_bit_cast(half8, make_uint4(any[0], any[1], any[2], any[3]));
     r.sign = __builtin_bit_cast(half8, make_uint4(sign[0], sign[1], sign[2], sign[3]));
-    r.high = __builtin_bit_cast(half8, make_uint4(high[0], high[1], high[2], high[3]));
-    r.low = __builtin_bit_cast(half8, make_uint4(low[0], low[1], low[2], low[3]));
     return r;
 }
 
-// The blocks of 16 pixels with a sum that is not finite (`odd`: a bit per block), once more from the tensor:
-// in two sums of whole numbers whether an infinity or a NaN met a kept weight, and with which sign (kept zeros
-// are -0 in the high part), and the sum over the finite inputs.
+// Blocks of 16 pixels with a sum that is not finite or too small (`again`: a bit per block), once more from the
+// tensor: the sum over the finite inputs in fp32 (the weights are put together again, the matrix
+// instruction takes one channel of each quarter of the lanes), and in two sums of whole numbers whether an
+// infinity or a NaN met a kept weight, and with which sign (kept zeros are -0 in the high part).  The loads of the
+// next eight channels and tap are in flight meanwhile.
 template <int PN, int WF, int WP>
-static __device__ __forceinline__ void split_again(unsigned odd, int u, int wave, int sx)
+static __device__ __forceinline__ void split_again(unsigned again, int u, int wave)
 {
     constexpr int PIX = 16 * PN * WP;
     const SplitArgsPtr a = split_args();
     const int lane = threadIdx.x & 63, quarter = lane >> 4;
     const int wp = wave % WP, wf = wave / WP;
     const SplitUnit t = split_unit<PIX>(a, u);
+    const int block = t.fset * WF + wf;
+    if (block >= a->fblocks) return;
     const int plane = a->h * a->w;
     const size_t tail = (size_t)(a->n - t.img0) * a->c_in * plane * 4;
     __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(a->in + (size_t)t.img0 * a->c_in * plane), 0,
                                                                     (int)(unsigned)std::min<size_t>(tail, 0x80000000u), 0x00020000);
     const int oh = a->pool ? a->ho >> 1 : a->ho, ow = a->pool ? a->wo >> 1 : a->wo;
-    const float m = __int_as_float((sx + 127) << 23);
+    const int last = a->steps * 9 - 1;
+    int scale[4];                                     // of the filter whose weights this lane holds
+#pragma unroll
+    for (int f = 0; f < 4; ++f) scale[f] = -a->filters[block * 64 + f * 16 + (lane & 15)].y;
 #pragma unroll 1
     for (int p = 0; p < PN; ++p) {
-        if (!__any(odd >> p & 1)) continue;
+        if (!__any(again >> p & 1)) continue;
         const int q = t.pix0 + (wp * PN + p) * 16 + (lane & 15);
         int img, oy, px;
         split_pixel(a, min(q, t.last), img, oy, px);
@@ -212,54 +242,74 @@ static __device__ __forceinline__ void split_again(unsigned odd, int u, int wave
         bool ok = q <= t.last && ox < a->wo;
         if (a->pool) ok = ok && !(lane & 3) && (ox >> 1) < ow && (oy >> 1) < oh;
         const size_t at = (size_t)img * a->c_out * oh * ow + (size_t)(a->pool ? oy >> 1 : oy) * ow + (a->pool ? ox >> 1 : ox);
-#pragma unroll 1
-        for (int f = 0; f < 4; ++f) {
-            const int block = t.fset * WF + wf;
-            if (block >= a->fblocks) break;
-            const uint4* wt = a->weights + ((size_t)block * a->steps * (9 * 4) + f) * (2 * 64) + lane;
-            float4v up{}, down{}, high{}, low{};
-#pragma unroll 1
-            for (int step = 0; step < a->steps; ++step)
-#pragma unroll 1
-                for (int tap = 0; tap < 9; ++tap, wt += 4 * 2 * 64) {
-                    const int y = oy * a->conv_stride + tap / 3 - a->pad, x = ox * a->conv_stride + tap % 3 - a->pad;
-                    const int c = step * 32 + quarter * 8;
-                    const bool inside = y >= 0 && y < a->h && x >= 0 && x < a->w && c < a->c_in;
-                    const SplitInputs in = split_inputs(rsrc, inside ? 4 * (((img - t.img0) * a->c_in + c) * plane + y * a->w + x) : -1, plane,
-                                                        a->c_in - c, m);
-                    const half8 wh = __builtin_bit_cast(half8, wt[0]), wl = __builtin_bit_cast(half8, wt[64]);
-                    high = __builtin_amdgcn_mfma_f32_16x16x32_f16(wh, in.high, high, 0, 0, 0);
-                    low = __builtin_amdgcn_mfma_f32_16x16x32_f16(wh, in.low, low, 0, 0, 0);
-                    low = __builtin_amdgcn_mfma_f32_16x16x32_f16(wl, in.high, low, 0, 0, 0);
-                    if (!__any(in.some)) continue;
-                    // 1 where a weight is kept; its sign, 0 for a kept zero
-                    const unsigned word[4] = {wt[0].x, wt[0].y, wt[0].z, wt[0].w};
-                    unsigned k[4] = {}, g[4] = {};
+        float4v sum[4], up[4], down[4];
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        const unsigned b = word[j >> 1] >> (j & 1) * 16 & 0xFFFFu;
-                        k[j >> 1] |= (b ? 0x3C00u : 0u) << (j & 1) * 16;
-                        g[j >> 1] |= (b & 0x7FFFu ? 0x3C00u | (b & 0x8000u) : 0u) << (j & 1) * 16;
-                    }
-                    const half8 kept = __builtin_bit_cast(half8, make_uint4(k[0], k[1], k[2], k[3]));
-                    const half8 sign = __builtin_bit_cast(half8, make_uint4(g[0], g[1], g[2], g[3]));
-                    up = __builtin_amdgcn_mfma_f32_16x16x32_f16(kept, in.any, up, 0, 0, 0);
-                    up = __builtin_amdgcn_mfma_f32_16x16x32_f16(sign, in.sign, up, 0, 0, 0);
-                    down = __builtin_amdgcn_mfma_f32_16x16x32_f16(kept, in.any, down, 0, 0, 0);
-                    down = __builtin_amdgcn_mfma_f32_16x16x32_f16(sign, -in.sign, down, 0, 0, 0);
+        for (int f = 0; f < 4; ++f) sum[f] = up[f] = down[f] = float4v{};
+        struct Loads {
+            unsigned x[8];
+            uint4 w[4][2];
+        } next;
+        // `i`: tap i % 9 of channel step i / 9
+        const auto load = [&](int i) __attribute__((always_inline)) {
+            const int step = i / 9, tap = i - step * 9;
+            const int y = oy * a->conv_stride + tap / 3 - a->pad, x = ox * a->conv_stride + tap % 3 - a->pad;
+            const int c = step * 32 + quarter * 8;
+            const bool inside = y >= 0 && y < a->h && x >= 0 && x < a->w && c < a->c_in;
+            const int off = inside ? 4 * (((img - t.img0) * a->c_in + c) * plane + y * a->w + x) : -1;
+            const uint4* const wt = a->weights + ((size_t)block * a->steps * 9 + i) * (4 * 2 * 64) + lane;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) next.x[j] = (unsigned)__builtin_amdgcn_raw_buffer_load_b32(rsrc, j < a->c_in - c ? off : -1, j * plane * 4, 0);
+#pragma unroll
+            for (int f = 0; f < 4; ++f)
+#pragma unroll
+                for (int k = 0; k < 2; ++k) next.w[f][k] = wt[(f * 2 + k) * 64];
+        };
+        load(0);
+#pragma unroll 1
+        for (int i = 0; i <= last; ++i) {
+            const Loads now = next;
+            load(min(i + 1, last));
+            const SplitInputs in = split_inputs(now.x);
+            const bool some = __any(in.some);
+#pragma unroll
+            for (int f = 0; f < 4; ++f) {
+                const half8 wh = __builtin_bit_cast(half8, now.w[f][0]), wl = __builtin_bit_cast(half8, now.w[f][1]);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float w = ldexpf(fmaf((float)wl[j], 1.0f / 2048.0f, (float)wh[j]), scale[f]);
+                    sum[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, in.v[j], sum[f], 0, 0, 0);
                 }
+                if (!some) continue;
+                // 1 where a weight is kept; its sign, 0 for a kept zero
+                const unsigned word[4] = {now.w[f][0].x, now.w[f][0].y, now.w[f][0].z, now.w[f][0].w};
+                unsigned k[4] = {}, g[4] = {};
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int2 filter = a->filters[block * 64 + f * 16 + quarter * 4 + r];
-                float v = ldexpf(fmaf(low[r], 1.0f / 2048.0f, high[r]), -(sx + filter.y));
-                if (down[r] > 0.0f) v = -__builtin_inff();
-                if (up[r] > 0.0f) v = down[r] > 0.0f ? __builtin_nanf("") : __builtin_inff();
-                v += a->bias ? a->bias[max(filter.x, 0)] : 0.0f;
-                if (a->pool) v = split_pool(v);
-                if (a->relu) v = fmaxf(v, 0.0f);
-                if (ok && filter.x >= 0) a->out[at + (size_t)filter.x * oh * ow] = v;
+                for (int j = 0; j < 8; ++j) {
+                    const unsigned b = word[j >> 1] >> (j & 1) * 16 & 0xFFFFu;
+                    k[j >> 1] |= (b ? 0x3C00u : 0u) << (j & 1) * 16;
+                    g[j >> 1] |= (b & 0x7FFFu ? 0x3C00u | (b & 0x8000u) : 0u) << (j & 1) * 16;
+                }
+                const half8 kept = __builtin_bit_cast(half8, make_uint4(k[0], k[1], k[2], k[3]));
+                const half8 sign = __builtin_bit_cast(half8, make_uint4(g[0], g[1], g[2], g[3]));
+                up[f] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kept, in.any, up[f], 0, 0, 0);
+                up[f] = __builtin_amdgcn_mfma_f32_16x16x32_f16(sign, in.sign, up[f], 0, 0, 0);
+                down[f] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kept, in.any, down[f], 0, 0, 0);
+                down[f] = __builtin_amdgcn_mfma_f32_16x16x32_f16(sign, -in.sign, down[f], 0, 0, 0);
             }
         }
+#pragma unroll
+        for (int f = 0; f < 4; ++f)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int co = a->filters[block * 64 + f * 16 + quarter * 4 + r].x;
+                float v = sum[f][r];
+                if (down[f][r] > 0.0f) v = -__builtin_inff();
+                if (up[f][r] > 0.0f) v = down[f][r] > 0.0f ? __builtin_nanf("") : __builtin_inff();
+                v += a->bias ? a->bias[max(co, 0)] : 0.0f;
+                if (a->pool) v = split_pool(v);
+                if (a->relu) v = fmaxf(v, 0.0f);
+                if (ok && co >= 0) a->out[at + (size_t)co * oh * ow] = v;
+            }
     }
 }
 
@@ -274,10 +324,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int per_xcd = gridDim.x >> 3, rank = blockIdx.x >> 3;
     const int u0 = rank < per_xcd ? (blockIdx.x & 7) * per_xcd + rank : blockIdx.x;
     SplitArgsPtr a = split_args();
-    // behind the staging buffers: largest input of three chunks, exponents of two
-    unsigned* const top_bits = reinterpret_cast<unsigned*>(lds4 + 16 * a->npp);
-    int* const exps = reinterpret_cast<int*>(top_bits + 4);
-    if (threadIdx.x < 3) top_bits[threadIdx.x] = 0;
+    unsigned* const top_bits = reinterpret_cast<unsigned*>(lds4 + 16 * a->npp);       // see split_lds
+    unsigned* const marked = top_bits + 3;
+    int* const exps = reinterpret_cast<int*>(marked + kSplitMarks);
+    unsigned char* const marks = reinterpret_cast<unsigned char*>(top_bits + 8);
+    if (threadIdx.x < 3 + kSplitMarks) top_bits[threadIdx.x] = 0;
+    for (int e = threadIdx.x; e < kSplitMarks * a->npp / 4; e += 512) reinterpret_cast<unsigned*>(marks)[e] = 0;
     __syncthreads();
     const int steps = a->steps;
     const int my_units = (a->total - u0 + (int)gridDim.x - 1) / (int)gridDim.x;
@@ -285,7 +337,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
     if (wave >= 4) {
         // ---- staging: of iteration g the inputs of chunk g + 1 into LDS, the loads of chunk g + 3, the largest
-        // input of chunk g + 2
+        // input of chunk g + 2; the smallest one beside zero stays with the lane until its chunk's scale is known
         const int w4 = wave - 4;
         const int plane = a->h * a->w, c_in = a->c_in, npp = a->npp;
         unsigned off[UNITS];
@@ -309,6 +361,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         };
         const int units = a->npb;                     // this wavefront's eight channels of each
         float raw[2][UNITS][UPX][8];
+        unsigned low[2];
         int lu = u0, ls = 0;                          // what is loaded next
         auto load = [&](float (&dst)[UNITS][UPX][8]) __attribute__((always_inline)) {
             if (ls == 0) enter(lu);
@@ -333,12 +386,32 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             if (++ls == steps) { ls = 0; lu += gridDim.x; }
         };
         SplitScale scale;
-        int cs = 0;                                   // step of the chunk that is put into LDS next
-        auto put = [&](int chunk, const float (&src)[UNITS][UPX][8]) __attribute__((always_inline)) {
-            if (cs == 0) scale = SplitScale{};
+        int cs = 0, slot = kSplitMarks - 1;           // step of the chunk that is put into LDS next, marks of its unit
+        auto put = [&](int chunk, const float (&src)[UNITS][UPX][8], unsigned lowest) __attribute__((always_inline)) {
+            if (cs == 0) {
+                scale = SplitScale{};
+                slot = slot == kSplitMarks - 1 ? 0 : slot + 1;
+            }
             if (++cs == steps) cs = 0;
             scale.next((unsigned)__builtin_amdgcn_readfirstlane((int)top_bits[chunk % 3]));
-            if (threadIdx.x == 256) exps[chunk & 1] = scale.sx;
+            if (threadIdx.x == 256) {
+                exps[chunk & 1] = scale.sx;
+                if (scale.first - scale.sx > kSplitDrop) atomicOr(&marked[slot], kSplitAll);
+            }
+            if (__any(lowest < scale.least())) {
+                const unsigned least = scale.least();
+#pragma unroll
+                for (int k = 0; k < UNITS; ++k)
+                    if (k < units)
+#pragma unroll
+                        for (int q = 0; q < UPX; ++q) {
+                            unsigned v = ~0u;
+#pragma unroll
+                            for (int j = 0; j < 8; ++j) v = min(v, split_low(src[k][q][j]));
+                            if (v < least) marks[slot * npp + (k * 64 + lane) * UPX + q] = 1;
+                        }
+                if (lane == 0) atomicOr(&marked[slot], kSplitSome);
+            }
             const float m = __int_as_float((scale.sx + 127) << 23);
 #pragma unroll
             for (int k = 0; k < UNITS; ++k) {
@@ -357,14 +430,18 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 }
             }
         };
-        auto top = [&](int chunk, const float (&src)[UNITS][UPX][8]) __attribute__((always_inline)) {
+        auto top = [&](int chunk, const float (&src)[UNITS][UPX][8], unsigned& lowest) __attribute__((always_inline)) {
             // the maximum of two passes over a NaN
             float m = 0.0f;
+            lowest = ~0u;
 #pragma unroll
             for (int k = 0; k < UNITS; ++k)
                 if (k < units)
 #pragma unroll
-                    for (int j = 0; j < 8 * UPX; j += 2) m = fmaxf(fmaxf(fabsf(src[k][j >> 3][j & 7]), fabsf(src[k][j >> 3][(j + 1) & 7])), m);
+                    for (int j = 0; j < 8 * UPX; j += 2) {
+                        m = fmaxf(fmaxf(fabsf(src[k][j >> 3][j & 7]), fabsf(src[k][j >> 3][(j + 1) & 7])), m);
+                        lowest = min(min(split_low(src[k][j >> 3][j & 7]), split_low(src[k][j >> 3][(j + 1) & 7])), lowest);
+                    }
             if (__any(m > 3.402823466e38f)) {
                 m = 0.0f;
 #pragma unroll
@@ -379,18 +456,34 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             m = split_wave_max(m);
             if (lane == 63) atomicMax(&top_bits[chunk % 3], __float_as_uint(m));
         };
+        // When the first chunk of a unit is computed, the marks of the one before have been read.  (The next that
+        // are written, even of a unit of one step, are those of the unit after the one computed.)
+        int gs = 0, old = kSplitMarks - 1;            // step of chunk g, marks of the unit before its own
+        auto clear = [&]() __attribute__((always_inline)) {
+            if (gs == 0) {
+                if (w4 == 0 && marked[old]) {
+                    for (int e = lane; e < npp; e += 64) marks[old * npp + e] = 0;
+                    if (lane == 0) marked[old] = 0;
+                }
+                old = old == kSplitMarks - 1 ? 0 : old + 1;
+            }
+            if (++gs == steps) gs = 0;
+        };
         // set c & 1 holds chunk c
-        auto iteration = [&](int g, float (&near)[UNITS][UPX][8], float (&far)[UNITS][UPX][8]) __attribute__((always_inline)) {
+        auto iteration = [&](int g, float (&near)[UNITS][UPX][8], float (&far)[UNITS][UPX][8], unsigned& low_near, unsigned& low_far) __attribute__((always_inline)) {
             // near: chunk g + 1, then g + 3; far: chunk g + 2
-            if (g >= 0 && threadIdx.x == 256) top_bits[g % 3] = 0;
-            if (g + 1 >= 0 && g + 1 < chunks) put(g + 1, near);
+            if (g >= 0) {
+                if (threadIdx.x == 256) top_bits[g % 3] = 0;
+                clear();
+            }
+            if (g + 1 >= 0 && g + 1 < chunks) put(g + 1, near, low_near);
             if (g + 3 < chunks) load(near);
-            if (g + 2 >= 0 && g + 2 < chunks) top(g + 2, far);
+            if (g + 2 >= 0 && g + 2 < chunks) top(g + 2, far, low_far);
             __syncthreads();
         };
         for (int g = -3; g < chunks; g += 2) {
-            iteration(g, raw[0], raw[1]);
-            if (g + 1 < chunks) iteration(g + 1, raw[1], raw[0]);
+            iteration(g, raw[0], raw[1], low[0], low[1]);
+            if (g + 1 < chunks) iteration(g + 1, raw[1], raw[0], low[1], low[0]);
         }
         return;
     }
@@ -398,8 +491,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // ---- computing
     const int wp = wave % WP, wf = wave / WP;
     for (int g = -3; g < 0; ++g) __syncthreads();
-    int chunk = 0;
-    for (int u = u0; u < a->total; u += gridDim.x) {
+    int chunk = 0, slot = 0;
+    for (int u = u0; u < a->total; u += gridDim.x, slot = slot == kSplitMarks - 1 ? 0 : slot + 1) {
         a = split_args();
         const int npp = a->npp, pitch = a->pitch;
         int base[PN];
@@ -496,7 +589,22 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             at[p] = (size_t)img * a->c_out * oplane + (size_t)(a->pool ? oy >> 1 : oy) * ow + (a->pool ? ox >> 1 : ox);
         }
         const bool pool = a->pool, relu = a->relu;
-        unsigned odd = 0;                             // blocks of pixels with a sum that is not finite
+        unsigned again = 0;                           // blocks of pixels that are worked out again
+        unsigned low_px = 0;                          // ... for small sums: pixels over marked ones
+        const unsigned some = (unsigned)__builtin_amdgcn_readfirstlane((int)marked[slot]);
+        if (some) {
+            if (some & kSplitAll) again = ~0u;
+#pragma unroll
+            for (int p = 0; p < PN; ++p) {
+                int img, oy, px;
+                split_pixel(a, min(t.pix0 + (wp * PN + p) * 16 + l16, t.last), img, oy, px);
+                const unsigned char* const under = marks + slot * a->npp + (img * a->vh + oy * a->conv_stride - t.vrow0) * a->pitch + px * a->conv_stride + (a->lead - a->pad);
+                unsigned any = 0;
+#pragma unroll
+                for (int tap = 0; tap < 9; ++tap) any |= under[tap / 3 * a->pitch + tap % 3];
+                low_px |= (unsigned)(any != 0) << p;
+            }
+        }
         int2 filter[4][4];
         float bias[4][4];
         const int2* const mine = a->filters + (size_t)min(t.fset * WF + wf, a->fblocks - 1) * 64 + quarter * 4;
@@ -512,6 +620,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 if (!used) filter[f][r].x = -1;
                 bias[f][r] = a->bias ? a->bias[max(filter[f][r].x, 0)] : 0.0f;
             }
+        if (some)
+#pragma unroll
+            for (int f = 0; f < 4; ++f)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float seen = filter[f][r].x >= 0 && filter[f][r].y != kSplitEmpty ? a->seen : 0.0f;
+#pragma unroll
+                    for (int p = 0; p < PN; ++p)
+                        again |= fabsf(fmaf(low[f][p][r], 1.0f / 2048.0f, high[f][p][r])) < seen ? low_px & 1u << p : 0u;
+                }
 #pragma unroll
         for (int f = 0; f < 4; ++f)
 #pragma unroll
@@ -523,16 +641,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
                 for (int p = 0; p < PN; ++p) {
                     float v = ldexpf(fmaf(low[f][p][r], 1.0f / 2048.0f, high[f][p][r]), ex);
-                    odd |= (unsigned)!(fabsf(v) < __builtin_inff()) << p;
+                    again |= (unsigned)!(fabsf(v) < __builtin_inff()) << p;
                     v += b;
                     if (pool) v = split_pool(v);
                     if (relu) v = fmaxf(v, 0.0f);
                     if (ok[p] && has) dst[at[p]] = v;
                 }
             }
-        if (__any(odd)) {
+        if (__any(again)) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // after the stores above
-            split_again<PN, WF, WP>(odd, u, wave, sx);
+            split_again<PN, WF, WP>(again, u, wave);
         }
         __syncthreads();
     }
@@ -604,7 +722,7 @@ static bool split_tiles(const ConvShape& s, int pix, int widest, bool pair, Spli
     a.npb = (rows * a.pitch + unit - 1) / unit;
     a.npp = a.npb * unit;
     // byte offsets from a tile's first image, and a staging wavefront's registers
-    return (long long)(between + 2) * s.c_in * s.h * s.w < (1ll << 29) && a.npb <= split_units(pair) && a.npp * 256 + 32 <= 160 * 1024;
+    return (long long)(between + 2) * s.c_in * s.h * s.w < (1ll << 29) && a.npb <= split_units(pair) && split_lds(a.npp) <= 160 * 1024;
 }
 
 template <int PN, int WF, int WP, bool PAIR>
@@ -616,7 +734,7 @@ static hipError_t launch_split_t(SplitArgs a, hipStream_t stream)
     a.div_hr = make_fast_div((uint32_t)a.hr);
     a.div_vh = make_fast_div((uint32_t)a.vh);
     a.div_pitch = make_fast_div((uint32_t)a.pitch);
-    const size_t lds = (size_t)a.npp * 16 * 16 + 32;
+    const size_t lds = (size_t)split_lds(a.npp);
     if (lds > 64 * 1024) {
         static std::atomic<uint64_t> allowed{0};
         hipError_t e = allow_big_lds(reinterpret_cast<const void*>(&split_conv_kernel<PN, WF, WP, PAIR>), allowed);
@@ -678,6 +796,7 @@ hipError_t launch_split(const DevFkw& f, const ConvShape& s, const float* in, co
     a.in = in; a.bias = bias; a.out = out;
     a.weights = static_cast<const uint4*>(f.split_f16);
     a.filters = reinterpret_cast<const int2*>(f.split_filters);
+    a.seen = f.split_seen;
     a.n = s.n; a.c_in = s.c_in; a.c_out = s.c_out; a.h = s.h; a.w = s.w; a.ho = s.ho; a.wo = s.wo;
     a.conv_stride = s.stride; a.pad = s.pad; a.relu = s.relu; a.pool = s.pool;
     bool pair = split_pair_rows(s, in);

@@ -93,9 +93,11 @@ struct DevFkw {
     // those with a weight that is not finite in binary16
     const void* expanded_f16 = nullptr;
     // likewise as pairs of binary16 numbers (kernel_split.hip), and per stored filter, to whole blocks of 64,
-    // its channel (-1: none) and the power of two that its weights were multiplied with
+    // its channel (-1: none) and the power of two that its weights were multiplied with (kSplitEmpty: it has none)
     const void* split_f16 = nullptr;
     const int32_t* split_filters = nullptr;
+    // so small a sum, in the scales of weights and inputs, may be off by 2^-24 of itself for inputs below the scale
+    float split_seen = 0.0f;
 };
 
 // Filter-group layout on the device: record streams (sparse) or 9-tap weights (dense).
@@ -149,6 +151,7 @@ hipError_t launch_f16_expand(const DevFkw& f, int32_t c_in, int32_t c_out, void*
 // each and the pixels of a wavefront.
 bool split_cost(const ConvShape& s, int& rounds, int& steps, int& pixels);
 hipError_t launch_split(const DevFkw& f, const ConvShape& s, const float* in, const float* bias, float* out, hipStream_t stream);
+constexpr int kSplitEmpty = 1 << 20;
 size_t split_expanded_halves(int32_t c_in, int32_t c_out);
 // Fills `out` (split_expanded_halves, zeroed) from the FKW arrays and split_filters.
 hipError_t launch_split_expand(const DevFkw& f, int32_t c_in, int32_t c_out, void* out, hipStream_t stream);

@@ -574,28 +574,34 @@ bool f16_walk_pays(const patdnn_layer* h, const ConvShape& s)
 // Binary16 weights with the removed ones as zeros: up to 256 MB a layer.
 constexpr size_t kMaxExpandedHalves = (size_t)128 << 20;
 
-// Per stored filter the power of two that brings its largest weight to 2^14 .. 2^15; false where a weight is
-// not finite, or so small beside its filter's largest that nothing of it would be left in binary16.
-bool split_exponents(const LayerHost& L, std::vector<int32_t>& out)
+// DevFkw::split_filters and split_seen; false where a weight is not finite, or so small beside its filter's largest
+// that nothing of it would be left in binary16.
+bool split_filters(const LayerHost& L, std::vector<int32_t>& out, float& seen)
 {
     const Fkw& f = L.fkw;
     out.assign((size_t)(L.desc.c_out + 63) / 64 * 128, -1);
+    double sum = 0.0;                                 // largest of a filter's magnitudes, scaled
     for (int s = 0; s < L.desc.c_out; ++s) {
         out[2 * (size_t)s] = f.reorder[s];
-        int32_t& exponent = out[2 * (size_t)s + 1] = 0;
+        int32_t& exponent = out[2 * (size_t)s + 1] = kSplitEmpty;
         float most = 0.0f, least = INFINITY;
+        double all = 0.0;
         for (size_t i = (size_t)f.offset[s] * f.taps; i < (size_t)f.offset[s + 1] * f.taps; ++i) {
             const float w = std::fabs(f.weight[i]);
             if (!(w < INFINITY)) return false;
             if (w > 0.0f) least = std::min(least, w);
             most = std::max(most, w);
+            all += w;
         }
-        if (most == 0.0f) continue;
+        if (most == 0.0f) continue;                   // (kept zeros count as none: they are what they are in any scale)
         int e = 0;
         std::frexp(most, &e);                         // most < 2^e
         exponent = 15 - e;
         if (std::ldexp((double)least, exponent) < 0x1p-24) return false;
+        sum = std::max(sum, std::ldexp(all, exponent));
     }
+    // an input below the scale is off by 2^-36, and of its product with a weight as much is left out again
+    seen = (float)std::min(sum * 0x1p-35 * 0x1p24, 0x1p100);
     return true;
 }
 
@@ -613,8 +619,9 @@ bool split_layer(const LayerHost& L)
     if (L.desc.stride == 1 && keep < 0.4) return false;
     const double additions = 9.0 / 16 * c_in * (1.0 - std::pow(1.0 - 4.0 / 9 * keep, 16.0));
     if (53.3 + 2.75 * additions > 6.62 * kernels) return false;
-    std::vector<int32_t> exponents;
-    return split_expanded_halves(L.desc.c_in, L.desc.c_out) <= kMaxExpandedHalves && split_exponents(L, exponents);
+    std::vector<int32_t> filters;
+    float seen;
+    return split_expanded_halves(L.desc.c_in, L.desc.c_out) <= kMaxExpandedHalves && split_filters(L, filters, seen);
 }
 
 // Dense layers of few channels: filters are stored in the order of their channels there, and zero padding, which the
@@ -696,10 +703,10 @@ patdnn_status_t upload_layer(patdnn_layer* h)
         }
         up.add(dweight16, &dw_weight16);
     }
-    std::vector<int32_t> split_filters;
-    const size_t split = h->split && split_exponents(h->L, split_filters) ? split_expanded_halves(h->L.desc.c_in, h->L.desc.c_out) : 0;
+    std::vector<int32_t> filters;
+    const size_t split = h->split && split_filters(h->L, filters, d.split_seen) ? split_expanded_halves(h->L.desc.c_in, h->L.desc.c_out) : 0;
     const uint16_t* split16 = nullptr;
-    if (split) up.add(split_filters, &d.split_filters);
+    if (split) up.add(filters, &d.split_filters);
     size_t expanded = h->L.depthwise || !finite16 ? 0 : f16_expanded_halves(h->L.desc.c_in, h->L.desc.c_out);
     if (expanded > kMaxExpandedHalves) expanded = 0;
     // from a megabyte on by themselves, at the start of a page (512 -> 512 at 7 x 7, 64 images: 26.5 us, 27.2

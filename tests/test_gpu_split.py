@@ -109,6 +109,65 @@ def test_small_values_beside_large_ones(torch, oracle):
         assert np.abs(got[i] - ref[i]).max() <= TOL * np.abs(ref[i]).max(), i
 
 
+def _reference(torch, data, x, stride, pad=1):
+    """The layer in 64 bits, and for each output the sum of its terms' magnitudes."""
+    wt, ids, mask, lib = data
+    bits = (lib.astype(np.int64)[ids][..., None] >> np.arange(9)) & 1
+    w = torch.from_numpy((wt.reshape(*ids.shape, 9) * bits * mask[..., None]).reshape(*ids.shape, 3, 3).astype(np.float64))
+    xd = torch.from_numpy(x).double()
+    conv = torch.nn.functional.conv2d
+    return conv(xd, w, None, stride, pad), conv(xd.abs(), w.abs(), None, stride, pad)
+
+
+# Each factor keeps 22 bits or more and its product 2^-21; the sums' roundings, 2^-24 of a partial sum each, are
+# some hundred of random signs: an output is within 1e-6 of the sum of its terms' magnitudes
+OF_TERMS = 1e-6
+
+
+@pytest.mark.parametrize("large", [1e10, 1e20, -3.4028234663852886e38])
+@pytest.mark.parametrize("where", ["kept channel", "removed channel", "other image", "later channels"])
+@pytest.mark.parametrize("c_in,c_out,side,stride", [(160, 70, 14, 2), (96, 40, 20, 1)])
+def test_ordinary_values_beside_a_large_one(torch, c_in, c_out, side, stride, where, large):
+    """One large finite value costs the outputs whose kept weights do not meet it nothing: neighbours in its
+    image and tile, filters that removed its channel, images beside its own."""
+    rng = np.random.default_rng(11)
+    (wt, ids, mask, lib), L = _layer(rng, c_in, c_out, 0.9, stride)
+    L.close()
+    mask[:, 5] = 0
+    L = B.Layer(wt, ids, mask, lib, stride=stride)
+    x = np.maximum(rng.standard_normal((4, c_in, side, side)), 0).astype(np.float32)
+    x[:, 40] = 0
+    x[0, 40 if where == "later channels" else 5 if where == "removed channel" else 7, side // 2 - 1, 3] = large
+    if where == "later channels":
+        x[:, :32] *= np.float32(1e-20)
+    ref, terms = _reference(torch, (wt, ids, mask, lib), x, stride)
+    keep = slice(1, None) if where == "other image" else slice(None)
+    out = {}
+    for name in ("fkw", "split_f16"):
+        L.set_config(_variant(name))
+        out[name] = L.conv2d(torch.from_numpy(x).cuda(), None, relu=False).cpu().double()
+    L.close()
+    fits = terms < 1e38                              # beyond, the order of the sum decides what overflows
+    err = {name: float(((got - ref).abs() / terms.clamp(min=1e-300))[keep][fits[keep]].max()) for name, got in out.items()}
+    print(f"  {where} {large}: {err}", flush=True)
+    assert err["fkw"] <= OF_TERMS and err["split_f16"] <= OF_TERMS, err
+
+
+def test_inputs_of_many_magnitudes(torch):
+    """Magnitudes over sixty powers of ten, each output by the sum of its own terms."""
+    rng = np.random.default_rng(12)
+    data, L = _layer(rng, 100, 70, 1.0, 2)
+    x = (rng.standard_normal((3, 100, 17, 22)) * 10.0 ** rng.uniform(-30, 30, (3, 100, 17, 22))).astype(np.float32)
+    x[rng.random(x.shape) < 0.5] = 0
+    x[1, :, :9] = 0
+    x[1, rng.integers(0, 100, 40), rng.integers(0, 9, 40), rng.integers(0, 22, 40)] = np.float32(1e-15)
+    ref, terms = _reference(torch, data, x, 2)
+    L.set_config(_variant("split_f16"))
+    got = L.conv2d(torch.from_numpy(x).cuda(), None, relu=False).cpu().double()
+    L.close()
+    assert float(((got - ref).abs() / terms.clamp(min=1e-300))[terms > 0].max()) <= OF_TERMS
+
+
 @pytest.mark.parametrize("c_out,h,stride,pool", [(70, 21, 2, False), (33, 20, 1, True), (130, 34, 1, False)])
 @pytest.mark.parametrize("share", [1e-4, 1e-2, 1.0])
 def test_not_finite_inputs(torch, c_out, h, stride, pool, share):
