@@ -575,7 +575,7 @@ bool f16_walk_pays(const patdnn_layer* h, const ConvShape& s)
 constexpr size_t kMaxExpandedHalves = (size_t)128 << 20;
 
 // DevFkw::split_filters and split_seen; false where a weight is not finite, or so small beside its filter's largest
-// that nothing of it would be left in binary16.
+// that binary16 would not have all of its bits.
 bool split_filters(const LayerHost& L, std::vector<int32_t>& out, float& seen)
 {
     const Fkw& f = L.fkw;
@@ -597,7 +597,7 @@ bool split_filters(const LayerHost& L, std::vector<int32_t>& out, float& seen)
         int e = 0;
         std::frexp(most, &e);                         // most < 2^e
         exponent = 15 - e;
-        if (std::ldexp((double)least, exponent) < 0x1p-24) return false;
+        if (std::ldexp((double)least, exponent) < 0x1p-14) return false;
         sum = std::max(sum, std::ldexp(all, exponent));
     }
     // an input below the scale is off by 2^-36, and of its product with a weight as much is left out again
@@ -605,20 +605,23 @@ bool split_filters(const LayerHost& L, std::vector<int32_t>& out, float& seen)
     return true;
 }
 
-// Pruned layers for which the split kernel exists: where it is no less exact than the kernels that it stands in
-// for, which add a filter's products one after the other.  Errors against 64 bits, in 1e-8 of the result's
-// norm: theirs grow as 1.82 sqrt(2 kernels per filter); the split kernel has 7.3 from the halves' last
-// bits, and adds sixteen channels of a tap at a time, 1.66 sqrt(such additions that add anything).  (kept
-// 1/3.6: 64 channels 11.5 and 12.2, 128 15.4 and 15.1, 512 29.6 and 26.3; half of 64 channels 14.5 and 13.7.)
+// Pruned layers for which the split kernel exists: where each of its filters comes out no less exact than from the
+// kernels that it stands in for (the walk and the tiled kernels; the tap-product kernel is the more exact one), which
+// add a filter's products one after the other.  Errors against 64 bits, in 1e-8 of a filter's result, over inputs
+// that a ReLU left, 64 to 512 channels: theirs grow as 2.6 sqrt(kernels), 7.6 for 8 kernels, 10.5 for 16, 11.2 for 18, 11.8
+// for 20, 14.7 for 32, 58 for 512; the split kernel has 7.3 from the halves' last bits and adds 32 channels by
+// themselves, 10.2 for 8, 10.8 for 16, 11.0 for 18 and 20, 11.7 for 32, 15 for 512.  (Inputs of both signs: even at 8 kernels.)
+constexpr int kSplitKernels = 18;
 // At stride 1 it is slower than the others for less than about 0.4 of the kernels (128 -> 128 at 112 x 112, 64
-// images: 1/3.6 615 us against 560, one half 600 against 960).
+// images: 1/3.6 615 us against 560 when it still added without joins, one half 708 and 711; all of 64 -> 64 123 against 209).
 bool split_layer(const LayerHost& L)
 {
     if (L.depthwise || L.dense || L.kept == 0) return false;
-    const double c_in = L.desc.c_in, kernels = (double)L.kept / L.desc.c_out, keep = kernels / c_in;
-    if (L.desc.stride == 1 && keep < 0.4) return false;
-    const double additions = 9.0 / 16 * c_in * (1.0 - std::pow(1.0 - 4.0 / 9 * keep, 16.0));
-    if (53.3 + 2.75 * additions > 6.62 * kernels) return false;
+    if (L.desc.stride == 1 && (double)L.kept / L.desc.c_out / L.desc.c_in < 0.4) return false;
+    for (int s = 0; s < L.desc.c_out; ++s) {
+        const int32_t kernels = L.fkw.offset[s + 1] - L.fkw.offset[s];
+        if (kernels && kernels < kSplitKernels) return false;
+    }
     std::vector<int32_t> filters;
     float seen;
     return split_expanded_halves(L.desc.c_in, L.desc.c_out) <= kMaxExpandedHalves && split_filters(L, filters, seen);
