@@ -803,6 +803,25 @@ bool split_cost(const ConvShape& s, int& rounds, int& steps, int& pixels)
     return true;
 }
 
+// Number of the launch shape, twice, plus one with pairs; -1 where none fits.
+static int split_launch_plan(const ConvShape& s, const void* in, SplitArgs& a)
+{
+    for (const bool pair : {true, false}) {
+        if (pair && !split_pair_rows(s, in)) continue;
+        const int shape = split_plan(s, pair, a);
+        if (shape >= 0) return 2 * shape + pair;
+    }
+    return -1;
+}
+
+int split_choice(const ConvShape& s, const void* in, int& units)
+{
+    SplitArgs a{};
+    const int choice = split_launch_plan(s, in, a);
+    units = a.total;
+    return choice;
+}
+
 hipError_t launch_split(const DevFkw& f, const ConvShape& s, const float* in, const float* bias, float* out, hipStream_t stream)
 {
     SplitArgs a{};
@@ -812,11 +831,8 @@ hipError_t launch_split(const DevFkw& f, const ConvShape& s, const float* in, co
     a.seen = f.split_seen;
     a.n = s.n; a.c_in = s.c_in; a.c_out = s.c_out; a.h = s.h; a.w = s.w; a.ho = s.ho; a.wo = s.wo;
     a.conv_stride = s.stride; a.pad = s.pad; a.relu = s.relu; a.pool = s.pool;
-    bool pair = split_pair_rows(s, in);
-    int shape = split_plan(s, pair, a);
-    if (shape < 0 && pair) shape = split_plan(s, pair = false, a);
-    if (shape < 0) return hipErrorInvalidValue;
-    return kSplitShapes[shape].launch[pair](a, stream);
+    const int choice = split_launch_plan(s, in, a);
+    return choice < 0 ? hipErrorInvalidValue : kSplitShapes[choice >> 1].launch[choice & 1](a, stream);
 }
 
 }  // namespace patdnn

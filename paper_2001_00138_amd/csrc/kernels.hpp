@@ -150,6 +150,9 @@ hipError_t launch_f16_expand(const DevFkw& f, int32_t c_in, int32_t c_out, void*
 // False where its numbers do not reach; else the units of work that the busiest workgroup has, the channel steps of
 // each and the pixels of a wavefront.
 bool split_cost(const ConvShape& s, int& rounds, int& steps, int& pixels);
+// What launch_split launches for a tensor at `in`: twice the number of the shape, plus one for loads of pixel pairs
+// (-1: nothing fits), and the units of work.
+int split_choice(const ConvShape& s, const void* in, int& units);
 hipError_t launch_split(const DevFkw& f, const ConvShape& s, const float* in, const float* bias, float* out, hipStream_t stream);
 constexpr int kSplitEmpty = 1 << 20;
 size_t split_expanded_halves(int32_t c_in, int32_t c_out);

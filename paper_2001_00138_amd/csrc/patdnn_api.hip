@@ -970,6 +970,15 @@ int32_t patdnn_internal_f16_choice(patdnn_handle_t h, const void* input, int32_t
     return f16_walk_pays(h, s) ? -1 : f16_choice(s, input);
 }
 
+// Likewise: the launch of the split kernel for a tensor at `input` (see split_choice), pooled or not.
+int32_t patdnn_internal_split_choice(patdnn_handle_t h, const void* input, int32_t n, int32_t h_in, int32_t w_in, int32_t pool, int32_t* units)
+{
+    ConvShape s{};
+    if (shape_of(h, n, h_in, w_in, s) != PATDNN_OK) return -2;
+    s.pool = pool;
+    return split_choice(s, input, *units);
+}
+
 patdnn_status_t patdnn_conv2d(patdnn_handle_t h, const float* input, int32_t n, int32_t h_in,
                               int32_t w_in, const float* bias, float* output, int32_t fuse_relu,
                               void* stream)

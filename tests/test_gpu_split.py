@@ -1,6 +1,7 @@
 """GPU parity of fp32 layers on the binary16 matrix cores (csrc/kernel_split.hip) where it can go wrong: odd and
-even rows, strips, tiles over several images, remainders of channels and filters, every launch shape, both
-strides, pooled windows, inputs of all magnitudes, sums that are not finite - and where the library chooses it."""
+even rows, strips, tiles over several images, remainders of channels and filters, every launch shape (asserted),
+workgroups with several units of work, both strides, pooled windows, inputs of all magnitudes, sums that are not
+finite - and where the library chooses it."""
 
 import ctypes
 
@@ -76,6 +77,58 @@ def test_split_kernel(torch, oracle, case):
         L.conv2d_ws(xt, bt, out, relu=True, pool=pool)
         assert bool((buf[:guard] == 777.0).all()) and bool((buf[guard + numel:] == 777.0).all())
         assert float(np.abs(out.cpu().numpy().astype(np.float64) - ref).max() / np.abs(ref).max()) <= TOL
+    L.close()
+
+
+# c_in, c_out, n, h, w, stride, twice the number of the launch shape (plus one: pairs of pixels) and units of work, plain
+# and pooled.  256 workgroups: some take a second or a third unit.
+PERSISTENT = [
+    (32, 64, 22, 56, 56, 1, (1, 270), (1, 270)),       # one channel step: a unit an iteration
+    (32, 40, 23, 56, 57, 1, (0, 292), (0, 282)),
+    (70, 130, 7, 50, 50, 1, (3, 288), (3, 288)),       # three steps, two filter sets
+    (70, 130, 7, 50, 51, 1, (2, 288), (2, 288)),
+    (33, 64, 2100, 5, 4, 1, (5, 329), (5, 263)),           # two steps, tiles over several images
+    (40, 64, 5200, 3, 3, 1, (4, 366), (6, 325)),
+    (33, 100, 90, 28, 28, 2, (7, 276), (6, 276)),
+    (96, 130, 45, 37, 35, 2, (6, 482), (6, 508)),
+    (128, 70, 60, 37, 38, 2, (7, 357), (6, 338)),      # four steps
+]
+
+
+def _plan(L, x, n, h, w, pool):
+    plan, units = B.lib().patdnn_internal_split_choice, ctypes.c_int32()
+    plan.argtypes = [ctypes.c_void_p] * 2 + [ctypes.c_int32] * 4 + [ctypes.c_void_p]
+    plan.restype = ctypes.c_int32
+    return plan(L.handle, x, n, h, w, int(pool), ctypes.byref(units)), units.value
+
+
+@pytest.mark.parametrize("case", PERSISTENT)
+def test_workgroups_that_go_on(torch, case):
+    """Units after the first: scales, marks and sums start anew, whatever magnitudes the one before had and while the
+    next one's inputs come in; values that are not finite in some of them only."""
+    c_in, c_out, n, h, w, stride, *launches = case
+    rng = np.random.default_rng(c_in * 1000 + w)
+    _, L = _layer(rng, c_in, c_out, 0.9, stride)
+    magnitude = np.array([1.0, 1e4, 1e-6, 1e12, 1e-14], np.float32)[np.arange(n) % 5][:, None, None, None]
+    x = rng.standard_normal((n, c_in, h, w)).astype(np.float32) * magnitude
+    for k, value in enumerate((np.nan, np.inf, -np.inf)):
+        x[k + 1::37, 3, k % h, 1] = value
+    xt, bias = torch.from_numpy(x).cuda(), torch.from_numpy(rng.standard_normal(c_out).astype(np.float32) * 1e-15).cuda()
+    for pool, launch in zip((False, True), launches):
+        assert _plan(L, xt.data_ptr(), n, h, w, pool) == launch
+        assert launch[1] > 256 and launch[1] % 256
+        print(f"  {case} pool={pool}", flush=True)
+        got = {}
+        for name in ("fkw", "split_f16"):
+            L.set_config(_variant(name))
+            got[name] = L.conv2d_ws(xt, bias, None, relu=pool, pool=pool).flatten(1)
+        a, b = got["fkw"], got["split_f16"]
+        assert torch.equal(torch.isnan(a), torch.isnan(b)) and torch.equal(a[torch.isinf(a)], b[torch.isinf(a)])
+        ok = torch.isfinite(a)
+        assert torch.equal(ok, torch.isfinite(b))
+        zero = torch.zeros_like(a)
+        worst = torch.where(ok, (a - b).abs(), zero).amax(1) / torch.where(ok, a.abs(), zero).amax(1).clamp(min=1e-30)
+        assert float(worst.max()) <= TOL, int(worst.argmax())
     L.close()
 
 
