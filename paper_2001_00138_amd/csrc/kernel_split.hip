@@ -771,15 +771,16 @@ static const SplitShape kSplitShapes[] = {
 };
 #undef PATDNN_SPLIT
 
-static int split_plan(const ConvShape& s, bool pair, SplitArgs& a)
+static int split_plan(const ConvShape& s, bool pair, bool narrow, SplitArgs& a)
 {
     a.steps = (s.c_in + 31) / 32;
     a.fblocks = (s.c_out + 63) / 64;
     for (const SplitShape& v : kSplitShapes) {
         // (half of the last shape's wavefronts idle for 64 filters: narrow images of many rows only)
-        if ((v.wf > 1) != (a.fblocks > 1) && &v != std::end(kSplitShapes) - 1) continue;
+        const bool last = &v == std::end(kSplitShapes) - 1;
+        if ((v.wf > 1) != (a.fblocks > 1) && !last) continue;
         const int pix = 16 * v.pn * v.wp;
-        if (!split_tiles(s, pix, 32, pair, a) && !split_tiles(s, pix, 16, pair, a)) continue;
+        if (narrow ? !(last && split_tiles(s, pix, 8, pair, a)) : !split_tiles(s, pix, 32, pair, a) && !split_tiles(s, pix, 16, pair, a)) continue;
         a.fsets = (a.fblocks + v.wf - 1) / v.wf;
         const long long total = (long long)a.strips * a.tiles * a.fsets;
         if (total > INT32_MAX / 2 || total * a.steps > INT32_MAX / 2) continue;
@@ -795,7 +796,8 @@ static bool split_pair_rows(const ConvShape& s, const void* in) { return s.w % 2
 bool split_cost(const ConvShape& s, int& rounds, int& steps, int& pixels)
 {
     SplitArgs a{};
-    const int shape = split_plan(s, false, a);
+    int shape = split_plan(s, false, false, a);
+    if (shape < 0 && s.pool) shape = split_plan(s, false, true, a);
     if (shape < 0) return false;
     rounds = (a.total + 255) / 256;
     steps = a.steps;
@@ -806,11 +808,13 @@ bool split_cost(const ConvShape& s, int& rounds, int& steps, int& pixels)
 // Number of the launch shape, twice, plus one with pairs; -1 where none fits.
 static int split_launch_plan(const ConvShape& s, const void* in, SplitArgs& a)
 {
-    for (const bool pair : {true, false}) {
-        if (pair && !split_pair_rows(s, in)) continue;
-        const int shape = split_plan(s, pair, a);
-        if (shape >= 0) return 2 * shape + pair;
-    }
+    // (rows two at a time stage more: narrow strips then, so that a pooled call runs the kernel that the plain one does)
+    for (const bool narrow : {false, true})
+        for (const bool pair : {true, false}) {
+            if ((pair && !split_pair_rows(s, in)) || (narrow && !s.pool)) continue;
+            const int shape = split_plan(s, pair, narrow, a);
+            if (shape >= 0) return 2 * shape + pair;
+        }
     return -1;
 }
 

@@ -743,15 +743,17 @@ patdnn_status_t upload_layer(patdnn_layer* h)
 constexpr size_t kMaxSliceFloats = (size_t)128 << 20;
 
 // `scratch_floats`: room for the partial sums of a split launch (0: no split candidates).  The
-// choice does not depend on fused pooling, so that a pooled output is the pooling of the plain one.
+// choice does not depend on fused pooling, so that a pooled output is the pooling of the plain one (to the last
+// bits only where the split kernel meets inputs far apart: its tiles then differ in what is worked out again).
 patdnn_config_t default_config(patdnn_layer* h, const ConvShape& shape, size_t scratch_floats)
 {
-    ConvShape s = shape;
+    ConvShape s = shape, pooled = shape;
     s.pool = 0;
+    pooled.pool = s.ho >= 2 && s.wo >= 2;
     if (h->L.depthwise) return patdnn_config_t{variant_of_extra(kExtraDepthwise), 0, 0, 1};
     if (h->dense_mfma && dense_fits(s)) return patdnn_config_t{variant_of_extra(kExtraDense), 0, 0, 1};
     patdnn_config_t best{PATDNN_VARIANT_FKW, 0, 0, 1};
-    const bool taps = taps_fit_layer(h) && taps_fit_input(s) && taps_fit_input(shape) && !h->taps.empty();
+    const bool taps = taps_fit_layer(h) && taps_fit_input(s) && taps_fit_input(pooled) && !h->taps.empty();
     double best_us = taps ? fkw_estimate(h, s) : 0.0;
     for (int vi : h->order) {
         const TiledVariant& v = tiled_variant(vi);
@@ -765,7 +767,7 @@ patdnn_config_t default_config(patdnn_layer* h, const ConvShape& shape, size_t s
     // the split kernel stands in for those two only: the tap-product kernel is the more exact one
     const auto or_split = [&](const patdnn_config_t& c) {
         int rounds = 0, steps = 0, pixels = 0;
-        if (!h->split || !split_cost(shape, rounds, steps, pixels) || !split_cost(s, rounds, steps, pixels)) return c;
+        if (!h->split || !split_cost(pooled, rounds, steps, pixels) || !split_cost(s, rounds, steps, pixels)) return c;
         const double other = taps ? best_us : c.variant == PATDNN_VARIANT_FKW ? fkw_estimate(h, s) : tiled2_estimate(h, s);
         // (the estimate of the stride-2 variant is the coarser one)
         if (split_estimate(rounds, steps, pixels) * (s.stride == 1 ? 1.03 : 1.15) > other) return c;

@@ -247,6 +247,18 @@ def test_not_finite_inputs(torch, c_out, h, stride, pool, share):
     assert not ok.any() or np.abs(a[ok] - b[ok]).max() <= TOL * max(np.abs(a[ok]).max(), 1e-30)
 
 
+@pytest.mark.parametrize("c_in,c_out,n,h,w", [(128, 64, 2, 54, 57), (64, 128, 8, 8, 55), (64, 64, 8, 37, 197), (128, 128, 2, 56, 56)])
+def test_pooled_output_is_the_pooling_of_the_plain_one(torch, c_in, c_out, n, h, w):
+    """The library's choice for a plain call and for a pooled one, whose tiles are cut differently."""
+    rng = np.random.default_rng(w)
+    _, L = _layer(rng, c_in, c_out, 1.0, 2)
+    x = torch.randn((n, c_in, h, w), device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    plain = L.conv2d_ws(x, None, relu=True)
+    pooled = L.conv2d_ws(x, None, relu=True, pool=True)
+    assert bool((pooled == torch.nn.functional.max_pool2d(plain, 2)).all())
+    L.close()
+
+
 # c_in, c_out, side, n, stride, keep; what is chosen
 CHOICES = [((128, 128, 56, 8, 2, 1 / 3.6), "split_f16"), ((64, 64, 56, 8, 2, 1 / 3.6), "t_g16_p4x1_s2_x16_th"),
            ((64, 64, 56, 2, 2, 0.6), "split_f16"), ((328, 125, 72, 47, 1, 0.5), "split_f16"), ((64, 64, 112, 32, 1, 1.0), "split_f16"),
