@@ -10,6 +10,9 @@
 //     for the matrix instruction of that step.  The value after the last tap is a one that meets the bias.
 //   * Workgroups stay and go on to further blocks, those of an XCD side by side, so that rows are read from
 //     memory by one L2; the inputs of the next block are loaded before this one is multiplied.
+//   * Where windows are pooled a block is eight of them, each in four neighbouring lanes, which store a fourth of the
+//     filters each (3 -> 64 at 224 x 224, 64 images, 168 us where atomics on a cleared output took 2383 and the
+//     vector ALU's kernel 1338; 4 -> 88 at 100 x 100, 32 images, 49, 420 and 257).
 //
 // What bounds it: the output's way to memory (3 -> 64 at 224 x 224, 64 images: 176 us, 4.9 TB/s, where the vector
 // ALU's kernel took 233), small launches the chain of loads, 28 steps of 64 cycles and stores (one image of it 10.5
@@ -26,16 +29,25 @@ struct DenseArgs {
     const float* weight;             // [c_out][c_in][9]
     const float* bias;
     float* out;
-    int32_t n, c_out, h, w, ho, wo, pad, relu, pool;
-    int32_t blocks, pixels;          // n * ho * wo, and blocks of 32 of them
-    FastDiv div_wo, div_plane;       // wo, ho * wo
+    int32_t n, c_out, h, w, pad, relu;
+    int32_t wo, oplane;              // columns and pixels of an output plane, or of a pooled one
+    int32_t blocks, pixels;          // those of all images (pooled: four times as many), and blocks of 32 of them
+    FastDiv div_wo, div_plane;       // wo, oplane
 };
 
 // Steps of two values: nine taps of every channel, and the bias.
 constexpr int dense_steps(int c_in) { return (9 * c_in + 2) / 2; }
 
 // STREAM: stores that leave nothing in the caches (see launch_dense; the compiler makes one of two kinds of store in one kernel).
-template <int C, int FM, int STRIDE, bool STREAM>
+enum DenseOut { kDensePlain, kDenseStream, kDensePool };
+// Each of a window's four lanes has its largest value afterwards.
+static __device__ __forceinline__ float dense_window(float v)
+{
+    v = fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xf, 0xf, true)));      // quad_perm [1,0,3,2]
+    return fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xf, 0xf, true)));   // quad_perm [2,3,0,1]
+}
+
+template <int C, int FM, int STRIDE, DenseOut OUT>
 __global__ __launch_bounds__(256) void dense_conv_kernel(DenseArgs a)
 {
     constexpr int K = 9 * C, STEPS = dense_steps(C);
@@ -67,7 +79,8 @@ __global__ __launch_bounds__(256) void dense_conv_kernel(DenseArgs a)
     }
 
     const size_t image = (size_t)C * plane;
-    const int oplane = a.ho * a.wo;
+    const int oplane = a.oplane;
+    constexpr int PER = OUT == kDensePool ? 4 : 1;    // lanes of an output pixel
     // blocks of a step of the whole grid: an XCD's eighth of them side by side
     const int per_xcd = gridDim.x >> 3, share = (a.blocks + 31) / 32 * 4;
     const bool whole = (gridDim.x & 7) == 0;
@@ -75,19 +88,23 @@ __global__ __launch_bounds__(256) void dense_conv_kernel(DenseArgs a)
     const int past = whole ? min(a.blocks, ((int)(blockIdx.x & 7) + 1) * share) : a.blocks;
     const int stride = whole ? per_xcd * 4 : (int)gridDim.x * 4;
 
-    // the lane's pixel of a block, and that pixel's inputs
+    // the lane's pixel of a block (or its window), and that pixel's inputs
     struct Pixel { int img0, img, at; };
     auto locate = [&](int block) __attribute__((always_inline)) -> Pixel {
-        const int q = min(block * 32 + l32, a.pixels - 1);
+        const int q = min(block * 32 + l32, a.pixels - 1) / PER;
         Pixel p;
-        p.img0 = (int)fast_div((uint32_t)(block * 32), a.div_plane);
+        p.img0 = (int)fast_div((uint32_t)(block * (32 / PER)), a.div_plane);
         p.img = (int)fast_div((uint32_t)q, a.div_plane);
         p.at = q - p.img * oplane;
         return p;
     };
     auto load = [&](int block, float (&x)[STEPS]) __attribute__((always_inline)) {
         const Pixel p = locate(block);
-        const int oy = (int)fast_div((uint32_t)p.at, a.div_wo), ox = p.at - oy * a.wo;
+        int oy = (int)fast_div((uint32_t)p.at, a.div_wo), ox = p.at - oy * a.wo;
+        if constexpr (OUT == kDensePool) {
+            oy = 2 * oy + (lane & 1);
+            ox = 2 * ox + (lane >> 1 & 1);
+        }
         const int y = oy * STRIDE - a.pad, xx = ox * STRIDE - a.pad;
         unsigned cols = 0, outside = 0;               // bit t: tap column, then tap, outside the image
 #pragma unroll
@@ -125,22 +142,22 @@ __global__ __launch_bounds__(256) void dense_conv_kernel(DenseArgs a)
         const Pixel p = locate(block);
         const bool ok = block * 32 + l32 < a.pixels;
         const int left = a.c_out - f0 - 4 * half;     // filters from this lane's first one on
-        if (a.pool) {
-            const int oy = (int)fast_div((uint32_t)p.at, a.div_wo), ox = p.at - oy * a.wo;
-            const int ph = a.ho >> 1, pw = a.wo >> 1;
-            const bool in = ok && (oy >> 1) < ph && (ox >> 1) < pw;
-            unsigned* const dst = reinterpret_cast<unsigned*>(a.out) +
-                                  (((size_t)p.img * a.c_out + f0 + 4 * half) * ph + (oy >> 1)) * pw + (ox >> 1);
+        char* const dst = reinterpret_cast<char*>(a.out + ((size_t)p.img0 * a.c_out + f0) * oplane);
+        const unsigned at = 4u * (((unsigned)(p.img - p.img0) * (unsigned)a.c_out + 4u * half) * (unsigned)oplane + (unsigned)p.at);
+        if constexpr (OUT == kDensePool) {
+            const int mine = lane & 3;                // registers 4 i + mine
 #pragma unroll
             for (int f = 0; f < FM; ++f)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int s = f * 32 + 8 * (r >> 2) + (r & 3);
-                    if (in && s < left) atomicMax(dst + (size_t)s * ph * pw, __float_as_uint(fmaxf(acc[f][r], 0.0f)));
+                for (int i = 0; i < 4; ++i) {
+                    float m[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) m[k] = dense_window(acc[f][4 * i + k]);
+                    const float v = fmaxf(mine < 2 ? mine ? m[1] : m[0] : mine == 2 ? m[2] : m[3], 0.0f);
+                    const int s = f * 32 + 8 * i + mine;
+                    if (ok && s < left) *reinterpret_cast<float*>(dst + (size_t)s * oplane * 4 + at) = v;
                 }
         } else {
-            char* const dst = reinterpret_cast<char*>(a.out + ((size_t)p.img0 * a.c_out + f0) * oplane);
-            const unsigned at = 4u * (((unsigned)(p.img - p.img0) * (unsigned)a.c_out + 4u * half) * (unsigned)oplane + (unsigned)p.at);
             auto store = [&](bool some) __attribute__((always_inline)) {
 #pragma unroll
                 for (int f = 0; f < FM; ++f)
@@ -150,7 +167,7 @@ __global__ __launch_bounds__(256) void dense_conv_kernel(DenseArgs a)
                         const float v = a.relu ? fmaxf(acc[f][r], 0.0f) : acc[f][r];
                         float* const to = reinterpret_cast<float*>(dst + (size_t)s * oplane * 4 + at);
                         if (some && s >= left) continue;
-                        if constexpr (STREAM) __builtin_nontemporal_store(v, to);
+                        if constexpr (OUT == kDenseStream) __builtin_nontemporal_store(v, to);
                         else *to = v;
                     }
             };
@@ -169,50 +186,56 @@ __global__ __launch_bounds__(256) void dense_conv_kernel(DenseArgs a)
 bool dense_fits(const ConvShape& s)
 {
     if (s.c_in > kDenseChannels || s.stride > 2) return false;
-    const long long oplane = (long long)s.ho * s.wo, between = std::min<long long>(s.n - 1, 31 / oplane + 1);
+    // (images that a block spans: the more where windows are pooled; both have to fit, so that both kinds of call
+    // run the same kernel)
+    const long long oplane = (long long)s.ho * s.wo, whole = std::max(1ll, (long long)(s.ho / 2) * (s.wo / 2) * 4);
+    const long long between = std::min<long long>(s.n - 1, 31 / std::min(oplane, whole) + 1);
     return (long long)s.n * oplane <= INT32_MAX - 64 && (between + 1) * s.c_in * s.h * s.w < (1ll << 29) &&
            (between + 1) * s.c_out * oplane < (1ll << 29) && s.c_out <= 32 * 65535;
 }
 
 template <int C, int FM, int STRIDE>
-static hipError_t launch_dense_t(const DenseArgs& a, bool stream_out, hipStream_t stream)
+static hipError_t launch_dense_t(const DenseArgs& a, DenseOut out, hipStream_t stream)
 {
     const unsigned sets = (unsigned)((a.c_out + 32 * FM - 1) / (32 * FM));
     // as many workgroups as their registers let a CU hold
     const unsigned most = std::max(8u, (C == 4 && FM == 2 ? 512u : 768u) / sets / 8 * 8);
     const unsigned grid = std::min((unsigned)((a.blocks + 3) / 4), most);
-    if (stream_out) hipLaunchKernelGGL((dense_conv_kernel<C, FM, STRIDE, true>), dim3(grid, sets), dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL((dense_conv_kernel<C, FM, STRIDE, false>), dim3(grid, sets), dim3(256), 0, stream, a);
+    if (out == kDensePool) hipLaunchKernelGGL((dense_conv_kernel<C, FM, STRIDE, kDensePool>), dim3(grid, sets), dim3(256), 0, stream, a);
+    else if (out == kDenseStream) hipLaunchKernelGGL((dense_conv_kernel<C, FM, STRIDE, kDenseStream>), dim3(grid, sets), dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((dense_conv_kernel<C, FM, STRIDE, kDensePlain>), dim3(grid, sets), dim3(256), 0, stream, a);
     return hipGetLastError();
 }
 template <int C>
-static hipError_t launch_dense_c(const DenseArgs& a, int stride, bool stream_out, hipStream_t stream)
+static hipError_t launch_dense_c(const DenseArgs& a, int stride, DenseOut out, hipStream_t stream)
 {
     // 64 filters at a time unless all fit in 32: what is read is read once more for the next ones
     const bool two = a.c_out > 32;
-    if (stride == 2) return two ? launch_dense_t<C, 2, 2>(a, stream_out, stream) : launch_dense_t<C, 1, 2>(a, stream_out, stream);
-    return two ? launch_dense_t<C, 2, 1>(a, stream_out, stream) : launch_dense_t<C, 1, 1>(a, stream_out, stream);
+    if (stride == 2) return two ? launch_dense_t<C, 2, 2>(a, out, stream) : launch_dense_t<C, 1, 2>(a, out, stream);
+    return two ? launch_dense_t<C, 2, 1>(a, out, stream) : launch_dense_t<C, 1, 1>(a, out, stream);
 }
 
 hipError_t launch_dense(const DevFkw& f, const ConvShape& s, const float* in, const float* bias, float* out, hipStream_t stream)
 {
     DenseArgs a{};
     a.in = in; a.weight = f.weight; a.bias = bias; a.out = out;
-    a.n = s.n; a.c_out = s.c_out; a.h = s.h; a.w = s.w; a.ho = s.ho; a.wo = s.wo;
-    a.pad = s.pad; a.relu = s.relu; a.pool = s.pool;
-    a.pixels = s.n * s.ho * s.wo;
+    a.n = s.n; a.c_out = s.c_out; a.h = s.h; a.w = s.w; a.pad = s.pad; a.relu = s.relu;
+    a.wo = s.pool ? s.wo / 2 : s.wo;
+    a.oplane = s.pool ? s.ho / 2 * a.wo : s.ho * s.wo;
+    a.pixels = s.n * a.oplane * (s.pool ? 4 : 1);
     // Beyond the 256 MB of the last-level cache, and where a block's stores are whole cache lines (3 -> 64 at 224 x 224, 64
     // images, 822 MB: 230 us without, 176 to 187 with; 4 -> 88 at 100 x 100, 32 images, 113 MB, 47 and 46; 4 -> 24 at 150 x 133,
     // 30 images, which are not whole lines, 27 and 37).
     const bool stream_out = (size_t)a.pixels * s.c_out * 4 > ((size_t)256 << 20) && s.ho * s.wo % 32 == 0 && (reinterpret_cast<uintptr_t>(out) & 127) == 0;
     a.blocks = (a.pixels + 31) / 32;
-    a.div_wo = make_fast_div((uint32_t)s.wo);
-    a.div_plane = make_fast_div((uint32_t)(s.ho * s.wo));
+    a.div_wo = make_fast_div((uint32_t)a.wo);
+    a.div_plane = make_fast_div((uint32_t)a.oplane);
+    const DenseOut kind = s.pool ? kDensePool : stream_out ? kDenseStream : kDensePlain;
     switch (s.c_in) {
-    case 1: return launch_dense_c<1>(a, s.stride, stream_out, stream);
-    case 2: return launch_dense_c<2>(a, s.stride, stream_out, stream);
-    case 3: return launch_dense_c<3>(a, s.stride, stream_out, stream);
-    case 4: return launch_dense_c<4>(a, s.stride, stream_out, stream);
+    case 1: return launch_dense_c<1>(a, s.stride, kind, stream);
+    case 2: return launch_dense_c<2>(a, s.stride, kind, stream);
+    case 3: return launch_dense_c<3>(a, s.stride, kind, stream);
+    case 4: return launch_dense_c<4>(a, s.stride, kind, stream);
     }
     return hipErrorInvalidValue;
 }

@@ -15,8 +15,8 @@ namespace patdnn {
 struct ConvShape {
     int32_t n, c_in, c_out, h, w, ho, wo, stride, pad, relu;
     // pool != 0: ReLU, then 2x2 max pooling with stride 2 (floor), fused into the epilogue.
-    // The output tensor is [n][c_out][ho/2][wo/2] and, for all kernels but the tap-product and the split
-    // one (whole windows in registers), must hold zeros when the kernel starts: every lane folds its values in
+    // The output tensor is [n][c_out][ho/2][wo/2] and, for all kernels but the tap-product, the split and the
+    // dense one (whole windows in registers), must hold zeros when the kernel starts: every lane folds its values in
     // with an unsigned integer atomic max on the float bits, which orders non-negative floats like the
     // floats themselves.
     int32_t pool = 0;

@@ -897,7 +897,8 @@ static ZeroRegion zero_need(const patdnn_config_t& c, const ConvShape& s, float*
     if (split && slices_fit(scratch, scratch_floats, c.ksplit, full)) return ZeroRegion{};   // stores only
     if (!s.pool) return split ? ZeroRegion{output, full} : ZeroRegion{};
     if (split) return ZeroRegion{scratch, full};
-    if (taps_filters(c.variant) || extra_variant(c.variant) == kExtraSplit) return ZeroRegion{};    // whole pooling windows in registers
+    if (taps_filters(c.variant) || extra_variant(c.variant) == kExtraSplit || extra_variant(c.variant) == kExtraDense)
+        return ZeroRegion{};                                      // whole pooling windows in registers
     return ZeroRegion{output, (size_t)s.n * s.c_out * (s.ho / 2) * (s.wo / 2)};
 }
 

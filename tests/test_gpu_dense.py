@@ -1,6 +1,6 @@
 """GPU parity of dense layers of few input channels on the fp32 matrix cores (csrc/kernel_dense.hip) where it can go
 wrong: every channel count, both strides, blocks of pixels that span images and are not full, filters around
-its sets, pooled windows, inputs that are not finite or subnormal - and where the library chooses it."""
+its sets, pooled windows (and their time), inputs that are not finite or subnormal - and where the library chooses it."""
 
 import ctypes
 
@@ -56,6 +56,9 @@ CASES = [
     (4, 130, 2, 40, 23, 1, 0),
     (3, 31, 1, 1, 50, 1, 1),
     (4, 96, 9, 112, 97, 1, 1),
+    (2, 5, 41, 3, 3, 1, 1),            # one window an image, eight images in a block
+    (3, 40, 30, 4, 5, 1, 1),
+    (1, 70, 11, 5, 9, 2, 1),
 ]
 
 
@@ -125,6 +128,29 @@ def test_other_layers_keep_their_kernels(torch):
     with pytest.raises(B.PatdnnError):
         L.set_config(_variant("dense_mfma"))
     L.close()
+
+
+@pytest.mark.parametrize("c_in,c_out,n,side", [(3, 64, 8, 224), (4, 88, 32, 100)])
+def test_pooled_is_no_slower_than_the_tiled_kernel(torch, c_in, c_out, n, side):
+    rng = np.random.default_rng(9)
+    _, L = _layer(rng, c_in, c_out, 1, 1)
+    x = torch.randn((n, c_in, side, side), device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    out = torch.empty((n, c_out, side // 2, side // 2), device="cuda")
+    us = {}
+    for _ in range(5):
+        for name in ("dense_mfma", "d_g16_p7x1_s1_x16"):
+            L.set_config(_variant(name))
+            L.conv2d_ws(x, None, out, relu=True, pool=True)
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(10):
+                L.conv2d_ws(x, None, out, relu=True, pool=True)
+            e1.record()
+            torch.cuda.synchronize()
+            us.setdefault(name, []).append(e0.elapsed_time(e1) * 100)
+    L.close()
+    print(us, flush=True)
+    assert min(us["dense_mfma"]) <= 1.1 * min(us["d_g16_p7x1_s1_x16"])
 
 
 def test_choice_is_no_less_exact(torch):
