@@ -637,7 +637,17 @@ bool dense_layer(const LayerHost& L)
     return true;
 }
 
-// Its time, microseconds: units of work one after the other, channel steps and stores of each.  (Fitted to 14 layers.)
+// Whether the dense kernel, which computes 32 filters whatever there are, is the library's choice: large launches of very
+// few filters are left to the kernels before it.  64 images of 224 x 224, us of this one, of the tiled one and of the
+// walk: 1 -> 1 44, 38, 27; 3 -> 2 80, 73, 72; 3 -> 4 82, 75, 132; 3 -> 8 82, 79, 235; 4 -> 8 and all of 16 filters even or ahead,
+// pooled 3 -> 8 at 150 x 150, 32 images, 23, 60, 81; at stride 2 3 -> 1 25, --, 18, 1 -> 2 even.  Below half a million pixels
+// all end within a microsecond.
+bool dense_pays(const ConvShape& s)
+{
+    return s.c_out > (s.stride == 1 ? 4 : 1) || (long long)s.n * s.ho * s.wo < 1 << 19;
+}
+
+// Split kernel, microseconds: units of work one after the other, channel steps and stores of each.  (Fitted to 14 layers.)
 double split_estimate(int rounds, int steps, int pixels)
 {
     return 8.0 + rounds * (3.9 * steps + (pixels == 64 ? 8.7 : 3.5));
@@ -751,7 +761,7 @@ patdnn_config_t default_config(patdnn_layer* h, const ConvShape& shape, size_t s
     s.pool = 0;
     pooled.pool = s.ho >= 2 && s.wo >= 2;
     if (h->L.depthwise) return patdnn_config_t{variant_of_extra(kExtraDepthwise), 0, 0, 1};
-    if (h->dense_mfma && dense_fits(s)) return patdnn_config_t{variant_of_extra(kExtraDense), 0, 0, 1};
+    if (h->dense_mfma && dense_fits(s) && dense_pays(s)) return patdnn_config_t{variant_of_extra(kExtraDense), 0, 0, 1};
     patdnn_config_t best{PATDNN_VARIANT_FKW, 0, 0, 1};
     const bool taps = taps_fit_layer(h) && taps_fit_input(s) && taps_fit_input(pooled) && !h->taps.empty();
     double best_us = taps ? fkw_estimate(h, s) : 0.0;

@@ -58,6 +58,87 @@ def test_choice_is_close_to_the_fastest(case):
     L.close()
 
 
+# Layers that the split kernel can run: c_in, c_out, n, h, w, stride, pad, kept kernels; us of the walk, the tiled kernel
+# (at stride 2 the one that the library would take), the tap-product kernel (0: none) and the split kernel.
+MEASURED_SPLIT = [
+    ((128, 128, 64, 56, 56, 2, 1, 4560), (900, 104, 0, 86)),
+    ((256, 256, 64, 28, 28, 2, 1, 18204), (662, 196, 0, 81)),
+    ((512, 512, 64, 14, 14, 2, 1, 72817), (1216, 403, 0, 77)),
+    ((128, 256, 16, 56, 56, 2, 1, 9102), (460, 89, 0, 48)),
+    ((256, 256, 1, 28, 28, 2, 1, 18204), (34, 161, 0, 39)),
+    ((64, 64, 8, 56, 56, 2, 1, 2048), (68, 63, 0, 18)),
+    ((96, 96, 32, 112, 112, 2, 1, 4608), (1192, 212, 0, 120)),
+    ((200, 400, 20, 30, 30, 2, 0, 40000), (471, 226, 0, 41)),
+    ((64, 32, 40, 100, 120, 2, 1, 2048), (642, 235, 0, 95)),
+    ((300, 40, 2, 33, 41, 2, 1, 6000), (65, 227, 0, 51)),
+    ((40, 24, 30, 60, 60, 2, 1, 960), (91, 50, 0, 30)),
+    ((120, 500, 1, 20, 20, 2, 1, 30000), (28, 114, 0, 32)),
+    ((64, 64, 32, 112, 112, 1, 1, 4096), (2154, 200, 213, 124)),
+    ((328, 125, 47, 72, 72, 1, 1, 20500), (7275, 725, 951, 519)),
+    ((120, 300, 10, 70, 55, 1, 1, 18000), (764, 123, 138, 112)),
+    ((150, 150, 8, 150, 150, 1, 1, 13500), (3001, 328, 400, 352)),
+    ((32, 64, 30, 112, 112, 1, 0, 2048), (942, 111, 124, 77)),
+    ((40, 400, 10, 100, 100, 1, 1, 16000), (1758, 207, 282, 196)),
+]
+
+
+@pytest.mark.parametrize("case", MEASURED_SPLIT)
+def test_split_choice_is_no_slower_than_what_it_stands_in_for(case):
+    (c_in, c_out, n, h, w, stride, pad, kept), (walk, tiled, taps, split) = case
+    rng = np.random.default_rng(kept)
+    mask = np.zeros(c_out * c_in, np.uint8)
+    mask[rng.permutation(mask.size)[:kept]] = 1
+    L = B.Layer(rng.standard_normal((c_out, c_in, 3, 3), dtype=np.float32), rng.integers(0, 8, (c_out, c_in), dtype=np.uint8),
+                mask.reshape(c_out, c_in), wl.pattern_library(wl.PATTERN_SEED), stride=stride, pad=pad, host_only=True)
+    L.set_config({B.patdnn_variant_name(v): v for v in range(B.patdnn_num_variants())}["split_f16"])       # can run it
+    L.set_config(-1)
+    choice = B.lib().patdnn_internal_choice
+    choice.argtypes = [ctypes.c_void_p] + [ctypes.c_int32] * 3 + [ctypes.c_size_t, ctypes.c_void_p]
+    cfg = B.Config()
+    assert choice(L.handle, n, h, w, 0, ctypes.byref(cfg)) == 0
+    name = B.patdnn_variant_name(cfg.variant)
+    us = split if name == "split_f16" else walk if name == "fkw" else taps if name.startswith("taps") else tiled
+    # the estimates are fitted to 10 %, and two runs differ by some per cent
+    assert us <= 1.15 * (tiled if stride == 2 else min(walk, tiled, taps)), name
+    L.close()
+
+
+# Dense layers of few channels: c_in, c_out, n, h, w, stride, pad; us of the walk, the tiled kernel (0: none at stride 2)
+# and the dense kernel.
+MEASURED_DENSE = [
+    ((3, 64, 64, 224, 224, 1, 1), (1699, 255, 180)),
+    ((3, 64, 1, 224, 224, 1, 1), (34, 17, 12)),
+    ((1, 1, 64, 224, 224, 1, 1), (27, 37, 41)),
+    ((3, 2, 64, 224, 224, 1, 1), (71, 73, 78)),
+    ((3, 4, 64, 224, 224, 1, 1), (130, 75, 82)),
+    ((3, 8, 64, 224, 224, 1, 1), (236, 79, 82)),
+    ((1, 16, 64, 224, 224, 1, 1), (325, 53, 51)),
+    ((4, 16, 7, 97, 131, 1, 0), (20, 18, 11)),
+    ((4, 88, 32, 100, 100, 1, 1), (287, 70, 47)),
+    ((3, 1, 64, 224, 224, 2, 1), (18, 0, 24)),
+    ((1, 2, 64, 224, 224, 2, 1), (17, 0, 14)),
+    ((3, 32, 64, 112, 112, 2, 1), (114, 0, 15)),
+    ((4, 130, 2, 40, 23, 1, 0), (11, 17, 11)),
+    ((1, 1, 16, 112, 112, 1, 1), (11, 11, 11)),
+    ((2, 512, 8, 56, 56, 1, 1), (106, 21, 17)),
+]
+
+
+@pytest.mark.parametrize("case", MEASURED_DENSE)
+def test_dense_choice_is_no_slower_than_what_it_stands_in_for(case):
+    (c_in, c_out, n, h, w, stride, pad), (walk, tiled, dense) = case
+    L = B.Layer(np.ones((c_out, c_in, 3, 3), np.float32), np.zeros((c_out, c_in), np.uint8), np.ones((c_out, c_in), np.uint8),
+                wl.pattern_library(wl.PATTERN_SEED), stride=stride, pad=pad, dense=True, host_only=True)
+    choice = B.lib().patdnn_internal_choice
+    choice.argtypes = [ctypes.c_void_p] + [ctypes.c_int32] * 3 + [ctypes.c_size_t, ctypes.c_void_p]
+    cfg = B.Config()
+    assert choice(L.handle, n, h, w, 0, ctypes.byref(cfg)) == 0
+    name = B.patdnn_variant_name(cfg.variant)
+    us = dense if name == "dense_mfma" else walk if name == "fkw" else tiled
+    assert us <= 1.05 * (tiled if stride == 1 else walk), name
+    L.close()
+
+
 # c_in, c_out, n, h, w, stride, pad, patterns, kept kernels, dense; us of the walk over the kept weights and
 # of the matrix kernel
 MEASURED_F16 = [
