@@ -76,6 +76,10 @@ typedef struct {
  *   out            receives the handle; set to NULL on failure
  * Weights outside a kernel's pattern and weights of removed kernels are ignored
  * (or rejected with PATDNN_STRICT).  A filter with no kept kernel is legal.
+ * On the device a layer also keeps its weights with the removed ones as zeros, up to 256 MB each: 18
+ * bytes per pair of input and output channel for patdnn_conv2d_f16 (not for depthwise layers), and 36
+ * for the "split_f16" kernel where that can run the layer (each filter keeps none or at least 18
+ * kernels, and at stride 1 four in ten of all are kept).
  */
 patdnn_status_t patdnn_encode(const patdnn_layer_desc_t* desc, const float* dense_weights,
                               const uint8_t* pattern_ids, const uint8_t* kernel_mask,

@@ -87,6 +87,7 @@ struct patdnn_layer {
     bool on_device = false;
     bool dense_mfma = false;                               // the kernel of dense layers of few channels runs this one
     bool split = false;                                    // the weights as pairs of binary16 numbers exist
+    std::vector<int32_t> split_filters;                    // of those
     int device = -1;
     DevFkw dfkw;
     // by (variant index, ck); dense variants use ck = 0
@@ -614,7 +615,8 @@ bool split_filters(const LayerHost& L, std::vector<int32_t>& out, float& seen)
 constexpr int kSplitKernels = 18;
 // At stride 1 it is slower than the others for less than about 0.4 of the kernels (128 -> 128 at 112 x 112, 64
 // images: 1/3.6 615 us against 560 when it still added without joins, one half 708 and 711; all of 64 -> 64 123 against 209).
-bool split_layer(const LayerHost& L)
+// `filters`, `seen`: see split_filters.
+bool split_layer(const LayerHost& L, std::vector<int32_t>& filters, float& seen)
 {
     if (L.depthwise || L.dense || L.kept == 0) return false;
     if (L.desc.stride == 1 && (double)L.kept / L.desc.c_out / L.desc.c_in < 0.4) return false;
@@ -622,8 +624,6 @@ bool split_layer(const LayerHost& L)
         const int32_t kernels = L.fkw.offset[s + 1] - L.fkw.offset[s];
         if (kernels && kernels < kSplitKernels) return false;
     }
-    std::vector<int32_t> filters;
-    float seen;
     return split_expanded_halves(L.desc.c_in, L.desc.c_out) <= kMaxExpandedHalves && split_filters(L, filters, seen);
 }
 
@@ -717,10 +717,9 @@ patdnn_status_t upload_layer(patdnn_layer* h)
         }
         up.add(dweight16, &dw_weight16);
     }
-    std::vector<int32_t> filters;
-    const size_t split = h->split && split_filters(h->L, filters, d.split_seen) ? split_expanded_halves(h->L.desc.c_in, h->L.desc.c_out) : 0;
+    const size_t split = h->split ? split_expanded_halves(h->L.desc.c_in, h->L.desc.c_out) : 0;
     const uint16_t* split16 = nullptr;
-    if (split) up.add(filters, &d.split_filters);
+    if (split) up.add(h->split_filters, &d.split_filters);
     size_t expanded = h->L.depthwise || !finite16 ? 0 : f16_expanded_halves(h->L.desc.c_in, h->L.desc.c_out);
     if (expanded > kMaxExpandedHalves) expanded = 0;
     // from a megabyte on by themselves, at the start of a page (512 -> 512 at 7 x 7, 64 images: 26.5 us, 27.2
@@ -822,7 +821,7 @@ patdnn_status_t patdnn_encode(const patdnn_layer_desc_t* desc, const float* dens
         std::string err;
         patdnn_status_t st = build_fkw(*desc, dense_weights, pattern_ids, kernel_mask, h->L, err);
         if (st != PATDNN_OK) return fail(st, err);
-        h->split = split_layer(h->L);
+        h->split = split_layer(h->L, h->split_filters, h->dfkw.split_seen);
         h->dense_mfma = dense_layer(h->L);
         if (!(desc->flags & PATDNN_HOST_ONLY)) {
             st = upload_layer(h.get());
