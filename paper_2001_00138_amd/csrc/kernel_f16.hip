@@ -39,10 +39,10 @@
 //     buffer where wavefronts split the channels, whose chunks are larger.
 //     The loads are left as they come until they are put into LDS: packing them where they are issued waited for
 //     memory once per unit (128 -> 128 at 56 x 56, 64 images 94 -> 81 us).
-//   * Weights are read from L2 in fragment order, 16 bytes per lane, some taps ahead; in the widest shape, eight
-//     wavefronts on 128 filters x 512 pixels, each fragment comes once per workgroup straight into LDS (147 KB a chunk
-//     and CU would come from L2 otherwise, 36 KB do).
-//   * Channel and bias of the filters wait in LDS for the epilogue, which waited for each in turn (79 -> 72 us).
+//   * Weights are read from L2 in fragment order, 16 bytes per lane, some taps ahead.  (Eight wavefronts on 128 filters x
+//     512 pixels with each fragment brought into LDS once were no faster at 392 workgroups, 77 us and 78, and up to a
+//     fifth slower where their last round is nearly empty: 128 -> 128 at 56 x 56, 42 images 74 us and 63, 84 images 116 and 96.)
+//   * Channel and bias of the filters wait in LDS for the epilogue, which waited for each in turn.
 //
 // What bounds it: 128 -> 128 at 56 x 56, 64 images (59 GFLOP with the zeros, 51 MB in and out) takes
 // 72 us on changing tensors, 0.8 PFLOP/s, where the walk over the kept weights took 1990; one image of 256 -> 256
@@ -53,7 +53,6 @@
 
 #include <algorithm>
 #include <atomic>
-#include <iterator>
 
 #include "kernels.hpp"
 
@@ -226,8 +225,6 @@ constexpr int f16_waves(int blocks, bool most) { return blocks >= 8 ? 2 : blocks
 
 // Taps whose weights are on their way, as the registers allow.
 constexpr int f16_hold(int blocks, int wk, bool pair) { return wk > 1 ? 9 : blocks >= 8 ? pair ? 5 : 3 : blocks >= 4 ? 3 : 4; }
-// Where eight wavefronts share the weights of a workgroup's filters, those travel through LDS.
-constexpr bool f16_weights_in_lds(int wf, int wp, int wk) { return wk == 1 && wf * wp == 8; }
 
 // Staging units whose loads are in flight while a chunk is computed: what the usual tiles have for a wavefront.
 constexpr int f16_ahead(int blocks, int wk, bool pair) { return pair ? blocks >= 8 ? 2 : 4 : wk > 1 ? 6 : 4; }
@@ -241,7 +238,6 @@ void f16_conv_kernel(F16Args a)
     extern __shared__ uint4 lds4[];
     constexpr int WAVES = WF * WP * WK, PIX = 32 * PN * WP, G8 = 2 * WK;
     constexpr int UPX = PAIR ? 2 : 1, AHEAD = f16_ahead(FM * PN, WK, PAIR), BUFS = f16_buffers(WK);
-    constexpr bool WLDS = f16_weights_in_lds(WF, WP, WK);
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wk = wave % WK, wp = wave / WK % WP, wf = wave / (WK * WP);
@@ -290,7 +286,7 @@ void f16_conv_kernel(F16Args a)
         base[p] = (img * a.vh + oy * a.conv_stride - vrow0) * a.pitch + sx * a.conv_stride + (a.lead - a.pad) + (2 * wk + half) * a.npp;
     }
     // channel and bias of the workgroup's filters, for the epilogue (which would wait for each by itself)
-    const int behind = max(a.npp * (BUFS * G8 * 16 + 4) + (WLDS ? 2 * WF * FM * 9 * 1024 : 0), WK > 1 ? WAVES * 4096 : 0);
+    const int behind = max(a.npp * (BUFS * G8 * 16 + 4), WK > 1 ? WAVES * 4096 : 0);
     int2* const slots = reinterpret_cast<int2*>(reinterpret_cast<char*>(lds4) + behind);
     for (int e = threadIdx.x; e < WF * FM * 32; e += 64 * WAVES) {
         const int s = fset * WF * FM * 32 + e;
@@ -364,27 +360,12 @@ void f16_conv_kernel(F16Args a)
         for (int f = 0; f < FM; ++f)
             wv[tap][f] = __builtin_bit_cast(half8, a.weights[((size_t)fb[f] * a.steps + min(step, a.steps - 1)) * (9 * 64) + tap * 64 + lane]);
     };
-    // ... or of a step, the fragments of all taps and filters shared out to the wavefronts, straight into LDS
-    uint4* const wlds = lds4 + BUFS * G8 * a.npp + a.npp / 4;
-    __amdgpu_buffer_rsrc_t wsrc = __builtin_amdgcn_make_buffer_rsrc((void*)a.weights, 0, (int)((unsigned)a.fblocks * (unsigned)a.steps * (9u * 1024u)), 0x00020000);
-    auto share_weights = [&](int step, int wbuf) __attribute__((always_inline)) {
-        for (int e = wave; e < WF * FM * 9; e += WAVES) {
-            const int block = min(fset * WF * FM + e / 9, a.fblocks - 1);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(wsrc, (__attribute__((address_space(3))) void*)(wlds + (wbuf * WF * FM * 9 + e) * 64), 16, lane * 16,
-                                                     ((block * a.steps + step) * 9 + e % 9) * 1024, 0, 0);
-        }
-    };
     fetch(0);
-    if constexpr (WLDS) {
-        share_weights(0, 0);
-    } else {
 #pragma unroll
-        for (int tap = 0; tap < HOLD; ++tap) weights(wk, tap);
-    }
+    for (int tap = 0; tap < HOLD; ++tap) weights(wk, tap);
     int buf = 0;
     for (int c0 = 0; c0 < 16 * a.steps; c0 += 16 * WK) {
         if (BUFS == 1 && c0) __syncthreads();         // everyone has left the previous chunk
-        if constexpr (WLDS) __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wavefront's share of the weights
 #pragma unroll
         for (int k = 0; k < AHEAD; ++k)
             if (wave + k * WAVES < units) store_unit(wave + k * WAVES, buf, ahead[k]);
@@ -401,49 +382,25 @@ void f16_conv_kernel(F16Args a)
         const bool more = c0 + 16 * WK < 16 * a.steps;
 #pragma unroll
         for (int p = 0; p < PN; ++p) pixels(0, p);
-        if constexpr (WLDS) {
-            const uint4* const wsh = wlds + (buf * WF + wf) * (FM * 9 * 64) + lane;
-            half8 w[2][FM];
-            auto shared = [&](int tap) __attribute__((always_inline)) {
+        if (HOLD == 9 && more) fetch(c0 + 16 * WK);
 #pragma unroll
-                for (int f = 0; f < FM; ++f) w[tap & 1][f] = __builtin_bit_cast(half8, wsh[(f * 9 + tap) * 64]);
-            };
-            shared(0);
-            if (more) share_weights(step + 1, buf ^ 1);
-            fetch(c0 + 16);
+        for (int tap = 0; tap < 9; ++tap) {
 #pragma unroll
-            for (int tap = 0; tap < 9; ++tap) {
-                if (tap < 8) shared(tap + 1);
-#pragma unroll
-                for (int p = 0; p < PN; ++p) {
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int f = 0; f < FM; ++f) acc[f][p] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[tap & 1][f], x[p], acc[f][p], 0, 0, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (tap < 8) pixels(tap + 1, p);
-                }
-            }
-        } else {
-            if (HOLD == 9 && more) fetch(c0 + 16 * WK);
-#pragma unroll
-            for (int tap = 0; tap < 9; ++tap) {
-#pragma unroll
-                for (int p = 0; p < PN; ++p) {
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int f = 0; f < FM; ++f) acc[f][p] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wv[tap][f], x[p], acc[f][p], 0, 0, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (tap < 8) pixels(tap + 1, p);
-                }
-                if (tap + HOLD < 9) weights(step, tap + HOLD);
-                else if (HOLD < 9) weights(step + WK, tap + HOLD - 9);
+            for (int p = 0; p < PN; ++p) {
                 __builtin_amdgcn_sched_barrier(0);
-                if (tap + HOLD == 8) fetch(c0 + 16 * WK);
-            }
-            if (HOLD == 9 && more)
 #pragma unroll
-                for (int tap = 0; tap < 9; ++tap) weights(step + WK, tap);
+                for (int f = 0; f < FM; ++f) acc[f][p] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wv[tap][f], x[p], acc[f][p], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (tap < 8) pixels(tap + 1, p);
+            }
+            if (tap + HOLD < 9) weights(step, tap + HOLD);
+            else if (HOLD < 9) weights(step + WK, tap + HOLD - 9);
+            __builtin_amdgcn_sched_barrier(0);
+            if (tap + HOLD == 8) fetch(c0 + 16 * WK);
         }
+        if (HOLD == 9 && more)
+#pragma unroll
+            for (int tap = 0; tap < 9; ++tap) weights(step + WK, tap);
         if (BUFS == 2) buf ^= 1;
     }
 
@@ -620,9 +577,8 @@ static hipError_t launch_f16_t(const F16Args& args, const ConvShape& s, long lon
 // multiply-adds, small ones reach more CUs, and wavefronts that split the channels shorten
 // the chain of the last layers of a network.  us per pass, largest to smallest shape (f2 p4, f2 p2,
 // f1 p2, then the splitting ones):
-//   128 -> 128 at 56x56, 64 images     94   99  103  147  188  232     (784 workgroups of the first; 81 since the loads are in
-//                                                                       flight; the widest shape 79, and 72 without the
-//                                                                       epilogue's waits)
+//   128 -> 128 at 56x56, 64 images     94   99  103  147  188  232     (784 workgroups of the first; 78 since the loads are in
+//                                                                       flight and the epilogue does not wait)
 //    64 ->  64 at 112x112, 8 images    32   34   23   29   34   57     (784 of the third; half of the first idle)
 //   128 -> 256 at 56x56 / 2, 16 images 37   32   47   58   83   --     (196 of the second)
 //   512 -> 512 at 7x7, 64 images      136  146   95   52   68   69     (784 of the fourth)
@@ -642,7 +598,6 @@ static const F16Shape kF16Shapes[] = {
     PATDNN_F16(1, 2, 1, 1, 4, 400, false),
     PATDNN_F16(1, 1, 1, 1, 8, 0, false),
     PATDNN_F16(1, 1, 1, 1, 4, 0, false),
-    PATDNN_F16(2, 4, 2, 4, 1, 256, false),
 };
 #undef PATDNN_F16
 
@@ -657,9 +612,7 @@ static F16Plan f16_plan(const ConvShape& s, bool pair, F16Args& a)
     F16Plan plan;
     a.steps = (s.c_in + 15) / 16;
     a.fblocks = (s.c_out + 31) / 32;
-    constexpr int count = (int)std::size(kF16Shapes);
-    for (int i = 0; i < count; ++i) {
-        const F16Shape& v = kF16Shapes[i ? i - 1 : count - 1];    // the widest one, the last, first
+    for (const F16Shape& v : kF16Shapes) {
         const int filters = v.fm * v.wf;
         if (filters >= 2 * a.fblocks) continue;                   // half of every workgroup idle
         if (v.strided && s.stride == 1) continue;
@@ -667,8 +620,7 @@ static F16Plan f16_plan(const ConvShape& s, bool pair, F16Args& a)
         if (!f16_tiles(s, 32 * v.pn * v.wp, pair, a)) continue;
         a.fsets = (a.fblocks + filters - 1) / filters;
         plan.blocks = (long long)a.strips * a.tiles * a.fsets;
-        plan.lds = std::max((size_t)a.npp * (f16_buffers(v.wk) * 2 * v.wk * 16 + 4) + (f16_weights_in_lds(v.wf, v.wp, v.wk) ? 2 * filters * 9 * 1024 : 0),
-                            v.wk > 1 ? (size_t)v.wf * v.wp * v.wk * 4096 : 0) + (size_t)filters * 32 * 8;
+        plan.lds = std::max((size_t)a.npp * (f16_buffers(v.wk) * 2 * v.wk * 16 + 4), v.wk > 1 ? (size_t)v.wf * v.wp * v.wk * 4096 : 0) + (size_t)filters * 32 * 8;
         if (plan.blocks < v.min_blocks || plan.blocks > INT32_MAX || plan.lds > 160 * 1024) continue;
         plan.shape = (int)(&v - kF16Shapes);
         break;
