@@ -226,8 +226,14 @@ constexpr int f16_waves(int blocks, bool most) { return blocks >= 8 ? 2 : blocks
 // Taps whose weights are on their way, as the registers allow.
 constexpr int f16_hold(int blocks, int wk, bool pair) { return wk > 1 ? 9 : blocks >= 8 ? pair ? 5 : 3 : blocks >= 4 ? 3 : 4; }
 
-// Staging units whose loads are in flight while a chunk is computed: what the usual tiles have for a wavefront.
-constexpr int f16_ahead(int blocks, int wk, bool pair) { return pair ? blocks >= 8 ? 2 : 4 : wk > 1 ? 6 : 4; }
+// Staging units whose loads are in flight while a chunk is computed: what the smaller tiles have for a wavefront, since
+// those out of range cost as much as the others (four pairs, six pixels where wavefronts split the channels: 20 images of
+// 200 -> 60 at 25 x 25 33 us for 22, 52 of 453 -> 108 at 16 x 16 46 for 33, 22 of 151 -> 260 at 24 x 26 30 for 22), and with two
+// blocks, nine taps' weights and more of them a SIMD holds two wavefronts for three (28 of 280 -> 78 at 23 x 23 33 us for 28).
+constexpr int f16_ahead(int blocks, int wk, bool pair) { return pair || (wk == 4 && blocks == 2) ? 2 : 4; }
+// Where those that a wavefront does not have are branched around (20 images of 29 -> 239 at 36 x 36 15.6 us for 16.1, 20 of
+// 32 -> 56 at 79 x 79 16.8 for 19.2; the others are slower for it: the loads of large tiles would end in the branches).
+constexpr bool f16_branches(int blocks, int wk) { return wk == 1 && blocks == 2; }
 
 // PAIR: rows of whole aligned pairs of pixels (see f16_tiles): staged two pixels per load, and
 // stored two pixels at a time where the output's rows are the same.
@@ -345,11 +351,12 @@ void f16_conv_kernel(F16Args a)
     unsigned off_ahead[AHEAD];
 #pragma unroll
     for (int k = 0; k < AHEAD; ++k) off_ahead[k] = wave + k * WAVES < units ? voffs[(wave + k * WAVES) / G8 * 64 + lane] : ~0u;
-    // no branches, which the loads would have to end in: where there is nothing more to fetch they are out of range
+    // where there is nothing more to fetch the loads are out of range
     auto fetch = [&](int c0) __attribute__((always_inline)) {
         const unsigned none = c0 < 16 * a.steps ? 0u : ~0u;
 #pragma unroll
-        for (int k = 0; k < AHEAD; ++k) ahead[k] = load_unit(wave + k * WAVES, (int)(off_ahead[k] | none), c0);
+        for (int k = 0; k < AHEAD; ++k)
+            if (!f16_branches(FM * PN, WK) || wave + k * WAVES < units) ahead[k] = load_unit(wave + k * WAVES, (int)(off_ahead[k] | none), c0);
     };
     // weights of a tap; loads come back in the order in which they were issued, so those of a step are all issued
     // before the next chunk's inputs, and the next step's first ones after them
