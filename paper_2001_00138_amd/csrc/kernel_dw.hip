@@ -413,10 +413,15 @@ static hipError_t launch_dw_t(const DevFkw& f, const T* weights, const ConvShape
     // stride 2, binary16: 11.0 us, 11.3 with planes in LDS)
     if (!vec && launch_dw_planes<T>(f, s, in, bias, out, stream)) return hipGetLastError();
     const dim3 grid((unsigned)blocks), block(256);
-    // fp32 outputs beyond half of the 32 MB that the L2s hold leave nothing there, and the inputs more room: 144 channels of
-    // 56x56, 64 images 64.4 -> 60.4 us, 96 of 112x112, 32 images 84 -> 80, 144 of 112x112 / 2, 64 images 122 -> 119, 16 images of
-    // the first (29 MB) 15.5 -> 14.5
-    const bool stream_out = sizeof(T) == 4 && (size_t)s.n * s.c_out * s.ho * s.wo * sizeof(T) > ((size_t)16 << 20);
+    // fp32 outputs that leave nothing in the L2s, and the inputs more room: where both tensors are at most twice the 32 MB of
+    // those, and where what this layer and the next one touch exceeds the 256 MB of the last-level cache anyway.  Between
+    // them the next layer would find its input there.  us without and with such stores, alone and followed by a layer that
+    // reads the output: 144 channels of 56 x 56, 30 MB of output 16.3 and 14.1, 33.8 both; 60 MB 26 both, 52.7 and 58.8; 115 MB
+    // on changing tensors 63.3 and 59.4, 120 MB and the next one 112 and 108; 240 MB 127 and 88, 256 and 245.  144 channels of
+    // 112 x 112 / 2, 30 MB 28 both, 44.5 and 46.2; 60 MB 60.9 and 48.4, 91.8 and 84.9.
+    const size_t in_bytes = (size_t)s.n * s.c_out * s.h * s.w * sizeof(T), out_bytes = (size_t)s.n * s.c_out * s.ho * s.wo * sizeof(T);
+    constexpr size_t kMB = (size_t)1 << 20;
+    const bool stream_out = sizeof(T) == 4 && out_bytes > 16 * kMB && (in_bytes + out_bytes <= 64 * kMB || in_bytes + 2 * out_bytes > 256 * kMB);
 #define PATDNN_DW_LAUNCH(S, NP, V, W) \
     if (W && stream_out) hipLaunchKernelGGL((dw_conv_kernel<S, NP, V, W, T, W && sizeof(T) == 4>), grid, block, 0, stream, a); \
     else hipLaunchKernelGGL((dw_conv_kernel<S, NP, V, W, T, false>), grid, block, 0, stream, a)

@@ -10,8 +10,10 @@ from paper_2001_00138_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 
-# images, channels, h, w, stride; outputs above and, image by image, below 16 MB
-@pytest.mark.parametrize("n,c,h,w,stride", [(12, 144, 56, 56, 1), (12, 144, 57, 60, 1), (12, 144, 112, 112, 2), (12, 144, 112, 119, 2)])
+# images, channels, h, w, stride; outputs above and, image by image, below 16 MB: both tensors of up to 64 MB, of more, and
+# too large for the last-level cache
+@pytest.mark.parametrize("n,c,h,w,stride", [(12, 144, 56, 56, 1), (12, 144, 57, 60, 1), (12, 144, 112, 112, 2), (12, 144, 112, 119, 2),
+                                            (32, 144, 56, 56, 1), (50, 144, 57, 60, 1), (26, 144, 112, 112, 2), (26, 144, 112, 119, 2)])
 def test_large_outputs(n, c, h, w, stride):
     import torch
     if not torch.cuda.is_available():
