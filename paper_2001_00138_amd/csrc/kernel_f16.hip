@@ -224,7 +224,7 @@ static __device__ __forceinline__ void f16_again(unsigned odd, int wave)
 constexpr int f16_waves(int blocks, bool most) { return blocks >= 8 ? 2 : blocks >= 4 ? 3 : !most ? 2 : blocks >= 2 ? 5 : 6; }
 
 // Taps whose weights are on their way, as the registers allow.
-constexpr int f16_hold(int blocks, int wk, bool pair) { return wk > 1 ? 9 : blocks >= 8 ? pair ? 5 : 3 : blocks >= 4 ? 3 : 4; }
+constexpr int f16_hold(int blocks, int wk) { return wk > 1 ? 9 : blocks >= 4 ? 3 : 4; }
 
 // Staging units whose loads are in flight while a chunk is computed: what the smaller tiles have for a wavefront, since
 // those out of range cost as much as the others (four pairs, six pixels where wavefronts split the channels: 20 images of
@@ -360,7 +360,7 @@ void f16_conv_kernel(F16Args a)
     };
     // weights of a tap; loads come back in the order in which they were issued, so those of a step are all issued
     // before the next chunk's inputs, and the next step's first ones after them
-    constexpr int HOLD = f16_hold(FM * PN, WK, PAIR);
+    constexpr int HOLD = f16_hold(FM * PN, WK);
     half8 wv[9][FM];
     auto weights = [&](int step, int tap) __attribute__((always_inline)) {
 #pragma unroll
