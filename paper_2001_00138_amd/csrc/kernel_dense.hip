@@ -14,7 +14,7 @@
 //     filters each (3 -> 64 at 224 x 224, 64 images, 168 us where atomics on a cleared output took 2383 and the
 //     vector ALU's kernel 1338; 4 -> 88 at 100 x 100, 32 images, 49, 420 and 257).
 //
-// What bounds it: the output's way to memory (3 -> 64 at 224 x 224, 64 images: 176 us, 4.9 TB/s, where the vector
+// What bounds it: the output's way to memory (3 -> 64 at 224 x 224, 64 images: 165 to 176 us, 5 TB/s, where the vector
 // ALU's kernel took 233), small launches the chain of loads, 28 steps of 64 cycles and stores (one image of it 10.5
 // us for 15.9; 4 -> 88 at 100 x 100, 32 images, 44 to 51 for 69; 3 -> 32 at 112 x 112 / 2, 64 images, 13.4 where the walk over
 // the weights took 117).  Errors against 64 bits are those of the kernels before (9.35e-8 of the result's norm).

@@ -16,7 +16,7 @@
 // weight, and with which sign, and then the sum over the finite inputs (kept weights that
 // are zero are stored as -0, so that they can be told from the removed ones).  Layers with a weight
 // that is not finite in binary16 run the walk over the kept weights instead.
-// 128 -> 128 at 56 x 56, 64 images: 72 us with finite inputs, 1060 with one infinity in ten thousand
+// 128 -> 128 at 56 x 56, 64 images: 76 us with finite inputs, 1060 with one infinity in ten thousand
 // inputs, 1700 with nothing but NaN; one lane after the other walking the FKW arrays for its own
 // pixels took 19400 and 23800, the walk over the whole layer takes 2000.
 //
@@ -45,9 +45,9 @@
 //   * Channel and bias of the filters wait in LDS for the epilogue, which waited for each in turn.
 //
 // What bounds it: 128 -> 128 at 56 x 56, 64 images (59 GFLOP with the zeros, 51 MB in and out) takes
-// 72 us on changing tensors, 0.8 PFLOP/s, where the walk over the kept weights took 1990; one image of 256 -> 256
-// at 28 x 28 9 us (57).  392 workgroups are one and a half rounds of 256 CUs, LDS is read for three quarters of the
-// time that the matrix cores need, and the epilogue's stores and a tile's first loads are hidden by nothing.  (Inputs two
+// 76 us on changing tensors, 0.8 PFLOP/s, where the walk over the kept weights took 1990; one image of 256 -> 256
+// at 28 x 28 9 us (57).  784 workgroups, two on a CU, are one and a half rounds, the matrix cores are busy 43 % of the SIMDs'
+// cycles, LDS 25 % of the CUs', and the epilogue's stores and a tile's first loads are hidden by nothing.  (Inputs two
 // chunks ahead: 84 us; what is in flight is enough.)
 #include <hip/hip_fp16.h>
 

@@ -4,7 +4,7 @@
 // is left, which are kept multiplied with 2^11 so that they have the same range.  Of the product of two such
 // pairs three parts matter,
 //     w x = w.high x.high + (w.high x.low + w.low x.high) / 2^11,
-// each exact in fp32, and v_mfma_f32_16x16x32_f16 does 16384 of their multiply-adds in 16 cycles where the vector
+// each exact in fp32, and v_mfma_f32_16x16x32_f16 does 8192 of their multiply-adds in 16 cycles where the vector
 // ALU does 64 in 4: even with the removed weights as zeros (a layer is expanded to all nine taps at encode time)
 // and three products for one that is less work than the vector kernels' for layers that keep half of their kernels,
 // and at stride 2, where those leave lanes idle.
@@ -27,14 +27,16 @@
 //     cores work on a fourth; a barrier per step.  The matrix instructions leave the vector ALU to the other wavefront, and
 //     loads of weights (from L2 in fragment order, a tap ahead) do not wait behind those of the inputs.
 //   * The sums of a step's 32 channels start from zero and join those of the steps before at its end: fewer roundings
-//     at the size of the whole (128 -> 128, kept 1/3.6: error against 64 bits 11.2e-8, 15.1e-8 in one sum; 98 -> 101 us).  Nine
+//     at the size of the whole (128 -> 128 at 56 x 56 / 2, kept 1/3.6: error against 64 bits 11.2e-8, 15.1e-8 in one sum; 98 -> 101 us on changing tensors).  Nine
 //     taps of 32 filters, then nine of the other 32, so that only half of the step's sums are held.
 //   * Sums that are not finite, or too small for the scale, are worked out again from the tensor (see split_again).
 //
-// What bounds it: the matrix cores are busy 60 to 75 % of a computing wavefront's steps, and wait for its stores
-// (some 9000 cycles a tile).  us, the vector kernels' -> this one's: 128 -> 128 at 56 x 56 / 2, 64 images, kept 1/3.6 105 -> 85;
-// 256 -> 256 at 28 x 28 / 2 198 -> 77, one half kept, 128 -> 128 at 112 x 112 / 1, 64 images, 960 -> 610; 232 -> 96 at 95 x 95 / 2, three
-// images, all kept 411 -> 41.
+// What bounds it, 128 -> 128 at 56 x 56 / 2, 64 images: the tiles of 64 pixels that its strips allow are 784 units of work,
+// three rounds of 256 CUs and a fourth of 16; the matrix cores are busy 27 % of all SIMDs' cycles (two wavefronts of a
+// SIMD's time are one that computes and one that stages), LDS 26 % of the CUs', half of that conflicts of windows two pixels
+// apart.  us, the vector kernels' -> this one's, on tensors in the last-level cache: that layer, kept 1/3.6, 99 -> 86 (114 ->
+// 101 on changing ones); 256 -> 256 at 28 x 28 / 2 196 -> 81; 64 -> 64 at 112 x 112 / 1, 32 images, all kept 200 -> 124; 232 -> 96 at
+// 95 x 95 / 2, three images, all kept 428 -> 46.
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
