@@ -130,6 +130,22 @@ def test_other_layers_keep_their_kernels(torch):
     L.close()
 
 
+@pytest.mark.parametrize("c_in,c_out,n,h,w,stride", [(3, 64, 3, 57, 41, 1), (4, 40, 2, 64, 64, 2), (1, 3, 9, 5, 7, 1)])
+def test_pooled_output_is_the_pooling_of_the_plain_one(torch, c_in, c_out, n, h, w, stride):
+    """Bit for bit, and windows with NaN and infinities as the maximum after a ReLU has them."""
+    rng = np.random.default_rng(w)
+    _, L = _layer(rng, c_in, c_out, stride, 1)
+    x = rng.standard_normal((n, c_in, h, w)).astype(np.float32)
+    kind = rng.random(x.shape)
+    x[kind < 0.01] = np.nan
+    x[kind < 0.005] = np.inf
+    xt, bias = torch.from_numpy(x).cuda(), torch.from_numpy(rng.standard_normal(c_out).astype(np.float32)).cuda()
+    plain, pooled = L.conv2d_ws(xt, bias, relu=True), L.conv2d_ws(xt, bias, relu=True, pool=True)
+    L.close()
+    assert not bool(torch.isnan(plain).any())         # a ReLU makes a zero of a NaN
+    assert bool((pooled == torch.nn.functional.max_pool2d(plain, 2)).all())
+
+
 @pytest.mark.parametrize("c_in,c_out,n,side", [(3, 64, 8, 224), (4, 88, 32, 100)])
 def test_pooled_is_no_slower_than_the_tiled_kernel(torch, c_in, c_out, n, side):
     rng = np.random.default_rng(9)
