@@ -298,6 +298,8 @@ patdnn_status_t patdnn_get_config(patdnn_handle_t h, patdnn_config_t* cfg);
 /*
  * Parameter auto-tuning (section 5.5), reduced to an exhaustive timed search over
  * the variants and launch parameters that can run this layer at this input size.
+ * (At stride 1 "split_f16" is among them where the library would choose it by itself; the
+ * tap-product kernel, which it would displace elsewhere, is the more exact one.)
  * Runs every candidate on the caller's buffers (a few runs each; the fastest four again in
  * alternating turns, judged by the median of their turns; output ends up holding a valid
  * result of the winner), synchronises the stream, keeps the fastest in the handle and
