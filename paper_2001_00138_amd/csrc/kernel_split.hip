@@ -27,14 +27,14 @@
 //     cores work on a fourth; a barrier per step.  The matrix instructions leave the vector ALU to the other wavefront, and
 //     loads of weights (from L2 in fragment order, a tap ahead) do not wait behind those of the inputs.
 //   * The sums of a step's 32 channels start from zero and join those of the steps before at its end: fewer roundings
-//     at the size of the whole (128 -> 128 at 56 x 56 / 2, kept 1/3.6: error against 64 bits 11.2e-8, 15.1e-8 in one sum; 98 -> 101 us on changing tensors).  Nine
-//     taps of 32 filters, then nine of the other 32, so that only half of the step's sums are held.
+//     at the size of the whole (128 -> 128 at 56 x 56 / 2, kept 1/3.6: error against 64 bits 11.2e-8, 15.1e-8 in one sum;
+//     98 -> 101 us on changing tensors).  Nine taps of 32 filters, then nine of the other 32, so that only half of
+//     the step's sums are held.
 //   * Sums that are not finite, or too small for the scale, are worked out again from the tensor (see split_again).
 //
 // What bounds it, 128 -> 128 at 56 x 56 / 2, 64 images: the tiles of 64 pixels that its strips allow are 784 units of work,
-// three rounds of 256 CUs and a fourth of 16; the matrix cores are busy 27 % of all SIMDs' cycles (two wavefronts of a
-// SIMD's time are one that computes and one that stages), LDS 26 % of the CUs', half of that conflicts of windows two pixels
-// apart.  us, the vector kernels' -> this one's, on tensors in the last-level cache: that layer, kept 1/3.6, 99 -> 86 (114 ->
+// three rounds of 256 CUs and a fourth of 16; the matrix cores are busy 27 % of the SIMDs' cycles, LDS 26 % of the
+// CUs', half of that conflicts of windows two pixels apart.  us, the vector kernels' -> this one's, on tensors in the last-level cache: that layer, kept 1/3.6, 99 -> 86 (114 ->
 // 101 on changing ones); 256 -> 256 at 28 x 28 / 2 196 -> 81; 64 -> 64 at 112 x 112 / 1, 32 images, all kept 200 -> 124; 232 -> 96 at
 // 95 x 95 / 2, three images, all kept 428 -> 46.
 #include <hip/hip_fp16.h>
