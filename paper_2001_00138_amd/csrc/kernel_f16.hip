@@ -40,8 +40,9 @@
 //     The loads are left as they come until they are put into LDS: packing them where they are issued waited for
 //     memory once per unit (128 -> 128 at 56 x 56, 64 images 94 -> 81 us).
 //   * Weights are read from L2 in fragment order, 16 bytes per lane, some taps ahead.  (Eight wavefronts on 128 filters x
-//     512 pixels with each fragment brought into LDS once were no faster at 392 workgroups, 77 us and 78, and up to a
-//     fifth slower where their last round is nearly empty: 128 -> 128 at 56 x 56, 42 images 74 us and 63, 84 images 116 and 96.)
+//     512 pixels with each fragment brought into LDS once were even at 385 to 512 workgroups on resident tensors, 4 % ahead
+//     on changing ones and for 512 channels, and 10 to 20 % slower at other numbers: 128 -> 128 at 56 x 56, 42 images 74 us
+//     and 62, 84 images 110 and 92, 120 images 122 and 110.)
 //   * Channel and bias of the filters wait in LDS for the epilogue, which waited for each in turn.
 //
 // What bounds it: 128 -> 128 at 56 x 56, 64 images (59 GFLOP with the zeros, 51 MB in and out) takes
