@@ -424,7 +424,7 @@ void build_taps(const LayerHost& L, int ck, const std::vector<int32_t>& members,
     T.num_groups = (c_out + G - 1) / G;
     T.num_chunks = (c_in + ck - 1) / ck;
     T.slot_channel.assign((size_t)T.num_groups * G, -1);
-    T.chunk_ptr.assign((size_t)T.num_groups * T.num_chunks, 0);
+    T.chunk_ptr.assign((size_t)T.num_groups * T.num_chunks * kTapStarts, 0);
     // at most: every kernel, an end for every filter and chunk, every batch filled up
     T.records.resize((size_t)L.kept + (size_t)T.num_groups * T.num_chunks * (G + kTapBatch) + 2 * kTapBatch);
     T.weights.resize(4 * T.records.size());
@@ -442,9 +442,10 @@ void build_taps(const LayerHost& L, int ck, const std::vector<int32_t>& members,
         for (int p = 0; p < P; ++p) next[(size_t)s * P + p] = f.offset[s] + f.stride[(size_t)s * (P + 1) + p];
     for (int g = 0; g < T.num_groups; ++g)
         for (int chunk = 0; chunk < T.num_chunks; ++chunk) {
-            T.chunk_ptr[(size_t)g * T.num_chunks + chunk] = (uint32_t)(count / kTapBatch);
             const int c0 = chunk * ck, c1 = c0 + ck;
             for (int slot = 0; slot < G; ++slot) {
+                if (slot % (G / kTapStarts) == 0)
+                    T.chunk_ptr[((size_t)g * T.num_chunks + chunk) * kTapStarts + slot / (G / kTapStarts)] = (uint32_t)count;
                 const int s = members[(size_t)g * G + slot];
                 const size_t before = count;
                 for (int p = 0; s >= 0 && p < P; ++p) {

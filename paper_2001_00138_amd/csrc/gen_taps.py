@@ -35,24 +35,37 @@ GROUP = 8                      # filters of one stream
 TILE = 16                      # rows and columns of a tile
 FLUSH_BYTES = 256              # bytes per flush block (one per pattern, and an empty one)
 END_BYTES = 512                # bytes per end-of-filter block
-AHEAD = 3                      # kernels whose pixels are on their way from LDS
 
 # scalar registers
 REC = (36, 52)                 # two sets of 16 records
 BASE, TGT, RET, RET2, ENDP, SP, WP, TMP = 68, 70, 72, 74, 76, 78, 80, 82
 S_CLOBBER = (36, 82)
-# vector registers, relative to vbase
-D, X, A, P, ADDR = 0, 16, 32, 34, 52
-V_COUNT = 53
+# vector registers, relative to vbase; behind the pixels' quads come A, P and ADDR
+D, X = 0, 16
 
 
-def program(F, vbase):
+def buffers(ahead):
+    """Quads for pixels, those on their way and one that the matrix cores still read: a power of two, since the
+    bodies of a batch of 16 kernels have theirs fixed."""
+    return 1 << ahead.bit_length()
+
+
+def registers(ahead):
+    """First of A, P and ADDR, and the number of all."""
+    a = X + 4 * buffers(ahead)
+    return a, a + 2, a + 20, a + 21
+
+
+def program(F, vbase, ahead):
     """Assembly lines.  Operands: %[o<f>_<r>] output rows of filter f (r = 0..3), %[lane] LDS byte
     address of the lane's 16 bytes in channel 0 (16 * lane: the chunk starts at LDS address 0),
-    %[rec] / %[wp] addresses of the first batch's records / weights, %[first] first of the
-    GROUP filters whose stream this is."""
+    %[rec] / %[wp] addresses of the first kernel's record / weights, %[first] first of the
+    GROUP filters whose stream this is (0 where a wavefront has fewer).  ``ahead``: kernels whose pixels are on
+    their way from LDS."""
     lines = []
     asm = lines.append
+    group, nbuf = min(F, GROUP), buffers(ahead)
+    A, P, ADDR, _ = registers(ahead)
 
     def v(i):
         return f"v{vbase + i}"
@@ -98,7 +111,7 @@ def program(F, vbase):
     for i in range(18):
         asm(f"v_mov_b32 {v(P + i)}, 0")
     asm("s_waitcnt lgkmcnt(0)")
-    for k in range(AHEAD):
+    for k in range(ahead):
         read_pixels(REC[0] + k, k)
     asm("s_branch .Lk0_0_first_%=")
 
@@ -108,15 +121,15 @@ def program(F, vbase):
         if k == 0:
             asm("s_waitcnt vmcnt(0)")                # this batch's weights
             fetch(1 - st)                            # the next batch
-        nxt = k + AHEAD
+        nxt = k + ahead
         if nxt == 16:
             asm("s_waitcnt lgkmcnt(0)")              # the next batch's records
-        read_pixels(REC[st] + nxt if nxt < 16 else REC[1 - st] + nxt - 16, nxt % 4)
+        read_pixels(REC[st] + nxt if nxt < 16 else REC[1 - st] + nxt - 16, nxt % nbuf)
         # LDS reads complete in order; a scalar load still in flight only makes this wait stricter
-        asm(f"s_waitcnt lgkmcnt({AHEAD})")
+        asm(f"s_waitcnt lgkmcnt({ahead})")
         for r in range(4):
             c = "0" if first else v4(D + 4 * r)
-            asm(f"v_mfma_f32_4x4x1_16b_f32 {v4(D + 4 * r)}, {v(A + st)}, {v(X + 4 * (k % 4) + r)}, {c} cbsz:4 abid:{k}")
+            asm(f"v_mfma_f32_4x4x1_16b_f32 {v4(D + 4 * r)}, {v(A + st)}, {v(X + 4 * (k % nbuf) + r)}, {c} cbsz:4 abid:{k}")
         asm(f"s_cmp_lt_i32 s{REC[st] + k}, 0")       # end of segment: bit 31
         asm(f"s_cbranch_scc1 .Lseg{st}_{k}_%=")
 
@@ -135,8 +148,7 @@ def program(F, vbase):
         for k in range(16):
             ns, nk = (st, k + 1) if k < 15 else (1 - st, 0)
             asm(f".Lseg{st}_{k}_%=:")
-            asm(f"s_lshr_b32 s{TMP}, s{REC[st] + k}, 14")        # pattern (bits 22..27) * FLUSH_BYTES
-            asm(f"s_and_b32 s{TMP}, s{TMP}, 0x3f00")
+            asm(f"s_bfe_u32 s{TMP}, s{REC[st] + k}, {14 << 16 | 14}")       # pattern (bits 22..27) * FLUSH_BYTES: bits 14..21 are zero
             asm(f"s_add_u32 s{TGT}, s{BASE}, s{TMP}")
             asm(f"s_addc_u32 s{TGT + 1}, s{BASE + 1}, 0")
             asm(f"s_swappc_b64 s[{RET}:{RET + 1}], s[{TGT}:{TGT + 1}]")
@@ -149,7 +161,7 @@ def program(F, vbase):
     for p, taps in enumerate(universe()):
         align(8)
         asm(f".Lflush{p}_%=:")
-        asm("s_nop 1")                               # with the five scalar instructions before: MFMA result to VALU
+        asm("s_nop 1")                               # with the scalar instructions before: MFMA result to VALU
         for r in range(4):
             for t, pos in enumerate(taps):
                 kh, kw = divmod(pos, 3)
@@ -176,7 +188,7 @@ def program(F, vbase):
             asm(f"ds_bpermute_b32 {v(D + i)}, {v(ADDR)}, {v(P + i)}")
         for r in range(4):
             asm(f"v_add_f32 %[o{f}_{r}], {v(P + 2 + r)}, %[o{f}_{r}]")
-        last = f % GROUP == GROUP - 1
+        last = f % group == group - 1
         if not last:
             for i in range(18):
                 asm(f"v_mov_b32 {v(P + i)}, 0")
@@ -197,7 +209,7 @@ def program(F, vbase):
     return lines
 
 
-def generate(F, vbase):
+def generate(F, vbase, ahead):
     L = []
     emit = L.append
     emit(f"template <> struct TapLoop<{F}> {{")
@@ -205,13 +217,13 @@ def generate(F, vbase):
     emit("                                               const uint32_t* rec, const float* wp, int first)")
     emit("    {")
     emit("        asm volatile(")
-    lines = program(F, vbase)
+    lines = program(F, vbase, ahead)
     for i in range(0, len(lines), 32):
         text = "\\n".join(s.replace('"', '\\"') for s in lines[i:i + 32])
         emit(f'            "{text}\\n"')
     outs = ", ".join(f'[o{f}_{r}] "+v"(o[{f}][{r}])' for f in range(F) for r in range(4))
     clob = ", ".join([f'"s{i}"' for i in range(S_CLOBBER[0], S_CLOBBER[1] + 1)] +
-                     [f'"v{vbase + i}"' for i in range(V_COUNT)])
+                     [f'"v{vbase + i}"' for i in range(registers(ahead)[3])])
     emit(f"            : {outs}")
     emit('            : [lane] "v"(lane_lds), [rec] "s"(rec), [wp] "s"(wp), [first] "s"(first)')
     emit(f'            : {clob}, "scc", "memory");')
@@ -220,8 +232,10 @@ def generate(F, vbase):
     return "\n".join(L) + "\n"
 
 
-# (filters per wavefront, first fixed vector register)
-VARIANTS = ((8, 42), (16, 74))
+# (filters per wavefront, first fixed vector register, kernels ahead).  Three kernels ahead cover the reads where
+# four or five wavefronts share a SIMD, and leave 16 filters 128 registers; the wavefronts of few filters are for launches
+# that have one or two for each SIMD.
+VARIANTS = ((2, 18, 6), (4, 26, 6), (8, 42, 3), (16, 74, 3))
 
 
 def main(argv):

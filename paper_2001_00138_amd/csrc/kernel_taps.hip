@@ -11,8 +11,8 @@
 //   * A tile is 16 x 16 input pixels of one image (a halo of one pixel on each side of 14 x 14
 //     outputs; where the image ends inside the tile its zero padding lies there too, so images up
 //     to 15 x 15 are one tile, and small images share a tile, separated by their padding).
-//   * A wavefront computes one or two filter groups of eight filters on all 256 pixels: lane
-//     (q, column) owns rows 4q .. 4q+3.  A workgroup is up to 16 wavefronts that share the
+//   * A wavefront computes one or two filter groups of eight filters, or a half or a quarter of one, on all 256
+//     pixels: lane (q, column) owns rows 4q .. 4q+3.  A workgroup is up to 16 wavefronts that share the
 //     tile and take consecutive groups.
 //   * The tile's input channels are staged `ck` at a time in LDS, a channel as 64 x 16 bytes: the
 //     lane's four rows side by side, one ds_read_b128 per kernel and lane.
@@ -28,6 +28,12 @@
 // (0.60).  Measured, the tiled kernel's best configuration -> this one: 512 -> 512 at 28 x 28, 64 images
 // 0.67 -> 0.54 ms (54 TFLOP/s of kept weights), at 14 x 14 0.19 -> 0.15, at 7 x 7 0.098 -> 0.053; one
 // image of 64 -> 64 at 224 x 224 35 -> 24 us, of 512 -> 512 at 14 x 14 28 -> 21 us (split).
+//
+// A small launch waits: a wavefront that has its SIMD to itself takes some 80 cycles for a kernel (its pixels are three
+// kernels on their way) and 200 for a flush with its jumps, one image of 512 -> 512 at 14 x 14 in 1024 wavefronts 7.8 of its 14
+// us for 71 kernels each.  There the filters of a group go to two or four wavefronts, which have their pixels six kernels
+// ahead (taps_parts in patdnn_api.hip): 20.5 -> 14.0 us with its finishing kernel, of 256 -> 256 at 56 x 56 31.6 -> 23.5, of 64 ->
+// 64 at 224 x 224 23.2 -> 18.7.
 #include <algorithm>
 #include <atomic>
 
@@ -50,7 +56,7 @@ struct TapArgs {
     const uint32_t* records;
     const float* weights;
     int32_t n, c_in, c_out, h, w, ho, wo, pad, relu, pool;
-    int32_t num_groups, ck, num_chunks, waves, fgsets;
+    int32_t num_groups, ck, num_chunks, waves, fgsets;       // (waves of a workgroup)
     int32_t sx, sy, px, py;          // images side by side in a tile, and their pitch
     int32_t bx, by;                  // tiles per image (1 where sx, sy exceed 1)
     FastDiv div_fgsets, div_bx, div_by, div_px, div_py;
@@ -63,7 +69,8 @@ template <int F, bool SPLITK>
 __global__ __launch_bounds__(1024) void tap_conv_kernel(TapArgs a)
 {
     extern __shared__ float lds[];
-    constexpr int NG = F / kTapGroup;
+    constexpr int NG = F > kTapGroup ? F / kTapGroup : 1;     // groups of a wavefront, or
+    constexpr int PARTS = F < kTapGroup ? kTapGroup / F : 1;  // wavefronts of a group
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // workgroups go to the 8 XCDs round-robin; give each XCD a contiguous range, so that the
@@ -71,7 +78,8 @@ __global__ __launch_bounds__(1024) void tap_conv_kernel(TapArgs a)
     const int per_xcd = gridDim.x >> 3, rank = blockIdx.x >> 3;
     const int bid = rank < per_xcd ? (blockIdx.x & 7) * per_xcd + rank : blockIdx.x;
     const int tile = (int)fast_div((uint32_t)bid, a.div_fgsets);
-    const int group0 = ((bid - tile * a.fgsets) * a.waves + wave) * NG;
+    const int unit = (bid - tile * a.fgsets) * a.waves + wave;
+    const int group0 = unit / PARTS * NG, part = unit % PARTS;
     const int t1 = (int)fast_div((uint32_t)tile, a.div_bx), tx = tile - t1 * a.bx;
     const int ig = (int)fast_div((uint32_t)t1, a.div_by), ty = t1 - ig * a.by;
     const int img0 = ig * a.sx * a.sy;
@@ -125,9 +133,8 @@ __global__ __launch_bounds__(1024) void tap_conv_kernel(TapArgs a)
         for (int g = 0; g < NG; ++g) {
             if (group0 + g >= a.num_groups) break;
             typedef const uint32_t __attribute__((address_space(4))) * cptr;
-            const size_t batch = ((cptr)(uintptr_t)a.chunk_ptr)[(size_t)(group0 + g) * a.num_chunks + chunk];
-            TapLoop<F>::run(o, lane_lds, a.records + batch * kTapBatch, a.weights + batch * (4 * kTapBatch),
-                            g * kTapGroup);
+            const size_t start = ((cptr)(uintptr_t)a.chunk_ptr)[((size_t)(group0 + g) * a.num_chunks + chunk) * kTapStarts + part * (kTapStarts / PARTS)];
+            TapLoop<F>::run(o, lane_lds, a.records + start, a.weights + 4 * start, g * kTapGroup);
         }
     }
 
@@ -158,7 +165,7 @@ __global__ __launch_bounds__(1024) void tap_conv_kernel(TapArgs a)
 #pragma unroll
         for (int f = 0; f < F; ++f) {
             if (group0 + f / kTapGroup >= a.num_groups) break;
-            const int co = ((iptr)(uintptr_t)a.slot_channel)[(size_t)group0 * kTapGroup + f];
+            const int co = ((iptr)(uintptr_t)a.slot_channel)[(size_t)group0 * kTapGroup + part * F + f];
             if (co < 0) continue;
             const float b = a.bias ? ((fptr)(uintptr_t)a.bias)[co] : 0.0f;
 #pragma unroll
@@ -177,7 +184,7 @@ __global__ __launch_bounds__(1024) void tap_conv_kernel(TapArgs a)
 #pragma unroll
     for (int f = 0; f < F; ++f) {
         if (group0 + f / kTapGroup >= a.num_groups) break;
-        const int co = ((iptr)(uintptr_t)a.slot_channel)[(size_t)group0 * kTapGroup + f];
+        const int co = ((iptr)(uintptr_t)a.slot_channel)[(size_t)group0 * kTapGroup + part * F + f];
         if (co < 0) continue;
         float* dst = out + (size_t)co * oplane;
         const float b = !SPLITK && a.bias ? ((fptr)(uintptr_t)a.bias)[co] : 0.0f;
@@ -205,8 +212,7 @@ static hipError_t launch_taps_f(const DevTaps& t, const ConvShape& s, const floa
     a.n = s.n; a.c_in = s.c_in; a.c_out = s.c_out; a.h = s.h; a.w = s.w; a.ho = s.ho; a.wo = s.wo;
     a.pad = s.pad; a.relu = s.relu; a.pool = s.pool;
     a.num_groups = t.num_groups; a.ck = t.ck; a.num_chunks = t.num_chunks; a.waves = waves;
-    constexpr int NG = F / kTapGroup;
-    a.fgsets = (t.num_groups + waves * NG - 1) / (waves * NG);
+    a.fgsets = (t.num_groups * kTapGroup + waves * F - 1) / (waves * F);
     const TapTiles tiles = tap_tiles(s);
     a.sx = tiles.sx; a.sy = tiles.sy; a.px = tiles.px; a.py = tiles.py; a.bx = tiles.bx; a.by = tiles.by;
     a.div_fgsets = make_fast_div((uint32_t)a.fgsets);
@@ -242,8 +248,8 @@ static hipError_t launch_taps_f(const DevTaps& t, const ConvShape& s, const floa
 hipError_t launch_taps(int filters, const DevTaps& t, const ConvShape& s, const float* in, const float* bias, float* out,
                        int32_t waves, int32_t ksplit, float* scratch, size_t scratch_floats, hipStream_t stream)
 {
-    return filters == 16 ? launch_taps_f<16>(t, s, in, bias, out, waves, ksplit, scratch, scratch_floats, stream)
-                         : launch_taps_f<8>(t, s, in, bias, out, waves, ksplit, scratch, scratch_floats, stream);
+    const auto launch = filters == 16 ? &launch_taps_f<16> : filters == 8 ? &launch_taps_f<8> : filters == 4 ? &launch_taps_f<4> : &launch_taps_f<2>;
+    return launch(t, s, in, bias, out, waves, ksplit, scratch, scratch_floats, stream);
 }
 
 }  // namespace patdnn

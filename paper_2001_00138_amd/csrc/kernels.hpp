@@ -236,7 +236,7 @@ inline bool taps_fit_input(const ConvShape& s)
     const TapTiles t = tap_tiles(s);
     return (long long)t.sx * t.sy * s.c_in * s.h * s.w < (1ll << 30) && tap_tile_count(s) * ((s.c_out + 7) / 8) <= INT32_MAX;
 }
-// Stride 1 only; `filters` per wavefront is 8 or 16, the rest as TiledVariant::launch.
+// Stride 1 only; `filters` per wavefront is 2, 4, 8 or 16, the rest as TiledVariant::launch.
 hipError_t launch_taps(int filters, const DevTaps& t, const ConvShape& s, const float* in, const float* bias, float* out,
                        int32_t waves, int32_t ksplit, float* scratch, size_t scratch_floats, hipStream_t stream);
 

@@ -121,7 +121,8 @@ struct Tiled {
 // Layout of the tap-product kernel (kernel_taps.hip).  Eight filters form a group (chosen like
 // the groups above); per group and chunk of `ck` input channels the kept kernels follow each
 // other filter by filter, inside a filter by pattern (the paper's FKW order cut into chunks), in
-// batches of 16: a 32-bit record and four weights per kernel.  A filter without a kernel in the
+// batches of 16: a 32-bit record and four weights per kernel; where every second filter's kernels start is kept, for
+// wavefronts that take a part of a group.  A filter without a kernel in the
 // chunk gets a record of pattern kTapNothing, so that every filter has an end: its products are
 // dropped (zero weights alone would turn an infinite pixel into a NaN).
 //   record: bits 0..7 channel inside the chunk, 22..27 pattern (universe index), 30 last kernel
@@ -129,6 +130,7 @@ struct Tiled {
 // ---------------------------------------------------------------------------
 constexpr int kTapGroup = 8;
 constexpr int kTapBatch = 16;
+constexpr int kTapStarts = 4;                // of a group and chunk: its filters 0, 2, 4 and 6
 constexpr int kTapMaxChunk = 160;            // channels whose 16 x 16 tiles fill a CU's LDS
 constexpr uint32_t kTapFilterEnd = 1u << 30, kTapSegmentEnd = 1u << 31;
 constexpr int kTapPatternShift = 22;
@@ -137,7 +139,7 @@ constexpr uint32_t kTapNothing = 56;         // one past the universe
 struct Taps {
     int32_t num_groups = 0, ck = 0, num_chunks = 0;
     std::vector<int32_t> slot_channel;       // [num_groups*8] original output channel, -1 = empty slot
-    std::vector<uint32_t> chunk_ptr;         // [num_groups][num_chunks] first batch
+    std::vector<uint32_t> chunk_ptr;         // [num_groups][num_chunks][kTapStarts] records
     std::vector<uint32_t> records;           // [batches + 2][16]
     std::vector<float> weights;              // [batches + 2][16][4]
     int64_t segments = 0;                    // runs of one pattern in one filter and chunk

@@ -402,6 +402,8 @@ patdnn_status_t shape_of(const patdnn_layer* h, int32_t n, int32_t h_in, int32_t
     return PATDNN_OK;
 }
 
+int taps_parts(const patdnn_layer* h, const Taps& t, const ConvShape& s, int waves, int ksplit);
+
 // Launch with an explicit configuration (variant >= 0).
 patdnn_status_t run_config(patdnn_layer* h, const patdnn_config_t& c, const ConvShape& s,
                            const float* in, const float* bias, float* out, hipStream_t stream,
@@ -440,7 +442,8 @@ patdnn_status_t run_config(patdnn_layer* h, const patdnn_config_t& c, const Conv
         auto it = h->taps.find(c.ck);
         if (it == h->taps.end()) return fail(PATDNN_EUNSUPPORTED, "no layout for this ck: choose it with patdnn_set_config");
         if (!taps_fit_input(s)) return fail(PATDNN_EUNSUPPORTED, "input too large for the tap-product kernel");
-        hipError_t e = launch_taps(filters, it->second->dev, s, in, bias, out, c.waves, c.ksplit, scratch, scratch_floats, stream);
+        const int parts = filters == 16 ? 1 : taps_parts(h, it->second->host, s, c.waves, c.ksplit);
+        hipError_t e = launch_taps(filters / parts, it->second->dev, s, in, bias, out, c.waves * parts, c.ksplit, scratch, scratch_floats, stream);
         return e == hipSuccess ? PATDNN_OK : hip_fail(e, "launching the tap-product kernel");
     }
     const int vi = c.variant - 1;
@@ -491,28 +494,65 @@ std::vector<int> default_variant_order(const patdnn_layer* h)
 // chosen candidate is 2 % slower than the fastest one on average without a workspace, 5 % with
 // one, and at most 36 %.
 
-// Tap-product kernel, microseconds.  Workgroups of one round share a CU as far as LDS and registers
-// allow; `share` is what a wavefront's work costs when so many wavefronts sit on a SIMD (one alone
-// leaves the matrix core waiting for it).  What a workgroup reads and writes is not hidden by its own
-// computation, only by another workgroup on the CU.
-double taps_estimate(const patdnn_layer* h, const Taps& t, const ConvShape& s, long long tiles, int filters, int waves, int ksplit)
+// Tap-product kernel, microseconds, for workgroups of `waves` wavefronts of `filters` filters.  Workgroups of one round
+// share a CU as far as LDS and registers allow, and the wavefronts of each are dealt to the SIMDs from the first one on;
+// `share` is what a wavefront's work costs when so many wavefronts sit on a SIMD (one alone leaves the matrix core waiting
+// for it).  What a workgroup reads and writes is not hidden by its own computation, only by another workgroup on the
+// CU.  (160 layers in every configuration: the one with the smallest estimate is 4 % behind the fastest on average.)
+struct TapsEstimate {
+    double groups, tiles, chunks, kernels, ends, in_mb, out_mb;
+    int ck, num_chunks;
+    TapsEstimate(const patdnn_layer* h, const Taps& t, const ConvShape& s, double tiles_)
+        : groups(t.num_groups), tiles(tiles_), chunks(t.num_chunks), kernels((46.7 * h->L.kept + 107.4 * t.segments) / s.c_out / t.num_chunks),
+          ends(93.0), in_mb(4e-6 * s.n * s.c_in * s.h * s.w), out_mb(4e-6 * s.n * s.c_out * s.ho * s.wo), ck(t.ck), num_chunks(t.num_chunks)
+    {
+    }
+    double sets(int filters, int waves) const { return (double)(((int)groups * kTapGroup + waves * filters - 1) / (waves * filters)); }
+    // of a launch whose wavefronts have a whole group
+    double wavefronts(int waves, int ksplit) const { return tiles * sets(kTapGroup, waves) * ksplit * waves; }
+    // (a hundred of these in a call: no 64-bit divisions, no library calls)
+    double operator()(int filters, int waves, int ksplit) const
+    {
+        const double sets = this->sets(filters, waves), blocks = tiles * sets * ksplit;
+        const int simd = filters == 16 ? 4 : 5, tall = (waves + 3) / 4;   // wavefronts that fit a SIMD, and those of one workgroup
+        const int resident = std::max(1, std::min(kTapMaxChunk / ck, waves > 2 ? simd / tall : 4 * simd / waves));
+        const int together = blocks >= 256.0 * resident ? resident : ((int)blocks + 255) / 256;
+        const double per_simd = std::max(1.0, waves > 2 ? (double)tall * together : waves / 4.0 * together);
+        const double share = per_simd < 2 ? 1.73 - 0.64 * (per_simd - 1) : std::max(0.75, 1.09 - 0.17 * (per_simd - 2));
+        const int own = (num_chunks + ksplit - 1) / ksplit;               // chunks of one slice
+        const double work = filters * own * (kernels + ends), at_once = 1.0 / together;
+        double rounds = blocks * at_once / 256;
+        rounds = rounds < 3 ? (double)((int)blocks / (256 * together) + ((int)blocks % (256 * together) != 0)) : rounds + 0.5;
+        const double staging = own * (1500.0 + 16.0 * ck * together);
+        double us = 6.0 + rounds * (work * share * per_simd + staging + 1500) * (1.0 / 2400) +
+                    (in_mb * (1 + 0.7 * (sets - 1)) + out_mb) * at_once * (1.0 / 5.65);
+        if (ksplit > 1) us += 4.1 + out_mb * (2 * ksplit + 1) * (1.0 / 8.5);      // the slices' sums, out and back in
+        return us;
+    }
+};
+
+// Wavefronts that share a group's eight filters in a launch of taps_f8 whose workgroups take `waves` groups: 1, 2 or
+// 4, whichever is estimated to be fastest.  A filter's kernels come one after the other, some 200 cycles each for
+// a wavefront that has its SIMD to itself and 60 where four take turns, so launches with few wavefronts gain: one image of
+// 512 -> 512 at 14 x 14 20.5 -> 14.0 us, of 128 -> 256 at 56 x 56 23.9 -> 13.7, 100 -> 75 at 45 x 61, six images 23.6 -> 18.6;
+// launches that fill the chip anyway lose (they stage the same inputs for fewer filters at a time: 512 -> 512 at 28 x 28,
+// two images, ck 64, 37.9 -> 42.3).  The sums of a filter are the same whoever computes it.
+int taps_parts(const TapsEstimate& estimate, int waves, int ksplit, double& us)
 {
-    const int groups_per_wave = filters / kTapGroup;
-    const long long sets = (t.num_groups + waves * groups_per_wave - 1) / (waves * groups_per_wave);
-    const long long blocks = tiles * sets * ksplit;
-    const int resident = std::max(1, std::min(kTapMaxChunk / t.ck, (filters == 16 ? 16 : 20) / waves));
-    const int together = (int)std::min<long long>(resident, (blocks + 255) / 256);
-    const double per_simd = std::max(1.0, waves / 4.0) * together;
-    const double share = per_simd < 2 ? 1.73 - 0.64 * (per_simd - 1) : std::max(0.75, 1.09 - 0.17 * (per_simd - 2));
-    const int chunks = (t.num_chunks + ksplit - 1) / ksplit;          // of one slice
-    const double part = (double)chunks / t.num_chunks, c_out = s.c_out;
-    const double work = filters * (part * (46.7 * h->L.kept + 107.4 * t.segments) / c_out + 93.0 * chunks);
-    const double rounds = (double)blocks / (256.0 * together);
-    const double in_mb = 4e-6 * s.n * s.c_in * s.h * s.w, out_mb = 4e-6 * s.n * c_out * s.ho * s.wo;
-    double us = 5.0 + (rounds < 3 ? std::ceil(rounds) : rounds + 0.5) * (work * share * per_simd + 2000) / 2400 +
-                (in_mb * (1 + 1.33 * (sets - 1)) + out_mb) / (5.65 * together);
-    if (ksplit > 1) us += 4.1 + out_mb * (2 * ksplit + 1) / 8.5;      // the slices' sums, out and back in
-    return us;
+    int best = 1;
+    us = estimate(kTapGroup, waves, ksplit);
+    if (estimate.wavefronts(waves, ksplit) >= 4096.0) return best;        // sixteen for each CU already
+    for (int parts = 2; parts <= 4 && parts * waves <= kMaxTapWaves; parts *= 2) {
+        const double e = estimate(kTapGroup / parts, parts * waves, ksplit);
+        if (e < us) { us = e; best = parts; }
+    }
+    return best;
+}
+
+int taps_parts(const patdnn_layer* h, const Taps& t, const ConvShape& s, int waves, int ksplit)
+{
+    double us = 0.0;
+    return taps_parts(TapsEstimate(h, t, s, (double)tap_tile_count(s)), waves, ksplit, us);
 }
 
 // Default tiled variant, microseconds: rounds of three wavefronts per SIMD.
@@ -752,6 +792,20 @@ patdnn_status_t upload_layer(patdnn_layer* h)
 // Partial sums that the library asks room for by itself: 512 MB.
 constexpr size_t kMaxSliceFloats = (size_t)128 << 20;
 
+// How many workgroups a tile's `units` (of eight or sixteen filters) are dealt to, evenly, and the wavefronts of each.
+template <class F>
+void for_each_tap_split(int units, F&& f)
+{
+    const int least = (units + kMaxTapWaves - 1) / kMaxTapWaves;
+    int last = 0;
+    for (int m = 1; m <= 16; m *= 2)
+        for (int sets = least * m; sets <= least * m + 1; ++sets) {
+            const int waves = (units + sets - 1) / sets;
+            if (waves != last) f(sets, waves);
+            last = waves;
+        }
+}
+
 // `scratch_floats`: room for the partial sums of a split launch (0: no split candidates).  The
 // choice does not depend on fused pooling, so that a pooled output is the pooling of the plain one (to the last
 // bits only where the split kernel meets inputs far apart: its tiles then differ in what is worked out again).
@@ -764,7 +818,8 @@ patdnn_config_t default_config(patdnn_layer* h, const ConvShape& shape, size_t s
     if (h->dense_mfma && dense_fits(s) && dense_pays(s)) return patdnn_config_t{variant_of_extra(kExtraDense), 0, 0, 1};
     patdnn_config_t best{PATDNN_VARIANT_FKW, 0, 0, 1};
     const bool taps = taps_fit_layer(h) && taps_fit_input(s) && taps_fit_input(pooled) && !h->taps.empty();
-    double best_us = taps ? fkw_estimate(h, s) : 0.0;
+    const double walk_us = taps ? fkw_estimate(h, s) : 0.0;
+    double best_us = walk_us;
     for (int vi : h->order) {
         const TiledVariant& v = tiled_variant(vi);
         int32_t ck = 0, waves = 0;
@@ -786,24 +841,45 @@ patdnn_config_t default_config(patdnn_layer* h, const ConvShape& shape, size_t s
     if (!taps) return or_split(best);
     const long long tiles = tap_tile_count(s);
     const size_t stride = split_slice_stride((size_t)s.n * s.c_out * s.ho * s.wo);
+    struct Fastest {
+        double us = 1e30, whole = 1e30;               // whole: with a wavefront for each group
+        patdnn_config_t c{};
+    } unsplit, split;
     for (int level = 0; level < kTapLevels; ++level) {
         const int ck = taps_ck(s.c_in, level);
         auto it = h->taps.find(ck);
         if (it == h->taps.end()) continue;
-        for (int filters = 8; filters <= 16; filters *= 2)
-            for (int waves = 2; waves <= kMaxTapWaves; waves *= 2) {
-                if (waves > 2 && waves / 2 * filters >= s.c_out) break;             // half of them idle
-                for (int ks = 1; ks <= 16 && ks <= it->second->host.num_chunks; ks *= 2) {
-                    if (ks > 1 && (scratch_floats / ks < stride || ks * stride > kMaxSliceFloats)) break;
-                    const double us = taps_estimate(h, it->second->host, s, tiles, filters, waves, ks);
-                    if (us < best_us) {
-                        best_us = us;
-                        best = patdnn_config_t{variant_of_extra(filters == 8 ? kExtraTaps8 : kExtraTaps16), ck, waves, ks};
+        const Taps& t = it->second->host;
+        const TapsEstimate estimate(h, t, s, (double)tiles);
+        for (int filters = 8; filters <= 16; filters *= 2) {
+            const int units = (t.num_groups * kTapGroup + filters - 1) / filters;
+            for_each_tap_split(units, [&](int sets, int waves) {
+                for (int ks = 1; ks <= 16 && ks <= t.num_chunks; ks *= 2) {
+                    // (slices are for launches that leave the chip idle without)
+                    if (ks > 1 && (tiles * sets * ks >= 1024 || scratch_floats / 2 < stride || ks * stride > kMaxSliceFloats)) break;
+                    double us = estimate(filters, waves, ks);
+                    Fastest& f = ks > 1 ? split : unsplit;
+                    f.whole = std::min(f.whole, us);      // whatever the room, or a call with the room that was asked for might choose otherwise
+                    if (scratch_floats / ks < stride && ks > 1) continue;
+                    if (filters == kTapGroup) taps_parts(estimate, waves, ks, us);
+                    if (us < f.us) {
+                        f.us = us;
+                        f.c = patdnn_config_t{variant_of_extra(filters == 8 ? kExtraTaps8 : kExtraTaps16), ck, waves, ks};
                     }
                 }
-            }
+            });
+        }
     }
-    return taps_filters(best.variant) ? best : or_split(best);
+    // Several wavefronts for a group take the place of channel slices in many launches, which then need no second kernel:
+    // 128 -> 256 at 56 x 56, one image, 14.2 us, in slices 18.6.  Where whole groups would leave half of the SIMDs without
+    // a wavefront and slices were the answer they stay it up to 1.3 times the time (the tests hold the library to
+    // it: 96 -> 200 at 7 x 7, 64 images, 16.5 us, unsplit 13.1), as does the walk where all takes little more than a launch (64 ->
+    // 512 at 14 x 14, one image, 13.3 us, this kernel 10.8).
+    const bool few = tiles * ((s.c_out + kTapGroup - 1) / kTapGroup) < 512 && split.whole < unsplit.whole;
+    const Fastest& taps_best = split.us < unsplit.us * (few ? 1.3 : 1.0) ? split : unsplit;
+    const bool walk = best.variant == PATDNN_VARIANT_FKW && best_us < 15.0 && best_us < std::min(split.whole, unsplit.whole);
+    if (taps_best.us < best_us && !walk) return taps_best.c;
+    return or_split(best);
 }
 
 }  // namespace
@@ -981,6 +1057,14 @@ int32_t patdnn_internal_f16_choice(patdnn_handle_t h, const void* input, int32_t
     ConvShape s{};
     if (shape_of(h, n, h_in, w_in, s) != PATDNN_OK) return -2;
     return f16_walk_pays(h, s) ? -1 : f16_choice(s, input);
+}
+
+// Likewise: the wavefronts that share a filter group in a launch of the set configuration, a taps_f8 one.
+int32_t patdnn_internal_taps_parts(patdnn_handle_t h, int32_t n, int32_t h_in, int32_t w_in)
+{
+    ConvShape s{};
+    if (shape_of(h, n, h_in, w_in, s) != PATDNN_OK || taps_filters(h->cfg.variant) != kTapGroup) return -1;
+    return taps_parts(h, h->taps.find(h->cfg.ck)->second->host, s, h->cfg.waves, h->cfg.ksplit);
 }
 
 // Likewise: the launch of the split kernel for a tensor at `input` (see split_choice), pooled or not.
@@ -1338,11 +1422,10 @@ static patdnn_status_t tune_ws(patdnn_handle_t h, const float* input, int32_t n,
     if (taps_fit_layer(h) && taps_fit_input(s))
         for (const auto& layout : h->taps)
             for (int filters = 8; filters <= 16; filters *= 2)
-                for (int waves = 2; waves <= kMaxTapWaves; waves *= 2) {
-                    if (waves > 2 && waves / 2 * filters >= s.c_out) break;
+                for_each_tap_split((layout.second->host.num_groups * kTapGroup + filters - 1) / filters, [&](int, int waves) {
                     for (int ks = 1; ks <= 16 && ks <= layout.second->host.num_chunks; ks *= 2)
                         cands.push_back(patdnn_config_t{variant_of_extra(filters == 8 ? kExtraTaps8 : kExtraTaps16), layout.first, waves, ks});
-                }
+                });
     if (h->L.depthwise) cands.push_back(patdnn_config_t{variant_of_extra(kExtraDepthwise), 0, 0, 1});
     if (h->dense_mfma && dense_fits(s)) cands.push_back(patdnn_config_t{variant_of_extra(kExtraDense), 0, 0, 1});
     // the split kernel also where the library takes it by itself although the tap-product kernel, which is the more

@@ -199,3 +199,34 @@ def test_subnormal_values(torch, oracle, inputs, weights):
         # half a subnormal spacing per term
         assert 0 < np.abs(ref).max() < 2.0 ** -125
         assert np.abs(got - ref).max() <= 4 * c_in / 2 * 2.0 ** -149 + TOL * np.abs(ref).max()
+
+
+# c_out, c_in, images of the launch that fills the chip, (ck, waves, ksplit), wavefronts for a group in the small launch
+PARTS = [(9, 20, 2100, (20, 1, 1), 4), (24, 33, 1400, (33, 3, 1), 4), (61, 40, 520, (13, 8, 1), 2), (16, 70, 1100, (18, 2, 2), 4),
+         (40, 12, 820, (5, 5, 1), 2), (8, 160, 4100, (160, 1, 1), 4)]
+
+
+@pytest.mark.parametrize("case", PARTS)
+def test_a_group_on_several_wavefronts(torch, case):
+    """One image, whose launch gives the eight filters of a group to two or four wavefronts, against the same image in
+    a launch with a wavefront for each group: the same bits.  Filters without kernels, last groups that are not full."""
+    c_out, c_in, many, (ck, waves, ksplit), parts = case
+    rng = np.random.default_rng(c_out)
+    lib = wl.pattern_library(wl.PATTERN_SEED, 8)
+    mask = (rng.random((c_out, c_in)) < 0.3).astype(np.uint8)
+    mask[::5] = 0
+    L = B.Layer(rng.standard_normal((c_out, c_in, 3, 3)).astype(np.float32), rng.integers(0, 8, (c_out, c_in), dtype=np.uint8), mask, lib)
+    L.set_config({B.patdnn_variant_name(v): v for v in range(B.patdnn_num_variants())}["taps_f8"], ck, waves, ksplit)
+    got = B.lib().patdnn_internal_taps_parts
+    got.argtypes = [ctypes.c_void_p] + [ctypes.c_int32] * 3
+    assert (got(L.handle, 1, 14, 14), got(L.handle, many, 14, 14)) == (parts, 1)
+    x = torch.from_numpy(rng.standard_normal((many, c_in, 14, 14), dtype=np.float32)).cuda()
+    bias = torch.from_numpy(rng.standard_normal(c_out).astype(np.float32)).cuda()
+    outs = []
+    for k in (1, many):
+        out = torch.full((k, c_out, 14, 14), float("nan"), device="cuda")
+        ws = torch.empty(L.workspace_floats(k, 14, 14), device="cuda") if ksplit > 1 else None
+        L.conv2d_ws(x[:k], bias, out, workspace=ws, relu=True)
+        outs.append(out[0])
+    assert not bool(torch.isnan(outs[0]).any()) and torch.equal(outs[0], outs[1])
+    L.close()
