@@ -163,6 +163,10 @@ def _devptr(t) -> Optional[int]:
 def _stream_ptr(stream) -> Optional[int]:
     if stream is None:
         import torch
+        if torch.cuda.is_initialized():
+            # the current stream's handle without a Stream object around it (0.2 us, 2.7 with one: a third of a small
+            # layer's call)
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
         return torch.cuda.current_stream().cuda_stream or None
     if isinstance(stream, int):
         return stream or None
@@ -221,8 +225,11 @@ def patdnn_encode(dense_weights, pattern_ids, kernel_mask, pattern_masks, *, str
     return h.value
 
 
+_Shape = ctypes.c_int32 * 4
+
+
 def patdnn_output_shape(handle: int, n: int, h_in: int, w_in: int):
-    out = (ctypes.c_int32 * 4)()
+    out = _Shape()
     _check(lib().patdnn_output_shape(handle, n, h_in, w_in, ctypes.byref(out)))
     return tuple(out)
 
