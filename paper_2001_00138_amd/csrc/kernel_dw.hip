@@ -3,14 +3,11 @@
 // and is bound by HBM bandwidth, not by arithmetic.
 //
 // Design for that bound: one pass over the input and one over the output.  A lane owns
-// four consecutive output pixels of one row (one 16-byte store); per input row that its
-// channel's pattern touches it loads 16-byte vectors plus the one or two halo elements
-// (predicated, zero outside the image).  Rows are re-read by the lanes of the rows above
-// and below, which sit next to each other in the grid and hit the same cache lines, so the
-// traffic that reaches HBM is the tensor once.  Channels are walked in the stored filter
+// some neighbouring outputs of two rows (dw_rows_kernel).  Channels are walked in the stored filter
 // order of the FKW arrays; for one-kernel filters the filter reorder of section 5.2 sorts
-// them by pattern, so the lanes of a wavefront share one pattern and skip the same rows
-// and taps together (the `if`s on the pattern mask below are then uniform branches).
+// them by pattern, so the lanes of a wavefront share one pattern and skip the same
+// taps together (the `if`s on the pattern mask below are then uniform branches).  Small planes whose rows are
+// no whole vectors are taken several at a time through LDS (dw_planes_kernel).
 // Bias and ReLU are fused; the result goes to the original channel `reorder[f]`.
 // The same kernel runs on fp32 tensors and on half-precision storage (binary16 weights, input
 // and output, fp32 arithmetic in between - the paper's GPU runs keep weights and intermediate
@@ -37,10 +34,10 @@ struct DwArgs {
     int32_t c, h, w, ho, wo, wq, pad, relu;
     long long total;             // n * c * ho * wq lanes
     FastDiv div_wq, div_ho, div_c;   // for lane numbers below 2^31 (every realistic launch)
+    uint32_t div_rows;               // dw_rows_kernel: groups of rows (what div_ho divides by there)
 };
 
-// element access: one value, or four consecutive ones with one 16-byte (fp32) / 8-byte
-// (binary16) access at an address aligned to that size
+// element access: one value, a filter's four weights, or the outputs of a lane at an address aligned to them
 __device__ __forceinline__ float ld1(const float* p) { return *p; }
 __device__ __forceinline__ float ld1(const __half* p) { return __half2float(*p); }
 __device__ __forceinline__ void ld4(const float* p, float& a, float& b, float& c, float& d)
@@ -56,30 +53,6 @@ __device__ __forceinline__ void ld4(const __half* p, float& a, float& b, float& 
 }
 __device__ __forceinline__ void st1(float* p, float v) { *p = v; }
 __device__ __forceinline__ void st1(__half* p, float v) { *p = __float2half_rn(v); }
-// NP consecutive elements at an address aligned to NP elements: 16-byte accesses for four
-// floats or eight binary16 values
-template <int NP>
-__device__ __forceinline__ void ldv(const float* p, float* v)
-{
-#pragma unroll
-    for (int k = 0; k < NP; k += 4) ld4(p + k, v[k], v[k + 1], v[k + 2], v[k + 3]);
-}
-template <int NP>
-__device__ __forceinline__ void ldv(const __half* p, float* v)
-{
-    if constexpr (NP == 8) {
-        const uint4 m = *reinterpret_cast<const uint4*>(p);
-        const unsigned w[4] = {m.x, m.y, m.z, m.w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const __half2 h = *reinterpret_cast<const __half2*>(&w[k]);
-            v[2 * k] = __low2float(h);
-            v[2 * k + 1] = __high2float(h);
-        }
-    } else {
-        ld4(p, v[0], v[1], v[2], v[3]);
-    }
-}
 // STREAM: stores that do not stay in the L2s
 template <bool STREAM, int NP>
 __device__ __forceinline__ void stv(float* p, const float (&v)[NP])
@@ -101,16 +74,21 @@ __device__ __forceinline__ void stv(__half* p, const float (&v)[NP])
         const __half2 h = __floats2half2_rn(v[2 * k], v[2 * k + 1]);
         w[k] = *reinterpret_cast<const unsigned*>(&h);
     }
-    if constexpr (NP == 8) *reinterpret_cast<uint4*>(p) = make_uint4(w[0], w[1], w[2], w[3]);
-    else *reinterpret_cast<uint2*>(p) = make_uint2(w[0], w[1]);
+    typedef unsigned Words __attribute__((ext_vector_type(NP / 2)));
+    Words q;
+#pragma unroll
+    for (int k = 0; k < NP / 2; ++k) q[k] = w[k];
+    if constexpr (STREAM) __builtin_nontemporal_store(q, reinterpret_cast<Words*>(p));
+    else *reinterpret_cast<Words*>(p) = q;
 }
 
-// S: stride.  NP: outputs per lane (4, or 8 where the rows allow and the launcher finds it faster).  VEC: rows start aligned to NP elements (w % NP == 0,
-// aligned base) -> vector loads.  VST: output rows aligned to NP elements -> one vector store.
-template <int S, int NP, bool VEC, bool VST, class T, bool STREAM>
+// Any layer: a lane owns four outputs of one row and reads element by element, its row's neighbours again for each of
+// three rows.  For what the kernels below leave out: weights that are not finite (rows outside the image are left out
+// here, and columns there zeros), rows of fewer than four outputs' columns, 2^31 lanes and more.
+template <int S, class T>
 __global__ __launch_bounds__(256) void dw_conv_kernel(DwArgs<T> a)
 {
-    constexpr int NC = (NP - 1) * S + 3;           // input columns under NP outputs
+    constexpr int NP = 4, NC = (NP - 1) * S + 3;   // outputs, input columns under them
     const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
     if (t >= a.total) return;
     // lane number -> (image n, stored channel f, output row oy, group of NP columns xq).  A
@@ -155,43 +133,10 @@ __global__ __launch_bounds__(256) void dw_conv_kernel(DwArgs<T> a)
         if (iy < 0 || iy >= a.h) continue;         // zero padding: the row contributes nothing
         const T* row = plane + (size_t)iy * a.w;
         float v[NC];
-        if constexpr (VEC) {
-            // pad is 0 or 1: columns ix0 + pad .. start a vector
-            if (a.pad == 1) {
-                v[0] = ((rowbits & 1u) && ix0 >= 0) ? ld1(row + ix0) : 0.0f;
 #pragma unroll
-                for (int q = 0; q < (NC - 1) / NP; ++q) {
-                    const int ix = ix0 + 1 + NP * q;
-                    float m[NP];
-#pragma unroll
-                    for (int k = 0; k < NP; ++k) m[k] = 0.0f;
-                    if (ix < a.w) ldv<NP>(row + ix, m);
-#pragma unroll
-                    for (int k = 0; k < NP; ++k) v[1 + NP * q + k] = m[k];
-                }
-                if constexpr (S == 1) {
-                    const int ix = ix0 + NP + 1;
-                    v[NP + 1] = ((rowbits & 4u) && ix < a.w) ? ld1(row + ix) : 0.0f;
-                }
-            } else {
-#pragma unroll
-                for (int q = 0; q < (NC + NP - 1) / NP; ++q) {
-                    const int ix = ix0 + NP * q;
-                    float m[NP];
-#pragma unroll
-                    for (int k = 0; k < NP; ++k) m[k] = 0.0f;
-                    if (ix < a.w) ldv<NP>(row + ix, m);
-#pragma unroll
-                    for (int k = 0; k < NP; ++k)
-                        if (NP * q + k < NC) v[NP * q + k] = m[k];
-                }
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < NC; ++j) {
-                const int ix = ix0 + j;
-                v[j] = (ix >= 0 && ix < a.w) ? ld1(row + ix) : 0.0f;
-            }
+        for (int j = 0; j < NC; ++j) {
+            const int ix = ix0 + j;
+            v[j] = (ix >= 0 && ix < a.w) ? ld1(row + ix) : 0.0f;
         }
 #pragma unroll
         for (int dx = 0; dx < 3; ++dx) {
@@ -204,18 +149,133 @@ __global__ __launch_bounds__(256) void dw_conv_kernel(DwArgs<T> a)
         }
     }
     const float b = a.bias ? a.bias[co] : 0.0f;
+    T* dst = a.out + (((size_t)n * a.c + co) * a.ho + oy) * (size_t)a.wo + ox0;
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
         acc[i] += b;
         if (a.relu) acc[i] = fmaxf(acc[i], 0.0f);
+        if (ox0 + i < a.wo) st1(dst + i, acc[i]);
     }
-    T* dst = a.out + (((size_t)n * a.c + co) * a.ho + oy) * (size_t)a.wo + ox0;
-    if constexpr (VST) {
-        stv<STREAM, NP>(dst, acc);
-    } else {
+}
+
+// A lane owns R rows of V neighbouring outputs and reads the rows under them once, where dw_conv_kernel reads three for
+// every row, in vectors of its own columns, and takes the columns beside them from the lanes beside it, which hold
+// them.  (A load for each of those is 64 accesses of the texture addresser, as many as two of a row's vectors: that and
+// not HBM was the bound of a row kernel of vectors, at 3.9 TB/s.)  WHOLE: padding 1 and rows of whole aligned vectors; otherwise
+// rows start anywhere, vectors are accessed at the elements' alignment, and the last lane of a row reads its vector where it ends
+// with the row and shifts it.  What bounds it: HBM at the rate of a copy, 144 channels of 56 x 56, 64 images, fp32 on
+// changing tensors 231 MB in 47 us, of 112 x 112 / 2 578 MB in 103; binary16 at stride 1 (34 us for 116 MB) conversions and the tap
+// branches of eight columns.  R = 2: us of one, two, three and four rows 58, 47, 55, 57 and, of binary16, 37, 34, 34, 36.  (Branches on
+// one pattern after the other of a wavefront: 38.)  The sums are those of dw_conv_kernel, term by term; weights are finite
+// (rows outside the image are zeros here, not left out).
+constexpr int kDwRows = 2;
+template <int S, int R, int V, bool WHOLE, class T, bool STREAM>
+__global__ __launch_bounds__(256) void dw_rows_kernel(DwArgs<T> a)
+{
+    constexpr int C = S * V, ROWS = (R - 1) * S + 3;          // own columns, input rows
+    constexpr int E = C * (int)sizeof(T) < 16 ? C : 16 / (int)sizeof(T);      // elements of a load
+    // (rows that start anywhere: 16- and 8-byte accesses want no more than the elements' alignment)
+    typedef unsigned Raw __attribute__((ext_vector_type(E * sizeof(T) / 4), aligned(WHOLE ? E * sizeof(T) : sizeof(T))));
+    typedef unsigned RawOut __attribute__((ext_vector_type(V * sizeof(T) / 4), aligned(sizeof(T))));
+    const uint32_t t = blockIdx.x * 256u + threadIdx.x;
+    if (t >= (uint32_t)a.total) return;            // whole rows of lanes: the last lane that stays ends one
+    const uint32_t r1 = fast_div(t, a.div_wq);
+    const int xq = (int)(t - r1 * (uint32_t)a.wq);
+    const uint32_t r2 = fast_div(r1, a.div_ho);    // groups of R rows
+    const int y0 = (int)(r1 - r2 * a.div_rows) * R;
+    const uint32_t n = fast_div(r2, a.div_c);
+    const int f = (int)(r2 - n * (uint32_t)a.c);
+    const int co = a.reorder[f];
+    const unsigned mask = (unsigned)a.dw_mask[f];
+    float4 wv;
+    ld4(a.dw_weight + (size_t)f * 4, wv.x, wv.y, wv.z, wv.w);
+    const int pad = WHOLE ? 1 : a.pad;
+    // its first input column, that of tap column 1, and how far before it the columns start that lie in the row
+    const int x = xq * C + 1 - pad, shift = WHOLE ? 0 : max(x + C - a.w, 0);
+    const size_t plane = (size_t)n * a.c + co;
+    const T* const src = a.in + plane * ((size_t)a.h * a.w) + x;
+    const int lane = threadIdx.x & 63;
+    // the ends of a wavefront have no neighbour, and those of a row none that holds what is there without padding
+    const bool left_own = x > 0 && (lane == 0 || xq == 0), right_own = S == 1 && x + C < a.w && (lane == 63 || xq == a.wq - 1);
+
+    // as loaded: a conversion where a row is loaded would wait for each row by itself
+    Raw raw[ROWS][C / E];
+    T before[ROWS], behind[ROWS];
 #pragma unroll
-        for (int i = 0; i < NP; ++i)
-            if (ox0 + i < a.wo) st1(dst + i, acc[i]);
+    for (int r = 0; r < ROWS; ++r) {
+        const int y = y0 * S + r - pad;
+#pragma unroll
+        for (int k = 0; k < C / E; ++k) raw[r][k] = Raw{};
+        before[r] = behind[r] = T(0.0f);
+        if (y >= 0 && y < a.h) {
+            const T* const row = src + (size_t)y * a.w;
+#pragma unroll
+            for (int k = 0; k < C / E; ++k) raw[r][k] = *reinterpret_cast<const Raw*>(row - shift + k * E);
+            if (left_own) before[r] = row[-1];
+            if (right_own) behind[r] = row[C];
+        }
+    }
+    float v[ROWS][C + 2];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+#pragma unroll
+        for (int k = 0; k < C / E; ++k) {
+            union { Raw u; T t[E]; } m;
+            m.u = raw[r][k];
+#pragma unroll
+            for (int e = 0; e < E; ++e) v[r][k * E + e + 1] = ld1(&m.t[e]);
+        }
+        if constexpr (!WHOLE) {
+#pragma unroll
+            for (int d = 1; d < C; d *= 2)
+#pragma unroll
+                for (int k = 1; k <= C; ++k) v[r][k] = shift & d ? (k + d <= C ? v[r][k + d <= C ? k + d : 0] : 0.0f) : v[r][k];
+        }
+        const float left = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v[r][C]), 0x138, 0xf, 0xf, false));       // wave_shr:1
+        v[r][0] = xq == 0 || left_own ? ld1(&before[r]) : left;
+        if constexpr (S == 1) {
+            const float right = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v[r][1]), 0x130, 0xf, 0xf, false));  // wave_shl:1
+            v[r][C + 1] = xq == a.wq - 1 || right_own ? ld1(&behind[r]) : right;
+        }
+    }
+    float acc[R][V];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int i = 0; i < V; ++i) acc[r][i] = 0.0f;
+#pragma unroll
+    for (int pos = 0; pos < 9; ++pos) {
+        if (!(mask >> pos & 1u)) continue;
+        const int rank = __builtin_popcount(mask & ((1u << pos) - 1u));
+        const float wt = rank == 0 ? wv.x : rank == 1 ? wv.y : rank == 2 ? wv.z : wv.w;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int i = 0; i < V; ++i) acc[r][i] = fmaf(wt, v[r * S + pos / 3][i * S + pos % 3], acc[r][i]);
+    }
+    const float b = a.bias ? a.bias[co] : 0.0f;
+    T* const dst = a.out + plane * ((size_t)a.ho * a.wo) + xq * V;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (y0 + r >= a.ho) break;
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            acc[r][i] += b;
+            if (a.relu) acc[r][i] = fmaxf(acc[r][i], 0.0f);
+        }
+        T* const row = dst + (size_t)(y0 + r) * a.wo;
+        if (WHOLE) {
+            stv<STREAM, V>(row, acc[r]);
+        } else if (xq * V + V <= a.wo) {
+            union { RawOut u; T t[V]; } m;
+#pragma unroll
+            for (int i = 0; i < V; ++i) st1(&m.t[i], acc[r][i]);
+            *reinterpret_cast<RawOut*>(row) = m.u;
+        } else {
+#pragma unroll
+            for (int i = 0; i < V - 1; ++i)
+                if (xq * V + i < a.wo) st1(row + i, acc[r][i]);
+        }
     }
 }
 
@@ -242,7 +302,7 @@ struct DwPlanesArgs {
 // The sums are those of dw_conv_kernel, term by term.
 // What bounds it: below about 12 MB of tensors the launch (9 us a pass); above, address arithmetic of
 // the LDS layout on both sides, 2.0 to 2.7 TB/s.  The row kernel's lanes load single elements of such rows.
-// us per pass, row kernel -> this one, 64 images: 960 channels of 7x7 binary16 15.9 -> 9.2, fp32
+// us per pass, a row kernel of single elements -> this one, 64 images: 960 channels of 7x7 binary16 15.9 -> 9.2, fp32
 // 15.2 -> 9.7; 576 of 14x14 binary16 28.0 -> 15.5, fp32 26.1 -> 17.5, stride 2 17.8 -> 12.5; 96 of 37x35
 // binary16 27.9 -> 18.3, fp32 33.9 -> 22.6.
 template <int S, class T>
@@ -381,6 +441,43 @@ static bool launch_dw_planes(const DevFkw& f, const ConvShape& s, const T* in, c
     return true;
 }
 
+// True where dw_rows_kernel took the layer.  us of the kernels before -> of this one, on changing tensors, 64 images unless
+// said: fp32 144 channels of 56 x 56 60 -> 47, 8 images 9.5 -> 7.2, one 6.8 both; 96 of 112 x 112 156 -> 106; 96 of 37 x 35 23.7 ->
+// 15.0; 144 of 57 x 61, 16 images 40 -> 12.8; 144 of 112 x 112 / 2 120 -> 103; 75 x 110 / 2 9.7 -> 7.4; binary16 56 x 56 42 -> 33, 60 x 58 120 ->
+// 52, 112 x 112 / 2 77 -> 59.  Rows of up to 12 elements that are not whole stay with dw_planes_kernel, whose 16-byte loads they
+// leave idle less: 400 channels of 9 x 9 7.7 there, 8.0 here, 10 x 10 9.3 and 10.0, 11 x 11 10.8 and 11.9, 13 x 13 13.6 and 10.3.
+template <class T>
+static bool launch_dw_rows(const DevFkw& f, const ConvShape& s, DwArgs<T> a, hipStream_t stream)
+{
+    constexpr int kWide = 16 / sizeof(T);
+    const uintptr_t at = reinterpret_cast<uintptr_t>(a.in) | reinterpret_cast<uintptr_t>(a.out);
+    if (!(sizeof(T) == 4 ? f.dw_finite : f.dw_taps != nullptr) || s.stride > 2 || s.pad > 1 || s.w < 4 * s.stride) return false;
+    // outputs of a lane: four, or a whole vector; at stride 2 the columns of four are one or two
+    const int v = s.stride == 1 && s.pad == 1 && s.w % kWide == 0 && (at & 15) == 0 ? kWide : 4;
+    const bool whole = s.pad == 1 && s.w % (v * s.stride) == 0 && (at & std::min<size_t>(15, v * s.stride * sizeof(T) - 1)) == 0;
+    if (!whole && s.w <= 12 && launch_dw_planes<T>(f, s, a.in, a.bias, a.out, stream)) return true;
+    a.wq = (s.wo + v - 1) / v;
+    a.div_rows = (uint32_t)(s.ho + kDwRows - 1) / kDwRows;
+    a.total = (long long)s.n * s.c_out * a.div_rows * a.wq;
+    if (a.total > INT32_MAX - 256) return false;
+    a.div_wq = make_fast_div((uint32_t)a.wq);
+    a.div_ho = make_fast_div(a.div_rows);
+    a.div_c = make_fast_div((uint32_t)a.c);
+    // Outputs that leave nothing in the L2s, where both tensors exceed the last-level cache and rows are most of two cache lines:
+    // 96 channels of 112 x 112, alone / followed by a layer that reads the output, 109 / 219 us without, 106 / 211 with, binary16
+    // 72.7 / 148 and 70.8 / 142; below that size 144 channels of 56 x 56, 64 images 47.6 / 91.6 and 46.9 / 94.2; 576 of 28 x 28 54 / 96
+    // and 60 / 120.
+    const size_t bytes = (size_t)s.n * s.c_out * s.h * s.w * sizeof(T);
+    const bool past = 2 * bytes > (size_t)256 << 20 && s.w * sizeof(T) >= 224;
+    const dim3 grid((unsigned)((a.total + 255) / 256)), block(256);
+    const auto kernel = s.stride == 2 ? (whole ? &dw_rows_kernel<2, kDwRows, 4, true, T, false> : &dw_rows_kernel<2, kDwRows, 4, false, T, false>)
+                        : !whole      ? &dw_rows_kernel<1, kDwRows, 4, false, T, false>
+                        : v == kWide  ? (past ? &dw_rows_kernel<1, kDwRows, kWide, true, T, true> : &dw_rows_kernel<1, kDwRows, kWide, true, T, false>)
+                                      : (past ? &dw_rows_kernel<1, kDwRows, 4, true, T, true> : &dw_rows_kernel<1, kDwRows, 4, true, T, false>);
+    hipLaunchKernelGGL(kernel, grid, block, 0, stream, a);
+    return true;
+}
+
 template <class T>
 static hipError_t launch_dw_t(const DevFkw& f, const T* weights, const ConvShape& s, const T* in, const float* bias,
                               T* out, hipStream_t stream)
@@ -388,57 +485,18 @@ static hipError_t launch_dw_t(const DevFkw& f, const T* weights, const ConvShape
     DwArgs<T> a{};
     a.reorder = f.reorder; a.dw_mask = f.dw_mask; a.dw_weight = weights;
     a.in = in; a.bias = bias; a.out = out;
-    a.c = s.c_out; a.h = s.h; a.w = s.w; a.ho = s.ho; a.wo = s.wo;
-    // eight outputs per lane where every row, in and out, is whole vectors of eight elements
-    // (more bytes in flight per lane and half the index arithmetic: 3.0 -> 3.5 TB/s from HBM on
-    // the 112x112 fp32 layer); not for fp32 at stride 2, where the seventeen columns under
-    // eight outputs made the lanes slower; four otherwise
-    constexpr uintptr_t kAlign8 = 8 * sizeof(T) - 1;
-    const bool wide = (sizeof(T) == 2 || s.stride == 1) && s.w % 8 == 0 && s.wo % 8 == 0 &&
-                      ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & kAlign8) == 0;
-    const int np = wide ? 8 : 4;
-    a.wq = (s.wo + np - 1) / np; a.pad = s.pad; a.relu = s.relu;
+    a.c = s.c_out; a.h = s.h; a.w = s.w; a.ho = s.ho; a.wo = s.wo; a.pad = s.pad; a.relu = s.relu;
+    if (launch_dw_rows<T>(f, s, a, stream)) return hipGetLastError();
+    if (s.w % 4 != 0 && launch_dw_planes<T>(f, s, in, bias, out, stream)) return hipGetLastError();
+    a.wq = (s.wo + 3) / 4;
     a.total = (long long)s.n * s.c_out * s.ho * a.wq;
     a.div_wq = make_fast_div((uint32_t)a.wq);
     a.div_ho = make_fast_div((uint32_t)a.ho);
     a.div_c = make_fast_div((uint32_t)a.c);
     const long long blocks = (a.total + 255) / 256;
     if (blocks > 0x7FFFFFFFll) return hipErrorInvalidValue;
-    // vector loads need every row to start aligned to four elements and to be read in whole
-    // vectors: the columns a lane reads beyond its last tap stay inside the row when w % 4 == 0
-    constexpr uintptr_t kAlign = 4 * sizeof(T) - 1;
-    const bool vec = s.w % 4 == 0 && (reinterpret_cast<uintptr_t>(in) & kAlign) == 0;
-    const bool vst = s.wo % 4 == 0 && (reinterpret_cast<uintptr_t>(out) & kAlign) == 0;
-    // rows that are whole vectors on the way in stay with the row kernel (192 channels of 28x28 at
-    // stride 2, binary16: 11.0 us, 11.3 with planes in LDS)
-    if (!vec && launch_dw_planes<T>(f, s, in, bias, out, stream)) return hipGetLastError();
-    const dim3 grid((unsigned)blocks), block(256);
-    // fp32 outputs that leave nothing in the L2s, and the inputs more room: where both tensors are at most twice the 32 MB of
-    // those, and where what this layer and the next one touch exceeds the 256 MB of the last-level cache anyway.  Between
-    // them the next layer would find its input there.  us without and with such stores, alone and followed by a layer that
-    // reads the output: 144 channels of 56 x 56, 30 MB of output 16.3 and 14.1, 33.8 both; 60 MB 26 both, 52.7 and 58.8; 115 MB
-    // on changing tensors 63.3 and 59.4, 120 MB and the next one 112 and 108; 240 MB 127 and 88, 256 and 245.  144 channels of
-    // 112 x 112 / 2, 30 MB 28 both, 44.5 and 46.2; 60 MB 60.9 and 48.4, 91.8 and 84.9.
-    const size_t in_bytes = (size_t)s.n * s.c_out * s.h * s.w * sizeof(T), out_bytes = (size_t)s.n * s.c_out * s.ho * s.wo * sizeof(T);
-    constexpr size_t kMB = (size_t)1 << 20;
-    const bool stream_out = sizeof(T) == 4 && out_bytes > 16 * kMB && (in_bytes + out_bytes <= 64 * kMB || in_bytes + 2 * out_bytes > 256 * kMB);
-#define PATDNN_DW_LAUNCH(S, NP, V, W) \
-    if (W && stream_out) hipLaunchKernelGGL((dw_conv_kernel<S, NP, V, W, T, W && sizeof(T) == 4>), grid, block, 0, stream, a); \
-    else hipLaunchKernelGGL((dw_conv_kernel<S, NP, V, W, T, false>), grid, block, 0, stream, a)
-    if (wide && s.stride == 1) { PATDNN_DW_LAUNCH(1, 8, true, true); }
-    else if (wide) { PATDNN_DW_LAUNCH(2, 8, true, true); }
-    else if (s.stride == 1) {
-        if (vec && vst) { PATDNN_DW_LAUNCH(1, 4, true, true); }
-        else if (vec) { PATDNN_DW_LAUNCH(1, 4, true, false); }
-        else if (vst) { PATDNN_DW_LAUNCH(1, 4, false, true); }
-        else { PATDNN_DW_LAUNCH(1, 4, false, false); }
-    } else {
-        if (vec && vst) { PATDNN_DW_LAUNCH(2, 4, true, true); }
-        else if (vec) { PATDNN_DW_LAUNCH(2, 4, true, false); }
-        else if (vst) { PATDNN_DW_LAUNCH(2, 4, false, true); }
-        else { PATDNN_DW_LAUNCH(2, 4, false, false); }
-    }
-#undef PATDNN_DW_LAUNCH
+    const auto kernel = s.stride == 1 ? &dw_conv_kernel<1, T> : &dw_conv_kernel<2, T>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, stream, a);
     return hipGetLastError();
 }
 

@@ -80,6 +80,7 @@ struct DevFkw {
     // kernel was removed) and its four weights
     const int32_t* dw_mask = nullptr;
     const float* dw_weight = nullptr;
+    bool dw_finite = false;          // all of those weights are finite
     // the same by channel, four tap positions in nibbles (-1: removed); NULL where a weight is
     // not finite in binary16 (zero padding must not meet it)
     const int32_t* dw_taps = nullptr;

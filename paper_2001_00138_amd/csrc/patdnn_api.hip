@@ -751,6 +751,7 @@ patdnn_status_t upload_layer(patdnn_layer* h)
         }
         up.add(dmask, &d.dw_mask);
         up.add(dweight, &d.dw_weight);
+        d.dw_finite = std::all_of(dweight.begin(), dweight.end(), [](float w) { return std::isfinite(w); });
         if (to_f16(dweight, dweight16)) {         // else zero padding would meet an infinite weight
             up.add(taps, &d.dw_taps);
             up.add(tap_weight, &d.dw_tap_weight);
