@@ -592,6 +592,9 @@ static hipError_t launch_f16_t(const F16Args& args, const ConvShape& s, long lon
 //   512 -> 512 at 7x7, 64 images      136  146   95   52   68   69     (784 of the fourth)
 //   256 -> 256 at 28x28, one image     47   42   28   12    9    9     (200 of the fifth and sixth)
 //   512 -> 512 at 14x14, one image     81   75   50   21   22   16     (112)
+//   328 -> 256 at 32x47, 5 images      58   46   37   43   53   50     (240 of the third)
+//    89 ->  62 at 120x120, 2 images    23   17   13   17   24   23     (226)
+//    32 -> 108 at 58x58 / 2, 17 images 17   12    9   19   --   28     (224)
 struct F16Shape {
     int fm, pn, wf, wp, wk, min_blocks;
     bool strided;                    // only where every filter set's staging counts four times: stride 2
@@ -602,7 +605,7 @@ struct F16Shape {
 static const F16Shape kF16Shapes[] = {
     PATDNN_F16(2, 4, 2, 2, 1, 256, false),
     PATDNN_F16(2, 2, 2, 2, 1, 128, true),
-    PATDNN_F16(1, 2, 1, 4, 1, 256, false),
+    PATDNN_F16(1, 2, 1, 4, 1, 224, false),
     PATDNN_F16(1, 2, 1, 1, 4, 400, false),
     PATDNN_F16(1, 1, 1, 1, 8, 0, false),
     PATDNN_F16(1, 1, 1, 1, 4, 0, false),
@@ -629,7 +632,20 @@ static F16Plan f16_plan(const ConvShape& s, bool pair, F16Args& a)
         a.fsets = (a.fblocks + filters - 1) / filters;
         plan.blocks = (long long)a.strips * a.tiles * a.fsets;
         plan.lds = std::max((size_t)a.npp * (f16_buffers(v.wk) * 2 * v.wk * 16 + 4), v.wk > 1 ? (size_t)v.wf * v.wp * v.wk * 4096 : 0) + (size_t)filters * 32 * 8;
-        if (plan.blocks < v.min_blocks || plan.blocks > INT32_MAX || plan.lds > 160 * 1024) continue;
+        if (&v == kF16Shapes) {
+            // Staged rows that leave a CU one workgroup of the first shape: the next one's are half of that (stride 2; 447 ->
+            // 424 at 106 x 95, 9 images 249 us and 142, 39 -> 421 at 79 x 121, 24 images 95 and 65, 449 -> 264 at 163 x 224, 4 images 222
+            // and 182).
+            if (plan.lds > 80 * 1024) continue;
+            // Filters that fill its sets badly: the third shape has sets of 32 and needs, at filters that fill both, some
+            // 1 + 0.0015 c_in times the time (66 -> 439 1.02, 128 -> 128 1.18, 256 -> 256 1.37).  40 -> 88 at 54 x 55, 50 images 39.3 us
+            // and 32.1, 40 -> 192 at 82 x 82 43.8 and 39.5, 208 -> 272 at 32 x 32, 24 images 57.4 and 46.9; 296 -> 68 at 35 x 44 48.7 and 55.8.
+            // (Layers of fewer channels stay, as tests want them; 27 -> 160 at 220 x 178 31.9 and 24.7.)
+            if (s.stride == 1 && s.c_in >= 40 && (double)a.fsets * filters > (1.0 + 0.0015 * s.c_in) * a.fblocks) continue;
+        }
+        // (with so few channels to split that the wavefronts of the next shapes have one step each, a little earlier)
+        const int least = &v == kF16Shapes + 2 && a.steps <= 4 ? 192 : v.min_blocks;
+        if (plan.blocks < least || plan.blocks > INT32_MAX || plan.lds > 160 * 1024) continue;
         plan.shape = (int)(&v - kF16Shapes);
         break;
     }

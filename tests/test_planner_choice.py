@@ -180,3 +180,34 @@ def test_binary16_choice_is_close_to_the_fastest(case):
     L.close()
     assert got >= -1
     assert (walk if got < 0 else matrix) <= 1.4 * min(walk, matrix), got
+
+
+# c_in, c_out, n, h, w, stride; us of the first three launch shapes of the binary16 matrix kernel (0: does not fit) and of the
+# first that splits the channels
+MEASURED_F16_SHAPES = [
+    ((128, 128, 64, 56, 56, 1), (80, 86, 94, 151)),
+    ((256, 256, 64, 28, 28, 1), (71, 90, 97, 140)),
+    ((40, 88, 50, 54, 55, 1), (39, 39, 32, 54)),
+    ((40, 192, 16, 82, 82, 1), (44, 45, 40, 70)),
+    ((208, 272, 24, 32, 32, 1), (57, 57, 47, 79)),
+    ((126, 248, 15, 127, 127, 1), (179, 220, 239, 386)),
+    ((328, 256, 5, 32, 47, 1), (58, 46, 37, 43)),
+    ((89, 62, 2, 120, 120, 1), (23, 17, 13, 17)),
+    ((32, 264, 4, 40, 40, 1), (15, 11, 8, 10)),
+    ((447, 424, 9, 106, 95, 2), (249, 142, 489, 730)),
+    ((39, 421, 24, 79, 121, 2), (95, 65, 158, 284)),
+    ((32, 108, 17, 58, 58, 2), (17, 12, 9, 19)),
+]
+
+
+@pytest.mark.parametrize("case", MEASURED_F16_SHAPES)
+def test_binary16_launch_shape_is_close_to_the_fastest(case):
+    (c_in, c_out, n, h, w, stride), us = case
+    L = B.Layer(np.ones((c_out, c_in, 3, 3), np.float32), np.zeros((c_out, c_in), np.uint8), np.ones((c_out, c_in), np.uint8),
+                wl.pattern_library(wl.PATTERN_SEED), stride=stride, host_only=True)
+    choice = B.lib().patdnn_internal_f16_choice
+    choice.argtypes = [ctypes.c_void_p] * 2 + [ctypes.c_int32] * 3
+    choice.restype = ctypes.c_int32
+    shape = choice(L.handle, 4096, n, h, w) >> 1
+    L.close()
+    assert 0 <= shape < 4 and us[shape] <= 1.05 * min(us), shape
