@@ -43,11 +43,12 @@
 //     512 pixels with each fragment brought into LDS once were even at 385 to 512 workgroups on resident tensors, 4 % ahead
 //     on changing ones and for 512 channels, and 10 to 20 % slower at other numbers: 128 -> 128 at 56 x 56, 42 images 74 us
 //     and 62, 84 images 110 and 92, 120 images 122 and 110.)
-//   * Channel and bias of the filters wait in LDS for the epilogue, which waited for each in turn.
+//   * Channel and bias of the filters wait in LDS for the epilogue, which waited for each in turn; its stores are 32-bit
+//     offsets into a buffer that ends where the tensor does.
 //
 // What bounds it: 128 -> 128 at 56 x 56, 64 images (59 GFLOP with the zeros, 51 MB in and out) takes
-// 76 us on changing tensors, 0.8 PFLOP/s, where the walk over the kept weights took 1990; one image of 256 -> 256
-// at 28 x 28 9 us (57).  784 workgroups, two on a CU, are one and a half rounds, the matrix cores are busy 43 % of the SIMDs'
+// 72 us on changing tensors, 0.8 PFLOP/s, where the walk over the kept weights took 1990; one image of 256 -> 256
+// at 28 x 28 7 us (57).  784 workgroups, two on a CU, are one and a half rounds, the matrix cores are busy 43 % of the SIMDs'
 // cycles, LDS 25 % of the CUs', and the epilogue's stores and a tile's first loads are hidden by nothing.  (Inputs two
 // chunks ahead: 84 us; what is in flight is enough.)
 #include <hip/hip_fp16.h>
@@ -436,12 +437,17 @@ void f16_conv_kernel(F16Args a)
             }
     }
 
-    // ---- epilogue: register r of a block is filter 8 * (r / 4) + 4 * half + r % 4, pixel lane % 32
+    // ---- epilogue: register r of a block is filter 8 * (r / 4) + 4 * half + r % 4, pixel lane % 32.  Byte offsets from
+    // the tile's first image, those of pixels and filters that do not exist out of range whatever is added to them: no
+    // branch and no 64-bit address a store (128 values a lane were 8 of a tile's 37 us at 128 -> 128, 6 of 15 at 24 -> 400).
+    // us before -> after: 128 -> 128 at 56 x 56, 64 images 76 -> 72; 24 -> 400 at 46 x 33, 45 images 40 -> 32; 24 -> 408 at 51 x 69 45 -> 37;
+    // 28 -> 416 at 193 x 224, 5 images 130 -> 120
     const size_t oplane = (size_t)a.ho * a.wo;
     const int reg0 = WK > 1 ? wk * RK : 0;
-    unsigned odd = 0;                                 // pixels of this lane with a sum that is not finite
+    const bool pair_out = PAIR && RK >= 2 && a.pair_out;
+    float finite[PN];                                 // NaN where a sum is not
+    unsigned off[PN];
     bool ok[PN];
-    size_t off[PN];
 #pragma unroll
     for (int p = 0; p < PN; ++p) {
         const int q = pix0 + (wp * PN + p) * 32 + l32;
@@ -449,48 +455,50 @@ void f16_conv_kernel(F16Args a)
         split_row(min(q, last), img, oy, sx);
         const int ox = strip * a.sw + sx;
         ok[p] = q <= last && ox < a.wo;
-        off[p] = (size_t)img * a.c_out * oplane + (size_t)oy * a.wo + ox;
+        off[p] = ok[p] ? 2u * ((unsigned)((img - img0) * a.c_out) * (unsigned)oplane + (unsigned)(oy * a.wo + ox - (pair_out ? lane & 1 : 0))) : 0x7FFFFFFFu;
+        finite[p] = 0.0f;
     }
-    const bool pair_out = PAIR && RK >= 2 && a.pair_out;
+    const size_t out_tail = (size_t)(a.n - img0) * a.c_out * oplane * 2;
+    __amdgpu_buffer_rsrc_t osrc = __builtin_amdgcn_make_buffer_rsrc((void*)(a.out + (size_t)img0 * a.c_out * oplane), 0,
+                                                                    (int)(unsigned)std::min<size_t>(out_tail, 0x7FFFFFFFu), 0x00020000);
+    const float least = a.relu ? 0.0f : __builtin_nanf("");      // the maximum of a value and a NaN is the value
+    // neighbouring pixels trade: the even one takes both of filter r, the odd one both of r + 1
+    const unsigned trade = lane & 1 ? 0x03020706u : 0x05040100u;
 #pragma unroll
     for (int f = 0; f < FM; ++f)
 #pragma unroll
         for (int r = 0; r < RK; r += 2) {
-            int co[2];
+            unsigned co[2];
             float b[2];
-            bool has[2];
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
                 const int2 slot = slots[(wf * FM + f) * 32 + 8 * ((reg0 + r + k) >> 2) + 4 * half + ((reg0 + r + k) & 3)];
-                co[k] = slot.x;
+                co[k] = slot.x >= 0 ? 2u * (unsigned)slot.x * (unsigned)oplane : 0x80000000u;
                 b[k] = __int_as_float(slot.y);
-                has[k] = co[k] >= 0;
             }
 #pragma unroll
             for (int p = 0; p < PN; ++p) {
-                float v[2];
+                __half v[2];
 #pragma unroll
                 for (int k = 0; k < 2; ++k) {
-                    v[k] = acc[f][p][r + k];
-                    odd |= (unsigned)(ok[p] && !(fabsf(v[k]) < __builtin_inff())) << p;
-                    v[k] += b[k];
-                    if (a.relu) v[k] = fmaxf(v[k], 0.0f);
+                    const float sum = acc[f][p][r + k];
+                    finite[p] = fmaf(sum, 0.0f, finite[p]);
+                    v[k] = __float2half_rn(fmaxf(sum + b[k], least));
                 }
                 if (pair_out) {
-                    // neighbouring pixels trade: the even one takes both of filter r, the odd one both of r + 1
-                    const bool right = lane & 1;
-                    const float give = right ? v[0] : v[1];
-                    const float got = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(give), 0xB1, 0xf, 0xf, true));   // quad_perm [1,0,3,2]
-                    const __half2 h = right ? __floats2half2_rn(got, v[1]) : __floats2half2_rn(v[0], got);
-                    if (ok[p] && (right ? has[1] : has[0]))
-                        *reinterpret_cast<__half2*>(&a.out[off[p] - (right ? 1 : 0) + (size_t)(right ? co[1] : co[0]) * oplane]) = h;
+                    const unsigned mine = (unsigned)__half_as_ushort(v[0]) | (unsigned)__half_as_ushort(v[1]) << 16;
+                    const unsigned next = (unsigned)__builtin_amdgcn_mov_dpp((int)mine, 0xB1, 0xf, 0xf, true);      // quad_perm [1,0,3,2]
+                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_amdgcn_perm(next, mine, trade), osrc, (int)(off[p] + (lane & 1 ? co[1] : co[0])), 0, 0);
                 } else {
 #pragma unroll
                     for (int k = 0; k < 2; ++k)
-                        if (ok[p] && has[k]) a.out[off[p] + (size_t)co[k] * oplane] = __float2half_rn(v[k]);
+                        __builtin_amdgcn_raw_buffer_store_b16((short)__half_as_ushort(v[k]), osrc, (int)(off[p] + co[k]), 0, 0);
                 }
             }
         }
+    unsigned odd = 0;                                 // pixels of this lane with a sum that is not finite
+#pragma unroll
+    for (int p = 0; p < PN; ++p) odd |= (unsigned)(ok[p] && finite[p] != 0.0f) << p;
     if (!__any(odd)) return;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // after the stores above, the neighbour's among them
     f16_again<FM, PN, WF, WP, WK>(odd, wave);
@@ -557,8 +565,8 @@ static bool f16_tiles(const ConvShape& s, int pix, bool pair, F16Args& a)
     const int between = std::min(s.n - 1, (rows_out - 1 + s.ho - 1) / s.ho);
     const int rows = (rows_out - 1) * s.stride + between * (a.vh - s.ho * s.stride) + 3;
     a.npp = (rows * a.pitch + 127) / 128 * 128;
-    // byte offsets from a tile's first image
-    return (long long)(between + 2) * s.c_in * s.h * s.w < (1ll << 30);
+    // byte offsets from a tile's first image, in and out
+    return (long long)(between + 2) * s.c_in * s.h * s.w < (1ll << 30) && (long long)(between + 2) * s.c_out * s.ho * s.wo < (1ll << 30);
 }
 
 template <int FM, int PN, int WF, int WP, int WK, bool PAIR>
