@@ -22,7 +22,7 @@
 //   * Pixels are cut into strips, rows and tiles as in kernel_f16.hip; two rows are numbered together
 //     where windows are pooled, so that a window lies in four neighbouring lanes.
 //   * A workgroup is eight wavefronts, two per SIMD, and goes on to further tiles.  Four compute 64 filters x 64
-//     (or 32) pixels each, four stage the inputs: the loads of one step of 32 channels are in flight, the
+//     (or 32) pixels each, four (or eight) stage the inputs: the loads of one step of 32 channels are in flight, the
 //     largest magnitude of the next is found, and the one after it is split and put into LDS, while the matrix
 //     cores work on a fourth; a barrier per step.  The matrix instructions leave the vector ALU to the other wavefront, and
 //     loads of weights (from L2 in fragment order, a tap ahead) do not wait behind those of the inputs.
@@ -107,7 +107,15 @@ static __device__ __forceinline__ void split_pixel(SplitArgsPtr a, int q, int& i
     oy = (r - img * a->hr) * a->rp + sub;
 }
 
-// units of 64 lanes x 8 channels that a staging wavefront holds per step, a lane with one pixel or a pair
+// Wavefronts that stage: each of the four eights of a step's channels has one, or two that take every other unit of
+// its pixels.  Tiles of few pixels are taken where those pixels lie two apart and four wavefronts cannot stage
+// as fast as the others compute; the third wavefront of a SIMD leaves each 168 registers, enough for two blocks of
+// sums and not for four.  us with 4 / 8, 64 images of stride 2: 256 -> 256 at 28 x 28 80.8 / 74.5, 512 -> 512 at 14 x 14
+// 76.3 / 70.4, 128 -> 128 at 56 x 56, whose weights come as fast as L1 gives them, 88.1 / 88.6 (kept 1/3.6 each).
+constexpr int split_stagers(int pn) { return pn == 2 ? 8 : 4; }
+constexpr int split_threads(int pn) { return 64 * (4 + split_stagers(pn)); }
+
+// units of 64 lanes x 8 channels that the wavefronts of eight channels hold per step, a lane with one pixel or a pair
 constexpr int split_units(bool pair) { return pair ? 5 : 9; }
 constexpr int kSplitTop = 13;        // exponent that the largest input of a tile is brought to
 constexpr int kSplitMost = 14;       // up to which exponent later channels are taken as they are
@@ -319,11 +327,13 @@ static __device__ __forceinline__ void split_again(unsigned again, int u, int wa
 }
 
 template <int PN, int WF, int WP, bool PAIR>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void split_conv_kernel(SplitArgs)
+__global__ __launch_bounds__(split_threads(PN)) __attribute__((amdgpu_waves_per_eu(split_threads(PN) / 256, split_threads(PN) / 256)))
+void split_conv_kernel(SplitArgs)
 {
     extern __shared__ uint4 lds4[];
-    constexpr int PIX = 16 * PN * WP, UPX = PAIR ? 2 : 1, UNITS = split_units(PAIR);
-    static_assert(WF * WP == 4, "four wavefronts compute, four stage");
+    constexpr int PARTS = split_stagers(PN) / 4;      // staging wavefronts of eight channels
+    constexpr int PIX = 16 * PN * WP, UPX = PAIR ? 2 : 1, UNITS = (split_units(PAIR) + PARTS - 1) / PARTS;
+    static_assert(WF * WP == 4, "four wavefronts compute");
     const int lane = threadIdx.x & 63, quarter = lane >> 4, l16 = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int per_xcd = gridDim.x >> 3, rank = blockIdx.x >> 3;
@@ -334,7 +344,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     int* const exps = reinterpret_cast<int*>(marked + kSplitMarks);
     unsigned char* const marks = reinterpret_cast<unsigned char*>(top_bits + 8);
     if (threadIdx.x < 3 + kSplitMarks) top_bits[threadIdx.x] = 0;
-    for (int e = threadIdx.x; e < kSplitMarks * a->npp / 4; e += 512) reinterpret_cast<unsigned*>(marks)[e] = 0;
+    for (int e = threadIdx.x; e < kSplitMarks * a->npp / 4; e += split_threads(PN)) reinterpret_cast<unsigned*>(marks)[e] = 0;
     __syncthreads();
     const int steps = a->steps;
     const int my_units = (a->total - u0 + (int)gridDim.x - 1) / (int)gridDim.x;
@@ -343,7 +353,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (wave >= 4) {
         // ---- staging: of iteration g the inputs of chunk g + 1 into LDS, the loads of chunk g + 3, the largest
         // input of chunk g + 2; the smallest one beside zero stays with the lane until its chunk's scale is known
-        const int w4 = wave - 4;
+        const int w4 = wave & 3, part = (wave >> 2) - 1;
+        auto unit = [&](int k) __attribute__((always_inline)) -> int { return k * PARTS + part; };
         const int plane = a->h * a->w, c_in = a->c_in, npp = a->npp;
         unsigned off[UNITS];
         const char* in_blk = nullptr;
@@ -356,7 +367,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             range = (unsigned)std::min<size_t>(tail, 0x80000000u);
 #pragma unroll
             for (int k = 0; k < UNITS; ++k) {
-                const int e = (k * 64 + lane) * UPX;
+                const int e = (unit(k) * 64 + lane) * UPX;
                 const int rr = div_by(e, b->div_pitch), cc = e - rr * b->pitch;
                 const int v = t.vrow0 + rr, img = div_by(v, b->div_vh);
                 const int y = v - img * b->vh - b->pad, x = t.strip * b->sw * b->conv_stride + cc - b->lead;
@@ -364,7 +375,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 off[k] = ok ? 4u * (unsigned)((img - t.img0) * c_in * plane + y * b->w + x) : ~0u;
             }
         };
-        const int units = a->npb;                     // this wavefront's eight channels of each
+        const int units = (a->npb - part + PARTS - 1) / PARTS;   // this wavefront's: eight channels of each
         float raw[2][UNITS][UPX][8];
         unsigned low[2];
         int lu = u0, ls = 0;                          // what is loaded next
@@ -406,7 +417,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                             unsigned v = ~0u;
 #pragma unroll
                             for (int j = 0; j < 8; ++j) v = min(v, split_low(src[k][q][j]));
-                            if (v < least) marks[slot * npp + (k * 64 + lane) * UPX + q] = 1;
+                            if (v < least) marks[slot * npp + (unit(k) * 64 + lane) * UPX + q] = 1;
                         }
                 if (lane == 0) atomicOr(&marked[slot], kSplitSome);
             }
@@ -420,7 +431,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 unsigned* const pl = &lo.x;
 #pragma unroll
                 for (int j = 0; j < 8; j += 2) split_pair(src[q][j], src[q][j + 1], m, ph[j >> 1], pl[j >> 1]);
-                uint4* dst = lds4 + ((chunk & 1) * 4 + w4) * 2 * npp + (k * 64 + lane) * UPX + q;
+                uint4* dst = lds4 + ((chunk & 1) * 4 + w4) * 2 * npp + (unit(k) * 64 + lane) * UPX + q;
                 dst[0] = hi;
                 dst[npp] = lo;
             }
@@ -453,7 +464,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         int gs = 0, old = kSplitMarks - 1;            // step of chunk g, marks of the unit before its own
         auto clear = [&]() __attribute__((always_inline)) {
             if (gs == 0) {
-                if (w4 == 0 && marked[old]) {
+                if (wave == 4 && marked[old]) {
                     for (int e = lane; e < npp; e += 64) marks[old * npp + e] = 0;
                     if (lane == 0) marked[old] = 0;
                 }
@@ -761,7 +772,7 @@ static hipError_t launch_split_t(SplitArgs a, hipStream_t stream)
         if (e != hipSuccess) return e;
     }
     const int grid = std::min(a.total, 256);
-    hipLaunchKernelGGL((split_conv_kernel<PN, WF, WP, PAIR>), dim3((unsigned)grid), dim3(512), lds, stream, a);
+    hipLaunchKernelGGL((split_conv_kernel<PN, WF, WP, PAIR>), dim3((unsigned)grid), dim3(split_threads(PN)), lds, stream, a);
     return hipGetLastError();
 }
 
