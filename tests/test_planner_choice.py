@@ -211,3 +211,32 @@ def test_binary16_launch_shape_is_close_to_the_fastest(case):
     shape = choice(L.handle, 4096, n, h, w) >> 1
     L.close()
     assert 0 <= shape < 4 and us[shape] <= 1.05 * min(us), shape
+
+
+# c_in, c_out, n, h, w, pad, patterns, kept kernels; us of the walk and of the tap-product kernel: layers that take little
+# more than a launch, where a group on several wavefronts is faster than the walk.  One tile of at most 64 groups keeps the walk.
+SMALL = [
+    ((40, 155, 21, 10, 10, 1, 8, 1722), (22.9, 9.1)),
+    ((24, 240, 2, 18, 18, 1, 12, 2880), (13.6, 8.3)),
+    ((36, 16, 8, 39, 39, 1, 12, 160), (12.6, 7.8)),
+    ((114, 24, 1, 19, 19, 1, 6, 760), (15.9, 11.3)),
+    ((64, 512, 1, 14, 14, 1, 8, 9102), (13.3, 10.8)),
+]
+
+
+@pytest.mark.parametrize("case", SMALL)
+def test_walk_of_small_layers_only_where_one_tile_has_few_groups(case):
+    (c_in, c_out, n, h, w, pad, patterns, kept), _ = case
+    rng = np.random.default_rng(3)
+    mask = np.zeros(c_in * c_out, np.uint8)
+    mask[rng.permutation(mask.size)[:kept]] = 1
+    layer = B.Layer(rng.standard_normal((c_out, c_in, 3, 3), dtype=np.float32),
+                    rng.integers(0, patterns, (c_out, c_in), dtype=np.uint8), mask.reshape(c_out, c_in),
+                    wl.pattern_library(wl.PATTERN_SEED, patterns), pad=pad, host_only=True)
+    choice = B.lib().patdnn_internal_choice
+    choice.argtypes = [ctypes.c_void_p] + [ctypes.c_int32] * 3 + [ctypes.c_size_t, ctypes.c_void_p]
+    for room in (1 << 27, 0):
+        chosen = B.Config()
+        choice(layer.handle, n, h, w, room, ctypes.byref(chosen))
+        one_tile = n == 1 and (h, w) == (14, 14)
+        assert B.patdnn_variant_name(chosen.variant) == ("fkw" if one_tile else "taps_f8")
