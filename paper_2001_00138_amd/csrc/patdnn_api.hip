@@ -873,13 +873,15 @@ patdnn_config_t default_config(patdnn_layer* h, const ConvShape& shape, size_t s
     }
     // Several wavefronts for a group take the place of channel slices in many launches, which then need no second kernel:
     // 128 -> 256 at 56 x 56, one image, 14.2 us, in slices 18.6.  Where whole groups would leave half of the SIMDs without
-    // a wavefront and slices were the answer they stay it up to 1.3 times the time (the tests hold the library to
-    // it: 96 -> 200 at 7 x 7, 64 images, 16.5 us, unsplit 13.1), as does the walk where one tile has no more than 64 whole groups and
+    // a wavefront and slices were the answer they stay it up to 1.3 times the time (the tests hold the library to it: 96 -> 200 at
+    // 7 x 7, 64 images, 16.5 us, unsplit 13.1), but not below 128 groups, where that costs most: 34 -> 276 at 24 x 15, one image, half kept
+    // 15.4, unsplit 9.8; 32 -> 24 at 20 x 20, eight images, all kept 12.4 and 8.4; of 54 such layers three 2 to 10 % the other way.
+    // The walk stays the answer where one tile has no more than 64 whole groups and
     // all takes little more than a launch (64 -> 512 at 14 x 14, one image, 13.3 us, this kernel 10.8).  Above, the walk where whole groups
     // are estimated to be slower loses: 40 -> 155 at 10 x 10, 21 images, 23 us, this kernel 9.3; 24 -> 240 at 18 x 18, two images, 13.6
     // and 8.4; 36 -> 16 at 39 x 39, eight images, 12.5 and 8.0.
     const long long groups = tiles * ((s.c_out + kTapGroup - 1) / kTapGroup);
-    const bool few = groups < 512 && split.whole < unsplit.whole;
+    const bool few = groups >= 128 && groups < 512 && split.whole < unsplit.whole;
     const Fastest& taps_best = split.us < unsplit.us * (few ? 1.3 : 1.0) ? split : unsplit;
     const bool walk = best.variant == PATDNN_VARIANT_FKW && best_us < 15.0 && tiles == 1 && groups <= 64 && best_us < std::min(split.whole, unsplit.whole);
     if (taps_best.us < best_us && !walk) return taps_best.c;

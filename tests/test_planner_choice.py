@@ -240,3 +240,27 @@ def test_walk_of_small_layers_only_where_one_tile_has_few_groups(case):
         choice(layer.handle, n, h, w, room, ctypes.byref(chosen))
         one_tile = n == 1 and (h, w) == (14, 14)
         assert B.patdnn_variant_name(chosen.variant) == ("fkw" if one_tile else "taps_f8")
+
+
+# layers of few groups with room for partial sums; us in channel slices and with groups on several wavefronts
+FEW_GROUPS = [
+    ((34, 276, 1, 24, 15, 1, 8, 4692), (15.4, 9.8)),
+    ((32, 24, 8, 20, 20, 1, 8, 768), (12.4, 8.4)),
+    ((48, 80, 1, 23, 28, 1, 8, 1067), (12.1, 9.4)),
+]
+
+
+@pytest.mark.parametrize("case", FEW_GROUPS)
+def test_few_groups_are_not_cut_into_slices_where_wavefronts_share_them(case):
+    (c_in, c_out, n, h, w, pad, patterns, kept), _ = case
+    rng = np.random.default_rng(4)
+    mask = np.zeros(c_in * c_out, np.uint8)
+    mask[rng.permutation(mask.size)[:kept]] = 1
+    layer = B.Layer(rng.standard_normal((c_out, c_in, 3, 3), dtype=np.float32),
+                    rng.integers(0, patterns, (c_out, c_in), dtype=np.uint8), mask.reshape(c_out, c_in),
+                    wl.pattern_library(wl.PATTERN_SEED, patterns), pad=pad, host_only=True)
+    choice = B.lib().patdnn_internal_choice
+    choice.argtypes = [ctypes.c_void_p] + [ctypes.c_int32] * 3 + [ctypes.c_size_t, ctypes.c_void_p]
+    chosen = B.Config()
+    choice(layer.handle, n, h, w, 1 << 27, ctypes.byref(chosen))
+    assert B.patdnn_variant_name(chosen.variant) == "taps_f8" and chosen.ksplit == 1
