@@ -248,7 +248,7 @@ patdnn_status_t patdnn_layout_stats(patdnn_handle_t h, patdnn_stats_t* out);
  *                           (section 5.4 load-redundancy elimination); see
  *                           patdnn_variant_name
  *   after the tiled ones    "dw_p1x4": depthwise layers (groups == c_in), one pass over
- *                           input and output with 16-byte accesses, four outputs per lane;
+ *                           input and output with vector accesses, two rows of outputs per lane;
  *                           the default for such layers (section 6.1 evaluates MobileNet-V2)
  *                           "noopt", "csr": comparison kernels of the paper's evaluation, never
  *                           chosen by the library: the layer before filter-kernel reorder with
@@ -257,8 +257,9 @@ patdnn_status_t patdnn_layout_stats(patdnn_handle_t h, patdnn_stats_t* out);
  *                           layer as a CSR matrix (the control of section 6.2); pruned,
  *                           non-depthwise layers only
  *                           "taps_f8", "taps_f16": tap-product kernel on the matrix cores in
- *                           fp32 (stride 1, pruned layers), 8 or 16 filters per wavefront; `ck` up
- *                           to 160 channels, `waves` up to 16
+ *                           fp32 (stride 1, pruned layers), groups of 8 or 16 filters; `ck` up
+ *                           to 160 channels, `waves` (groups a workgroup) up to 16; launches of
+ *                           few groups may run one of 8 on two or four wavefronts
  *                           "split_f16": pruned layers in fp32 on the binary16 matrix cores
  *                           (outputs keep fp32's precision whatever lies beside their inputs; values
  *                           that make ordinary ones vanish beside them, -1e30 say, cost time)

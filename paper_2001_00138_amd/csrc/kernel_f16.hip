@@ -48,8 +48,8 @@
 //
 // What bounds it: 128 -> 128 at 56 x 56, 64 images (59 GFLOP with the zeros, 51 MB in and out) takes
 // 72 us on changing tensors, 0.8 PFLOP/s, where the walk over the kept weights took 1990; one image of 256 -> 256
-// at 28 x 28 7 us (57).  784 workgroups, two on a CU, are one and a half rounds, the matrix cores are busy 43 % of the SIMDs'
-// cycles, LDS 25 % of the CUs', and the epilogue's stores and a tile's first loads are hidden by nothing.  (Inputs two
+// at 28 x 28 7 us (57).  784 workgroups, two on a CU, are one and a half rounds, the matrix cores are busy 48 % of the SIMDs'
+// cycles, LDS 28 % of the CUs', and a tile's first loads are hidden by nothing.  (Inputs two
 // chunks ahead: 84 us; what is in flight is enough.)
 #include <hip/hip_fp16.h>
 

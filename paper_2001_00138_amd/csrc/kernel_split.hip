@@ -33,10 +33,12 @@
 //   * Sums that are not finite, or too small for the scale, are worked out again from the tensor (see split_again).
 //
 // What bounds it, 128 -> 128 at 56 x 56 / 2, 64 images: the tiles of 64 pixels that its strips allow are 784 units of work,
-// three rounds of 256 CUs and a fourth of 16; the matrix cores are busy 27 % of the SIMDs' cycles, LDS 26 % of the
-// CUs', half of that conflicts of windows two pixels apart.  us, the vector kernels' -> this one's, on tensors in the last-level cache: that layer, kept 1/3.6, 99 -> 86 (114 ->
-// 101 on changing ones); 256 -> 256 at 28 x 28 / 2 196 -> 81; 64 -> 64 at 112 x 112 / 1, 32 images, all kept 200 -> 124; 232 -> 96 at
-// 95 x 95 / 2, three images, all kept 428 -> 46.
+// three rounds of 256 CUs and a fourth of 16; a step of 32 channels takes 4.6 us while others are staged,
+// 3.0 without, 1.4 of them matrix instructions: weights, 288 KB a step and CU through L1, and inputs share the texture
+// addresser.  (LDS is busy 28 % of the cycles, half of that conflicts of windows two pixels apart; a layout
+// without them is no faster.)  us, the vector kernels' -> this one's, on tensors in the last-level cache: that layer, kept
+// 1/3.6, 99 -> 87 (114 -> 97 on changing ones); 256 -> 256 at 28 x 28 / 2 196 -> 74; 64 -> 64 at 112 x 112 / 1, 32 images, all kept
+// 200 -> 124; 232 -> 96 at 95 x 95 / 2, three images, all kept 428 -> 46.
 #include <hip/hip_fp16.h>
 
 #include <algorithm>

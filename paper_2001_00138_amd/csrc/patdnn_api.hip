@@ -490,9 +490,9 @@ std::vector<int> default_variant_order(const patdnn_layer* h)
 // ---- the configuration used when the caller has not chosen or tuned one: the candidate with the
 // smallest estimate of its time.  The estimates are a few products; their constants were fitted to
 // measurements of layers from 16 to 512 channels, 7x7 to 224x224 pixels and 1 to 64 images in every
-// candidate configuration; on 110 other layers of 6 to 56 patterns (profiles/planner_choice.txt) the
-// chosen candidate is 2 % slower than the fastest one on average without a workspace, 5 % with
-// one, and at most 36 %.
+// candidate configuration; on 80 other layers of 6 to 56 patterns (profiles/planner_choice.txt) the
+// chosen candidate is 4.6 % slower than the fastest one on average (median 0.1 %) without a workspace, 8.1 % (1.2 %) with one,
+// and once, a layer of 56 patterns in 43 small images, 2.2 times as slow.
 
 // Tap-product kernel, microseconds, for workgroups of `waves` wavefronts of `filters` filters.  Workgroups of one round
 // share a CU as far as LDS and registers allow, and the wavefronts of each are dealt to the SIMDs from the first one on;
