@@ -238,8 +238,9 @@ constexpr int f16_ahead(int blocks, int wk, bool pair) { return pair || (wk == 4
 constexpr bool f16_branches(int blocks, int wk) { return wk == 1 && blocks == 2; }
 
 // PAIR: rows of whole aligned pairs of pixels (see f16_tiles): staged two pixels per load, and
-// stored two pixels at a time where the output's rows are the same.
-template <int FM, int PN, int WF, int WP, int WK, bool PAIR>
+// stored two pixels at a time where the output's rows are the same.  FAR: a tile's outputs reach 2^30 elements past its
+// first image's first one (3 -> 64 at 4200 x 4200), stores are through 64-bit addresses.
+template <int FM, int PN, int WF, int WP, int WK, bool PAIR, bool FAR>
 __global__ __launch_bounds__(64 * WF * WP * WK) __attribute__((amdgpu_waves_per_eu(f16_waves(FM * PN, false), f16_waves(FM * PN, true))))
 void f16_conv_kernel(F16Args a)
 {
@@ -447,6 +448,7 @@ void f16_conv_kernel(F16Args a)
     const bool pair_out = PAIR && RK >= 2 && a.pair_out;
     float finite[PN];                                 // NaN where a sum is not
     unsigned off[PN];
+    size_t pixel[PN];                                 // FAR: elements instead
     bool ok[PN];
 #pragma unroll
     for (int p = 0; p < PN; ++p) {
@@ -455,12 +457,13 @@ void f16_conv_kernel(F16Args a)
         split_row(min(q, last), img, oy, sx);
         const int ox = strip * a.sw + sx;
         ok[p] = q <= last && ox < a.wo;
+        if constexpr (FAR) pixel[p] = (size_t)(img - img0) * a.c_out * oplane + (size_t)oy * a.wo + (ox - (pair_out ? lane & 1 : 0));
         off[p] = ok[p] ? 2u * ((unsigned)((img - img0) * a.c_out) * (unsigned)oplane + (unsigned)(oy * a.wo + ox - (pair_out ? lane & 1 : 0))) : 0x7FFFFFFFu;
         finite[p] = 0.0f;
     }
     const size_t out_tail = (size_t)(a.n - img0) * a.c_out * oplane * 2;
-    __amdgpu_buffer_rsrc_t osrc = __builtin_amdgcn_make_buffer_rsrc((void*)(a.out + (size_t)img0 * a.c_out * oplane), 0,
-                                                                    (int)(unsigned)std::min<size_t>(out_tail, 0x7FFFFFFFu), 0x00020000);
+    __half* const out_blk = a.out + (size_t)img0 * a.c_out * oplane;
+    __amdgpu_buffer_rsrc_t osrc = __builtin_amdgcn_make_buffer_rsrc((void*)out_blk, 0, (int)(unsigned)std::min<size_t>(out_tail, 0x7FFFFFFFu), 0x00020000);
     const float least = a.relu ? 0.0f : __builtin_nanf("");      // the maximum of a value and a NaN is the value
     // neighbouring pixels trade: the even one takes both of filter r, the odd one both of r + 1
     const unsigned trade = lane & 1 ? 0x03020706u : 0x05040100u;
@@ -468,11 +471,13 @@ void f16_conv_kernel(F16Args a)
     for (int f = 0; f < FM; ++f)
 #pragma unroll
         for (int r = 0; r < RK; r += 2) {
+            int channel[2];
             unsigned co[2];
             float b[2];
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
                 const int2 slot = slots[(wf * FM + f) * 32 + 8 * ((reg0 + r + k) >> 2) + 4 * half + ((reg0 + r + k) & 3)];
+                channel[k] = slot.x;
                 co[k] = slot.x >= 0 ? 2u * (unsigned)slot.x * (unsigned)oplane : 0x80000000u;
                 b[k] = __int_as_float(slot.y);
             }
@@ -488,11 +493,18 @@ void f16_conv_kernel(F16Args a)
                 if (pair_out) {
                     const unsigned mine = (unsigned)__half_as_ushort(v[0]) | (unsigned)__half_as_ushort(v[1]) << 16;
                     const unsigned next = (unsigned)__builtin_amdgcn_mov_dpp((int)mine, 0xB1, 0xf, 0xf, true);      // quad_perm [1,0,3,2]
-                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_amdgcn_perm(next, mine, trade), osrc, (int)(off[p] + (lane & 1 ? co[1] : co[0])), 0, 0);
+                    const unsigned both = __builtin_amdgcn_perm(next, mine, trade);
+                    if constexpr (FAR) {
+                        const int c = lane & 1 ? channel[1] : channel[0];
+                        if (ok[p] && c >= 0) *reinterpret_cast<unsigned*>(out_blk + pixel[p] + (size_t)c * oplane) = both;
+                    } else {
+                        __builtin_amdgcn_raw_buffer_store_b32(both, osrc, (int)(off[p] + (lane & 1 ? co[1] : co[0])), 0, 0);
+                    }
                 } else {
 #pragma unroll
                     for (int k = 0; k < 2; ++k)
-                        __builtin_amdgcn_raw_buffer_store_b16((short)__half_as_ushort(v[k]), osrc, (int)(off[p] + co[k]), 0, 0);
+                        if constexpr (!FAR) __builtin_amdgcn_raw_buffer_store_b16((short)__half_as_ushort(v[k]), osrc, (int)(off[p] + co[k]), 0, 0);
+                        else if (ok[p] && channel[k] >= 0) out_blk[pixel[p] + (size_t)channel[k] * oplane] = v[k];
                 }
             }
         }
@@ -542,8 +554,8 @@ hipError_t launch_f16_expand(const DevFkw& f, int32_t c_in, int32_t c_out, void*
 }
 
 // How the pixels of an output are cut into tiles of `pix`; false where the kernel's 32-bit numbers
-// do not reach.
-static bool f16_tiles(const ConvShape& s, int pix, bool pair, F16Args& a)
+// do not reach.  `far`: see f16_conv_kernel.
+static bool f16_tiles(const ConvShape& s, int pix, bool pair, F16Args& a, bool& far)
 {
     a.strips = (s.wo + 31) / 32;
     a.sw = (s.wo + a.strips - 1) / a.strips;
@@ -565,11 +577,12 @@ static bool f16_tiles(const ConvShape& s, int pix, bool pair, F16Args& a)
     const int between = std::min(s.n - 1, (rows_out - 1 + s.ho - 1) / s.ho);
     const int rows = (rows_out - 1) * s.stride + between * (a.vh - s.ho * s.stride) + 3;
     a.npp = (rows * a.pitch + 127) / 128 * 128;
-    // byte offsets from a tile's first image, in and out
-    return (long long)(between + 2) * s.c_in * s.h * s.w < (1ll << 30) && (long long)(between + 2) * s.c_out * s.ho * s.wo < (1ll << 30);
+    // byte offsets from a tile's first image; its outputs lie in at most between + 1 images
+    far = (long long)(between + 1) * s.c_out * s.ho * s.wo >= (1ll << 30);
+    return (long long)(between + 2) * s.c_in * s.h * s.w < (1ll << 30);
 }
 
-template <int FM, int PN, int WF, int WP, int WK, bool PAIR>
+template <int FM, int PN, int WF, int WP, int WK, bool PAIR, bool FAR>
 static hipError_t launch_f16_t(const F16Args& args, const ConvShape& s, long long blocks, size_t lds, hipStream_t stream)
 {
     F16Args a = args;
@@ -581,10 +594,10 @@ static hipError_t launch_f16_t(const F16Args& args, const ConvShape& s, long lon
     a.div_pitch = make_fast_div((uint32_t)a.pitch);
     if (lds > 64 * 1024) {
         static std::atomic<uint64_t> allowed{0};
-        hipError_t e = allow_big_lds(reinterpret_cast<const void*>(&f16_conv_kernel<FM, PN, WF, WP, WK, PAIR>), allowed);
+        hipError_t e = allow_big_lds(reinterpret_cast<const void*>(&f16_conv_kernel<FM, PN, WF, WP, WK, PAIR, FAR>), allowed);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((f16_conv_kernel<FM, PN, WF, WP, WK, PAIR>), dim3((unsigned)blocks), dim3(64 * WF * WP * WK), lds, stream, a);
+    hipLaunchKernelGGL((f16_conv_kernel<FM, PN, WF, WP, WK, PAIR, FAR>), dim3((unsigned)blocks), dim3(64 * WF * WP * WK), lds, stream, a);
     return hipGetLastError();
 }
 
@@ -606,10 +619,12 @@ static hipError_t launch_f16_t(const F16Args& args, const ConvShape& s, long lon
 struct F16Shape {
     int fm, pn, wf, wp, wk, min_blocks;
     bool strided;                    // only where every filter set's staging counts four times: stride 2
-    hipError_t (*launch[2])(const F16Args&, const ConvShape&, long long, size_t, hipStream_t);
+    hipError_t (*launch[2][2])(const F16Args&, const ConvShape&, long long, size_t, hipStream_t);       // far or not, pairs or not
 };
+// (outputs that need FAR are more than a hundred thousand workgroups of any of the shapes that do not split the channels)
 #define PATDNN_F16(fm, pn, wf, wp, wk, min_blocks, strided) \
-    {fm, pn, wf, wp, wk, min_blocks, strided, {&launch_f16_t<fm, pn, wf, wp, wk, false>, &launch_f16_t<fm, pn, wf, wp, wk, true>}}
+    {fm, pn, wf, wp, wk, min_blocks, strided, {{&launch_f16_t<fm, pn, wf, wp, wk, false, false>, &launch_f16_t<fm, pn, wf, wp, wk, true, false>}, \
+                                               {&launch_f16_t<fm, pn, wf, wp, wk, false, wk == 1>, &launch_f16_t<fm, pn, wf, wp, wk, true, wk == 1>}}}
 static const F16Shape kF16Shapes[] = {
     PATDNN_F16(2, 4, 2, 2, 1, 256, false),
     PATDNN_F16(2, 2, 2, 2, 1, 128, true),
@@ -623,6 +638,7 @@ static const F16Shape kF16Shapes[] = {
 // The shape that a launch takes, as an index of kF16Shapes (-1: beyond the kernel's 32-bit numbers).
 struct F16Plan {
     int shape = -1;
+    bool far = false;
     long long blocks = 0;
     size_t lds = 0;
 };
@@ -636,7 +652,7 @@ static F16Plan f16_plan(const ConvShape& s, bool pair, F16Args& a)
         if (filters >= 2 * a.fblocks) continue;                   // half of every workgroup idle
         if (v.strided && s.stride == 1) continue;
         if (v.wk == 8 && a.steps <= 4) continue;                  // four wavefronts hold all channels
-        if (!f16_tiles(s, 32 * v.pn * v.wp, pair, a)) continue;
+        if (!f16_tiles(s, 32 * v.pn * v.wp, pair, a, plan.far) || (plan.far && v.wk > 1)) continue;
         a.fsets = (a.fblocks + filters - 1) / filters;
         plan.blocks = (long long)a.strips * a.tiles * a.fsets;
         plan.lds = std::max((size_t)a.npp * (f16_buffers(v.wk) * 2 * v.wk * 16 + 4), v.wk > 1 ? (size_t)v.wf * v.wp * v.wk * 4096 : 0) + (size_t)filters * 32 * 8;
@@ -684,7 +700,7 @@ hipError_t launch_f16(const DevFkw& f, const ConvShape& s, const void* in, const
     const bool pair = f16_pair(s, in);
     const F16Plan plan = f16_plan(s, pair, a);
     if (plan.shape < 0) return launch_fkw_f16(f, s, in, bias, out, stream);
-    return kF16Shapes[plan.shape].launch[pair](a, s, plan.blocks, plan.lds, stream);
+    return kF16Shapes[plan.shape].launch[plan.far][pair](a, s, plan.blocks, plan.lds, stream);
 }
 
 }  // namespace patdnn
