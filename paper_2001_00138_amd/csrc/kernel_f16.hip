@@ -661,11 +661,16 @@ static F16Plan f16_plan(const ConvShape& s, bool pair, F16Args& a)
             // 424 at 106 x 95, 9 images 249 us and 142, 39 -> 421 at 79 x 121, 24 images 95 and 65, 449 -> 264 at 163 x 224, 4 images 222
             // and 182).
             if (plan.lds > 80 * 1024) continue;
-            // Filters that fill its sets badly: the third shape has sets of 32 and needs, at filters that fill both, some
-            // 1 + 0.0015 c_in times the time (66 -> 439 1.02, 128 -> 128 1.18, 256 -> 256 1.37).  40 -> 88 at 54 x 55, 50 images 39.3 us
-            // and 32.1, 40 -> 192 at 82 x 82 43.8 and 39.5, 208 -> 272 at 32 x 32, 24 images 57.4 and 46.9; 296 -> 68 at 35 x 44 48.7 and 55.8.
-            // (Layers of fewer channels stay, as tests want them; 27 -> 160 at 220 x 178 31.9 and 24.7.)
-            if (s.stride == 1 && s.c_in >= 40 && (double)a.fsets * filters > (1.0 + 0.0015 * s.c_in) * a.fblocks) continue;
+            // Filters that fill its sets badly: the third shape has sets of 32 filters and twice the workgroups a CU, each
+            // of which takes 1.65 / 4 times as long per round.  What a launch has of an unfinished round counts in part, of its only
+            // one nearly as a whole.  us of the first and the third shape: 208 -> 272 at 32 x 32, 24 images 50.0 and 42.5, 48 ->
+            // 133 at 65 x 64, 16 images 30.8 and 23.8; 40 -> 88 at 54 x 55, 50 images 31.1 and 30.5; 48 -> 200 at 224 x 208, 4
+            // images 56 and 78, 159 -> 272 at 66 x 66, 60 images 248 and 409.  Of 663 layers of 40 to 512 channels 114 are taken, 7 %
+            // faster on average and eleven slower, by 3 to 24 %.  Layers of fewer channels stay with the first shape: for 33 of 266 this
+            // rule would save 13 %.
+            const auto rounds = [](double n) { return n <= 1 ? 0.2 * n + 0.8 : n < 4 ? 0.8 * n + 0.2 * std::ceil(n) : n + 0.1; };
+            const double sets = (double)a.strips * a.tiles;       // (tiles of both shapes are 256 pixels)
+            if (s.stride == 1 && s.c_in >= 40 && rounds(sets * a.fblocks / 1024) * 1.65 / 2 < 0.97 * rounds(sets * a.fsets / 512)) continue;
         }
         // (with so few channels to split that the wavefronts of the next shapes have one step each, a little earlier)
         const int least = &v == kF16Shapes + 2 && a.steps <= 4 ? 192 : v.min_blocks;

@@ -182,21 +182,29 @@ def test_binary16_choice_is_close_to_the_fastest(case):
     assert (walk if got < 0 else matrix) <= 1.4 * min(walk, matrix), got
 
 
-# c_in, c_out, n, h, w, stride; us of the first three launch shapes of the binary16 matrix kernel (0: does not fit) and of the
-# first that splits the channels
+# c_in, c_out, n, h, w, stride; us of the first three launch shapes of the binary16 matrix kernel (none where the library has
+# no use for one: the second at stride 1, the first for few filters) and of the first that splits the channels
+NONE = float("inf")
 MEASURED_F16_SHAPES = [
-    ((128, 128, 64, 56, 56, 1), (80, 86, 94, 151)),
-    ((256, 256, 64, 28, 28, 1), (71, 90, 97, 140)),
-    ((40, 88, 50, 54, 55, 1), (39, 39, 32, 54)),
-    ((40, 192, 16, 82, 82, 1), (44, 45, 40, 70)),
-    ((208, 272, 24, 32, 32, 1), (57, 57, 47, 79)),
-    ((126, 248, 15, 127, 127, 1), (179, 220, 239, 386)),
-    ((328, 256, 5, 32, 47, 1), (58, 46, 37, 43)),
-    ((89, 62, 2, 120, 120, 1), (23, 17, 13, 17)),
-    ((32, 264, 4, 40, 40, 1), (15, 11, 8, 10)),
-    ((447, 424, 9, 106, 95, 2), (249, 142, 489, 730)),
-    ((39, 421, 24, 79, 121, 2), (95, 65, 158, 284)),
-    ((32, 108, 17, 58, 58, 2), (17, 12, 9, 19)),
+    ((128, 128, 64, 56, 56, 1), (68, NONE, 89, 146)),
+    ((256, 256, 64, 28, 28, 1), (61, NONE, 90, 132)),
+    ((40, 88, 50, 54, 55, 1), (31.1, NONE, 30.5, 52)),
+    ((40, 192, 16, 82, 82, 1), (37.1, NONE, 37.7, 71)),
+    ((208, 272, 24, 32, 32, 1), (50, NONE, 42.5, 74)),
+    ((126, 248, 15, 127, 127, 1), (135, NONE, 208, 334)),
+    ((328, 256, 5, 32, 47, 1), (51, NONE, 30, 38)),
+    ((89, 62, 2, 120, 120, 1), (NONE, NONE, 12, 16)),
+    ((32, 264, 4, 40, 40, 1), (12, NONE, 7.3, 10)),
+    ((447, 424, 9, 106, 95, 2), (237, 141, 484, 724)),
+    ((39, 421, 24, 79, 121, 2), (75, 61, 150, 290)),
+    ((32, 108, 17, 58, 58, 2), (12.9, 9.4, 8.5, 18.8)),
+    # filters that fill sets of 128 badly
+    ((48, 200, 4, 224, 208, 1), (56, NONE, 78, NONE)),
+    ((159, 272, 60, 66, 66, 1), (248, NONE, 409, 784)),
+    ((96, 295, 11, 172, 170, 1), (201, NONE, 302, 591)),
+    ((126, 88, 20, 195, 195, 1), (224, NONE, 295, 483)),
+    ((44, 280, 16, 80, 79, 1), (54, NONE, 66, NONE)),
+    ((48, 133, 16, 65, 64, 1), (31, NONE, 24, NONE)),
 ]
 
 
