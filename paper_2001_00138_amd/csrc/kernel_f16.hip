@@ -662,15 +662,18 @@ static F16Plan f16_plan(const ConvShape& s, bool pair, F16Args& a)
             // and 182).
             if (plan.lds > 80 * 1024) continue;
             // Filters that fill its sets badly: the third shape has sets of 32 filters and twice the workgroups a CU, each
-            // of which takes 1.65 / 4 times as long per round.  What a launch has of an unfinished round counts in part, of its only
-            // one nearly as a whole.  us of the first and the third shape: 208 -> 272 at 32 x 32, 24 images 50.0 and 42.5, 48 ->
-            // 133 at 65 x 64, 16 images 30.8 and 23.8; 40 -> 88 at 54 x 55, 50 images 31.1 and 30.5; 48 -> 200 at 224 x 208, 4
-            // images 56 and 78, 159 -> 272 at 66 x 66, 60 images 248 and 409.  Of 663 layers of 40 to 512 channels 114 are taken, 7 %
-            // faster on average and eleven slower, by 3 to 24 %.  Layers of fewer channels stay with the first shape: for 33 of 266 this
-            // rule would save 13 %.
-            const auto rounds = [](double n) { return n <= 1 ? 0.2 * n + 0.8 : n < 4 ? 0.8 * n + 0.2 * std::ceil(n) : n + 0.1; };
-            const double sets = (double)a.strips * a.tiles;       // (tiles of both shapes are 256 pixels)
-            if (s.stride == 1 && s.c_in >= 40 && rounds(sets * a.fblocks / 1024) * 1.65 / 2 < 0.97 * rounds(sets * a.fsets / 512)) continue;
+            // of which takes 1.75 / 4 times as long per round, less with up to three channel steps.  What a launch has of an
+            // unfinished round counts in part, most in the first.  us of the first and the third shape: 208 -> 272 at 32 x 32, 24
+            // images 50.0 and 42.5, 48 -> 133 at 65 x 64, 16 images 30.8 and 23.8, 40 -> 88 at 54 x 55, 50 images 31.1 and 30.5; 48 -> 200 at 224
+            // x 208, 4 images 56 and 78, 159 -> 272 at 66 x 66, 60 images 248 and 409.  Of 963 layers of 40 to 512 channels 233 are
+            // taken, 7 % faster on average and 32 more than 3 % slower.  Layers of fewer channels stay with the first shape, as before there was
+            // a rule: for 73 of 266 this one would save 10 %.
+            const auto rounds = [](double n) {
+                const double open = n <= 1 ? 0.6 : n <= 2 ? 0.3 : 0.1;
+                return (1 - open) * n + open * std::ceil(n);
+            };
+            const double sets = (double)a.strips * a.tiles, part = a.steps > 3 ? 1.75 : pair ? 1.38 : 1.55;     // (both: tiles of 256 pixels)
+            if (s.stride == 1 && s.c_in >= 40 && rounds(sets * a.fblocks / 1024) * part / 2 < rounds(sets * a.fsets / 512)) continue;
         }
         // (with so few channels to split that the wavefronts of the next shapes have one step each, a little earlier)
         const int least = &v == kF16Shapes + 2 && a.steps <= 4 ? 192 : v.min_blocks;
