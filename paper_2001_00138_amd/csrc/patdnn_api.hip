@@ -487,6 +487,9 @@ std::vector<int> default_variant_order(const patdnn_layer* h)
     return order;
 }
 
+// Partial sums that the library asks room for by itself: 512 MB.
+constexpr size_t kMaxSliceFloats = (size_t)128 << 20;
+
 // ---- the configuration used when the caller has not chosen or tuned one: the candidate with the
 // smallest estimate of its time.  The estimates are a few products; their constants were fitted to
 // measurements of layers from 16 to 512 channels, 7x7 to 224x224 pixels and 1 to 64 images in every
@@ -553,6 +556,45 @@ int taps_parts(const patdnn_layer* h, const Taps& t, const ConvShape& s, int wav
 {
     double us = 0.0;
     return taps_parts(TapsEstimate(h, t, s, (double)tap_tile_count(s)), waves, ksplit, us);
+}
+
+// A launch and its estimate.
+struct Launch {
+    double us = 1e30;
+    patdnn_config_t c{};
+};
+
+// The shortest launch in workgroups of 2, 4, 8 or 16 wavefronts with whole groups, in up to 16 slices as `room` floats allow,
+// by an estimate that the finer one above has replaced for the choice among this kernel's launches.  It goes on telling which
+// layers are this kernel's, the one with the smallest errors (in 1e-8 of the result against 64 bits, 64 to 512 channels, kept
+// 1/3.6: 8 to 9.5, the tiled kernel 12 to 30, the split kernel 11 to 13): by the finer one alone 20 of 2500 layers went to one of
+// those, most of them for more time (136 -> 48 at 141 x 141, nine images, kept 0.15 70 -> 86 us), two to the split kernel for less (80 ->
+// 292 at 52 x 52, 37 images, all kept 375 -> 228).
+Launch whole_groups(const patdnn_layer* h, const ConvShape& s, double tiles, size_t room)
+{
+    const size_t slice_stride = split_slice_stride((size_t)s.n * s.c_out * s.ho * s.wo);
+    const double in_mb = 4e-6 * s.n * s.c_in * s.h * s.w, out_mb = 4e-6 * s.n * s.c_out * (double)s.ho * s.wo;
+    Launch best;
+    for (const auto& layout : h->taps) {
+        const Taps& t = layout.second->host;
+        const double kernels = (46.7 * h->L.kept + 107.4 * t.segments) / s.c_out / t.num_chunks + 93.0;       // of one chunk
+        for (int filters = 8; filters <= 16; filters *= 2)
+            for (int waves = 2; waves <= kMaxTapWaves && (waves == 2 || waves / 2 * filters < s.c_out); waves *= 2) {
+                const int sets = (t.num_groups * kTapGroup + waves * filters - 1) / (waves * filters);
+                const int resident = std::max(1, std::min(kTapMaxChunk / t.ck, (filters == 16 ? 16 : 20) / waves));
+                for (int ks = 1; ks <= 16 && ks <= t.num_chunks && (ks == 1 || (room / ks >= slice_stride && ks * slice_stride <= kMaxSliceFloats)); ks *= 2) {
+                    const double blocks = tiles * sets * ks, together = blocks >= 256.0 * resident ? resident : std::ceil(blocks / 256);
+                    const double per_simd = std::max(1.0, waves / 4.0) * together, rounds = blocks / (256 * together);
+                    const double share = per_simd < 2 ? 1.73 - 0.64 * (per_simd - 1) : std::max(0.75, 1.09 - 0.17 * (per_simd - 2));
+                    const double work = filters * ((t.num_chunks + ks - 1) / ks) * kernels;
+                    double us = 5.0 + (rounds < 3 ? std::ceil(rounds) : rounds + 0.5) * (work * share * per_simd + 2000) / 2400 +
+                                (in_mb * (1 + 1.33 * (sets - 1)) + out_mb) / (5.65 * together);
+                    if (ks > 1) us += 4.1 + out_mb * (2 * ks + 1) / 8.5;
+                    if (us < best.us) best = Launch{us, patdnn_config_t{variant_of_extra(filters == 8 ? kExtraTaps8 : kExtraTaps16), t.ck, waves, ks}};
+                }
+            }
+    }
+    return best;
 }
 
 // Default tiled variant, microseconds: rounds of three wavefronts per SIMD.
@@ -790,9 +832,6 @@ patdnn_status_t upload_layer(patdnn_layer* h)
     return PATDNN_OK;
 }
 
-// Partial sums that the library asks room for by itself: 512 MB.
-constexpr size_t kMaxSliceFloats = (size_t)128 << 20;
-
 // How many workgroups a tile's `units` (of eight or sixteen filters) are dealt to, evenly, and the wavefronts of each.
 template <class F>
 void for_each_tap_split(int units, F&& f)
@@ -819,8 +858,7 @@ patdnn_config_t default_config(patdnn_layer* h, const ConvShape& shape, size_t s
     if (h->dense_mfma && dense_fits(s) && dense_pays(s)) return patdnn_config_t{variant_of_extra(kExtraDense), 0, 0, 1};
     patdnn_config_t best{PATDNN_VARIANT_FKW, 0, 0, 1};
     const bool taps = taps_fit_layer(h) && taps_fit_input(s) && taps_fit_input(pooled) && !h->taps.empty();
-    const double walk_us = taps ? fkw_estimate(h, s) : 0.0;
-    double best_us = walk_us;
+    double best_us = taps ? fkw_estimate(h, s) : 0.0;
     for (int vi : h->order) {
         const TiledVariant& v = tiled_variant(vi);
         int32_t ck = 0, waves = 0;
@@ -884,8 +922,14 @@ patdnn_config_t default_config(patdnn_layer* h, const ConvShape& shape, size_t s
     const bool few = groups >= 128 && groups < 512 && split.whole < unsplit.whole;
     const Fastest& taps_best = split.us < unsplit.us * (few ? 1.3 : 1.0) ? split : unsplit;
     const bool walk = best.variant == PATDNN_VARIANT_FKW && best_us < 15.0 && tiles == 1 && groups <= 64 && best_us < std::min(split.whole, unsplit.whole);
-    if (taps_best.us < best_us && !walk) return taps_best.c;
-    return or_split(best);
+    if (best.variant == PATDNN_VARIANT_FKW) return taps_best.us < best_us && !walk ? taps_best.c : or_split(best);
+    // Against the tiled kernel, and the split kernel in its place, slices count as whole_groups has them; that much room or
+    // more, or a call with the room that was asked for might choose otherwise.
+    if (unsplit.us < best_us) return taps_best.c;
+    const Launch whole = whole_groups(h, s, (double)tiles, scratch_floats / 2 >= stride ? kMaxSliceFloats : 0);
+    if (whole.us >= best_us) return or_split(best);
+    const bool fits = whole.c.ksplit == 1 || scratch_floats / whole.c.ksplit >= stride;
+    return taps_best.us < best_us || !fits ? taps_best.c : whole.c;
 }
 
 }  // namespace

@@ -272,3 +272,36 @@ def test_few_groups_are_not_cut_into_slices_where_wavefronts_share_them(case):
     chosen = B.Config()
     choice(layer.handle, n, h, w, 1 << 27, ctypes.byref(chosen))
     assert B.patdnn_variant_name(chosen.variant) == "taps_f8" and chosen.ksplit == 1
+
+
+# Layers that stay with the tap-product kernel, the most exact one: c_in, c_out, n, h, w, pad, patterns, kept kernels; us of
+# that kernel and of the one that an estimate of its launches put ahead, the tiled or (all kept) the split kernel.  The
+# last one is its own only with room for slices.
+MOST_EXACT = [
+    ((136, 48, 9, 141, 141, 1, 8, 979), (69.6, 85.9)),
+    ((384, 56, 5, 170, 170, 1, 8, 3226), (180, 198)),
+    ((288, 51, 9, 134, 134, 1, 6, 4080), (188, 200)),
+    ((140, 40, 22, 85, 100, 0, 8, 1556), (88, 100)),
+    ((312, 24, 6, 219, 219, 1, 6, 2080), (203, 228)),
+    ((80, 292, 37, 52, 52, 1, 8, 23360), (375, 228)),
+    ((72, 232, 1, 190, 206, 1, 24, 16704), (150, 75)),
+    ((504, 128, 5, 144, 128, 1, 8, 9677), (313, 275)),
+]
+
+
+@pytest.mark.parametrize("case", MOST_EXACT)
+def test_layers_of_the_most_exact_kernel_stay_with_it(case):
+    (c_in, c_out, n, h, w, pad, patterns, kept), _ = case
+    rng = np.random.default_rng(5)
+    mask = np.zeros(c_in * c_out, np.uint8)
+    mask[rng.permutation(mask.size)[:kept]] = 1
+    lib = wl.pattern_library(wl.PATTERN_SEED, patterns) if patterns < 56 else wl.pattern_universe()
+    layer = B.Layer(rng.standard_normal((c_out, c_in, 3, 3), dtype=np.float32), rng.integers(0, patterns, (c_out, c_in), dtype=np.uint8),
+                    mask.reshape(c_out, c_in), lib, pad=pad, host_only=True)
+    choice = B.lib().patdnn_internal_choice
+    choice.argtypes = [ctypes.c_void_p] + [ctypes.c_int32] * 3 + [ctypes.c_size_t, ctypes.c_void_p]
+    chosen = B.Config()
+    for room in (1 << 27,) if case is MOST_EXACT[-1] else (1 << 27, 0):
+        choice(layer.handle, n, h, w, room, ctypes.byref(chosen))
+        assert B.patdnn_variant_name(chosen.variant).startswith("taps")
+    layer.close()
