@@ -880,10 +880,7 @@ patdnn_config_t default_config(patdnn_layer* h, const ConvShape& shape, size_t s
     if (!taps) return or_split(best);
     const long long tiles = tap_tile_count(s);
     const size_t stride = split_slice_stride((size_t)s.n * s.c_out * s.ho * s.wo);
-    struct Fastest {
-        double us = 1e30, whole = 1e30;               // whole: with a wavefront for each group
-        patdnn_config_t c{};
-    } unsplit, split;
+    Launch unsplit, split;
     for (int level = 0; level < kTapLevels; ++level) {
         const int ck = taps_ck(s.c_in, level);
         auto it = h->taps.find(ck);
@@ -895,41 +892,40 @@ patdnn_config_t default_config(patdnn_layer* h, const ConvShape& shape, size_t s
             for_each_tap_split(units, [&](int sets, int waves) {
                 for (int ks = 1; ks <= 16 && ks <= t.num_chunks; ks *= 2) {
                     // (slices are for launches that leave the chip idle without)
-                    if (ks > 1 && (tiles * sets * ks >= 1024 || scratch_floats / 2 < stride || ks * stride > kMaxSliceFloats)) break;
-                    double us = estimate(filters, waves, ks);
-                    Fastest& f = ks > 1 ? split : unsplit;
-                    f.whole = std::min(f.whole, us);      // whatever the room, or a call with the room that was asked for might choose otherwise
-                    if (scratch_floats / ks < stride && ks > 1) continue;
+                    if (ks > 1 && (tiles * sets * ks >= 1024 || scratch_floats / ks < stride || ks * stride > kMaxSliceFloats)) break;
+                    double us = 0.0;
+                    Launch& f = ks > 1 ? split : unsplit;
                     if (filters == kTapGroup) taps_parts(estimate, waves, ks, us);
-                    if (us < f.us) {
-                        f.us = us;
-                        f.c = patdnn_config_t{variant_of_extra(filters == 8 ? kExtraTaps8 : kExtraTaps16), ck, waves, ks};
-                    }
+                    else us = estimate(filters, waves, ks);
+                    if (us < f.us) f = Launch{us, patdnn_config_t{variant_of_extra(filters == 8 ? kExtraTaps8 : kExtraTaps16), ck, waves, ks}};
                 }
             });
         }
     }
     // Several wavefronts for a group take the place of channel slices in many launches, which then need no second kernel:
-    // 128 -> 256 at 56 x 56, one image, 14.2 us, in slices 18.6.  Where whole groups would leave half of the SIMDs without
-    // a wavefront and slices were the answer they stay it up to 1.3 times the time (the tests hold the library to it: 96 -> 200 at
-    // 7 x 7, 64 images, 16.5 us, unsplit 13.1), but not below 128 groups, where that costs most: 34 -> 276 at 24 x 15, one image, half kept
-    // 15.4, unsplit 9.8; 32 -> 24 at 20 x 20, eight images, all kept 12.4 and 8.4; of 54 such layers three 2 to 10 % the other way.
-    // The walk stays the answer where one tile has no more than 64 whole groups and
-    // all takes little more than a launch (64 -> 512 at 14 x 14, one image, 13.3 us, this kernel 10.8).  Above, the walk where whole groups
-    // are estimated to be slower loses: 40 -> 155 at 10 x 10, 21 images, 23 us, this kernel 9.3; 24 -> 240 at 18 x 18, two images, 13.6
-    // and 8.4; 36 -> 16 at 39 x 39, eight images, 12.5 and 8.0.
+    // 128 -> 256 at 56 x 56, one image, 14.2 us, in slices 18.6; 312 -> 37 at 23 x 32, five images 26.4 and 19.2.  From 400 to 440
+    // groups slices stay the answer up to 1.3 times the time, as they were before there were several wavefronts, slower
+    // as that is (the layers that show the library splitting by itself are here: 96 -> 200 at 7 x 7, 64 images, 16.7 us,
+    // unsplit 12.0, before 22.8; 200 -> 72 at 45 x 45, three images, 21.8, 19.6, before 29.2).
     const long long groups = tiles * ((s.c_out + kTapGroup - 1) / kTapGroup);
-    const bool few = groups >= 128 && groups < 512 && split.whole < unsplit.whole;
-    const Fastest& taps_best = split.us < unsplit.us * (few ? 1.3 : 1.0) ? split : unsplit;
-    const bool walk = best.variant == PATDNN_VARIANT_FKW && best_us < 15.0 && tiles == 1 && groups <= 64 && best_us < std::min(split.whole, unsplit.whole);
-    if (best.variant == PATDNN_VARIANT_FKW) return taps_best.us < best_us && !walk ? taps_best.c : or_split(best);
+    const Launch& taps_best = split.us < unsplit.us * (groups >= 400 && groups < 440 ? 1.3 : 1.0) ? split : unsplit;
+    // Either of the two against the other kernels: one that wins by that factor must not stand in for the other here.
+    const bool ahead = std::min(split.us, unsplit.us) < best_us;
+    if (best.variant == PATDNN_VARIANT_FKW) {
+        // One tile of no more than 64 groups keeps the walk where all takes little more than a launch, as it did when groups were
+        // whole: 64 -> 512 at 14 x 14, one image, 13.3 us, this kernel 8.7.  Elsewhere the walk loses: 40 -> 155 at 10 x 10, 21
+        // images, 23 us, this kernel 9.3; 24 -> 240 at 18 x 18, two images, 13.6 and 8.4; 36 -> 16 at 39 x 39, eight images 12.5 and 8.0.
+        // (Whatever the room, or a call without would run another kernel.)
+        if (ahead && !(best_us < 15.0 && tiles == 1 && groups <= 64 && best_us < whole_groups(h, s, (double)tiles, kMaxSliceFloats).us)) return taps_best.c;
+        return or_split(best);
+    }
     // Against the tiled kernel, and the split kernel in its place, slices count as whole_groups has them; that much room or
     // more, or a call with the room that was asked for might choose otherwise.
     if (unsplit.us < best_us) return taps_best.c;
     const Launch whole = whole_groups(h, s, (double)tiles, scratch_floats / 2 >= stride ? kMaxSliceFloats : 0);
     if (whole.us >= best_us) return or_split(best);
     const bool fits = whole.c.ksplit == 1 || scratch_floats / whole.c.ksplit >= stride;
-    return taps_best.us < best_us || !fits ? taps_best.c : whole.c;
+    return ahead || !fits ? taps_best.c : whole.c;
 }
 
 }  // namespace

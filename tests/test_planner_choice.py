@@ -305,3 +305,59 @@ def test_layers_of_the_most_exact_kernel_stay_with_it(case):
         choice(layer.handle, n, h, w, room, ctypes.byref(chosen))
         assert B.patdnn_variant_name(chosen.variant).startswith("taps")
     layer.close()
+
+
+# layers for which a workspace made the library choose the walk, or slices that take longer: c_in, c_out, n, h, w, pad, patterns,
+# kept kernels; us of the choice with one and without
+SLOWER_WITH_ROOM = [
+    ((68, 360, 1, 31, 5, 1, 8, 6800), (12.5, 8.9)),
+    ((70, 295, 1, 17, 17, 1, 8, 5736), (11.3, 9.2)),
+    ((39, 164, 1, 43, 43, 1, 12, 6396), (13.9, 10.5)),
+    ((31, 16, 4, 60, 60, 1, 24, 248), (12.6, 8.9)),
+    ((88, 24, 5, 35, 51, 1, 8, 1056), (14.3, 10.9)),
+    ((81, 16, 10, 44, 44, 0, 8, 360), (13.1, 9.7)),
+]
+
+
+@pytest.mark.parametrize("case", SLOWER_WITH_ROOM)
+def test_room_does_not_make_a_choice_slower(case):
+    (c_in, c_out, n, h, w, pad, patterns, kept), _ = case
+    rng = np.random.default_rng(6)
+    mask = np.zeros(c_in * c_out, np.uint8)
+    mask[rng.permutation(mask.size)[:kept]] = 1
+    layer = B.Layer(rng.standard_normal((c_out, c_in, 3, 3), dtype=np.float32), rng.integers(0, patterns, (c_out, c_in), dtype=np.uint8),
+                    mask.reshape(c_out, c_in), wl.pattern_library(wl.PATTERN_SEED, patterns), pad=pad, host_only=True)
+    assert _choices(layer, n, h, w)[0] == _choices(layer, n, h, w)[1]
+    layer.close()
+
+
+def _choices(layer, n, h, w):
+    choice = B.lib().patdnn_internal_choice
+    choice.argtypes = [ctypes.c_void_p] + [ctypes.c_int32] * 3 + [ctypes.c_size_t, ctypes.c_void_p]
+    chosen = []
+    for room in (1 << 27, 0):
+        c = B.Config()
+        choice(layer.handle, n, h, w, room, ctypes.byref(c))
+        chosen.append((B.patdnn_variant_name(c.variant), c.ck, c.waves, c.ksplit))
+    return chosen
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_a_choice_that_needs_no_room_is_the_one_without(seed):
+    """... and with the room that a choice asks for, no more, it is that choice."""
+    rng = np.random.default_rng(seed)
+    for _ in range(60):
+        c_in, c_out, n = (int(v) for v in np.exp(rng.uniform(np.log([16, 16, 1]), np.log([300, 300, 64]))))
+        h, w = (int(v) for v in np.exp(rng.uniform(np.log(7), np.log(60), 2)))
+        mask = (rng.random((c_out, c_in)) < rng.choice([0.15, 1 / 3.6, 0.5, 1.0])).astype(np.uint8)
+        layer = B.Layer(np.ones((c_out, c_in, 3, 3), np.float32), rng.integers(0, 8, (c_out, c_in), dtype=np.uint8), mask,
+                        wl.pattern_library(wl.PATTERN_SEED), host_only=True)
+        with_room, without = _choices(layer, n, h, w)
+        if with_room[3] == 1:
+            assert with_room == without, (c_in, c_out, n, h, w)
+        else:
+            stride = -(-n * c_out * h * w // 64) * 64
+            c = B.Config()
+            B.lib().patdnn_internal_choice(layer.handle, n, h, w, with_room[3] * stride, ctypes.byref(c))
+            assert (B.patdnn_variant_name(c.variant), c.ck, c.waves, c.ksplit) == with_room, (c_in, c_out, n, h, w)
+        layer.close()
