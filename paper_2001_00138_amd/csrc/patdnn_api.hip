@@ -498,16 +498,18 @@ constexpr size_t kMaxSliceFloats = (size_t)128 << 20;
 // and once, a layer of 56 patterns in 43 small images, 2.2 times as slow.
 
 // Tap-product kernel, microseconds, for workgroups of `waves` wavefronts of `filters` filters.  Workgroups of one round
-// share a CU as far as LDS and registers allow, and the wavefronts of each are dealt to the SIMDs from the first one on;
-// `share` is what a wavefront's work costs when so many wavefronts sit on a SIMD (one alone leaves the matrix core waiting
-// for it).  What a workgroup reads and writes is not hidden by its own computation, only by another workgroup on the
-// CU.  (160 layers in every configuration: the one with the smallest estimate is 4 % behind the fastest on average.)
+// share a CU as far as LDS and registers allow; `share` is what a wavefront's work costs when so many sit on a SIMD (one alone
+// leaves the matrix core waiting for it), where more than three of a workgroup are counted from the first SIMD on.  What a
+// workgroup reads and writes is not hidden by its own computation, only by another workgroup on the CU, and few wavefronts
+// stage a chunk longer.  (770 layers in every configuration: the one with the smallest estimate is 2.3 % behind the fastest on
+// average, the median 0 %, with five wavefronts of 98 registers on a SIMD and five chunks of 32 KB in LDS 3.6 %.)
 struct TapsEstimate {
-    double groups, tiles, chunks, kernels, ends, in_mb, out_mb;
-    int ck, num_chunks;
+    double groups, tiles, kernels, in_mb, out_mb;
+    int ck, num_chunks, chunks_in_lds;
     TapsEstimate(const patdnn_layer* h, const Taps& t, const ConvShape& s, double tiles_)
-        : groups(t.num_groups), tiles(tiles_), chunks(t.num_chunks), kernels((46.7 * h->L.kept + 107.4 * t.segments) / s.c_out / t.num_chunks),
-          ends(93.0), in_mb(4e-6 * s.n * s.c_in * s.h * s.w), out_mb(4e-6 * s.n * s.c_out * s.ho * s.wo), ck(t.ck), num_chunks(t.num_chunks)
+        : groups(t.num_groups), tiles(tiles_), kernels((46.7 * h->L.kept + 102.0 * t.segments) / s.c_out / t.num_chunks + 93.0),
+          in_mb(4e-6 * s.n * s.c_in * s.h * s.w), out_mb(4e-6 * s.n * s.c_out * s.ho * s.wo), ck(t.ck), num_chunks(t.num_chunks),
+          chunks_in_lds(128 / ((4 * t.ck + 4) / 5))                       // of 1 KB a channel, in units of 1280 bytes: four of 32 channels, not five
     {
     }
     double sets(int filters, int waves) const { return (double)(((int)groups * kTapGroup + waves * filters - 1) / (waves * filters)); }
@@ -517,19 +519,21 @@ struct TapsEstimate {
     double operator()(int filters, int waves, int ksplit) const
     {
         const double sets = this->sets(filters, waves), blocks = tiles * sets * ksplit;
-        const int simd = filters == 16 ? 4 : 5, tall = (waves + 3) / 4;   // wavefronts that fit a SIMD, and those of one workgroup
-        const int resident = std::max(1, std::min(kTapMaxChunk / ck, waves > 2 ? simd / tall : 4 * simd / waves));
+        // wavefronts that a SIMD has registers for: 128 each, or 98 for eight and four filters (five fit with 96, and those whose slices
+        // leave bias and pooling to another kernel need no more)
+        const int simd = filters == 16 || (filters != 2 && ksplit == 1) ? 4 : 5;
+        const int resident = std::max(1, std::min(chunks_in_lds, 4 * simd / waves));
         const int together = blocks >= 256.0 * resident ? resident : ((int)blocks + 255) / 256;
-        const double per_simd = std::max(1.0, waves > 2 ? (double)tall * together : waves / 4.0 * together);
-        const double share = per_simd < 2 ? 1.73 - 0.64 * (per_simd - 1) : std::max(0.75, 1.09 - 0.17 * (per_simd - 2));
+        const double per_simd = std::max(1.0, waves > 3 ? (double)((waves + 3) / 4 * together) : waves / 4.0 * together);
+        const double share = per_simd < 2 ? 1.405 - 0.37 * (per_simd - 1) : std::max(0.75, 1.035 - 0.153 * (per_simd - 2));
         const int own = (num_chunks + ksplit - 1) / ksplit;               // chunks of one slice
-        const double work = filters * own * (kernels + ends), at_once = 1.0 / together;
+        const double at_once = 1.0 / together;
         double rounds = blocks * at_once / 256;
-        rounds = rounds < 3 ? (double)((int)blocks / (256 * together) + ((int)blocks % (256 * together) != 0)) : rounds + 0.5;
-        const double staging = own * (1500.0 + 16.0 * ck * together);
-        double us = 6.0 + rounds * (work * share * per_simd + staging + 1500) * (1.0 / 2400) +
-                    (in_mb * (1 + 0.7 * (sets - 1)) + out_mb) * at_once * (1.0 / 5.65);
-        if (ksplit > 1) us += 4.1 + out_mb * (2 * ksplit + 1) * (1.0 / 8.5);      // the slices' sums, out and back in
+        rounds = rounds < 3 ? (double)((int)blocks / (256 * together) + ((int)blocks % (256 * together) != 0)) : rounds + 0.65;
+        const double staging = own * (1280.0 + ck * (18.5 * together + 60.0 / waves));
+        double us = 6.0 + rounds * (filters * own * kernels * share * per_simd + staging + 1690) * (1.0 / 2400) +
+                    (in_mb * (1 + 0.665 * (sets - 1)) + out_mb) * at_once * (1.0 / 5.65);
+        if (ksplit > 1) us += 3.55 + out_mb * (2 * ksplit + 1) * (1.0 / 5.75);    // the slices' sums, out and back in
         return us;
     }
 };
@@ -832,18 +836,16 @@ patdnn_status_t upload_layer(patdnn_layer* h)
     return PATDNN_OK;
 }
 
-// How many workgroups a tile's `units` (of eight or sixteen filters) are dealt to, evenly, and the wavefronts of each.
+// The workgroups that a tile's `units` (of eight or sixteen filters) are dealt to: up to so many wavefronts each, evenly.
 template <class F>
 void for_each_tap_split(int units, F&& f)
 {
-    const int least = (units + kMaxTapWaves - 1) / kMaxTapWaves;
     int last = 0;
-    for (int m = 1; m <= 16; m *= 2)
-        for (int sets = least * m; sets <= least * m + 1; ++sets) {
-            const int waves = (units + sets - 1) / sets;
-            if (waves != last) f(sets, waves);
-            last = waves;
-        }
+    for (const int most : {1, 2, 3, 4, 6, 8, 12, kMaxTapWaves}) {
+        const int sets = (units + most - 1) / most, waves = (units + sets - 1) / sets;
+        if (waves != last) f(waves);
+        last = waves;
+    }
 }
 
 // `scratch_floats`: room for the partial sums of a split launch (0: no split candidates).  The
@@ -889,10 +891,9 @@ patdnn_config_t default_config(patdnn_layer* h, const ConvShape& shape, size_t s
         const TapsEstimate estimate(h, t, s, (double)tiles);
         for (int filters = 8; filters <= 16; filters *= 2) {
             const int units = (t.num_groups * kTapGroup + filters - 1) / filters;
-            for_each_tap_split(units, [&](int sets, int waves) {
+            for_each_tap_split(units, [&](int waves) {
                 for (int ks = 1; ks <= 16 && ks <= t.num_chunks; ks *= 2) {
-                    // (slices are for launches that leave the chip idle without)
-                    if (ks > 1 && (tiles * sets * ks >= 1024 || scratch_floats / ks < stride || ks * stride > kMaxSliceFloats)) break;
+                    if (ks > 1 && (scratch_floats / ks < stride || ks * stride > kMaxSliceFloats)) break;
                     double us = 0.0;
                     Launch& f = ks > 1 ? split : unsplit;
                     if (filters == kTapGroup) taps_parts(estimate, waves, ks, us);
@@ -1468,7 +1469,7 @@ static patdnn_status_t tune_ws(patdnn_handle_t h, const float* input, int32_t n,
     if (taps_fit_layer(h) && taps_fit_input(s))
         for (const auto& layout : h->taps)
             for (int filters = 8; filters <= 16; filters *= 2)
-                for_each_tap_split((layout.second->host.num_groups * kTapGroup + filters - 1) / filters, [&](int, int waves) {
+                for_each_tap_split((layout.second->host.num_groups * kTapGroup + filters - 1) / filters, [&](int waves) {
                     for (int ks = 1; ks <= 16 && ks <= layout.second->host.num_chunks; ks *= 2)
                         cands.push_back(patdnn_config_t{variant_of_extra(filters == 8 ? kExtraTaps8 : kExtraTaps16), layout.first, waves, ks});
                 });

@@ -361,3 +361,34 @@ def test_a_choice_that_needs_no_room_is_the_one_without(seed):
             B.lib().patdnn_internal_choice(layer.handle, n, h, w, with_room[3] * stride, ctypes.byref(c))
             assert (B.patdnn_variant_name(c.variant), c.ck, c.waves, c.ksplit) == with_room, (c_in, c_out, n, h, w)
         layer.close()
+
+
+# Launches of the tap-product kernel, us by (ck, waves) without slices: how many workgroups share a CU decides, four wavefronts a SIMD
+# and four chunks of 32 channels in LDS.
+MEASURED_LAUNCHES = [
+    ((384, 270, 5, 33, 33, 1, 12, 28800), {(128, 8): 86.6, (128, 2): 100.4, (128, 7): 71.4}),
+    ((110, 288, 2, 86, 86, 1, 8, 8800), {(55, 8): 44.1, (110, 6): 59.6, (110, 8): 45.0}),
+    ((56, 392, 51, 10, 9, 1, 56, 3293), {(56, 8): 22.4, (28, 2): 24.9, (56, 10): 18.9}),
+    ((104, 29, 4, 172, 167, 1, 12, 452), {(52, 4): 30.1, (26, 2): 39.1}),
+    ((40, 36, 6, 117, 117, 0, 56, 720), {(40, 4): 34.9, (10, 1): 41.5, (20, 1): 32.1}),
+    ((53, 40, 6, 88, 137, 1, 6, 589), {(53, 8): 22.7, (27, 2): 26.8, (53, 5): 21.9}),
+    ((251, 312, 10, 31, 31, 1, 12, 21753), {(63, 8): 100.9, (126, 4): 115.5, (126, 8): 96.4}),
+    ((75, 288, 43, 16, 10, 1, 56, 10800), {(75, 8): 53.9, (75, 2): 62.2}),
+    ((32, 127, 24, 29, 39, 1, 24, 610), {(32, 4): 15.5, (32, 2): 17.6}),
+    ((24, 93, 1, 221, 224, 1, 56, 620), {(24, 4): 18.4, (24, 2): 21.3, (24, 3): 18.7}),
+]
+
+
+@pytest.mark.parametrize("case", MEASURED_LAUNCHES)
+def test_launch_of_the_tap_product_kernel_is_close_to_the_fastest(case):
+    (c_in, c_out, n, h, w, pad, patterns, kept), us = case
+    rng = np.random.default_rng(7)
+    mask = np.zeros(c_in * c_out, np.uint8)
+    mask[rng.permutation(mask.size)[:kept]] = 1
+    lib = wl.pattern_library(wl.PATTERN_SEED, patterns) if patterns < 56 else wl.pattern_universe()
+    layer = B.Layer(rng.standard_normal((c_out, c_in, 3, 3), dtype=np.float32), rng.integers(0, patterns, (c_out, c_in), dtype=np.uint8),
+                    mask.reshape(c_out, c_in), lib, pad=pad, host_only=True)
+    name, ck, waves, ksplit = _choices(layer, n, h, w)[1]
+    layer.close()
+    assert name.startswith("taps") and ksplit == 1
+    assert us[ck, waves] <= 1.08 * min(us.values()), (ck, waves)
