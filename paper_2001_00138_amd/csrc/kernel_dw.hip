@@ -405,9 +405,9 @@ __global__ __launch_bounds__(256) void dw_planes_kernel(DwPlanesArgs<T> a)
     }
 }
 
-// True where dw_planes_kernel took the layer.
+// True where dw_planes_kernel takes the layer, which it then does if `run`.
 template <class T>
-static bool launch_dw_planes(const DevFkw& f, const ConvShape& s, const T* in, const float* bias, T* out, hipStream_t stream)
+static bool launch_dw_planes(const DevFkw& f, const ConvShape& s, const T* in, const float* bias, T* out, hipStream_t stream, bool run)
 {
     constexpr int V = 16 / sizeof(T);
     if (!f.dw_taps || s.pad > 1 || ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15) != 0) return false;
@@ -425,6 +425,7 @@ static bool launch_dw_planes(const DevFkw& f, const ConvShape& s, const T* in, c
     // 44 images, 528 workgroups 17.4 against 20.8).  Small planes are equal from 256 on
     // (21x21, 384 workgroups: 9.3 and 9.2) and ahead above.
     if (lds > kDwPlanesLds || (total + planes - 1) / planes < (lds > 16 * 1024 ? 512 : 256)) return false;
+    if (!run) return true;
     DwPlanesArgs<T> a{};
     a.taps = f.dw_taps; a.weight = reinterpret_cast<const float4*>(f.dw_tap_weight);
     a.in = in; a.bias = bias; a.out = out;
@@ -441,25 +442,25 @@ static bool launch_dw_planes(const DevFkw& f, const ConvShape& s, const T* in, c
     return true;
 }
 
-// True where dw_rows_kernel took the layer.  us of the kernels before -> of this one, on changing tensors, 64 images unless
+// Not 0 where dw_rows_kernel, or dw_planes_kernel in its place, takes the layer (see dw_choice).  us of the kernels before -> of this one, on changing tensors, 64 images unless
 // said: fp32 144 channels of 56 x 56 60 -> 47, 8 images 9.5 -> 7.2, one 6.8 both; 96 of 112 x 112 156 -> 106; 96 of 37 x 35 23.7 ->
 // 15.0; 144 of 57 x 61, 16 images 40 -> 12.8; 144 of 112 x 112 / 2 120 -> 103; 75 x 110 / 2 9.7 -> 7.4; binary16 56 x 56 42 -> 33, 60 x 58 120 ->
 // 52, 112 x 112 / 2 77 -> 59.  Rows of up to 12 elements that are not whole stay with dw_planes_kernel, whose 16-byte loads they
 // leave idle less: 400 channels of 9 x 9 7.7 there, 8.0 here, 10 x 10 9.3 and 10.0, 11 x 11 10.8 and 11.9, 13 x 13 13.6 and 10.3.
 template <class T>
-static bool launch_dw_rows(const DevFkw& f, const ConvShape& s, DwArgs<T> a, hipStream_t stream)
+static int launch_dw_rows(const DevFkw& f, const ConvShape& s, DwArgs<T> a, hipStream_t stream, bool run)
 {
     constexpr int kWide = 16 / sizeof(T);
     const uintptr_t at = reinterpret_cast<uintptr_t>(a.in) | reinterpret_cast<uintptr_t>(a.out);
-    if (!(sizeof(T) == 4 ? f.dw_finite : f.dw_taps != nullptr) || s.stride > 2 || s.pad > 1 || s.w < 4 * s.stride) return false;
+    if (!(sizeof(T) == 4 ? f.dw_finite : f.dw_taps != nullptr) || s.stride > 2 || s.pad > 1 || s.w < 4 * s.stride) return 0;
     // outputs of a lane: four, or a whole vector; at stride 2 the columns of four are one or two
     const int v = s.stride == 1 && s.pad == 1 && s.w % kWide == 0 && (at & 15) == 0 ? kWide : 4;
     const bool whole = s.pad == 1 && s.w % (v * s.stride) == 0 && (at & std::min<size_t>(15, v * s.stride * sizeof(T) - 1)) == 0;
-    if (!whole && s.w <= 12 && launch_dw_planes<T>(f, s, a.in, a.bias, a.out, stream)) return true;
+    if (!whole && s.w <= 12 && launch_dw_planes<T>(f, s, a.in, a.bias, a.out, stream, run)) return 1;
     a.wq = (s.wo + v - 1) / v;
     a.div_rows = (uint32_t)(s.ho + kDwRows - 1) / kDwRows;
     a.total = (long long)s.n * s.c_out * a.div_rows * a.wq;
-    if (a.total > INT32_MAX - 256) return false;
+    if (a.total > INT32_MAX - 256) return 0;
     a.div_wq = make_fast_div((uint32_t)a.wq);
     a.div_ho = make_fast_div(a.div_rows);
     a.div_c = make_fast_div((uint32_t)a.c);
@@ -468,26 +469,29 @@ static bool launch_dw_rows(const DevFkw& f, const ConvShape& s, DwArgs<T> a, hip
     // 72.7 / 148 and 70.8 / 142; below that size 144 channels of 56 x 56, 64 images 47.6 / 91.6 and 46.9 / 94.2; 576 of 28 x 28 54 / 96
     // and 60 / 120.
     const size_t bytes = (size_t)s.n * s.c_out * s.h * s.w * sizeof(T);
-    const bool past = 2 * bytes > (size_t)256 << 20 && s.w * sizeof(T) >= 224;
+    const bool past = s.stride == 1 && whole && 2 * bytes > (size_t)256 << 20 && s.w * sizeof(T) >= 224;
+    const int choice = 2 + whole + 2 * (v == 8) + 4 * past;
+    if (!run) return choice;
     const dim3 grid((unsigned)((a.total + 255) / 256)), block(256);
     const auto kernel = s.stride == 2 ? (whole ? &dw_rows_kernel<2, kDwRows, 4, true, T, false> : &dw_rows_kernel<2, kDwRows, 4, false, T, false>)
                         : !whole      ? &dw_rows_kernel<1, kDwRows, 4, false, T, false>
                         : v == kWide  ? (past ? &dw_rows_kernel<1, kDwRows, kWide, true, T, true> : &dw_rows_kernel<1, kDwRows, kWide, true, T, false>)
                                       : (past ? &dw_rows_kernel<1, kDwRows, 4, true, T, true> : &dw_rows_kernel<1, kDwRows, 4, true, T, false>);
     hipLaunchKernelGGL(kernel, grid, block, 0, stream, a);
-    return true;
+    return choice;
 }
 
 template <class T>
 static hipError_t launch_dw_t(const DevFkw& f, const T* weights, const ConvShape& s, const T* in, const float* bias,
-                              T* out, hipStream_t stream)
+                              T* out, hipStream_t stream, bool run, int& choice)
 {
     DwArgs<T> a{};
     a.reorder = f.reorder; a.dw_mask = f.dw_mask; a.dw_weight = weights;
     a.in = in; a.bias = bias; a.out = out;
     a.c = s.c_out; a.h = s.h; a.w = s.w; a.ho = s.ho; a.wo = s.wo; a.pad = s.pad; a.relu = s.relu;
-    if (launch_dw_rows<T>(f, s, a, stream)) return hipGetLastError();
-    if (s.w % 4 != 0 && launch_dw_planes<T>(f, s, in, bias, out, stream)) return hipGetLastError();
+    choice = launch_dw_rows<T>(f, s, a, stream, run);
+    if (!choice && s.w % 4 != 0 && launch_dw_planes<T>(f, s, in, bias, out, stream, run)) choice = 1;
+    if (choice || !run) return run ? hipGetLastError() : hipSuccess;
     a.wq = (s.wo + 3) / 4;
     a.total = (long long)s.n * s.c_out * s.ho * a.wq;
     a.div_wq = make_fast_div((uint32_t)a.wq);
@@ -503,14 +507,24 @@ static hipError_t launch_dw_t(const DevFkw& f, const T* weights, const ConvShape
 hipError_t launch_dw(const DevFkw& f, const ConvShape& s, const float* in, const float* bias,
                      float* out, hipStream_t stream)
 {
-    return launch_dw_t<float>(f, f.dw_weight, s, in, bias, out, stream);
+    int choice = 0;
+    return launch_dw_t<float>(f, f.dw_weight, s, in, bias, out, stream, true, choice);
 }
 
 hipError_t launch_dw_f16(const DevFkw& f, const ConvShape& s, const void* in, const float* bias,
                          void* out, hipStream_t stream)
 {
+    int choice = 0;
     return launch_dw_t<__half>(f, static_cast<const __half*>(f.dw_weight_f16), s, static_cast<const __half*>(in), bias,
-                               static_cast<__half*>(out), stream);
+                               static_cast<__half*>(out), stream, true, choice);
+}
+
+int dw_choice(const DevFkw& f, const ConvShape& s, const void* in, const void* out, bool half)
+{
+    int choice = 0;
+    if (half) launch_dw_t<__half>(f, nullptr, s, static_cast<const __half*>(in), nullptr, static_cast<__half*>(const_cast<void*>(out)), nullptr, false, choice);
+    else launch_dw_t<float>(f, nullptr, s, static_cast<const float*>(in), nullptr, static_cast<float*>(const_cast<void*>(out)), nullptr, false, choice);
+    return choice;
 }
 
 }  // namespace patdnn

@@ -128,7 +128,7 @@ struct DevCompare {
 hipError_t launch_compare(bool csr, const DevCompare& d, const ConvShape& s, const float* in, const float* bias,
                           float* out, hipStream_t stream);
 
-// Depthwise layers: one pass over input and output, 16-byte accesses, four outputs per lane.
+// Depthwise layers: one pass over input and output, vector accesses, two rows of four or eight outputs per lane.
 hipError_t launch_dw(const DevFkw& f, const ConvShape& s, const float* in, const float* bias,
                      float* out, hipStream_t stream);
 // The same two kernels on binary16 tensors and weights (fp32 arithmetic, fp32 bias); the walk where
@@ -137,6 +137,9 @@ hipError_t launch_dw_f16(const DevFkw& f, const ConvShape& s, const void* in, co
                          void* out, hipStream_t stream);
 hipError_t launch_fkw_f16(const DevFkw& f, const ConvShape& s, const void* in, const float* bias,
                           void* out, hipStream_t stream);
+// What a depthwise call launches: 0 element by element, 1 planes through LDS, else rows: 2, one more where they are whole vectors, two
+// more for eight outputs a lane, four more for stores past the L2s.
+int dw_choice(const DevFkw& f, const ConvShape& s, const void* in, const void* out, bool half);
 // Pruned and dense layers on the matrix cores (needs DevFkw::expanded_f16).
 hipError_t launch_f16(const DevFkw& f, const ConvShape& s, const void* in, const float* bias,
                       void* out, hipStream_t stream);

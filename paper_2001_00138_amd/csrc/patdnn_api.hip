@@ -1106,6 +1106,13 @@ int32_t patdnn_internal_f16_choice(patdnn_handle_t h, const void* input, int32_t
     return f16_walk_pays(h, s) ? -1 : f16_choice(s, input);
 }
 
+// Likewise: the kernel of a depthwise call (see dw_choice).
+int32_t patdnn_internal_dw_choice(patdnn_handle_t h, const void* input, const void* output, int32_t n, int32_t h_in, int32_t w_in, int32_t half)
+{
+    ConvShape s{};
+    return h->L.depthwise && h->on_device && shape_of(h, n, h_in, w_in, s) == PATDNN_OK ? dw_choice(h->dfkw, s, input, output, half != 0) : -1;
+}
+
 // Likewise: the wavefronts that share a filter group in a launch of the set configuration, a taps_f8 one.
 int32_t patdnn_internal_taps_parts(patdnn_handle_t h, int32_t n, int32_t h_in, int32_t w_in)
 {
