@@ -300,11 +300,10 @@ struct DwPlanesArgs {
 // planes; results leave through LDS with 16-byte stores.  Channels stay in memory order (tap
 // positions and weights are looked up per plane), since nothing here branches on the pattern.
 // The sums are those of dw_conv_kernel, term by term.
-// What bounds it: below about 12 MB of tensors the launch (9 us a pass); above, address arithmetic of
-// the LDS layout on both sides, 2.0 to 2.7 TB/s.  The row kernel's lanes load single elements of such rows.
-// us per pass, a row kernel of single elements -> this one, 64 images: 960 channels of 7x7 binary16 15.9 -> 9.2, fp32
-// 15.2 -> 9.7; 576 of 14x14 binary16 28.0 -> 15.5, fp32 26.1 -> 17.5, stride 2 17.8 -> 12.5; 96 of 37x35
-// binary16 27.9 -> 18.3, fp32 33.9 -> 22.6.
+// What bounds it: below about 12 MB of tensors the launch (8 us a pass); above, address arithmetic of
+// the LDS layout on both sides, 2.0 to 2.7 TB/s.
+// us per pass, a kernel of single elements -> this one, 64 images: 960 channels of 7x7 binary16 15.9 -> 9.2, fp32
+// 15.2 -> 9.7 (7.8 and 8.2 since a call from Python makes no Stream object).
 template <int S, class T>
 __global__ __launch_bounds__(256) void dw_planes_kernel(DwPlanesArgs<T> a)
 {
@@ -405,9 +404,9 @@ __global__ __launch_bounds__(256) void dw_planes_kernel(DwPlanesArgs<T> a)
     }
 }
 
-// True where dw_planes_kernel takes the layer, which it then does if `run`.
+// True where dw_planes_kernel takes the layer, with no more than `most_lds` bytes a workgroup, which it then does if `run`.
 template <class T>
-static bool launch_dw_planes(const DevFkw& f, const ConvShape& s, const T* in, const float* bias, T* out, hipStream_t stream, bool run)
+static bool launch_dw_planes(const DevFkw& f, const ConvShape& s, const T* in, const float* bias, T* out, long long most_lds, hipStream_t stream, bool run)
 {
     constexpr int V = 16 / sizeof(T);
     if (!f.dw_taps || s.pad > 1 || ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15) != 0) return false;
@@ -420,11 +419,11 @@ static bool launch_dw_planes(const DevFkw& f, const ConvShape& s, const T* in, c
     const long long in_units = (((planes * (s.h + 1) + 1) * (s.w + 1) + 1) * (long long)sizeof(T) + 15) / 16;
     const long long out_units = planes * px / V;
     const long long lds = (in_units + out_units + 2 * planes) * 16;
-    // Planes are not cut up: too few workgroups leave CUs idle while the others walk large planes (96
-    // channels of 37x35 binary16: 16 images, 192 workgroups 12.7 us against the row kernel's 9.3;
-    // 44 images, 528 workgroups 17.4 against 20.8).  Small planes are equal from 256 on
-    // (21x21, 384 workgroups: 9.3 and 9.2) and ahead above.
-    if (lds > kDwPlanesLds || (total + planes - 1) / planes < (lds > 16 * 1024 ? 512 : 256)) return false;
+    // Planes are not cut up: too few workgroups leave CUs idle while the others walk large planes.  Against single elements, us
+    // of this kernel over those: up to 16 KB from 512 workgroups on (fewer take no longer than a launch) 0.59 to 1.01 times, 16 to 32 KB from
+    // 512 on 0.42 to 1.11, 384 to 511 0.86 to 1.25; 32 to 52 KB from 512 on 0.66 to 1.05, below 0.77 to 1.47 (174 layers of up to
+    // seven columns).
+    if (lds > most_lds || (total + planes - 1) / planes < (lds > 16 * 1024 ? 512 : 256)) return false;
     if (!run) return true;
     DwPlanesArgs<T> a{};
     a.taps = f.dw_taps; a.weight = reinterpret_cast<const float4*>(f.dw_tap_weight);
@@ -446,7 +445,9 @@ static bool launch_dw_planes(const DevFkw& f, const ConvShape& s, const T* in, c
 // said: fp32 144 channels of 56 x 56 60 -> 47, 8 images 9.5 -> 7.2, one 6.8 both; 96 of 112 x 112 156 -> 106; 96 of 37 x 35 23.7 ->
 // 15.0; 144 of 57 x 61, 16 images 40 -> 12.8; 144 of 112 x 112 / 2 120 -> 103; 75 x 110 / 2 9.7 -> 7.4; binary16 56 x 56 42 -> 33, 60 x 58 120 ->
 // 52, 112 x 112 / 2 77 -> 59.  Rows of up to 12 elements that are not whole stay with dw_planes_kernel, whose 16-byte loads they
-// leave idle less: 400 channels of 9 x 9 7.7 there, 8.0 here, 10 x 10 9.3 and 10.0, 11 x 11 10.8 and 11.9, 13 x 13 13.6 and 10.3.
+// leave idle less (400 channels of 9 x 9 7.7 there, 8.0 here, 10 x 10 9.3 and 10.0, 11 x 11 10.8 and 11.9, 13 x 13 13.6 and 10.3),
+// where a workgroup's planes take up to 18 KB of LDS: of 491 layers that take more than a launch the two are even there (0.70 to 1.33),
+// from 24 to 40 KB, tall planes, dw_planes_kernel takes 1.18 times as long (0.79 to 1.59), above 1.36 (0.89 to 2.01).
 template <class T>
 static int launch_dw_rows(const DevFkw& f, const ConvShape& s, DwArgs<T> a, hipStream_t stream, bool run)
 {
@@ -456,7 +457,7 @@ static int launch_dw_rows(const DevFkw& f, const ConvShape& s, DwArgs<T> a, hipS
     // outputs of a lane: four, or a whole vector; at stride 2 the columns of four are one or two
     const int v = s.stride == 1 && s.pad == 1 && s.w % kWide == 0 && (at & 15) == 0 ? kWide : 4;
     const bool whole = s.pad == 1 && s.w % (v * s.stride) == 0 && (at & std::min<size_t>(15, v * s.stride * sizeof(T) - 1)) == 0;
-    if (!whole && s.w <= 12 && launch_dw_planes<T>(f, s, a.in, a.bias, a.out, stream, run)) return 1;
+    if (!whole && s.w <= 12 && launch_dw_planes<T>(f, s, a.in, a.bias, a.out, 18 * 1024, stream, run)) return 1;
     a.wq = (s.wo + v - 1) / v;
     a.div_rows = (uint32_t)(s.ho + kDwRows - 1) / kDwRows;
     a.total = (long long)s.n * s.c_out * a.div_rows * a.wq;
@@ -490,7 +491,7 @@ static hipError_t launch_dw_t(const DevFkw& f, const T* weights, const ConvShape
     a.in = in; a.bias = bias; a.out = out;
     a.c = s.c_out; a.h = s.h; a.w = s.w; a.ho = s.ho; a.wo = s.wo; a.pad = s.pad; a.relu = s.relu;
     choice = launch_dw_rows<T>(f, s, a, stream, run);
-    if (!choice && s.w % 4 != 0 && launch_dw_planes<T>(f, s, in, bias, out, stream, run)) choice = 1;
+    if (!choice && s.w % 4 != 0 && launch_dw_planes<T>(f, s, in, bias, out, kDwPlanesLds, stream, run)) choice = 1;
     if (choice || !run) return run ? hipGetLastError() : hipSuccess;
     a.wq = (s.wo + 3) / 4;
     a.total = (long long)s.n * s.c_out * s.ho * a.wq;

@@ -1,7 +1,9 @@
-"""The depthwise kernel for planes whose rows are no whole vectors (csrc/kernel_dw.hip,
-dw_planes_kernel) against the lane-per-row kernel, which an input or output that is not 16-byte
-aligned still takes: the sums are the same term by term, so every bit is the same, also where inputs
-are infinite or NaN.  The lane-per-row kernel has its own comparison with the oracle."""
+"""The depthwise kernel for narrow planes whose rows are no whole vectors (csrc/kernel_dw.hip,
+dw_planes_kernel) against the kernels that an input or output that is not 16-byte aligned takes:
+the sums are the same term by term, so every bit is the same, also where inputs
+are infinite or NaN.  The kernel that reads element by element has its own comparison with the oracle."""
+
+import ctypes
 
 import numpy as np
 import pytest
@@ -40,11 +42,46 @@ CASES = [
     (5, 1, 7, 7, 1, 1, 1.0),         # too few planes: the row kernel on both sides
     (4, 2, 67, 67, 1, 1, 1.0),       # too large ones
 ]
+# Rows of more than twelve elements are dw_rows_kernel's; these are not, by what a call is said to launch
+PLANES = [
+    (960, 3, 7, 7, 1, 1, 1.0),
+    (307, 9, 24, 10, 1, 1, 0.7),     # 240 outputs,
+    (299, 9, 51, 5, 1, 1, 1.0),      # 255,
+    (299, 9, 27, 10, 1, 1, 1.0),     # 270: more than a workgroup has threads
+    (419, 5, 40, 11, 1, 1, 1.0),     # 440
+    (299, 18, 46, 11, 1, 1, 0.9),    # more than 16 KB of LDS
+    (419, 18, 41, 11, 2, 0, 0.8),    # stride 2 without padding
+    (307, 40, 13, 9, 2, 1, 1.0),
+    (299, 40, 8, 7, 2, 0, 1.0),      # rows of less than eight elements at stride 2
+    (103, 40, 501, 2, 1, 1, 1.0),    # and of less than four, 40 KB of LDS
+]
+
+
+def _choice(torch, L, x, out, half):
+    choice = B.lib().patdnn_internal_dw_choice
+    choice.argtypes = [ctypes.c_void_p] * 3 + [ctypes.c_int32] * 4
+    return choice(L.handle, x.data_ptr(), out.data_ptr(), x.shape[0], x.shape[2], x.shape[3], int(half))
+
+
+def test_tall_narrow_planes_go_to_the_row_kernel(torch):
+    rng = np.random.default_rng(1)
+    L = B.Layer(rng.standard_normal((419, 1, 3, 3)).astype(np.float32), rng.integers(0, 8, (419, 1), dtype=np.uint8), np.ones((419, 1), np.uint8),
+                wl.pattern_library(wl.PATTERN_SEED), depthwise=True)
+    for h, w, want in ((40, 11, 1), (61, 11, 2), (120, 11, 2), (13, 13, 2)):
+        x = torch.zeros((18, 419, h, w), device="cuda")
+        assert _choice(torch, L, x, x, False) == _choice(torch, L, x, x, True) == want, (h, w)
+    L.close()
+
+
+@pytest.mark.parametrize("half", [False, True])
+@pytest.mark.parametrize("case", PLANES)
+def test_planes_kernel_is_taken_and_gives_the_same_bits(torch, case, half):
+    test_same_bits_as_the_row_kernel(torch, case, half, planes=True)
 
 
 @pytest.mark.parametrize("half", [False, True])
 @pytest.mark.parametrize("case", CASES)
-def test_same_bits_as_the_row_kernel(torch, case, half):
+def test_same_bits_as_the_row_kernel(torch, case, half, planes=False):
     c, n, h, w, stride, pad, keep = case
     rng = np.random.default_rng(c * 1000 + h * 40 + w)
     L = B.Layer((rng.standard_normal((c, 1, 3, 3)) * 0.3).astype(np.float32), rng.integers(0, 8, (c, 1), dtype=np.uint8),
@@ -63,6 +100,8 @@ def test_same_bits_as_the_row_kernel(torch, case, half):
         xs.copy_(x)
         buf = torch.full((size + 2 * guard + 8,), 7.0, dtype=dtype, device="cuda")
         out = buf[guard + shift_out:guard + shift_out + size].view(shape)
+        if planes:
+            assert (_choice(torch, L, xs, out, half) == 1) == (shift_in == shift_out == 0)
         if half:
             L.conv2d_f16(xs, b, out, relu=relu)
         else:
