@@ -7,12 +7,12 @@ layer dense, He-normal weights, every layer on a seeded input of its own shape).
 A "step" is one pass over all 13 layers.  Inputs, weights and outputs are resident
 in HBM before the timed region starts.
 
-Prints ONE JSON line.  `value` is effective GFLOP/s over non-zero FLOPs
-(2 x 4 x kept kernels x output pixels; 2 x 9 for the dense first layer).  Beside it:
-the roofline of the dominant kernel, per-layer rows of this stack and of the
-ResNet-50-shaped and MobileNet-V2-shaped (depthwise, HBM-bound) stacks, peaks measured
-in the same run (stream copy, plain FMA loop), batch-1 stack latencies, the dense
-comparison and the CPU oracle's rate.
+Prints ONE JSON line on standard output.  `value` is effective GFLOP/s over non-zero FLOPs
+(2 x 4 x kept kernels x output pixels; 2 x 9 for the dense first layer).  With it:
+the roofline of the dominant kernel, peaks measured in the same run (stream copy, plain FMA
+loop) and the CPU oracle's rate.  On standard error, a line each, and with `--details` in a
+file: per-layer rows of this stack and of the ResNet-50-shaped and MobileNet-V2-shaped
+(depthwise, HBM-bound) stacks, batch-1 stack latencies, the dense comparison, the ablation.
 """
 
 from __future__ import annotations
@@ -74,6 +74,9 @@ def main() -> int:
                     help="per-kernel HBM bytes per launch written by profile_summary.py from --pmc runs "
                          "of this same command; fills roofline.traffic when it names the dominant kernel")
     ap.add_argument("--cpu-seconds", type=float, default=15.0)
+    ap.add_argument("--details", default=None,
+                    help="write the result with what was measured beside the timed step (per layer, other stacks, ablation) to "
+                         "this JSON file; standard error has it in any case")
     args = ap.parse_args()
     if args.gpus != 1:
         print("bench.py: this build runs on ONE GPU only (no sharding, no collectives); "
@@ -630,6 +633,9 @@ def main() -> int:
         "roofline": roofline,
         "cpu_baseline": cpu,
         "measured_peaks": peaks,
+    }
+    # what was measured beside the step, tens of kilobytes: whoever keeps only the end of standard output would lose the result
+    details = {
         "two_stream_halves": halves,
         "batch1_stack_latency": latency,
         "layers": layer_rows,
@@ -638,6 +644,12 @@ def main() -> int:
         "ablation": ablation,
         "pattern_count_sweep": sweep,
     }
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump({**result, **details}, f)
+    for key, v in details.items():
+        if v is not None:
+            _log(f"[details] {json.dumps({key: v})}")
     print(json.dumps(result), flush=True)
     return 0
 
