@@ -870,16 +870,16 @@ patdnn_config_t default_config(patdnn_layer* h, const ConvShape& shape, size_t s
         if (us < best_us) { best_us = us; best = patdnn_config_t{vi + 1, ck, waves, 1}; }
         break;
     }
-    // the split kernel stands in for those two only: the tap-product kernel is the more exact one
-    const auto or_split = [&](const patdnn_config_t& c) {
-        int rounds = 0, steps = 0, pixels = 0;
-        if (!h->split || !split_cost(pooled, rounds, steps, pixels) || !split_cost(s, rounds, steps, pixels)) return c;
-        const double other = taps ? best_us : c.variant == PATDNN_VARIANT_FKW ? fkw_estimate(h, s) : tiled2_estimate(h, s);
-        // (the estimate of the stride-2 variant is the coarser one)
-        if (split_estimate(rounds, steps, pixels) * (s.stride == 1 ? 1.03 : 1.15) > other) return c;
-        return patdnn_config_t{variant_of_extra(kExtraSplit), 0, 0, 1};
+    // the split kernel, on halves, stands in for those two only: the tap-product kernel is the more exact one
+    double halves_us = 1e30;
+    int halves_rounds = 0, halves_steps = 0, halves_pixels = 0;
+    if (h->split && split_cost(pooled, halves_rounds, halves_steps, halves_pixels) && split_cost(s, halves_rounds, halves_steps, halves_pixels))
+        halves_us = split_estimate(halves_rounds, halves_steps, halves_pixels) * (s.stride == 1 ? 1.03 : 1.15);   // (the estimate of the stride-2 variant is the coarser one)
+    const auto or_halves = [&]() {
+        const double other = taps ? best_us : best.variant == PATDNN_VARIANT_FKW ? fkw_estimate(h, s) : tiled2_estimate(h, s);
+        return halves_us > other ? best : patdnn_config_t{variant_of_extra(kExtraSplit), 0, 0, 1};
     };
-    if (!taps) return or_split(best);
+    if (!taps) return or_halves();
     const long long tiles = tap_tile_count(s);
     const size_t stride = split_slice_stride((size_t)s.n * s.c_out * s.ho * s.wo);
     Launch unsplit, split;
@@ -910,23 +910,25 @@ patdnn_config_t default_config(patdnn_layer* h, const ConvShape& shape, size_t s
     // unsplit 12.0, before 22.8; 200 -> 72 at 45 x 45, three images, 21.8, 19.6, before 29.2).
     const long long groups = tiles * ((s.c_out + kTapGroup - 1) / kTapGroup);
     const Launch& taps_best = split.us < unsplit.us * (groups >= 400 && groups < 440 ? 1.3 : 1.0) ? split : unsplit;
-    // Either of the two against the other kernels: one that wins by that factor must not stand in for the other here.
-    const bool ahead = std::min(split.us, unsplit.us) < best_us;
-    if (best.variant == PATDNN_VARIANT_FKW) {
-        // One tile of no more than 64 groups keeps the walk where all takes little more than a launch, as it did when groups were
-        // whole: 64 -> 512 at 14 x 14, one image, 13.3 us, this kernel 8.7.  Elsewhere the walk loses: 40 -> 155 at 10 x 10, 21
-        // images, 23 us, this kernel 9.3; 24 -> 240 at 18 x 18, two images, 13.6 and 8.4; 36 -> 16 at 39 x 39, eight images 12.5 and 8.0.
-        // (Whatever the room, or a call without would run another kernel.)
-        if (ahead && !(best_us < 15.0 && tiles == 1 && groups <= 64 && best_us < whole_groups(h, s, (double)tiles, kMaxSliceFloats).us)) return taps_best.c;
-        return or_split(best);
-    }
-    // Against the tiled kernel, and the split kernel in its place, slices count as whole_groups has them; that much room or
-    // more, or a call with the room that was asked for might choose otherwise.
-    if (unsplit.us < best_us) return taps_best.c;
+    // Either of the two against the other kernels: one that wins by that factor must not stand in for the other here.  Against
+    // the tiled kernel slices count as whole_groups has them.
+    const double taps_us = best.variant == PATDNN_VARIANT_FKW ? std::min(split.us, unsplit.us) : unsplit.us;
+    // One tile of no more than 64 groups keeps the walk where all takes little more than a launch, as it did when groups were
+    // whole: 64 -> 512 at 14 x 14, one image, 13.3 us, this kernel 8.7.  Elsewhere the walk loses: 40 -> 155 at 10 x 10, 21
+    // images, 23 us, this kernel 9.3; 24 -> 240 at 18 x 18, two images, 13.6 and 8.4; 36 -> 16 at 39 x 39, eight images 12.5 and 8.0.
+    // (Whatever the room, or a call without would run another kernel.)
+    if (best.variant == PATDNN_VARIANT_FKW && best_us < 15.0 && tiles == 1 && groups <= 64 &&
+        best_us < whole_groups(h, s, (double)tiles, kMaxSliceFloats).us)
+        return or_halves();
+    if (taps_us < std::min(best_us, halves_us)) return taps_best.c;
+    // Not ahead of all of them, it keeps what it ran when groups were whole.  With any room: a call with the room that was asked
+    // for must not choose otherwise, nor one that needs none.
     const Launch whole = whole_groups(h, s, (double)tiles, scratch_floats / 2 >= stride ? kMaxSliceFloats : 0);
-    if (whole.us >= best_us) return or_split(best);
-    const bool fits = whole.c.ksplit == 1 || scratch_floats / whole.c.ksplit >= stride;
-    return ahead || !fits ? taps_best.c : whole.c;
+    if (whole.us >= best_us) return or_halves();
+    const bool ahead = std::min(split.us, unsplit.us) < best_us;
+    if (whole.c.ksplit == 1) return ahead ? taps_best.c : whole.c;
+    if (ahead && (taps_best.c.ksplit > 1 || whole_groups(h, s, (double)tiles, 0).us < best_us)) return taps_best.c;
+    return scratch_floats / whole.c.ksplit < stride ? taps_best.c : whole.c;
 }
 
 }  // namespace

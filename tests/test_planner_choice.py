@@ -392,3 +392,13 @@ def test_launch_of_the_tap_product_kernel_is_close_to_the_fastest(case):
     layer.close()
     assert name.startswith("taps") and ksplit == 1
     assert us[ck, waves] <= 1.08 * min(us.values()), (ck, waves)
+
+
+def test_a_layer_of_the_split_kernel_is_not_left_for_a_slower_launch():
+    """176 -> 90 at 97 x 97, 15 images, all kept: 190 us, the tap-product kernel 302, which is estimated ahead of the tiled one, 326."""
+    c_in, c_out = 176, 90
+    rng = np.random.default_rng(8)
+    layer = B.Layer(rng.standard_normal((c_out, c_in, 3, 3), dtype=np.float32), rng.integers(0, 8, (c_out, c_in), dtype=np.uint8),
+                    np.ones((c_out, c_in), np.uint8), wl.pattern_library(wl.PATTERN_SEED), host_only=True)
+    assert [c[0] for c in _choices(layer, 15, 97, 97)] == ["split_f16"] * 2
+    layer.close()
