@@ -112,7 +112,7 @@ static __device__ __forceinline__ void split_pixel(SplitArgsPtr a, int q, int& i
 // Wavefronts that stage: each of the four eights of a step's channels has one, or two that take every other unit of
 // its pixels.  Tiles of few pixels are taken where those pixels lie two apart and four wavefronts cannot stage
 // as fast as the others compute; the third wavefront of a SIMD leaves each 168 registers, enough for two blocks of
-// sums and not for four.  us with 4 / 8, 64 images of stride 2: 256 -> 256 at 28 x 28 80.8 / 74.5, 512 -> 512 at 14 x 14
+// sums, but for 14 that are spilled (some eight reloads a step of 32 channels), and not for four.  us with 4 / 8, 64 images of stride 2: 256 -> 256 at 28 x 28 80.8 / 74.5, 512 -> 512 at 14 x 14
 // 76.3 / 70.4, 128 -> 128 at 56 x 56, whose weights come as fast as L1 gives them, 88.1 / 88.6 (kept 1/3.6 each).
 constexpr int split_stagers(int pn) { return pn == 2 ? 8 : 4; }
 constexpr int split_threads(int pn) { return 64 * (4 + split_stagers(pn)); }

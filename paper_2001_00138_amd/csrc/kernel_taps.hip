@@ -29,8 +29,8 @@
 // 0.67 -> 0.54 ms (54 TFLOP/s of kept weights), at 14 x 14 0.19 -> 0.15, at 7 x 7 0.098 -> 0.053; one
 // image of 64 -> 64 at 224 x 224 35 -> 24 us, of 512 -> 512 at 14 x 14 28 -> 21 us (split).
 //
-// A small launch waits: a wavefront that has its SIMD to itself takes some 80 cycles for a kernel (its pixels are three
-// kernels on their way) and 200 for a flush with its jumps, one image of 512 -> 512 at 14 x 14 in 1024 wavefronts 7.8 of its 14
+// A small launch waits: a wavefront that has its SIMD to itself takes some 230 cycles a kernel, for pixels that are three
+// kernels on their way and flushes with their jumps, one image of 512 -> 512 at 14 x 14 in 1024 wavefronts 7.8 of its 14
 // us for 71 kernels each.  There the filters of a group go to two or four wavefronts, which have their pixels six kernels
 // ahead (taps_parts in patdnn_api.hip): 20.5 -> 14.0 us with its finishing kernel, of 256 -> 256 at 56 x 56 31.6 -> 23.5, of 64 ->
 // 64 at 224 x 224 23.2 -> 18.7.

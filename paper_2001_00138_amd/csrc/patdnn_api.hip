@@ -493,9 +493,9 @@ constexpr size_t kMaxSliceFloats = (size_t)128 << 20;
 // ---- the configuration used when the caller has not chosen or tuned one: the candidate with the
 // smallest estimate of its time.  The estimates are a few products; their constants were fitted to
 // measurements of layers from 16 to 512 channels, 7x7 to 224x224 pixels and 1 to 64 images in every
-// candidate configuration; on 80 other layers of 6 to 56 patterns (profiles/planner_choice.txt) the
-// chosen candidate is 4.6 % slower than the fastest one on average (median 0.1 %) without a workspace, 8.1 % (1.2 %) with one,
-// and once, a layer of 56 patterns in 43 small images, 2.2 times as slow.
+// candidate configuration; on 80 layers of 6 to 56 patterns (profiles/planner_choice.txt) the
+// chosen candidate is 5.0 % slower than the fastest one on average (median 1.1 %) without a workspace, 6.6 % (2.9 %) with one,
+// and at most 2.1 times as slow, a layer of 56 patterns in 43 small images that the split kernel would run, less exactly.
 
 // Tap-product kernel, microseconds, for workgroups of `waves` wavefronts of `filters` filters.  Workgroups of one round
 // share a CU as far as LDS and registers allow; `share` is what a wavefront's work costs when so many sit on a SIMD (one alone
@@ -539,8 +539,8 @@ struct TapsEstimate {
 };
 
 // Wavefronts that share a group's eight filters in a launch of taps_f8 whose workgroups take `waves` groups: 1, 2 or
-// 4, whichever is estimated to be fastest.  A filter's kernels come one after the other, some 200 cycles each for
-// a wavefront that has its SIMD to itself and 60 where four take turns, so launches with few wavefronts gain: one image of
+// 4, whichever is estimated to be fastest.  A filter's kernels come one after the other, some 230 cycles each, flushes
+// included, for a wavefront that has its SIMD to itself, so launches with few wavefronts gain: one image of
 // 512 -> 512 at 14 x 14 20.5 -> 14.0 us, of 128 -> 256 at 56 x 56 23.9 -> 13.7, 100 -> 75 at 45 x 61, six images 23.6 -> 18.6;
 // launches that fill the chip anyway lose (they stage the same inputs for fewer filters at a time: 512 -> 512 at 28 x 28,
 // two images, ck 64, 37.9 -> 42.3).  The sums of a filter are the same whoever computes it.
