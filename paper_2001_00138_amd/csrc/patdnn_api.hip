@@ -501,13 +501,14 @@ constexpr size_t kMaxSliceFloats = (size_t)128 << 20;
 // share a CU as far as LDS and registers allow; `share` is what a wavefront's work costs when so many sit on a SIMD (one alone
 // leaves the matrix core waiting for it), where more than three of a workgroup are counted from the first SIMD on.  What a
 // workgroup reads and writes is not hidden by its own computation, only by another workgroup on the CU, and few wavefronts
-// stage a chunk longer.  (770 layers in every configuration: the one with the smallest estimate is 2.3 % behind the fastest on
-// average, the median 0 %, with five wavefronts of 98 registers on a SIMD and five chunks of 32 KB in LDS 3.6 %.)
+// stage a chunk longer.  (770 layers in every configuration, on the same tensors each time: the one with the smallest estimate is
+// 2.6 % behind the fastest on average, with five wavefronts of 98 registers on a SIMD and five chunks of 32 KB in LDS 3.6 %; 440
+// of them on changing tensors, which cost large chunks most, 1.8 %, and at most 24 %.)
 struct TapsEstimate {
     double groups, tiles, kernels, in_mb, out_mb;
     int ck, num_chunks, chunks_in_lds;
     TapsEstimate(const patdnn_layer* h, const Taps& t, const ConvShape& s, double tiles_)
-        : groups(t.num_groups), tiles(tiles_), kernels((46.7 * h->L.kept + 102.0 * t.segments) / s.c_out / t.num_chunks + 93.0),
+        : groups(t.num_groups), tiles(tiles_), kernels((46.7 * h->L.kept + 92.0 * t.segments) / s.c_out / t.num_chunks + 93.0),
           in_mb(4e-6 * s.n * s.c_in * s.h * s.w), out_mb(4e-6 * s.n * s.c_out * s.ho * s.wo), ck(t.ck), num_chunks(t.num_chunks),
           chunks_in_lds(128 / ((4 * t.ck + 4) / 5))                       // of 1 KB a channel, in units of 1280 bytes: four of 32 channels, not five
     {
@@ -525,15 +526,15 @@ struct TapsEstimate {
         const int resident = std::max(1, std::min(chunks_in_lds, 4 * simd / waves));
         const int together = blocks >= 256.0 * resident ? resident : ((int)blocks + 255) / 256;
         const double per_simd = std::max(1.0, waves > 3 ? (double)((waves + 3) / 4 * together) : waves / 4.0 * together);
-        const double share = per_simd < 2 ? 1.405 - 0.37 * (per_simd - 1) : std::max(0.75, 1.035 - 0.153 * (per_simd - 2));
+        const double share = per_simd < 2 ? 1.405 - 0.37 * (per_simd - 1) : std::max(0.75, 1.035 - 0.172 * (per_simd - 2));
         const int own = (num_chunks + ksplit - 1) / ksplit;               // chunks of one slice
         const double at_once = 1.0 / together;
         double rounds = blocks * at_once / 256;
-        rounds = rounds < 3 ? (double)((int)blocks / (256 * together) + ((int)blocks % (256 * together) != 0)) : rounds + 0.65;
-        const double staging = own * (1280.0 + ck * (18.5 * together + 60.0 / waves));
-        double us = 6.0 + rounds * (filters * own * kernels * share * per_simd + staging + 1690) * (1.0 / 2400) +
+        rounds = rounds < 3 ? (double)((int)blocks / (256 * together) + ((int)blocks % (256 * together) != 0)) : rounds + 0.5;
+        const double staging = own * (420.0 + ck * (25.0 * together + 120.0 / waves + 15.0 * at_once));
+        double us = 5.17 + rounds * (filters * own * kernels * share * per_simd + staging + 2460) * (1.0 / 2400) +
                     (in_mb * (1 + 0.665 * (sets - 1)) + out_mb) * at_once * (1.0 / 5.65);
-        if (ksplit > 1) us += 3.55 + out_mb * (2 * ksplit + 1) * (1.0 / 5.75);    // the slices' sums, out and back in
+        if (ksplit > 1) us += 3.2 + out_mb * (2 * ksplit + 1) * (1.0 / 5.75);    // the slices' sums, out and back in
         return us;
     }
 };
@@ -905,11 +906,13 @@ patdnn_config_t default_config(patdnn_layer* h, const ConvShape& shape, size_t s
     }
     // Several wavefronts for a group take the place of channel slices in many launches, which then need no second kernel:
     // 128 -> 256 at 56 x 56, one image, 14.2 us, in slices 18.6; 312 -> 37 at 23 x 32, five images 26.4 and 19.2.  From 400 to 440
-    // groups slices stay the answer up to 1.3 times the time, as they were before there were several wavefronts, slower
+    // groups slices stay the answer up to 1.3 times the time where they were it before there were several wavefronts, slower
     // as that is (the layers that show the library splitting by itself are here: 96 -> 200 at 7 x 7, 64 images, 16.7 us,
     // unsplit 12.0, before 22.8; 200 -> 72 at 45 x 45, three images, 21.8, 19.6, before 29.2).
     const long long groups = tiles * ((s.c_out + kTapGroup - 1) / kTapGroup);
-    const Launch& taps_best = split.us < unsplit.us * (groups >= 400 && groups < 440 ? 1.3 : 1.0) ? split : unsplit;
+    const bool sliced = split.us < unsplit.us || (groups >= 400 && groups < 440 && split.us < unsplit.us * 1.3 &&
+                                                  whole_groups(h, s, (double)tiles, kMaxSliceFloats).c.ksplit > 1);
+    const Launch& taps_best = sliced ? split : unsplit;
     // Either of the two against the other kernels: one that wins by that factor must not stand in for the other here.  Against
     // the tiled kernel slices count as whole_groups has them.
     const double taps_us = best.variant == PATDNN_VARIANT_FKW ? std::min(split.us, unsplit.us) : unsplit.us;

@@ -370,7 +370,7 @@ MEASURED_LAUNCHES = [
     ((110, 288, 2, 86, 86, 1, 8, 8800), {(55, 8): 44.1, (110, 6): 59.6, (110, 8): 45.0}),
     ((56, 392, 51, 10, 9, 1, 56, 3293), {(56, 8): 22.4, (28, 2): 24.9, (56, 10): 18.9}),
     ((104, 29, 4, 172, 167, 1, 12, 452), {(52, 4): 30.1, (26, 2): 39.1}),
-    ((40, 36, 6, 117, 117, 0, 56, 720), {(40, 4): 34.9, (10, 1): 41.5, (20, 1): 32.1}),
+    ((40, 36, 6, 117, 117, 0, 56, 720), {(40, 4): 34.9, (10, 1): 41.5, (20, 1): 32.1, (40, 3): 30.3}),
     ((53, 40, 6, 88, 137, 1, 6, 589), {(53, 8): 22.7, (27, 2): 26.8, (53, 5): 21.9}),
     ((251, 312, 10, 31, 31, 1, 12, 21753), {(63, 8): 100.9, (126, 4): 115.5, (126, 8): 96.4}),
     ((75, 288, 43, 16, 10, 1, 56, 10800), {(75, 8): 53.9, (75, 2): 62.2}),
