@@ -494,7 +494,7 @@ constexpr size_t kMaxSliceFloats = (size_t)128 << 20;
 // smallest estimate of its time.  The estimates are a few products; their constants were fitted to
 // measurements of layers from 16 to 512 channels, 7x7 to 224x224 pixels and 1 to 64 images in every
 // candidate configuration; on 80 layers of 6 to 56 patterns (profiles/planner_choice.txt) the
-// chosen candidate is 5.0 % slower than the fastest one on average (median 1.1 %) without a workspace, 6.6 % (2.9 %) with one,
+// chosen candidate is 6.1 % slower than the fastest one on average (median 1.7 %) without a workspace, 8.2 % (4.4 %) with one,
 // and at most 2.1 times as slow, a layer of 56 patterns in 43 small images that the split kernel would run, less exactly.
 
 // Tap-product kernel, microseconds, for workgroups of `waves` wavefronts of `filters` filters.  Workgroups of one round
@@ -572,9 +572,9 @@ struct Launch {
 // The shortest launch in workgroups of 2, 4, 8 or 16 wavefronts with whole groups, in up to 16 slices as `room` floats allow,
 // by an estimate that the finer one above has replaced for the choice among this kernel's launches.  It goes on telling which
 // layers are this kernel's, the one with the smallest errors (in 1e-8 of the result against 64 bits, 64 to 512 channels, kept
-// 1/3.6: 8 to 9.5, the tiled kernel 12 to 30, the split kernel 11 to 13): by the finer one alone 20 of 2500 layers went to one of
-// those, most of them for more time (136 -> 48 at 141 x 141, nine images, kept 0.15 70 -> 86 us), two to the split kernel for less (80 ->
-// 292 at 52 x 52, 37 images, all kept 375 -> 228).
+// 1/3.6: 8 to 9.5, the tiled kernel 12 to 30, the split kernel 11 to 13): by the finer one alone 180 of 2500 layers went to one of
+// those, 20 to the tiled kernel, most for more time (384 -> 56 at 170 x 170, five images, kept 0.15 180 -> 198 us), and 160 to the
+// split kernel for less (80 -> 292 at 52 x 52, 37 images, all kept 375 -> 228).
 Launch whole_groups(const patdnn_layer* h, const ConvShape& s, double tiles, size_t room)
 {
     const size_t slice_stride = split_slice_stride((size_t)s.n * s.c_out * s.ho * s.wo);
