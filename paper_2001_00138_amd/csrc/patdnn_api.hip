@@ -494,7 +494,7 @@ constexpr size_t kMaxSliceFloats = (size_t)128 << 20;
 // smallest estimate of its time.  The estimates are a few products; their constants were fitted to
 // measurements of layers from 16 to 512 channels, 7x7 to 224x224 pixels and 1 to 64 images in every
 // candidate configuration; on 80 layers of 6 to 56 patterns (profiles/planner_choice.txt) the
-// chosen candidate is 6.1 % slower than the fastest one on average (median 1.7 %) without a workspace, 8.2 % (4.4 %) with one,
+// chosen candidate is 5.0 % slower than the fastest one on average (median 1.2 %) without a workspace, 7.0 % (3.2 %) with one,
 // and at most 2.1 times as slow, a layer of 56 patterns in 43 small images that the split kernel would run, less exactly.
 
 // Tap-product kernel, microseconds, for workgroups of `waves` wavefronts of `filters` filters.  Workgroups of one round
@@ -502,14 +502,15 @@ constexpr size_t kMaxSliceFloats = (size_t)128 << 20;
 // leaves the matrix core waiting for it), where more than three of a workgroup are counted from the first SIMD on.  What a
 // workgroup reads and writes is not hidden by its own computation, only by another workgroup on the CU, and few wavefronts
 // stage a chunk longer.  (770 layers in every configuration, on the same tensors each time: the one with the smallest estimate is
-// 2.6 % behind the fastest on average, with five wavefronts of 98 registers on a SIMD and five chunks of 32 KB in LDS 3.6 %; 440
+// 2.5 % behind the fastest on average, with five wavefronts of 98 registers on a SIMD and five chunks of 32 KB in LDS 3.6 %; 440
 // of them on changing tensors, which cost large chunks most, 1.8 %, and at most 24 %.)
 struct TapsEstimate {
-    double groups, tiles, kernels, in_mb, out_mb;
+    double groups, tiles, kernels, in_mb, again_mb, out_mb;
     int ck, num_chunks, chunks_in_lds;
     TapsEstimate(const patdnn_layer* h, const Taps& t, const ConvShape& s, double tiles_)
         : groups(t.num_groups), tiles(tiles_), kernels((46.7 * h->L.kept + 92.0 * t.segments) / s.c_out / t.num_chunks + 93.0),
-          in_mb(4e-6 * s.n * s.c_in * s.h * s.w), out_mb(4e-6 * s.n * s.c_out * s.ho * s.wo), ck(t.ck), num_chunks(t.num_chunks),
+          in_mb(4e-6 * s.n * s.c_in * s.h * s.w), again_mb(0.665 * in_mb * in_mb / (in_mb + 3.0)),    // few megabytes come from the L2s
+          out_mb(4e-6 * s.n * s.c_out * s.ho * s.wo), ck(t.ck), num_chunks(t.num_chunks),
           chunks_in_lds(128 / ((4 * t.ck + 4) / 5))                       // of 1 KB a channel, in units of 1280 bytes: four of 32 channels, not five
     {
     }
@@ -526,14 +527,14 @@ struct TapsEstimate {
         const int resident = std::max(1, std::min(chunks_in_lds, 4 * simd / waves));
         const int together = blocks >= 256.0 * resident ? resident : ((int)blocks + 255) / 256;
         const double per_simd = std::max(1.0, waves > 3 ? (double)((waves + 3) / 4 * together) : waves / 4.0 * together);
-        const double share = per_simd < 2 ? 1.405 - 0.37 * (per_simd - 1) : std::max(0.75, 1.035 - 0.172 * (per_simd - 2));
+        const double share = per_simd < 2 ? 1.2 - 0.165 * (per_simd - 1) : std::max(0.75, 1.035 - 0.172 * (per_simd - 2));
         const int own = (num_chunks + ksplit - 1) / ksplit;               // chunks of one slice
         const double at_once = 1.0 / together;
         double rounds = blocks * at_once / 256;
         rounds = rounds < 3 ? (double)((int)blocks / (256 * together) + ((int)blocks % (256 * together) != 0)) : rounds + 0.5;
         const double staging = own * (420.0 + ck * (25.0 * together + 120.0 / waves + 15.0 * at_once));
-        double us = 5.17 + rounds * (filters * own * kernels * share * per_simd + staging + 2460) * (1.0 / 2400) +
-                    (in_mb * (1 + 0.665 * (sets - 1)) + out_mb) * at_once * (1.0 / 5.65);
+        double us = 5.28 + rounds * (filters * own * kernels * share * per_simd + staging + 2460) * (1.0 / 2400) +
+                    (in_mb + again_mb * (sets - 1) + out_mb) * at_once * (1.0 / 5.65);
         if (ksplit > 1) us += 3.2 + out_mb * (2 * ksplit + 1) * (1.0 / 5.75);    // the slices' sums, out and back in
         return us;
     }

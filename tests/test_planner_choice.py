@@ -376,6 +376,9 @@ MEASURED_LAUNCHES = [
     ((75, 288, 43, 16, 10, 1, 56, 10800), {(75, 8): 53.9, (75, 2): 62.2}),
     ((32, 127, 24, 29, 39, 1, 24, 610), {(32, 4): 15.5, (32, 2): 17.6}),
     ((24, 93, 1, 221, 224, 1, 56, 620), {(24, 4): 18.4, (24, 2): 21.3, (24, 3): 18.7}),
+    ((128, 256, 1, 56, 56, 1, 8, 9102), {(128, 2): 13.5, (128, 3): 14.7, (64, 2): 15.6}),
+    ((256, 256, 1, 56, 56, 1, 8, 18204), {(128, 2): 22.6, (128, 3): 25.0, (64, 2): 26.1}),
+    ((512, 512, 1, 28, 28, 1, 8, 72818), {(128, 1): 36.2, (128, 2): 39.8, (64, 1): 44.5}),
 ]
 
 
